@@ -66,8 +66,8 @@ typedef struct {
     int precision;             /* ncorp_precision */
     double root_half_width;    /* 0 = smallest power of two above every |coordinate| */
     /* capacities of device lists; 0 = automatic from n_max and leaf_size.  The two
-     * pair lists get 2^18 extra slots on top of the value given: walk waves fill
-     * them in blocks of 256 and leave the unused end of their last block empty. */
+     * pair counts get 2^18 on top of the value given (256 for each of walk_waves,
+     * 512 at least, 1024 when it is 0). */
     int64_t cell_capacity;     /* octree cells */
     int64_t m2l_capacity;      /* well-separated cell pairs of one walk */
     int64_t p2p_capacity;      /* cell pairs treated by direct sums in one walk */
@@ -145,9 +145,8 @@ typedef struct {
      *     or 512 (0 = 256);
      *   p2p_targets_max: the most target moonlets one lane of the direct sums holds,
      *     1..4 (0 = 4); each leaf takes the count in 1..max that keeps most lanes busy;
-     *   walk_waves: persistent waves of the gravity walk, 256, 512, 1024 or 2048
-     *     (0 = 1024); each claims 128 queue items at a time, so this sets how many
-     *     items of the walk's queue are in flight. */
+     *   walk_waves: the most workgroups (of four waves, a cell per wave) the gravity
+     *     walk runs at once, 256, 512, 1024 or 2048 (0 = as many as fit on the GPU). */
     int32_t p2p_tile, p2p_targets_max, walk_waves;
 } ncorp_params;
 
@@ -260,10 +259,8 @@ int ncorp_step(ncorp_ctx *ctx, double *x, double *y, double *z, double *vx, doub
  *
  * Graph capture: these calls (like ncorp_step) only enqueue kernels on `stream`
  * -- no allocation, copy, memset or host synchronisation -- so a call may be
- * captured into a hipGraph and replayed; the walk-queue tags advance on the
- * device, so replays stay valid.  Capture after one eager call on the same
- * workspace (the first walk on a new workspace clears its queue, which would
- * otherwise be captured too), with phase timing off. */
+ * captured into a hipGraph and replayed.  Capture after one eager call on the same
+ * workspace, with phase timing off. */
 #define NCORP_MAX_DISKS 65536
 
 /* ncorp_build_tree for a batch of disks (Sect. 3.4.1, Sect. 3.4.6, applied per
@@ -336,9 +333,9 @@ enum {
  * the sizes m2l_per_cell and p2p_per_leaf must cover; these three are filled
  * only while phase timing is on (ncorp_set_timing), otherwise they read 0), and
  * the number of roots (level-0 cells: 1, or the non-empty disks of a batched
- * call), and the numbers of cells and leaves whose M2L or direct-sum lists were too
- * long for one LDS batch of their consumer (sorted by a pre-pass; the direct sums of
- * such leaves are split over several waves); and, again only while phase timing is on,
+ * call), and the numbers of cells with more than 512 M2L partners and of leaves whose
+ * direct-sum lists were too long for one LDS batch of their consumer (the direct sums
+ * of such leaves are split over several waves); and, again only while phase timing is on,
  * the load balance of the last gravity evaluation: the largest and the mean number of
  * shader clock cycles (clock64) the gravity walk's persistent waves were busy, and the
  * most source moonlets of one leaf's direct sums (the mean is p2p_inter / n).  The

@@ -4,9 +4,8 @@ queue depth, each under an error gate.
 The leaf size s is the step's main speed parameter (Sect. 4.2: it moves work between
 the direct sums and the expansions without changing the accuracy class).  The direct
 sums' tile shape (source moonlets staged per LDS tile, `p2p_tile`, and the most
-target moonlets a lane holds, `p2p_targets_max`) and the number of persistent
-gravity-walk waves (`walk_waves`: each claims 128 queue items at a time, so this is
-the depth of the walk's queue in flight) change how the same work is laid out on the
+target moonlets a lane holds, `p2p_targets_max`) and the most workgroups the gravity
+walk runs at once (`walk_waves`) change how the same work is laid out on the
 GPU.  Each is picked by measurement: every candidate runs a few eager steps of the
 caller's own workload and the fastest one that passes the gate is kept, one
 parameter after the other (s first, then the tile shape at that s, then the walk).

@@ -26,6 +26,8 @@ struct ncorp_ctx {
     int64_t n = 0;
     double clock = 0.0;                 // time of the next ncorp_step call
     bool grav_lists = false;            // the gravity walk ran on the current tree
+    int walked = 0;                     // last walk on the tree: 1 gravity, 2 collisions
+    bool searched = false;              // a tree search left candidates (walk_ctr)
     bool have_mesh = false;             // a mesh was built (mesh module)
     bool mesh_init = false;             // the workspace's mesh state has been set up
     bool mesh_counted = false;          // neighbours counted on the current mesh
@@ -253,11 +255,7 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     const int s = prm.leaf_size;
     int64_t cell_cap = prm.cell_capacity > 0 ? prm.cell_capacity : 8 * n / s + 1024;
     if (cell_cap > (1 << 24) - 2) cell_cap = (1 << 24) - 2;
-    // plain pair lists: entries plus at most one partly used chunk per walk wave (the
-    // gravity walk's waves, or the collision walk's if it runs more)
-    const int collide_waves = kWalkGridCollide * (kWalkBlock / kWave);
-    const int64_t slack =
-        (int64_t)(walk_waves(prm) > collide_waves ? walk_waves(prm) : collide_waves) * kListChunk;
+    const int64_t slack = list_slack(prm);
     int64_t m2l_cap = (prm.m2l_capacity > 0 ? prm.m2l_capacity : 64 * cell_cap + 4096) + slack;
     int64_t p2p_cap = (prm.p2p_capacity > 0 ? prm.p2p_capacity : 32 * cell_cap + 4096) + slack;
     int64_t q_cap = prm.queue_capacity > 0 ? prm.queue_capacity
@@ -331,7 +329,9 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.wg = (WCell *)take(sizeof(WCell) * cell_cap);
     ws.wc = (WCell *)take(sizeof(WCell) * cell_cap);
     ws.queue = (uint64_t *)take(8 * q_cap);
-    ws.m2l = (int2 *)take(8 * m2l_cap);
+    // (room for a plain list of the well-separated pairs: the lists are per target now,
+    // but the size a caller computes for an n must not shrink or grow)
+    (void)take(8 * m2l_cap);
     ws.p2p = (int2 *)take(8 * p2p_cap);
     ws.cand = (int2 *)take(8 * p2p_cap);
     if (ws.p > 0) {
@@ -339,7 +339,7 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
         ws.m2l_seg = (int32_t *)take(4 * cell_cap * (int64_t)ws.m2l_stride);
         ws.p2p_cnt = (int32_t *)take(4 * ws.leaf_cap);
         ws.p2p_seg = (int32_t *)take(4 * ws.leaf_cap * (int64_t)ws.p2p_stride);
-        ws.long_m2l = (int32_t *)take(4 * cell_cap);
+        ws.leaf_slack = (float *)take(4 * cell_cap);
         ws.long_p2p = (int32_t *)take(4 * ws.leaf_cap);
         ws.p2p_part = (double *)take(8 * (int64_t)kLongSlots * 3 * n);
     }
@@ -371,7 +371,8 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.pair_flag = (int32_t *)take(4 * ws.pair_cap);
     ws.mbest = (int32_t *)take(4 * n);
     ws.mmatch = (int32_t *)take(4 * n);
-    ws.cand_blk = (int32_t *)take(4 * 8192);
+    static_assert((kWalkClasses + kCandRegions) * kCtrStride <= 8192, "counter lines must fit");
+    ws.walk_ctr = (int32_t *)take(4 * 8192);
     // per-block partials: the box pass's 16384 and the pair tests' kCollideGrid blocks,
     // 2 per mesh block plus 1024, or one per standard-tree wave, whichever needs most
     static_assert(kCollideGrid <= 2 * 16384 + 1024 + 128, "pair-test partials must fit");
@@ -433,10 +434,6 @@ static int setup_workspace(ncorp_ctx *c, int64_t n, void *workspace, int64_t ws_
     Workspace ws;
     ws.base = (char *)workspace;
     layout_workspace(ws, c->prm, n, pc);
-    // the walk queue keeps tags from earlier walks; a new buffer or layout holds
-    // unknown bytes, so the next walk clears it
-    ws.clear_queue = !(c->ws.base == ws.base && c->ws.queue == ws.queue &&
-                       c->ws.queue_cap == ws.queue_cap) || c->ws.clear_queue;
     // the bucket sort's boundaries from the last build are usable only where it wrote them
     ws.sort_prev = c->ws.base == ws.base && c->ws.bs_prev == ws.bs_prev && c->ws.sort_prev;
     // so are the cleared climb counters
@@ -491,6 +488,7 @@ static int build_tree_impl(ncorp_ctx *c, const double *x, const double *y, const
     }
     c->have_tree = true;
     c->grav_lists = false;
+    if (fresh) { c->walked = 0; c->searched = false; }
     c->n = n;
     c->last = s;
     return NCORP_OK;
@@ -634,11 +632,11 @@ static int gravity_impl(ncorp_ctx *c, const double *m, double *ax, double *ay, d
         PhaseTimer t(c, NCORP_PHASE_GWALK, s);
         ws.timing = c->timing;
         HIPCHK(c, launch_walk(ws, 0, c->prm.ncs, c->prm.ncc_pre, c->prm.ncc_post,
-                              walk_waves(c->prm), s, &c->prm));
+                              c->prm.walk_waves, s, &c->prm));
+        c->walked = 1;
     }
     {
         PhaseTimer t(c, NCORP_PHASE_M2L, s);
-        HIPCHK(c, launch_sort_long_lists(ws, s));
         HIPCHK(c, launch_m2l(ws, c->prm.p, c->prm.precision, s));
     }
     {
@@ -704,6 +702,7 @@ static int collide_impl(ncorp_ctx *c, const double *vx, const double *vy, const 
         HIPCHK(c, launch_standard_tree_collide(ws, n, c->prm.ncb_pre, c->prm.ncb_post, dt, s));
     } else {
         tree_tests = true;
+        c->searched = true;
         if (c->grav_lists) {
             // candidates from the gravity walk's lists of this tree, culled with the
             // moonlets' bounding boxes (no collision climb needed); the box pass gathers
@@ -721,6 +720,7 @@ static int collide_impl(ncorp_ctx *c, const double *vx, const double *vy, const 
             }
             HIPCHK(c, launch_walk(ws, 1, c->prm.ncs_col, c->prm.ncc_pre_col,
                                   c->prm.ncc_post_col, 0, s));
+            c->walked = 2;
             HIPCHK(c, launch_collide_pairs(ws, n, dt, false, s));
         }
     }
@@ -728,11 +728,11 @@ static int collide_impl(ncorp_ctx *c, const double *vx, const double *vy, const 
         HIPCHK(c, launch_resolve(ws, state[0], state[1], state[2], state[3], state[4], state[5],
                                  m, R, dt, c->prm.collision_f, pairs, cap, n_pairs_dev, step,
                                  &ws.st->pair_cursor, tree_tests ? ws.count_part : nullptr,
-                                 kCollideGrid, s));
+                                 collide_grid(ws), s));
     else
         HIPCHK(c, launch_emit_pairs(ws, pairs, cap, n_pairs_dev, triple, step,
                                     &ws.st->pair_cursor, tree_tests ? ws.count_part : nullptr,
-                                    kCollideGrid, s));
+                                    collide_grid(ws), s));
     c->last = s;
     return NCORP_OK;
 }
@@ -964,29 +964,65 @@ extern "C" int ncorp_get_status(ncorp_ctx *c, int64_t *required) {
     return NCORP_OK;
 }
 
+// Totals of the last walk (its classes' counters) and the lengths of the candidate
+// regions of the last collision search.
+struct WalkCounts {
+    int64_t visited = 0, m2l = 0, p2p = 0, long_m2l = 0, cand = 0;
+    int64_t busy = 0, busy_max = 0, waves = 0;
+    int32_t region[kCandRegions];
+};
+
+static int read_counts(ncorp_ctx *c, WalkCounts &w) {
+    std::vector<int32_t> v((kWalkClasses + kCandRegions) * kCtrStride);
+    HIPCHK(c, hipMemcpy(v.data(), c->ws.walk_ctr, v.size() * sizeof(int32_t),
+                        hipMemcpyDeviceToHost));
+    for (int k = 0; k < kWalkClasses && c->walked; k++) {
+        const int32_t *line = v.data() + k * kCtrStride;
+        int64_t vis;
+        std::memcpy(&vis, line + kCtrVisited, sizeof(vis));
+        w.visited += vis;
+        w.m2l += c->walked == 1 ? line[kCtrM2L] : 0;
+        w.p2p += c->walked == 1 ? line[kCtrP2P] : 0;
+        w.long_m2l += c->walked == 1 ? line[kCtrLongM2L] : 0;
+        int64_t busy, most;
+        std::memcpy(&busy, line + kCtrBusy, sizeof(busy));
+        std::memcpy(&most, line + kCtrBusyMax, sizeof(most));
+        w.busy += busy;
+        w.busy_max = most > w.busy_max ? most : w.busy_max;
+        w.waves += line[kCtrWaves];
+    }
+    for (int k = 0; k < kCandRegions; k++) {
+        w.region[k] = c->searched ? v[(kWalkClasses + k) * kCtrStride] : 0;
+        w.cand += w.region[k];
+    }
+    return NCORP_OK;
+}
+
 extern "C" int ncorp_tree_info(ncorp_ctx *c, int64_t *info) {
     if (!c || !info) return NCORP_E_INVALID;
     DevState h;
     int r = sync_state(c, h);
     if (r != NCORP_OK) return r;
+    WalkCounts w;
+    if ((r = read_counts(c, w)) != NCORP_OK) return r;
     info[NCORP_INFO_N] = c->n;
     info[NCORP_INFO_NCELLS] = h.ncells;
     info[NCORP_INFO_NLEAVES] = h.nleaves;
     info[NCORP_INFO_MAXLEVEL] = h.maxlevel;
-    info[NCORP_INFO_M2L] = h.nm2l;
-    info[NCORP_INFO_P2P] = h.np2p;
-    info[NCORP_INFO_VISITED] = h.visited;
-    info[NCORP_INFO_COL_CAND] = h.ncand;
+    info[NCORP_INFO_M2L] = w.m2l;
+    info[NCORP_INFO_P2P] = w.p2p;
+    info[NCORP_INFO_VISITED] = w.visited;
+    info[NCORP_INFO_COL_CAND] = w.cand;
     info[NCORP_INFO_COL_TESTS] = h.col_tests;
-    info[NCORP_INFO_M2L_DIR] = 2 * (int64_t)h.nm2l;
+    info[NCORP_INFO_M2L_DIR] = 2 * w.m2l;
     info[NCORP_INFO_NROOTS] = h.level_count[0];
-    info[NCORP_INFO_LONG_M2L] = h.nlong_m2l;
+    info[NCORP_INFO_LONG_M2L] = w.long_m2l;
     info[NCORP_INFO_LONG_P2P] = h.nlong_p2p;
     info[NCORP_INFO_P2P_INTER] = h.p2p_inter;
     info[NCORP_INFO_M2L_MAXLIST] = h.m2l_maxlist;
     info[NCORP_INFO_P2P_MAXLIST] = h.p2p_maxlist;
-    info[NCORP_INFO_WALK_BUSY_MAX] = h.walk_busy_max;
-    info[NCORP_INFO_WALK_BUSY_MEAN] = h.walk_busy_sum / walk_waves(c->prm);
+    info[NCORP_INFO_WALK_BUSY_MAX] = w.busy_max;
+    info[NCORP_INFO_WALK_BUSY_MEAN] = w.busy / (w.waves > 0 ? w.waves : 1);
     info[NCORP_INFO_P2P_SRC_MAX] = h.p2p_src_max;
     info[NCORP_INFO_SORT_PREV] = h.bs_prev_used;
     info[NCORP_INFO_SORT_SPILL] = h.bs_spill;
@@ -1020,6 +1056,22 @@ template <typename T>
 static int d2h(ncorp_ctx *c, std::vector<T> &v, const T *src, int64_t count) {
     v.resize(count > 0 ? count : 0);
     if (count > 0) HIPCHK(c, hipMemcpy(v.data(), src, sizeof(T) * count, hipMemcpyDeviceToHost));
+    return NCORP_OK;
+}
+
+// the first `width` (the longest length) entries of n per-target lists, packed
+static int read_rows(ncorp_ctx *c, int64_t n, const int32_t *cnt_d, const int32_t *seg,
+                     int64_t stride, std::vector<int32_t> &cnt, std::vector<int32_t> &rows,
+                     int64_t &width) {
+    int r = d2h(c, cnt, cnt_d, n);
+    if (r != NCORP_OK) return r;
+    width = 0;
+    for (int32_t k : cnt) width = k > width ? k : width;
+    if (width > stride) width = stride;
+    rows.resize(n * width);
+    if (!rows.empty())
+        HIPCHK(c, hipMemcpy2D(rows.data(), width * 4, seg, stride * 4, width * 4, n,
+                              hipMemcpyDeviceToHost));
     return NCORP_OK;
 }
 
@@ -1093,22 +1145,55 @@ extern "C" int64_t ncorp_export_host(ncorp_ctx *c, int what, void *dst, int64_t 
             std::vector<double> v; if ((r = d2h(c, v, ws.local, nc * ws.nl))) return r;
             put(v.data(), 8 * nc * ws.nl); break;
         }
-        case NCORP_EXPORT_M2L:
-        case NCORP_EXPORT_P2P:
-        case NCORP_EXPORT_COL_CAND: {
-            // copy the reserved slots and drop the gaps
-            const int2 *src = what == NCORP_EXPORT_M2L ? ws.m2l
-                              : what == NCORP_EXPORT_P2P ? ws.p2p : ws.cand;
-            const int64_t slots = what == NCORP_EXPORT_M2L ? h.m2l_slots
-                                  : what == NCORP_EXPORT_P2P ? h.p2p_slots : h.cand_slots;
-            const int64_t lcap = what == NCORP_EXPORT_M2L ? ws.m2l_cap : ws.p2p_cap;
+        case NCORP_EXPORT_M2L: {
+            // every pair stands in both cells' lists: take it from the lower cell's
+            std::vector<int32_t> cnt, rows;
+            int64_t width = 0;
+            if ((r = read_rows(c, c->walked == 1 ? nc : 0, ws.m2l_cnt, ws.m2l_seg, ws.m2l_stride,
+                               cnt, rows, width)))
+                return r;
             std::vector<int2> v;
-            if ((r = d2h(c, v, src, slots < lcap ? slots : lcap))) return r;
-            std::vector<int2> keep;
-            keep.reserve(v.size());
-            for (const int2 &q : v)
-                if (q.x >= 0) keep.push_back(q);
-            put(keep.data(), 8 * (int64_t)keep.size()); break;
+            for (int64_t A = 0; A < (int64_t)cnt.size(); A++)
+                for (int64_t k = 0; k < cnt[A] && k < width; k++)
+                    if (rows[A * width + k] > A)
+                        v.push_back(make_int2((int)A, rows[A * width + k]));
+            put(v.data(), 8 * (int64_t)v.size()); break;
+        }
+        case NCORP_EXPORT_P2P: {
+            // a cell pair (A, B) stands as B in the list of every leaf below A and as A in
+            // that of every leaf below B: take it from A's first leaf, the lower cell's
+            std::vector<int32_t> cnt, rows, ent, nent;
+            int64_t width = 0;
+            const int64_t nl = c->walked == 1 ? h.nleaves : 0;
+            if ((r = read_rows(c, nl, ws.p2p_cnt, ws.p2p_seg, ws.p2p_stride, cnt, rows, width)) ||
+                (r = d2h(c, ent, ws.c_entry, nc)) || (r = d2h(c, nent, ws.c_nent, nc)))
+                return r;
+            auto len = [&](int64_t e) { return cnt[e] < width ? (int64_t)cnt[e] : width; };
+            std::vector<int2> v;
+            for (int64_t e = 0; e < nl; e++)
+                for (int64_t k = 0; k < len(e); k++) {
+                    const int32_t B = rows[e * width + k];
+                    const int64_t f = ent[B];
+                    for (int64_t q = 0; q < len(f); q++) {
+                        const int32_t A = rows[f * width + q];
+                        if (e < ent[A] || e >= ent[A] + nent[A]) continue;
+                        if (e == ent[A] && A <= B) v.push_back(make_int2(A, B));
+                        break;
+                    }
+                }
+            put(v.data(), 8 * (int64_t)v.size()); break;
+        }
+        case NCORP_EXPORT_COL_CAND: {
+            WalkCounts w;
+            if ((r = read_counts(c, w))) return r;
+            const CandOut C = cand_out(ws);
+            std::vector<int2> v, part;
+            for (int k = 0; k < kCandRegions; k++) {
+                const int64_t len = w.region[k] < C.per ? w.region[k] : C.per;
+                if ((r = d2h(c, part, C.list + k * C.per, len))) return r;
+                v.insert(v.end(), part.begin(), part.end());
+            }
+            put(v.data(), 8 * (int64_t)v.size()); break;
         }
         default:
             return fail(c, NCORP_E_INVALID, "unknown export");

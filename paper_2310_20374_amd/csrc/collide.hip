@@ -218,13 +218,15 @@ __device__ __forceinline__ void test_cell_pair(
 // candidate slots a wave reads at a time; the cell ranges and spheres of both
 // sides of all of them are loaded in one go
 constexpr int kCandRound = 8;
+static_assert(kCandRegions == kWave && kWalkClasses == kWave, "a lane per counter line");
 
 // BOXES: the candidates are leaf pairs with bounding boxes (cbox: low corner and
 // largest reach, high corner, per cell); otherwise cell pairs with the collision
 // climb's spheres (ccell).
 template <bool BOXES>
 __global__ void __launch_bounds__(64)
-k_collide(DevState *st, const int2 *__restrict__ cand, int64_t cand_cap,
+k_collide(DevState *st, const CandOut C, const int32_t *__restrict__ walk_ctr,
+          int64_t visit_cap,
           const int32_t *__restrict__ c_first, const int32_t *__restrict__ c_count,
           const double4 *__restrict__ ccell, const double4 *__restrict__ cbox,
           const uint32_t *__restrict__ perm, const double4 *__restrict__ pcol,
@@ -236,14 +238,31 @@ k_collide(DevState *st, const int2 *__restrict__ cand, int64_t cand_cap,
         if (threadIdx.x == 0) tests_part[blockIdx.x] = 0;
         return;
     }
-    int nc = st->cand_slots;                 // candidate slots, gaps included
-    if (nc > cand_cap) nc = (int)cand_cap;
     const int lane = threadIdx.x;
+    if (!BOXES && blockIdx.x == 0) {
+        // the collision walk's visits, summed over its classes
+        unsigned long long v = *(const unsigned long long *)(walk_ctr + lane * kCtrStride +
+                                                             kCtrVisited);
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        if (lane == 0 && (int64_t)v > visit_cap) {
+            atomicOr(&st->status, (int32_t)ST_CAP_QUEUE);
+            atomicMax((unsigned long long *)&st->required, v);
+        }
+    }
+    // lane k: the candidates of region k, in rounds of kCandRound slots
+    const int my_len = C.ctr[lane * kCtrStride];
+    int nround;
+    const int my_rounds = (my_len + kCandRound - 1) / kCandRound;
+    const int my_first = wave_excl_sum_c(my_rounds, lane, nround);
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     unsigned long long tests = 0;
-    for (int q0 = blockIdx.x * kCandRound; q0 < nc; q0 += gridDim.x * kCandRound) {
+    for (int q = blockIdx.x; q < nround; q += gridDim.x) {
+        // the region of round q: the last that starts at or before it and is not empty
+        const int reg = __popcll(__ballot(my_first + my_rounds <= q));
+        const int q0 = (q - __builtin_amdgcn_readlane(my_first, reg)) * kCandRound;
+        const int len = __builtin_amdgcn_readlane(my_len, reg);
         int2 cq = make_int2(-1, -1);
-        if (lane < kCandRound && q0 + lane < nc) cq = cand[q0 + lane];
+        if (lane < kCandRound && q0 + lane < len) cq = C.list[(int64_t)reg * C.per + q0 + lane];
         // lane l < R: side A of candidate l (with B's sphere, for its cull); lane R + l:
         // side B (with A's sphere)
         const int src = lane < kCandRound ? lane : lane - kCandRound;
@@ -570,16 +589,15 @@ __global__ void k_pairs_done(DevState *st, int64_t *n_pairs_dev, int64_t cap, in
     if (triple) *cursor = base + n;
 }
 // ---------------------------------------------------------------- candidates from lists
-// Collision candidates from the gravity walk's lists of the same tree (well-separated
-// cell pairs, direct-sum cell pairs, direct-sum self cells).  Those lists cover every
-// moonlet pair exactly once, so the leaf pairs below their interactions, minus those
-// that provably cannot collide, are candidates covering every colliding pair once:
-// the pair set is the collision walk's.  A pair that touches within the step starts
-// at most R_a + R_b + dt (|v_a| + |v_b|) apart, so two cells can hold a colliding pair
-// only if their bounding boxes, each grown by its largest R + dt |v|, overlap.  A leaf's
-// box is the tight box of its moonlets (k_leaf_boxes); an interaction with an internal
-// cell is first tested on the gravity climb's spheres (cells_may_meet).  The pairs
-// inside each leaf are searched apart from the candidates (by k_collide, after them).
+// Collision candidates from the gravity walk's lists of the same tree (each leaf's
+// direct-sum sources, and the M2L partners of the leaf and its ancestors).  Those lists
+// cover every moonlet pair exactly once from either side, so the leaf pairs below their
+// entries, minus those that provably cannot collide, are candidates covering every
+// colliding pair once: the pair set is the collision walk's.  A pair that touches
+// within the step starts at most R_a + R_b + dt (|v_a| + |v_b|) apart, so two leaves can
+// hold a colliding pair only if their bounding boxes (the tight boxes of their moonlets,
+// k_leaf_boxes), each grown by its largest R + dt |v|, overlap.  The pairs inside each
+// leaf are searched apart from the candidates (by k_collide, after them).
 struct CBox {
     double lx, ly, lz, hx, hy, hz, r;
 };
@@ -595,65 +613,6 @@ __device__ __forceinline__ bool boxes_meet(const CBox &a, const CBox &b) {
 __device__ __forceinline__ CBox leaf_box(const double4 *__restrict__ cbox, int c) {
     const double4 lo = cbox[2 * (int64_t)c], hi = cbox[2 * (int64_t)c + 1];
     return CBox{lo.x, lo.y, lo.z, hi.x, hi.y, hi.z, lo.w};
-}
-
-struct BoxArgs {
-    const double4 *cbox;
-    const double4 *gcell;         // gravity climb: centre of mass (x, y, z)
-    const double *c_rmax;         // gravity climb: r_max (bounds every moonlet's distance)
-};
-
-// May cells a and b hold a colliding pair?  Their gravity climb spheres, grown by the
-// largest reach of all moonlets, must overlap: every moonlet of a cell lies within
-// r_max of its centre of mass (Eq. 11 and the corner clamp), so the pair's moonlets
-// are at least |s_a - s_b| - r_max,a - r_max,b apart.  (The walk's well-separated
-// pairs are far apart on that scale and drop here; the leaf pairs below the others
-// are then tested on their boxes.)
-__device__ __forceinline__ bool cells_may_meet(const BoxArgs &B, const DevState *st, int a,
-                                               int b) {
-    const double4 sa = B.gcell[a], sb = B.gcell[b];
-    const double r = __longlong_as_double((long long)st->reach_max);
-    const double dx = sa.x - sb.x, dy = sa.y - sb.y, dz = sa.z - sb.z;
-    const double rs = (B.c_rmax[a] + B.c_rmax[b] + 2.0 * r) * (1.0 + 1e-9);
-    return dx * dx + dy * dy + dz * dz <= rs * rs;
-}
-
-// Counts (out == nullptr) or writes the candidate leaf pairs of one interaction.
-__device__ __forceinline__ int leaf_candidates(int2 pr, const BoxArgs &B, const DevState *st,
-                                               const int32_t *__restrict__ c_entry,
-                                               const int32_t *__restrict__ c_nent,
-                                               const int32_t *__restrict__ c_count,
-                                               const int32_t *__restrict__ ent_cell, int2 *out,
-                                               int64_t pos, int64_t cap) {
-    if (pr.x < 0) return 0;
-    const bool self = pr.x == pr.y;
-    if (!self && !cells_may_meet(B, st, pr.x, pr.y)) return 0;
-    const int ea = c_entry[pr.x], na = c_nent[pr.x];
-    const int eb = c_entry[pr.y], nb = c_nent[pr.y];
-    int k = 0;
-    for (int i = 0; i < na; i++) {
-        const int la = ent_cell[ea + i];
-        const CBox sa = leaf_box(B.cbox, la);
-        // four leaves of B at a time: their loads are independent of each other
-        for (int j0 = self ? i : 0; j0 < nb; j0 += 4) {
-            int lb[4];
-            CBox sb[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++) lb[u] = j0 + u < nb ? ent_cell[eb + j0 + u] : la;
-#pragma unroll
-            for (int u = 0; u < 4; u++) sb[u] = leaf_box(B.cbox, lb[u]);
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                if (j0 + u >= nb) continue;
-                // a leaf with itself is searched by k_collide after the candidates
-                const bool take = la != lb[u] && boxes_meet(sa, sb[u]);
-                if (!take) continue;
-                if (out && pos + k < cap) out[pos + k] = make_int2(la, lb[u]);
-                k++;
-            }
-        }
-    }
-    return k;
 }
 
 // One wave per leaf: every moonlet's (x, y, z, R + dt |v|) record for the culling, the
@@ -710,11 +669,13 @@ k_leaf_boxes(DevState *st, const double *__restrict__ xs, const double *__restri
 
 // st->reach_max = the largest of the n partials
 __global__ void __launch_bounds__(1024)
-k_max_u64(const unsigned long long *__restrict__ part, int64_t n, DevState *st) {
+k_max_u64(const unsigned long long *__restrict__ part, int64_t n, DevState *st,
+          int32_t *cand_ctr) {
     __shared__ unsigned long long red[1024 / kWave];
-    // the box pass precedes every search on the gravity lists: the pair and test
-    // counts of that search start here
+    // the box pass precedes every search on the gravity lists: the pair, test and
+    // candidate counts of that search start here
     if (threadIdx.x == 0) { st->npairs = 0; st->col_tests = 0; }
+    if (threadIdx.x < kCandRegions) cand_ctr[threadIdx.x * kCtrStride] = 0;
     unsigned long long v = 0;
     for (int64_t i = threadIdx.x; i < n; i += 1024) v = part[i] > v ? part[i] : v;
     for (int o = 32; o > 0; o >>= 1) {
@@ -730,181 +691,133 @@ k_max_u64(const unsigned long long *__restrict__ part, int64_t n, DevState *st) 
     }
 }
 
+// waves of the box pass: 16384, or one per leaf slot of a small tree (the maximum over
+// its partials then reads less)
 constexpr int kBoxGrid = 16384;
 
 hipError_t launch_leaf_boxes(const Workspace &ws, int64_t n, double dt, hipStream_t s) {
     (void)n;
-    k_leaf_boxes<<<kBoxGrid, kWave, 0, s>>>(ws.st, ws.xs, ws.ys, ws.zs, ws.pack4, ws.idx, dt,
-                                            ws.ent_cell, ws.c_first, ws.c_count,
-                                            ws.cbox, ws.pcol, ws.vcol, ws.count_part);
-    k_max_u64<<<1, 1024, 0, s>>>(ws.count_part, kBoxGrid, ws.st);
+    const int64_t g = ws.leaf_cap < kBoxGrid ? ws.leaf_cap : kBoxGrid;
+    k_leaf_boxes<<<(int)g, kWave, 0, s>>>(ws.st, ws.xs, ws.ys, ws.zs, ws.pack4, ws.idx, dt,
+                                          ws.ent_cell, ws.c_first, ws.c_count,
+                                          ws.cbox, ws.pcol, ws.vcol, ws.count_part);
+    k_max_u64<<<1, 1024, 0, s>>>(ws.count_part, g, ws.st, cand_out(ws).ctr);
     return hipGetLastError();
 }
 
-constexpr int kCandBlock = 256;
-constexpr int kCandGrid = 8192;
-
-// The candidates are counted per block, the block counts scanned, and the blocks
-// write their candidates at their offsets: no contended atomics, no gaps.  Block b
-// takes list slots (r * grid + b) * kCandBlock + t, r = 0, 1, ... in both passes.
-struct CandLists {
-    const int2 *m2l, *p2p;
-    int64_t nm, total;
+struct CandArgs {
+    const DevState *st;
+    const double4 *cbox;
+    const double4 *gcell;                // gravity climb: centre of mass
+    const double *c_rmax;                // bounds every moonlet's distance from it
+    const WCell *wg;
+    const int32_t *ent_cell, *c_nent, *c_entry;
+    const int32_t *p2p_cnt, *p2p_seg, *m2l_cnt, *m2l_seg;
+    int p2p_stride, m2l_stride;
+    const float *leaf_slack;
+    const uint16_t *seg;                 // batched: disk of every tree position, else nullptr
+    const double *disk_L;
 };
 
-__device__ __forceinline__ CandLists cand_lists(const DevState *st, const int2 *m2l,
-                                                int64_t m2l_cap, const int2 *p2p,
-                                                int64_t p2p_cap) {
-    CandLists L;
-    L.m2l = m2l;
-    L.p2p = p2p;
-    L.nm = st->m2l_slots < m2l_cap ? st->m2l_slots : m2l_cap;
-    const int64_t np = st->p2p_slots < p2p_cap ? st->p2p_slots : p2p_cap;
-    L.total = L.nm + np;
-    return L;
-}
-
-// block-wide exclusive prefix of v (kCandBlock threads); returns the block total
-__device__ __forceinline__ int block_excl(int v, int &excl, int *wtot) {
-    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-    int tot;
-    const int off = wave_excl_sum_c(v, lane, tot);
-    if (lane == 0) wtot[w] = tot;
-    __syncthreads();
-    int before = 0, all = 0;
-    for (int k = 0; k < kCandBlock / kWave; k++) {
-        if (k < w) before += wtot[k];
-        all += wtot[k];
+// The candidate leaf pairs (c, l), l later than c in leaf order, below the lanes' list
+// entries B (-1: none): the leaves of B whose box meets that of the wave's leaf c.
+__device__ __forceinline__ void emit_leaves(const CandArgs &A, int c, int e, const CBox &box,
+                                            int B, int lane, int2 *buf, int &nb, int cls,
+                                            const CandOut &C, DevState *st) {
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    int eb = 0, left = 0;
+    if (B >= 0) {
+        eb = A.c_entry[B];
+        left = A.c_nent[B];
+        if (eb <= e) {                   // only leaves after e: each pair once
+            left -= e + 1 - eb;
+            eb = e + 1;
+        }
     }
-    __syncthreads();
-    excl = before + off;
-    return all;
-}
-
-__global__ void __launch_bounds__(kCandBlock)
-k_cand_count(const DevState *__restrict__ st, const int2 *__restrict__ m2l, int64_t m2l_cap,
-             const int2 *__restrict__ p2p, int64_t p2p_cap, const BoxArgs B,
-             const int32_t *__restrict__ c_entry, const int32_t *__restrict__ c_nent,
-             const int32_t *__restrict__ c_count, const int32_t *__restrict__ ent_cell,
-             int32_t *__restrict__ blk, uint64_t *__restrict__ live_bits) {
-    __shared__ int wtot[kCandBlock / kWave];
-    const CandLists L = cand_lists(st, m2l, m2l_cap, p2p, p2p_cap);
-    const bool skip = (st->status & kSkipMask) != 0;
-    int sum = 0;
-    for (int64_t q0 = (int64_t)blockIdx.x * kCandBlock; q0 < L.total && !skip;
-         q0 += (int64_t)gridDim.x * kCandBlock) {
-        const int64_t q = q0 + threadIdx.x;
-        int2 pr = make_int2(-1, -1);
-        if (q < L.total) pr = q < L.nm ? L.m2l[q] : L.p2p[q - L.nm];   // gaps are (-1, -1)
-        const int cnt = leaf_candidates(pr, B, st, c_entry, c_nent, c_count, ent_cell, nullptr,
-                                        0, 0);
-        // one bit per slot with candidates (a wave's 64 slots are one aligned word)
-        if (live_bits) {
-            const uint64_t m = __ballot(cnt > 0);
-            if ((threadIdx.x & (kWave - 1)) == 0) live_bits[(q0 + threadIdx.x) / kWave] = m;
+    while (__any(left > 0)) {
+        bool take = false;
+        int l = 0;
+        if (left > 0) {
+            l = A.ent_cell[eb];
+            take = boxes_meet(box, leaf_box(A.cbox, l));
+            eb++;
+            left--;
         }
-        int excl;
-        sum += block_excl(cnt, excl, wtot);
-    }
-    if (threadIdx.x == 0) blk[blockIdx.x] = sum;
-}
-
-// exclusive scan of the block counts (one block); the total is the candidate count
-__global__ void __launch_bounds__(1024) k_cand_scan(DevState *st, int32_t *blk, int nb) {
-    __shared__ int32_t wtot[1024 / kWave];
-    constexpr int kPer = 8;          // consecutive counts per thread: one round up to 8192
-    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-    int32_t carry = 0;
-    for (int b0 = 0; b0 < nb; b0 += 1024 * kPer) {
-        const int i0 = b0 + threadIdx.x * kPer;
-        int32_t x[kPer], sum = 0;
-#pragma unroll
-        for (int u = 0; u < kPer; u++) {
-            x[u] = i0 + u < nb ? blk[i0 + u] : 0;
-            sum += x[u];
-        }
-        int32_t v = sum;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int32_t y = __shfl_up(v, o);
-            if (lane >= o) v += y;
-        }
-        if (lane == kWave - 1) wtot[w] = v;
-        __syncthreads();
-        int32_t before = 0, all = 0;
-        for (int k = 0; k < 1024 / kWave; k++) {
-            if (k < w) before += wtot[k];
-            all += wtot[k];
-        }
-        int32_t run = carry + before + v - sum;
-#pragma unroll
-        for (int u = 0; u < kPer; u++) {
-            if (i0 + u < nb) blk[i0 + u] = run;
-            run += x[u];
-        }
-        carry += all;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        st->ncand = carry;
-        st->cand_slots = carry;
+        const uint64_t m = __ballot(take);
+        if (!m) continue;
+        if (take) buf[nb + __popcll(m & lt)] = make_int2(c, l);
+        nb += __popcll(m);
+        if (nb > kCandBuf - kWave) flush_cand(buf, nb, lane, cls, C, st);
     }
 }
 
-__global__ void __launch_bounds__(kCandBlock)
-k_cand_write(DevState *st, const int2 *__restrict__ m2l, int64_t m2l_cap,
-             const int2 *__restrict__ p2p, int64_t p2p_cap, const BoxArgs B,
-             const int32_t *__restrict__ c_entry, const int32_t *__restrict__ c_nent,
-             const int32_t *__restrict__ c_count, const int32_t *__restrict__ ent_cell,
-             const int32_t *__restrict__ blk, int2 *cand, int64_t cand_cap,
-             const uint64_t *__restrict__ live_bits) {
-    __shared__ int wtot[kCandBlock / kWave];
+constexpr int kCandWaves = 4;            // independent waves per block
+constexpr int kCandGrid = 2048;
+
+// One wave per leaf.  Its direct-sum sources give nearly all candidates.  A
+// well-separated pair lies at least slack_A + slack_B apart (slack = r_crit - r_max), so
+// the M2L lists of a leaf's chain matter only where the chain's smallest slack (formed
+// by the walk) is within twice the largest reach of any moonlet; 23 + 9 + 31 us of
+// count, scan and write passes over the cell-pair lists took 63 us before at N = 1e6.
+__global__ void __launch_bounds__(kWave * kCandWaves)
+k_cand_leaves(DevState *st, const CandArgs A, const CandOut C) {
+    __shared__ int2 bufs[kCandWaves][kCandBuf];
     if (st->status & kSkipMask) return;
-    const CandLists L = cand_lists(st, m2l, m2l_cap, p2p, p2p_cap);
-    int64_t run = blk[blockIdx.x];
-    for (int64_t q0 = (int64_t)blockIdx.x * kCandBlock; q0 < L.total;
-         q0 += (int64_t)gridDim.x * kCandBlock) {
-        const int64_t q = q0 + threadIdx.x;
-        // the count pass's bits: slots without candidates need no second look
-        const bool live = !live_bits ||
-                          ((live_bits[(q0 + threadIdx.x) / kWave] >> (threadIdx.x & (kWave - 1))) & 1ull);
-        int2 pr = make_int2(-1, -1);
-        if (q < L.total && live) pr = q < L.nm ? L.m2l[q] : L.p2p[q - L.nm];
-        const int cnt = leaf_candidates(pr, B, st, c_entry, c_nent, c_count, ent_cell, nullptr,
-                                        0, 0);
-        int excl;
-        const int all = block_excl(cnt, excl, wtot);
-        const int64_t pos = run + excl;
-        if (cnt) leaf_candidates(pr, B, st, c_entry, c_nent, c_count, ent_cell, cand, pos,
-                                 cand_cap);
-        if (cnt && pos + cnt > cand_cap) {
-            atomicOr(&st->status, (int32_t)ST_CAP_P2P);
-            atomicMax((unsigned long long *)&st->required, (unsigned long long)(pos + cnt));
+    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+    int2 *const buf = bufs[wid];
+    const int cls = (int)blockIdx.x % kCandRegions;
+    const int K = st->nleaves;
+    const double r = __longlong_as_double((long long)st->reach_max);
+    int nb = 0;
+    for (int e = blockIdx.x * kCandWaves + wid; e < K; e += gridDim.x * kCandWaves) {
+        const int c = A.ent_cell[e];
+        const CBox box = leaf_box(A.cbox, c);
+        const int np = A.p2p_cnt[e];
+        const float slack = A.leaf_slack[e];
+        const int32_t *row = A.p2p_seg + (int64_t)e * A.p2p_stride;
+        for (int q = lane; q - lane < np; q += kWave)
+            emit_leaves(A, c, e, box, q < np ? row[q] : -1, lane, buf, nb, cls, C, st);
+        const double L = A.seg ? A.disk_L[A.seg[A.wg[c].first]] : st->L;
+        const double far = 2.0 * r * (1.0 + 1e-6) + 1e-12 * L;
+        if ((double)slack > far) continue;
+        for (int a = c; a >= 0;) {
+            const WCell wa = A.wg[a];
+            const int up = wa.parent;
+            if (wa.rcrit - A.c_rmax[a] <= far) {
+                const int nm = A.m2l_cnt[a];
+                const int32_t *mrow = A.m2l_seg + (int64_t)a * A.m2l_stride;
+                for (int q = lane; q - lane < nm; q += kWave) {
+                    int B = q < nm ? mrow[q] : -1;
+                    if (B >= 0) {
+                        // B's moonlets lie within r_max of its centre of mass
+                        const double4 g = A.gcell[B];
+                        const double gx = fmax(0.0, fmax(box.lx - g.x, g.x - box.hx));
+                        const double gy = fmax(0.0, fmax(box.ly - g.y, g.y - box.hy));
+                        const double gz = fmax(0.0, fmax(box.lz - g.z, g.z - box.hz));
+                        const double rs = (A.c_rmax[B] + box.r + r) * (1.0 + 1e-9);
+                        if (gx * gx + gy * gy + gz * gz > rs * rs) B = -1;
+                    }
+                    if (__any(B >= 0)) emit_leaves(A, c, e, box, B, lane, buf, nb, cls, C, st);
+                }
+            }
+            a = up;
         }
-        run += all;
     }
+    flush_cand(buf, nb, lane, cls, C, st);
 }
 
 hipError_t launch_candidates_from_lists(const Workspace &ws, hipStream_t s) {
-    // one pass of blocks over the list slots when the lists are short enough
-    int64_t g = (ws.m2l_cap + ws.p2p_cap + kCandBlock - 1) / kCandBlock;
+    int64_t g = (ws.leaf_cap + kCandWaves - 1) / kCandWaves;
     if (g > kCandGrid) g = kCandGrid;
-    if (g < 1) g = 1;
-    BoxArgs B;
-    B.cbox = ws.cbox;
-    B.gcell = ws.gcell;
-    B.c_rmax = ws.c_rmax;
-    // one bit per list slot in the tree-order direct sums' buffer (3n words, free during
-    // a collision search), where the slots fit
-    const int64_t words = (ws.m2l_cap + ws.p2p_cap + kWave - 1) / kWave + kCandBlock / kWave;
-    uint64_t *bits = words <= 3 * ws.n_max ? (uint64_t *)ws.acc_s : nullptr;
-    k_cand_count<<<(int)g, kCandBlock, 0, s>>>(ws.st, ws.m2l, ws.m2l_cap, ws.p2p, ws.p2p_cap, B,
-                                               ws.c_entry, ws.c_nent, ws.c_count, ws.ent_cell,
-                                               ws.cand_blk, bits);
-    k_cand_scan<<<1, 1024, 0, s>>>(ws.st, ws.cand_blk, (int)g);
-    k_cand_write<<<(int)g, kCandBlock, 0, s>>>(ws.st, ws.m2l, ws.m2l_cap, ws.p2p, ws.p2p_cap, B,
-                                               ws.c_entry, ws.c_nent, ws.c_count, ws.ent_cell,
-                                               ws.cand_blk, ws.cand, ws.p2p_cap, bits);
+    CandArgs A;
+    A.st = ws.st; A.cbox = ws.cbox; A.gcell = ws.gcell; A.c_rmax = ws.c_rmax; A.wg = ws.wg;
+    A.ent_cell = ws.ent_cell; A.c_nent = ws.c_nent; A.c_entry = ws.c_entry;
+    A.p2p_cnt = ws.p2p_cnt; A.p2p_seg = ws.p2p_seg; A.m2l_cnt = ws.m2l_cnt; A.m2l_seg = ws.m2l_seg;
+    A.p2p_stride = ws.p2p_stride; A.m2l_stride = ws.m2l_stride;
+    A.leaf_slack = ws.leaf_slack;
+    A.seg = ws.ndisks > 1 ? ws.seg : nullptr;
+    A.disk_L = ws.disk_L;
+    k_cand_leaves<<<(int)g, kWave * kCandWaves, 0, s>>>(ws.st, A, cand_out(ws));
     return hipGetLastError();
 }
 
@@ -1171,18 +1084,12 @@ hipError_t launch_resolve(const Workspace &ws, double *x, double *y, double *z, 
 hipError_t launch_collide_pairs(const Workspace &ws, int64_t n, double dt, bool boxes,
                                 hipStream_t s) {
     (void)n;
-    if (!boxes) k_collide_init<<<1, 64, 0, s>>>(ws.st);   // boxes: done by the box pass
-    if (boxes) {
-        k_collide<true><<<kCollideGrid, 64, 0, s>>>(ws.st, ws.cand, ws.p2p_cap, ws.c_first,
-                                                    ws.c_count, ws.ccell, ws.cbox, ws.idx,
-                                                    ws.pcol, ws.vcol, ws.ent_cell, dt,
-                                                    ws.pairs_tmp, ws.pair_cap, ws.count_part);
-        return hipGetLastError();
-    }
-    k_collide<false><<<kCollideGrid, 64, 0, s>>>(ws.st, ws.cand, ws.p2p_cap, ws.c_first,
-                                                 ws.c_count, ws.ccell, ws.cbox, ws.idx, ws.pcol,
-                                                 ws.vcol, ws.ent_cell, dt, ws.pairs_tmp,
-                                                 ws.pair_cap, ws.count_part);
+    // the pair and test counts start at zero: cleared by the box pass or the walk's init
+    const auto kernel = boxes ? k_collide<true> : k_collide<false>;
+    kernel<<<collide_grid(ws), 64, 0, s>>>(ws.st, cand_out(ws), ws.walk_ctr, ws.queue_cap,
+                                           ws.c_first, ws.c_count, ws.ccell, ws.cbox, ws.idx,
+                                           ws.pcol, ws.vcol, ws.ent_cell, dt, ws.pairs_tmp,
+                                           ws.pair_cap, ws.count_part);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 // Interaction tensors (Eq. 25) for every well-separated pair found by the walk.
 //
-// Target-major: one wave per target cell A, lanes over A's sources B (grouped and
-// sorted by the list builder), each lane accumulating
+// Target-major: one wave per target cell A, lanes over A's sources B (in the order the
+// walk listed them, fixed by the tree), each lane accumulating
 //   C^(m)_a(s_A) += sum_{n=0, n!=1}^{p-m} (-1)^n sum_{|b|=n} D_{a+b}(R) Mt_b(B),
 // with R = s_A - s_B, D_g = d^g (1/|R|) and Mt_b = M_b / b! (the n! of Eq. 25 and
 // the multinomial weights of the symmetric inner product cancel into 1/b!).  The
@@ -91,24 +91,15 @@ __device__ __forceinline__ void m2l_pass(const double4 gA, const double4 *__rest
     }
 }
 
-// LDS of the wave-sum buffer, in ints: a target's list is sorted there first
-template <int P, typename T> constexpr int red_ints() {
-    return (int)(sizeof(T) * kWave * red_stride<P, T>() / 4) & ~3;
-}
-
 template <int P, typename T>
 __global__ void __launch_bounds__(kM2LBlock, 2)
 k_m2l(const DevState *__restrict__ st, const double4 *__restrict__ gcell,
-      const T *__restrict__ mult, const int32_t *__restrict__ cnt, int32_t *__restrict__ seg,
-      int stride, double *__restrict__ local) {
+      const T *__restrict__ mult, const int32_t *__restrict__ cnt,
+      const int32_t *__restrict__ seg, int stride, double *__restrict__ local) {
     constexpr int NL = n_local(P);
     constexpr int K1 = M2LSplit<P, T>::K1, K2 = M2LSplit<P, T>::K2;
     __shared__ __align__(16) T red[kWave * red_stride<P, T>()];
-    __shared__ int32_t s_list[kM2LListLDS];
-    extern __shared__ __align__(16) int32_t dyn[];   // sort scratch if red is too small
     if (st->status & kSkipMask) return;
-    const int need = ((stride < kM2LListLDS ? stride : kM2LListLDS) + 3) & ~3;
-    int32_t *scratch = need <= red_ints<P, T>() ? (int32_t *)red : dyn;
     const int nc = st->ncells;
     const int lane = threadIdx.x;
     for (int A = blockIdx.x; A < nc; A += gridDim.x) {
@@ -118,27 +109,7 @@ k_m2l(const DevState *__restrict__ st, const double4 *__restrict__ gcell,
             for (int k = lane; k < NL; k += kWave) out[k] = 0.0;
             continue;
         }
-        int32_t *list = seg + (int64_t)A * stride;
-        const int32_t *srcs = list;
-        if (len <= kM2LListLDS) {
-            // usual case: sorted copy in LDS
-            const int len4 = (len + 3) & ~3;
-            for (int i = lane; i < len4; i += kWave) scratch[i] = i < len ? list[i] : 0x7fffffff;
-            __syncthreads();
-            const int4 *s4 = reinterpret_cast<const int4 *>(scratch);
-            for (int i = lane; i < len; i += kWave) {
-                const int v = scratch[i];
-                int r = 0;
-                #pragma unroll 8
-                for (int j = 0; j < len4 / 4; j++) {
-                    const int4 t = s4[j];
-                    r += (t.x < v) + (t.y < v) + (t.z < v) + (t.w < v);
-                }
-                s_list[r] = v;
-            }
-            __syncthreads();
-            srcs = s_list;
-        }                                       // longer lists: sorted by the pre-pass
+        const int32_t *srcs = seg + (int64_t)A * stride;
         const double4 gA = gcell[A];
         m2l_pass<P, 1, K1, T>(gA, gcell, mult, srcs, len, out, red);
         if (K2 > K1) m2l_pass<P, (K1 < P ? K1 + 1 : P), K2, T>(gA, gcell, mult, srcs, len, out, red);
@@ -150,10 +121,8 @@ template <int P, typename T>
 static void launch_m2l_t(const Workspace &ws, const T *mult, hipStream_t s) {
     int g = (int)(ws.cell_cap < 16384 ? ws.cell_cap : 16384);
     if (g < 1) g = 1;
-    const int s4 = ((ws.m2l_stride < kM2LListLDS ? ws.m2l_stride : kM2LListLDS) + 3) & ~3;
-    const size_t dyn = s4 <= red_ints<P, T>() ? 0 : (size_t)s4 * sizeof(int32_t);
-    k_m2l<P, T><<<g, kM2LBlock, dyn, s>>>(ws.st, ws.gcell, mult, ws.m2l_cnt, ws.m2l_seg,
-                                          ws.m2l_stride, ws.local);
+    k_m2l<P, T><<<g, kM2LBlock, 0, s>>>(ws.st, ws.gcell, mult, ws.m2l_cnt, ws.m2l_seg,
+                                        ws.m2l_stride, ws.local);
 }
 
 template <int P>

@@ -49,8 +49,6 @@ enum StatusBits : int32_t {
 };
 // Any of these leaves the tree or the interaction lists incomplete: later passes
 // then do nothing rather than follow indices that were never written.
-// persistent walk: waves, and list slots a wave reserves at a time (the plain
-// cell-pair lists carry up to kWalkWaves * kListChunk slots of gaps)
 // items per tile of the radix sort's passes (the workspace sizes its histograms by it)
 constexpr int kSortTileItems = 2048;
 // bucket sort of a plain tree build: buckets of kBucketMean moonlets on average, a
@@ -64,32 +62,40 @@ constexpr int kBucketTile = 2048;
 // the previous build's keys at every kSubStride-th rank split each bucket again
 constexpr int kSubStride = 8;
 constexpr int kWalkBlock = 256;
-// persistent blocks: the gravity walk runs 1024 waves, the collision walk (less
-// work per item) 512; more only adds contention on the queue counters
-constexpr int kWalkGridGravity = 256;
-constexpr int kWalkGridCollide = 128;
-constexpr int kWalkWaves = kWalkGridGravity * kWalkBlock / kWave;
 constexpr int kWalkWavesMax = 2048;       // the largest walk_waves
-// persistent waves of the gravity walk under these parameters
-inline int walk_waves(const ncorp_params &p) { return p.walk_waves > 0 ? p.walk_waves : kWalkWaves; }
-constexpr int kListChunk = 256;
-// the walk's tail shares a 64-bit word with the processed count (32 bits each); an
-// item pushes at most 36 children, so a queue of this many slots keeps the tail
-// below 2^32 even when it overflows
+// a walk deals its cells in runs of kWalkRun to kWalkClasses classes of waves
+constexpr int kWalkRun = 8;
+constexpr int kWalkClasses = 64;
+// Counters of a walk, one 128-byte line per class (kCtrStride words): the ticket, the
+// entries taken of the shared list space (the first kXcds lines), and the class's part
+// of the pairs visited, well separated and summed directly, of the long M2L lists and,
+// in timing runs, of its waves' busy cycles (sum, maximum, waves).
+constexpr int kCtrTicket = 0, kCtrSpace = 2, kCtrVisited = 4, kCtrM2L = 6, kCtrP2P = 7,
+              kCtrLongM2L = 8, kCtrBusy = 10, kCtrBusyMax = 12, kCtrWaves = 14;
+// the collision candidates lie in kCandRegions equal parts of their list, each with a
+// counter line of its own after the walk's
+constexpr int kCandRegions = 64;
+constexpr int kCandBuf = 2 * kWave;       // candidates a wave stages before it takes room
+// hand-down entries a cell keeps in a slot of its own
+constexpr int64_t kWalkInline = 64;
+// the plain cell-pair lists carry this many slots on top of the caller's capacity
+// (256 for each of the walk_waves asked for, 1024 by default, 512 at least)
+inline int64_t list_slack(const ncorp_params &p) {
+    return 256ll * (p.walk_waves > 0 ? (p.walk_waves > 512 ? p.walk_waves : 512) : 1024);
+}
+// most cell pairs a walk may visit (queue_capacity)
 constexpr int64_t kMaxQueue = 100000000;
 // workspace bytes per colliding-pair slot: two key buffers, contact time, state
 constexpr int64_t kPairBytes = 8 + 8 + 8 + 4;
 
-// per-target interaction lists: default and largest slot counts (a consumer
-// sorts a whole list in LDS)
+// per-target interaction lists: default and largest slot counts
 constexpr int kDefaultM2LPerCell = 2048;
 constexpr int kDefaultP2PPerLeaf = 4096;
 constexpr int kMaxPerTarget = 8192;
-// lists up to these lengths are sorted in LDS by their consumer; longer ones (the
-// walk records them) by a pre-pass of kSortLongBlocks single-wave blocks per kind
+// M2L lists beyond this length are counted as long (NCORP_INFO_LONG_M2L); direct-sum
+// lists beyond one LDS batch of their consumer are recorded by the walk and split
 constexpr int kM2LListLDS = 512;
 constexpr int kP2PListLDS = kWave;
-constexpr int kSortLongBlocks = 1024;
 // direct sums of a leaf with a long source list are split over kLongSlots waves
 // (kLongGrid extra four-wave blocks); their partial sums meet in p2p_part
 constexpr int kLongSlots = 8;
@@ -115,21 +121,14 @@ struct DevState {
     double max_abs;            // max |coordinate| (bit pattern max for >= 0 doubles)
     int32_t ndisks, nroots;    // disks of the call; level-0 cells (non-empty disks)
     // gravity walk
-    int32_t nm2l, np2p;        // unordered cell pairs (exact counts)
-    int32_t m2l_slots, p2p_slots;  // list slots reserved (entries plus (-1,-1) gaps)
     int32_t m2l_maxlist, p2p_maxlist;  // longest per-target lists (timing runs only)
-    int32_t nlong_m2l, nlong_p2p;      // lists longer than their consumer's LDS sort
-    int64_t visited;
+    int32_t nlong_p2p;         // direct-sum lists longer than kP2PListLDS
     // collision walk
-    int32_t ncand, cand_slots;
     int64_t col_tests;
     int64_t npairs;            // colliding pairs found (may exceed capacity)
     int64_t pair_cursor;       // pairs already written by earlier steps of ncorp_step
     int64_t p2p_inter;         // directed moonlet pairs (i != j) of the direct sums
-    // load balance of the last gravity evaluation (timing runs only): busy cycles of
-    // the gravity walk's waves (sum and max over the persistent waves) and the most
-    // source moonlets any leaf's direct sums take
-    int64_t walk_busy_sum, walk_busy_max;
+    // the most source moonlets any leaf's direct sums take (timing runs only)
     int64_t p2p_src_max;
     // collisions: the largest R + dt |v| of any moonlet (bit pattern of a double >= 0)
     unsigned long long reach_max;
@@ -187,25 +186,29 @@ struct MeshState {
     int32_t pad[3];
 };
 
-// Work-queue state of a persistent walk; each counter on its own 128-byte line.
+__device__ __forceinline__ int32_t *walk_ctr(int32_t *ctr, int cls, int what) {
+    return ctr + cls * kCtrStride + what;
+}
+
+// Collision candidates (cell pairs) of a pass: kCandRegions regions of `per` slots.
+struct CandOut {
+    int2 *list;
+    int32_t *ctr;              // first counter line
+    int64_t per;
+};
+
+// What a walk's init pass hands the walk.
 struct WalkQueue {
-    uint64_t head;             // next slot to claim
-    uint64_t pad0[15];
-    uint64_t tp;               // next slot to reserve (high 32 bits) and items
-                               // processed (low 32 bits), updated by one atomic
-    uint64_t pad1[15];
-    uint64_t pad2[16];
-    uint32_t epoch;            // tag of the last walk's items (advanced on the device)
-    uint32_t epoch_next;       // tag of this walk's items (written by its init pass)
-    uint32_t pad3[30];
+    int32_t ncells;            // cells to walk: 0 after a failed build
+    int32_t pad[127];
 };
 
 // What the walk reads of a cell, one 64-byte line: centre, critical radius,
 // moonlet count, first child, number of children (0 for a leaf), first leaf and
-// number of leaves below it.
+// number of leaves below it, first moonlet, parent (-1: a root).
 struct alignas(64) WCell {
     double x, y, z, rcrit;
-    int32_t count, child, nchild, entry, nent, first, pad[2];
+    int32_t count, child, nchild, entry, nent, first, parent, pad;
 };
 
 // Waves of a multi-wave block that work independently synchronise their own LDS
@@ -217,27 +220,31 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Sorts a per-target list list[0..len) ascending, in place in global memory (its
-// values are distinct).  Called by a whole single-wave block; scratch is LDS of at
-// least round_up(len, 4) ints, 16-byte aligned.  Ends with a block barrier, so the
-// wave's later loads see the sorted list.
-__device__ __forceinline__ void sort_target_list(int32_t *list, int len, int32_t *scratch) {
-    const int lane = threadIdx.x;
-    const int len4 = (len + 3) & ~3;
-    for (int i = lane; i < len4; i += kWave) scratch[i] = i < len ? list[i] : 0x7fffffff;
-    __syncthreads();
-    const int4 *s4 = reinterpret_cast<const int4 *>(scratch);
-    for (int i = lane; i < len; i += kWave) {
-        const int v = scratch[i];
-        int r = 0;
-        #pragma unroll 8
-        for (int j = 0; j < len4 / 4; j++) {
-            const int4 t = s4[j];
-            r += (t.x < v) + (t.y < v) + (t.z < v) + (t.w < v);
+// Puts the n staged pairs of a wave into region r of the list, or the next with room,
+// and empties the stage.
+__device__ __forceinline__ void flush_cand(const int2 *buf, int &n, int lane, int r,
+                                           const CandOut &C, DevState *st) {
+    if (n == 0) return;
+    int t = 0;
+    for (; t < kCandRegions; t++) {
+        const int x = (r + t) % kCandRegions;
+        int old = 0;
+        if (lane == 0) old = atomicAdd(C.ctr + x * kCtrStride, n);
+        old = __builtin_amdgcn_readfirstlane(old);
+        if (old >= 0 && (int64_t)old + n <= C.per) {
+            wave_sync();
+            for (int i = lane; i < n; i += kWave) C.list[(int64_t)x * C.per + old + i] = buf[i];
+            wave_sync();
+            break;
         }
-        list[r] = v;
+        if (lane == 0) atomicSub(C.ctr + x * kCtrStride, n);       // no room: taken back
     }
-    __syncthreads();
+    if (t == kCandRegions && lane == 0) {
+        atomicOr(&st->status, (int32_t)ST_CAP_P2P);
+        atomicMax((unsigned long long *)&st->required,
+                  (unsigned long long)(C.per * kCandRegions + n));
+    }
+    n = 0;
 }
 
 // ---------------------------------------------------------------- workspace
@@ -286,14 +293,16 @@ struct Workspace {
     WCell *wg = nullptr, *wc = nullptr;               // walk records: gravity, collisions
     double *c_crmax = nullptr;
     // walks
-    uint64_t *queue = nullptr;
+    uint64_t *queue = nullptr;                        // a walk's hand-down lists
     WalkQueue *wq = nullptr;
-    int2 *m2l = nullptr, *p2p = nullptr;              // unordered cell pairs
+    int2 *p2p = nullptr;                              // room of p2p_cap pairs (list space)
     int2 *cand = nullptr;                             // collision candidate cell pairs
-    // per-target lists written by the gravity walk (unordered; consumers sort)
+    int32_t *walk_ctr = nullptr;                      // counter lines (walk, candidates)
+    float *leaf_slack = nullptr;                      // per leaf: slack of its chain (walk)
+    // per-target lists written by the gravity walk
     int32_t *m2l_cnt = nullptr, *m2l_seg = nullptr;   // by target cell, m2l_stride slots
     int32_t *p2p_cnt = nullptr, *p2p_seg = nullptr;   // by target leaf, p2p_stride slots
-    int32_t *long_m2l = nullptr, *long_p2p = nullptr; // targets of over-long lists
+    int32_t *long_p2p = nullptr;                      // leaves with a long direct-sum list
     double *p2p_part = nullptr;                       // kLongSlots x 3 x n partial sums
     int32_t *cnt_a = nullptr;                         // tree-build level counters
     int64_t *pairs_tmp = nullptr;                     // colliding pairs (i<<32|j)
@@ -303,7 +312,6 @@ struct Workspace {
     double *pair_dt = nullptr;
     int32_t *pair_flag = nullptr;
     int32_t *mbest = nullptr, *mmatch = nullptr;
-    int32_t *cand_blk = nullptr;                      // per-block candidate counts
     // scratch for scans and sorts
     int32_t *scan_part = nullptr;                     // block partials
     uint32_t *hist = nullptr;                         // radix histograms
@@ -348,7 +356,6 @@ struct Workspace {
     int64_t count_part_n = 0;
     DevState *st = nullptr;
     bool timing = false;                              // phase timing on: load-balance counters
-    bool clear_queue = false;                         // new buffer: clear before next walk
     bool clear_mesh = false;                          // new buffer: clear the mesh state
     // the climbs' arrival and leaf counters are zero: the last tree build's cell-range
     // pass cleared them and no climb has run since
@@ -399,11 +406,9 @@ hipError_t launch_collision_climb(const Workspace &ws, int64_t n, double dt, hip
 // walk: mode 0 gravity (M2L + P2P lists), 1 collisions (candidate list in p2p)
 // rcrit_prm (gravity walk): its init pass also forms the opening angles and critical
 // radii the climb left out
-hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_post, int waves,
+hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_post, int most,
                        hipStream_t s, const ncorp_params *rcrit_prm = nullptr);
 hipError_t launch_count_interactions(const Workspace &ws, hipStream_t s);
-// sorts, in place, the per-target lists longer than the consumers sort in LDS
-hipError_t launch_sort_long_lists(const Workspace &ws, hipStream_t s);
 
 hipError_t launch_m2l(const Workspace &ws, int p, int precision, hipStream_t s);
 hipError_t launch_l2l(const Workspace &ws, int p, hipStream_t s);
@@ -427,8 +432,17 @@ hipError_t launch_standard_tree(const Workspace &ws, int64_t n, int p, int ncb_p
                                 double *ax, double *ay, double *az, hipStream_t s);
 // blocks of the tree's pair tests (one wave each): each leaves its number of examined
 // pairs in ws.count_part (at least 33 920 entries at any n), which the pair ranking that
-// follows adds to st->col_tests
+// follows adds to st->col_tests.  A small tree has few candidates: two blocks a leaf
+// slot (5 us for the 265 leaves of 2000 moonlets, where 32768 empty blocks took 13).
 constexpr int kCollideGrid = 32768;
+inline int collide_grid(const Workspace &ws) {
+    const int64_t g = 2 * ws.leaf_cap;
+    return (int)(g < 256 ? 256 : (g > kCollideGrid ? kCollideGrid : g));
+}
+// the list of collision candidates and its counters
+inline CandOut cand_out(const Workspace &ws) {
+    return CandOut{ws.cand, ws.walk_ctr + kWalkClasses * kCtrStride, ws.p2p_cap / kCandRegions};
+}
 hipError_t launch_collide_pairs(const Workspace &ws, int64_t n, double dt, bool boxes,
                                 hipStream_t s);
 hipError_t launch_leaf_boxes(const Workspace &ws, int64_t n, double dt, hipStream_t s);

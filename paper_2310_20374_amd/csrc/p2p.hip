@@ -77,19 +77,64 @@ __device__ __forceinline__ void leaf_local_order(int cl, const int32_t *__restri
     for (int k = 0; k < NC; k++) out[cidx(M, 0, 0) + k] = acc[k];
 }
 
+// The gravity walk's totals (its classes' counter lines, one per lane) against the
+// capacities the caller gave; later passes stop on a list that is too long.
+struct WalkCaps {
+    int64_t visited, m2l, p2p;
+};
+__device__ __forceinline__ void walk_totals(DevState *st, const int32_t *ctr,
+                                            const WalkCaps &caps) {
+    static_assert(kWalkClasses == kWave, "a lane per class");
+    const int lane = threadIdx.x & (kWave - 1);
+    unsigned long long v = *(const unsigned long long *)(ctr + lane * kCtrStride + kCtrVisited);
+    long long m = ctr[lane * kCtrStride + kCtrM2L], p = ctr[lane * kCtrStride + kCtrP2P];
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        v += __shfl_xor(v, o);
+        m += __shfl_xor(m, o);
+        p += __shfl_xor(p, o);
+    }
+    if (lane != 0) return;
+    int32_t bits = 0;
+    unsigned long long need = 0;
+    if ((int64_t)v > caps.visited) { bits |= ST_CAP_QUEUE; need = v; }
+    if (m > caps.m2l) { bits |= ST_CAP_M2L; need = (unsigned long long)m > need ? m : need; }
+    if (p > caps.p2p) { bits |= ST_CAP_P2P; need = (unsigned long long)p > need ? p : need; }
+    if (bits) {
+        atomicOr(&st->status, bits);
+        atomicMax((unsigned long long *)&st->required, need);
+    }
+}
+
 template <int P>
 __global__ void __launch_bounds__(128)
-k_leaf_local(const DevState *__restrict__ st, const int32_t *__restrict__ ent_cell,
+k_leaf_local(DevState *st, const int32_t *__restrict__ ent_cell,
              const int32_t *__restrict__ c_parent, const double4 *__restrict__ gcell,
              const double *__restrict__ local, const int32_t *__restrict__ m2l_cnt,
-             double *__restrict__ cleaf) {
+             double *__restrict__ cleaf, const int32_t *__restrict__ p2p_cnt,
+             int32_t *__restrict__ longs, const int32_t *__restrict__ walk_ctr,
+             const WalkCaps caps) {
     constexpr int NL = n_local(P);
+    if (blockIdx.x == 0 && threadIdx.x < kWave) walk_totals(st, walk_ctr, caps);
     if (st->status & kSkipMask) return;
     const int K = st->nleaves;
     const int64_t total = (int64_t)K * P;
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
          t += (int64_t)gridDim.x * blockDim.x) {
         const int m = (int)(t / K) + 1, e = (int)(t % K);
+        if (m == 1) {
+            // leaves whose direct sums are split over several waves, one atomic per wave
+            const bool lng = p2p_cnt[e] > kP2PListLDS;
+            const uint64_t act = __ballot(1), ml = __ballot(lng);
+            if (ml) {
+                const int lane = threadIdx.x & (kWave - 1);
+                const int lead = __ffsll((unsigned long long)act) - 1;
+                int base = 0;
+                if (lane == lead) base = atomicAdd(&st->nlong_p2p, __popcll(ml));
+                base = __shfl(base, lead);
+                const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+                if (lng) longs[base + __popcll(ml & lt)] = e;
+            }
+        }
         const int cl = ent_cell[e];
         double *out = cleaf + (int64_t)e * NL;
         switch (m) {
@@ -380,10 +425,10 @@ __device__ __forceinline__ void p2p_targets_any(int ntc, int tmax, int tb, bool 
 }
 
 constexpr int kP2PWaves = 4;        // independent waves per block
-static_assert(kP2PListLDS == kP2PSrc, "one LDS batch holds a list the pre-pass leaves unsorted");
+static_assert(kP2PListLDS == kP2PSrc, "one LDS batch holds a list that is not split");
 
 // Direct sums of every leaf, one wave per work item.  A leaf whose source list fits
-// one LDS batch is one item.  A leaf whose list is longer (the pre-pass sorted it)
+// one LDS batch is one item.  A leaf whose list is longer (the descent recorded it)
 // would keep a single wave busy long after all others finished, so it is split over
 // kLongSlots items: item `slot` takes the batches slot, slot + kLongSlots, ... and
 // writes its partial sums to part[slot], which the evaluation kernel adds in slot
@@ -396,18 +441,16 @@ k_p2p(const DevState *__restrict__ st, const double *__restrict__ xs,
       const double *__restrict__ mus, const int32_t *__restrict__ ent_cell,
       const int32_t *__restrict__ c_first, const int32_t *__restrict__ c_count,
       const double4 *__restrict__ gcell, const int32_t *__restrict__ p2p_cnt,
-      int32_t *__restrict__ p2p_seg, int stride, const int32_t *__restrict__ longs,
+      const int32_t *__restrict__ p2p_seg, int stride, const int32_t *__restrict__ longs,
       double *__restrict__ part, double *__restrict__ acc_s, int64_t n, int tmax) {
     using V = typename Vec4<T>::type;
-    static_assert(TILE >= 128 && TILE % 64 == 0, "the tile doubles as the sort's scratch");
+    static_assert(TILE % 64 == 0, "a tile is staged one moonlet per lane");
     __shared__ __align__(16) V tiles[kP2PWaves][TILE];
     __shared__ int32_t firsts[kP2PWaves][kP2PSrc], prefs[kP2PWaves][kP2PSrc + 1];
     if (st->status & kSkipMask) return;
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     V *tile = tiles[wid];
     int32_t *s_first = firsts[wid], *s_pref = prefs[wid];
-    // the tile doubles as sort scratch before any moonlet is staged
-    int32_t *scratch = reinterpret_cast<int32_t *>(tile);
     const int K = st->nleaves;
     const int nlong = st->nlong_p2p * kLongSlots;
     for (int w = blockIdx.x * kP2PWaves + wid; w < nlong + K; w += gridDim.x * kP2PWaves) {
@@ -432,32 +475,41 @@ k_p2p(const DevState *__restrict__ st, const double *__restrict__ xs,
         const int c = ent_cell[e];
         const int f = c_first[c], nt = c_count[c];
         const double4 g = gcell[c];
-        int32_t *list = p2p_seg + (int64_t)e * stride;
+        const int32_t *list = p2p_seg + (int64_t)e * stride;
         const int len = p2p_cnt[e];
         if (len > kP2PSrc) continue;                  // split into the items above
         wave_sync();                                  // this wave's LDS is free again
-        // one batch: rank the sources in LDS and place each source's moonlet range
-        // at its rank directly
-        const int v = lane < len ? list[lane] : 0x7fffffff;
-        const int cf = lane < len ? c_first[v] : 0;
-        const int cn = lane < len ? c_count[v] : 0;
-        scratch[lane] = v;
-        wave_sync();
-        if (lane < len) {
-            const int4 *s4 = reinterpret_cast<const int4 *>(scratch);
-            int rk = 0;
+        int tot1;
+        if constexpr (sizeof(T) == 8) {
+            // one batch, in the walk's order
+            const int v = lane < len ? list[lane] : 0;
+            s_first[lane] = lane < len ? c_first[v] : 0;
+            tot1 = batch_prefix(lane < len ? c_count[v] : 0, s_pref, lane);
+        } else {
+            // one batch, in cell order (the FP32 tile sums are rounded in that order):
+            // rank the sources in LDS and place each source's moonlet range at its rank
+            const int v = lane < len ? list[lane] : 0x7fffffff;
+            const int cf = lane < len ? c_first[v] : 0;
+            const int cn = lane < len ? c_count[v] : 0;
+            int32_t *scratch = reinterpret_cast<int32_t *>(tile);   // no moonlet staged yet
+            scratch[lane] = v;
+            wave_sync();
+            if (lane < len) {
+                const int4 *s4 = reinterpret_cast<const int4 *>(scratch);
+                int rk = 0;
 #pragma unroll
-            for (int j = 0; j < kP2PSrc / 4; j++) {
-                const int4 t = s4[j];
-                rk += (t.x < v) + (t.y < v) + (t.z < v) + (t.w < v);
+                for (int j = 0; j < kP2PSrc / 4; j++) {
+                    const int4 t = s4[j];
+                    rk += (t.x < v) + (t.y < v) + (t.z < v) + (t.w < v);
+                }
+                s_first[rk] = cf;
+                s_pref[rk] = cn;
             }
-            s_first[rk] = cf;
-            s_pref[rk] = cn;
+            wave_sync();
+            const int c1 = lane < len ? s_pref[lane] : 0;
+            wave_sync();
+            tot1 = batch_prefix(c1, s_pref, lane);
         }
-        wave_sync();
-        const int c1 = lane < len ? s_pref[lane] : 0;
-        wave_sync();
-        const int tot1 = batch_prefix(c1, s_pref, lane);
         wave_sync();
         for (int t0 = 0; t0 < nt; t0 += kWave) {
             const int ntc = nt - t0 < kWave ? nt - t0 : kWave;
@@ -552,7 +604,9 @@ static void launch_leaf_local(const Workspace &ws, hipStream_t s) {
     if (g > 8192) g = 8192;
     if (g < 1) g = 1;
     k_leaf_local<P><<<(int)g, 128, 0, s>>>(ws.st, ws.ent_cell, ws.c_parent, ws.gcell, ws.local,
-                                           ws.m2l_cnt, ws.cleaf);
+                                           ws.m2l_cnt, ws.cleaf, ws.p2p_cnt, ws.long_p2p,
+                                           ws.walk_ctr,
+                                           WalkCaps{ws.queue_cap, ws.m2l_cap, ws.p2p_cap});
 }
 
 hipError_t launch_l2l(const Workspace &ws, int p, hipStream_t s) {
@@ -566,6 +620,41 @@ hipError_t launch_l2l(const Workspace &ws, int p, hipStream_t s) {
         default: break;
     }
     return hipGetLastError();
+}
+
+// Direct-sum lists beyond one LDS batch, sorted in place, one block per list (rank sort
+// in LDS, the keys split over four waves).  Only the FP32 form needs it: its tile sums
+// are rounded in cell order.
+constexpr int kSortThreads = 256;
+constexpr int kSortLongBlocks = 2048;
+
+__global__ void __launch_bounds__(kSortThreads)
+k_sort_long_lists(const DevState *__restrict__ st, const int32_t *__restrict__ cnt,
+                  int32_t *seg, int stride, const int32_t *__restrict__ longs) {
+    extern __shared__ __align__(16) int32_t scr[];   // round_up(stride, 4) ints
+    if (st->status & kSkipMask) return;
+    const int nl = st->nlong_p2p;
+    for (int q = blockIdx.x; q < nl; q += gridDim.x) {
+        const int t = longs[q];
+        const int len = cnt[t];
+        int32_t *list = seg + (int64_t)t * stride;
+        const int len4 = (len + 3) & ~3;
+        __syncthreads();
+        for (int i = threadIdx.x; i < len4; i += kSortThreads)
+            scr[i] = i < len ? list[i] : 0x7fffffff;
+        __syncthreads();
+        const int4 *s4 = reinterpret_cast<const int4 *>(scr);
+        for (int i = threadIdx.x; i < len; i += kSortThreads) {
+            const int v = scr[i];
+            int r = 0;
+            #pragma unroll 8
+            for (int j = 0; j < len4 / 4; j++) {
+                const int4 w = s4[j];
+                r += (w.x < v) + (w.y < v) + (w.z < v) + (w.w < v);
+            }
+            list[r] = v;
+        }
+    }
 }
 
 template <typename T, int TILE>
@@ -592,7 +681,12 @@ static void launch_p2p_tile(const Workspace &ws, int64_t n, int tile, int tmax, 
 hipError_t launch_p2p(const Workspace &ws, int64_t n, int precision, int tile, int tmax,
                       hipStream_t s) {
     const int tm = tmax > 0 ? tmax : 4;
-    if (precision == NCORP_FP32_BULK) launch_p2p_tile<float>(ws, n, tile, tm, s);
+    if (precision == NCORP_FP32_BULK) {
+        const size_t lds = (size_t)((ws.p2p_stride + 3) & ~3) * sizeof(int32_t);
+        k_sort_long_lists<<<kSortLongBlocks, kSortThreads, lds, s>>>(ws.st, ws.p2p_cnt, ws.p2p_seg,
+                                                                     ws.p2p_stride, ws.long_p2p);
+        launch_p2p_tile<float>(ws, n, tile, tm, s);
+    }
     else launch_p2p_tile<double>(ws, n, tile, tm, s);
     return hipGetLastError();
 }

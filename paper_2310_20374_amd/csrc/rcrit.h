@@ -35,7 +35,7 @@ struct RcritArgs {
     double *c_theta;
     double theta_min;
     int theta_mode;                  // 1: constant theta_min
-    const int32_t *c_count, *c_child, *c_nchild, *c_entry, *c_nent, *c_first;
+    const int32_t *c_count, *c_child, *c_nchild, *c_entry, *c_nent, *c_first, *c_parent;
     WCell *wg;
     const uint16_t *seg;             // batched: disk of every tree position, else nullptr
     const int32_t *disk_root;
@@ -47,6 +47,7 @@ inline RcritArgs rcrit_args(const Workspace &ws, const ncorp_params &prm) {
     R.theta_min = prm.theta_min; R.theta_mode = prm.theta_mode;
     R.c_count = ws.c_count; R.c_child = ws.c_child; R.c_nchild = ws.c_nchild;
     R.c_entry = ws.c_entry; R.c_nent = ws.c_nent; R.c_first = ws.c_first;
+    R.c_parent = ws.c_parent;
     R.wg = ws.wg;
     R.seg = ws.ndisks > 1 ? ws.seg : nullptr;
     R.disk_root = ws.disk_root;
@@ -67,7 +68,7 @@ __device__ inline void rcrit_cell(const RcritArgs &R, int c) {
     w.x = g.x; w.y = g.y; w.z = g.z; w.rcrit = rc;
     w.count = R.c_count[c]; w.child = R.c_child[c]; w.nchild = R.c_nchild[c];
     w.entry = R.c_entry[c]; w.nent = R.c_nent[c]; w.first = R.c_first[c];
-    w.pad[0] = w.pad[1] = 0;
+    w.parent = R.c_parent[c]; w.pad = 0;
     R.wg[c] = w;
 }
 

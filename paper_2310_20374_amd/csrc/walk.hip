@@ -1,539 +1,504 @@
-// The falcON dual tree walk (Alg. 2) on the GPU.
+// The falcON dual tree walk (Alg. 2) on the GPU, one wave per target cell.
 //
-// The paper's recursion (run iteratively from a stack) becomes one persistent
-// launch over a global work queue of cell pairs.  Every wave claims 128 queue
-// slots, polls them until their items appear, classifies each pair exactly as
-// Alg. 2 does (self pair / brute force before the opening test / well separated /
-// brute force after it / split the cell with the larger critical radius) and
-// pushes the child pairs with one wave-aggregated atomic on the tail.  Termination:
-// the tail and the count of processed items share one 64-bit word, and a wave
-// reserves its items' children and counts those items as processed in the same
-// atomic, so processed <= tail at every moment, with equality only when no item
-// is waiting or being worked on.  A wave that finds no work reads the word; if
-// the two halves are equal the walk is over (the tail can only grow from an item
-// not yet counted as processed, and there is none).  A wave that polls for too long without progress latches
-// ST_WALK_STALL and leaves, so the kernel always ends.
+// The paper's recursion visits unordered pairs of cells from (root, root) down.  Here
+// every cell A works through the pairs that hold it, by itself: its wave takes the
+// pairs its parent left to be opened on the parent's side, classifies each (A, B)
+// exactly as Alg. 2 does (self pair / brute force before the opening test / well
+// separated / brute force after it / split the cell with the larger critical radius)
+// and
+//   - where B is split, goes on with (A, B's children) at once, from a stack in LDS;
+//   - where A is split, leaves B in A's hand-down list, which A's children start from;
+//   - where the pair is well separated or summed directly, appends B to A's own lists.
+// Classification is symmetric in A and B bit for bit (sums, squares and comparisons
+// that commute, and ties broken by which cell holds the earlier moonlets), so the wave
+// of B takes the same decision on the same pair: the pairs are those of the recursion,
+// each seen once from either side.  That doubles the classifications, which are
+// cheap, and makes every list the property of one wave: no queue, no atomic and no
+// sort of a list whose order would depend on timing.  A cell's lists come out in an
+// order fixed by the tree alone.
 //
-// Pairs classified by the walk do not depend on the order of processing, so the
-// lists equal those of the recursive walk.  Besides the plain lists of cell pairs
-// the gravity walk appends every pair to per-target lists (each well-separated
-// pair to both cells' M2L lists, each direct-sum pair to the direct-sum lists of
-// every leaf below either cell).  Their order depends on timing; the consumers
-// sort a list before using it, so every sum is independent of the walk's timing.
+// The cells are dealt in runs of 8 (siblings mostly) to kWalkClasses classes and taken
+// in breadth-first order within each, by the waves of that class, from a ticket counter
+// (atomics on one address take about 15 ns each, so counters are many and nothing else
+// is counted per cell).  A wave waits until its cell's parent has published its list;
+// a class hands out its cells in ascending order and a parent precedes its children,
+// so the lowest unfinished cell never waits on an unclaimed one and the launch ends.  A
+// wave that polls for too long without progress latches ST_WALK_STALL and leaves.
+//
+// What bounds it: the chain of levels, about 6 us each (the parent's list, one or two
+// rounds of cell loads, publication), and for large or deep trees the rounds' loads.
+// A queue of cell pairs with atomics on its head and tail and on every list took 283 us
+// at N = 1e6 (s = 96, p = 6), 244 us at 1e5 (s = 52) and 1030 us for 2.6e5 moonlets in
+// leaves of 17; this takes 88, 57 and 176 us, and no list needs a sort afterwards.
 #include "ncorp_internal.h"
 #include "rcrit.h"
 
 namespace ncorp {
 
-constexpr uint64_t kSpinLimit = 1ull << 20;    // empty polls in a row before giving up
-
-__device__ __forceinline__ uint64_t make_item(uint32_t epoch, int a, int b) {
-    return ((uint64_t)(epoch & 0xffffu) << 48) | ((uint64_t)(uint32_t)a << 24) | (uint32_t)b;
-}
+constexpr uint32_t kSpinLimit = 1u << 20;    // empty polls in a row before giving up
 
 __device__ __forceinline__ uint64_t ld_relaxed(const uint64_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
-__device__ __forceinline__ int wave_excl_sum(int v, int lane, int &total) {
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int t = __shfl_up(x, o);
-        if (lane >= o) x += t;
-    }
-    total = __shfl(x, kWave - 1);
-    return x - v;
+__device__ __forceinline__ int32_t ld_relaxed(const int32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_relaxed(int32_t *p, int32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Every walk tags its items with a fresh 16-bit tag, advanced on the device, so a
-// captured and replayed sequence of walks never meets a stale item carrying its own
-// tag.  The init pass derives the walk's tag from the last walk's (which nothing
-// writes while it runs) and leaves it in epoch_next, which the walk reads and copies
-// to epoch.  When the tag wraps (or the host asks, for a new buffer) the init pass
-// clears the queue.
-__device__ __forceinline__ uint32_t next_epoch(uint32_t e, bool &wrap) {
-    uint32_t n = (e + 1u) & 0xffffu;
-    wrap = n == 0u;
-    return wrap ? 1u : n;
-}
-
-// Resets the queue (one root pair (r, r) per tree of the forest) and, for the
-// gravity walk, the per-target list counters; with do_rcrit also the cells' opening
-// angles, critical radii and walk records (the gravity climb then leaves them out).
-__global__ void k_walk_init(DevState *st, WalkQueue *wq, uint64_t *queue, int64_t qcap,
-                            int mode, int32_t *m2l_cnt, int32_t *p2p_cnt, int force_clear,
-                            const RcritArgs R, int do_rcrit) {
+// Sets up a walk: hand-down headers empty, counters at zero; with do_rcrit also the
+// cells' opening angles, critical radii and walk records (the gravity climb then leaves
+// them out).
+__global__ void k_walk_init(DevState *st, WalkQueue *wq, uint64_t *hdr, int32_t *ctr, int nctr,
+                            int mode, const RcritArgs R, int do_rcrit) {
     const int nc = st->ncells;
-    bool wrap = false;
-    const uint32_t epoch = next_epoch(wq->epoch, wrap);
     const bool go = nc > 0 && !(st->status & kSkipMask);
-    const int nroots = go ? st->level_count[0] : 0;
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
-    if (do_rcrit && go)
-        for (int64_t c = gid; c < nc; c += gstride) rcrit_cell(R, (int)c);
-    if (wrap || force_clear)
-        for (int64_t i = nroots + gid; i < qcap; i += gstride) queue[i] = 0ull;
-    if (mode == 0 && m2l_cnt) {
-        const int nl = st->nleaves;
-        for (int64_t i = gid; i < nc || i < nl; i += gstride) {
-            if (i < nc) m2l_cnt[i] = 0;
-            if (i < nl) p2p_cnt[i] = 0;
+    if (go)
+        for (int64_t c = gid; c < nc; c += gstride) {
+            hdr[c] = 0ull;
+            if (do_rcrit) rcrit_cell(R, (int)c);
         }
-    }
-    for (int64_t r = gid; r < nroots; r += gstride)
-        __hip_atomic_store(&queue[r], make_item(epoch, (int)r, (int)r), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+    for (int64_t t = gid; t < nctr; t += gstride) ctr[t] = 0;
     if (gid != 0) return;
-    wq->epoch_next = epoch;
-    wq->head = 0;
+    wq->ncells = go ? nc : 0;
     if (mode == 0) {
-        st->nm2l = 0; st->np2p = 0; st->m2l_slots = 0; st->p2p_slots = 0; st->visited = 0;
-        st->nlong_m2l = 0; st->nlong_p2p = 0;
-        st->walk_busy_sum = 0; st->walk_busy_max = 0;
+        st->nlong_p2p = 0;
     } else {
-        st->ncand = 0; st->cand_slots = 0;
+        st->npairs = 0; st->col_tests = 0;      // of the search on this walk's candidates
     }
-    wq->tp = (uint64_t)nroots << 32;
+}
+
+// Per-wave LDS.  kStack bounds the open pairs of a cell: a round is cut down until
+// what it pushes leaves kStackFree entries, and below that the walk is depth first on
+// one pair (at most 7 more entries a level, 21 levels).
+constexpr int kStack = 640;
+constexpr int kStackFree = 160;
+static_assert(7 * kMaxDepth < kStackFree, "a depth-first descent must fit");
+constexpr int kDown = 256;                   // hand-down entries staged
+struct WalkLds {
+    int32_t stack[kStack];
+    int32_t down[kDown];
+};
+template <int MODE> struct WalkPairs { int2 p[kCandBuf]; };      // collisions: candidates staged
+template <> struct WalkPairs<0> { int2 p[1]; };
+
+// A hand-down list is published as one 64-bit header per cell: valid | inline | slack
+// (16 bits, see below) | entry count (12 bits) | offset (32 bits) of its last segment in
+// the list space.  A list of
+// up to WalkArgs.inl entries sits in the cell's own slot of inl entries; a longer one
+// in segments of the shared space, each preceded by the offset and size of the one
+// before it (offset -1: none).  An entry is a cell B, with kDownDirect set where (A, B)
+// is a direct-sum pair that every leaf below A inherits.
+constexpr int32_t kDownDirect = (int32_t)0x80000000;
+__device__ __forceinline__ uint64_t down_header(bool inl, uint32_t slack16, int n, uint32_t off) {
+    return (1ull << 63) | ((uint64_t)(inl ? 1 : 0) << 62) | ((uint64_t)slack16 << 44) |
+           ((uint64_t)n << 32) | off;
+}
+// The smallest r_crit - r_max of a cell and its ancestors, as the upper half of a float,
+// rounded towards zero: the moonlets of a cell and of any well-separated partner are at
+// least that far apart, which spares the collision search most M2L lists.
+__device__ __forceinline__ uint32_t slack_bits(double v) {
+    return v > 0.0 ? (uint32_t)__float_as_int(__double2float_rz(v)) >> 16 : 0u;
 }
 
 struct WalkArgs {
     DevState *st;
     WalkQueue *wq;
-    uint64_t *queue;
-    int64_t qcap;
-    const WCell *cell;
+    const WCell *__restrict__ cell;
     int ncs, ncc_pre, ncc_post;
-    int2 *m2l, *p2p;                     // outputs (p2p = candidates in collision mode)
-    int64_t m2l_cap, p2p_cap;
-    int32_t *nm2l, *np2p;                // exact counts
-    int32_t *m2l_slots, *p2p_slots;      // reserved slots
-    uint32_t epoch;                      // this walk's tag, read at kernel start
-    // gravity: per-target lists
+    uint64_t *hdr;                       // hand-down header of every cell
+    int32_t *space;                      // hand-down lists: inl entries a cell, then shared
+    int32_t *ctr;                        // counters of the classes (walk_ctr)
+    int inl;
+    int64_t shared0, shared_n;           // shared part: kXcds regions of shared_n entries
+    int64_t visit_cap;                   // most pairs a walk may visit
+    CandOut cand;                        // collisions: candidate cell pairs
+    // gravity: per-target lists; per leaf, the slack of its chain
     int32_t *m2l_cnt, *m2l_seg, *p2p_cnt, *p2p_seg;
-    int32_t *long_m2l, *long_p2p;        // targets whose list outgrew the LDS sort
     int m2l_stride, p2p_stride;
+    const double *c_rmax;
+    float *leaf_slack;
     int timing;                          // record the waves' busy cycles
 };
 
-// Stores v at slot k of target t's list (slot order is arbitrary); k came from
-// the target's counter.  The append that makes a list longer than `lds` (what its
-// consumer sorts in LDS) records the target in `longs`, for the pre-pass that sorts
-// such lists.
-__device__ __forceinline__ void store_slot(int k, int32_t *seg, int stride, int t, int v,
-                                           int lds, int32_t *nlong, int32_t *longs,
-                                           DevState *st) {
-    if (k == lds) longs[atomicAdd(nlong, 1)] = t;
-    if (k < stride) {
-        seg[(int64_t)t * stride + k] = v;
-    } else {
-        atomicOr(&st->status, (int32_t)ST_CAP_LISTS);
-        atomicMax((unsigned long long *)&st->required, (unsigned long long)(k + 1));
-    }
+__device__ __forceinline__ void latch_cap(DevState *st, int32_t bit, int64_t need) {
+    atomicOr(&st->status, bit);
+    atomicMax((unsigned long long *)&st->required, (unsigned long long)need);
 }
 
-// A wave's current block of kListChunk slots of a plain cell-pair list.
-struct Chunk {
-    int64_t base;
-    int fill;
-    int total;                 // entries this wave emitted (published at exit)
-};
-
-// Marks the unused rest of a chunk as gaps (-1, -1).
-__device__ __forceinline__ void close_chunk(const Chunk &ch, int lane, int2 *list, int64_t cap) {
-    if (ch.base < 0) return;
-    for (int i = ch.fill + lane; i < kListChunk; i += kWave)
-        if (ch.base + i < cap) list[ch.base + i] = make_int2(-1, -1);
+// n entries of the shared list space, from this XCD's region or the next with room;
+// returns their offset, or -1 (latched) when no region has any.
+__device__ __forceinline__ int64_t take_space(const WalkArgs &A, int xcd, int n, int lane) {
+    for (int t = 0; t < kXcds; t++) {
+        const int x = (xcd + t) % kXcds;
+        int old = 0;
+        if (lane == 0) old = atomicAdd(walk_ctr(A.ctr, x, kCtrSpace), n);
+        old = __builtin_amdgcn_readfirstlane(old);
+        if (old >= 0 && (int64_t)old + n <= A.shared_n)
+            return A.shared0 + (int64_t)x * A.shared_n + old;
+        if (lane == 0) atomicSub(walk_ctr(A.ctr, x, kCtrSpace), n);   // no room: taken back
+    }
+    if (lane == 0) latch_cap(A.st, ST_CAP_QUEUE, 2 * A.visit_cap);
+    return -1;
 }
 
-// Appends the lanes' flagged pairs to a plain list.  Atomics on one shared
-// address are the walk's main cost, so the slot counter is touched once per
-// kListChunk entries and the exact count only once per wave, at exit.
-__device__ __forceinline__ void emit(bool flag, int a, int b, int lane, Chunk &ch,
-                                     int32_t *slots, int2 *list, int64_t cap, DevState *st,
-                                     int32_t bit) {
-    const uint64_t m = __ballot(flag);
-    if (!m) return;
-    const int k = __popcll(m);
-    if (ch.fill + k > kListChunk) {
-        close_chunk(ch, lane, list, cap);
-        int32_t nb = 0;
-        if (lane == 0) nb = atomicAdd(slots, (int32_t)kListChunk);
-        nb = __shfl(nb, 0);
-        ch.base = nb;
-        ch.fill = 0;
-        if (lane == 0 && (int64_t)nb + kListChunk > cap) {
-            atomicOr(&st->status, bit);
-            atomicMax((unsigned long long *)&st->required,
-                      (unsigned long long)((int64_t)nb + kListChunk));
-        }
+// Writes the staged hand-down entries as a segment after (poff, pn), which it replaces.
+__device__ __forceinline__ void flush_down(const WalkArgs &A, int xcd, const int32_t *down, int &n,
+                                           int lane, int &poff, int &pn) {
+    const int64_t off = take_space(A, xcd, n + 2, lane);
+    if (off >= 0) {
+        wave_sync();
+        if (lane < 2) st_relaxed(&A.space[off + lane], lane == 0 ? poff : pn);
+        for (int i = lane; i < n; i += kWave) st_relaxed(&A.space[off + 2 + i], down[i]);
+        wave_sync();
+        poff = (int)off;
+        pn = n;
     }
-    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    if (flag) {
-        const int64_t pos = ch.base + ch.fill + __popcll(m & lt);
-        if (pos < cap) list[pos] = make_int2(a, b);
-    }
-    ch.fill += k;
-    ch.total += k;
+    n = 0;
 }
-
-// One cell pair, classified as Alg. 2 does.
-struct Item {
-    int kind;                  // 0 nothing, 1 well separated (M2L), 2 direct sum
-    int split;                 // children to push: 1 self pair, 2 split A, 3 split B
-    int npush;
-    int a, b, na, nb, ca, cb;  // cells, their child counts and first children
-    int ea, la, eb, lb;        // first leaf and number of leaves below a and b
-};
 
 template <int MODE>
-__device__ __forceinline__ Item classify(bool valid, uint64_t item, const WalkArgs &A,
-                                         int ncells) {
-    Item it = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    if (!valid) return it;
-    int a = (int)((item >> 24) & 0xffffffu);
-    int b = (int)(item & 0xffffffu);
-    if (a >= ncells || b >= ncells) {                   // cannot happen; never follow it
-        atomicOr(&A.st->status, (int32_t)ST_BAD_ITEM);
-        a = b = 0;
-    }
-    it.a = a;
-    it.b = b;
-    const WCell wa = A.cell[a];
-    it.na = wa.nchild;
-    it.ca = wa.child;
-    it.ea = wa.entry;
-    it.la = wa.nent;
-    if (a == b) {
-        if (wa.count <= A.ncs || it.na == 0) it.kind = 2;
-        else { it.split = 1; it.npush = it.na * (it.na + 1) / 2; }
-        return it;
-    }
-    const WCell wb = A.cell[b];
-    it.nb = wb.nchild;
-    it.cb = wb.child;
-    it.eb = wb.entry;
-    it.lb = wb.nent;
-    const int64_t prod = (int64_t)wa.count * (int64_t)wb.count;
-    if (prod < (int64_t)A.ncc_pre) {
-        it.kind = 2;
-    } else {
-        const double dx = wa.x - wb.x, dy = wa.y - wb.y, dz = wa.z - wb.z;
-        const double d = sqrt(dx * dx + dy * dy + dz * dz);
-        if (wa.rcrit + wb.rcrit <= d) {
-            it.kind = MODE == 0 ? 1 : 0;                 // collisions: nothing
-        } else if (prod < (int64_t)A.ncc_post || (it.na == 0 && it.nb == 0)) {
-            it.kind = 2;
-        } else if (it.nb == 0 || (it.na != 0 && wa.rcrit > wb.rcrit)) {
-            it.split = 2; it.npush = it.na;
-        } else {
-            it.split = 3; it.npush = it.nb;
-        }
-    }
-    return it;
-}
-
-// Stores an item's child pairs at queue slots my, my+1, ...
-__device__ __forceinline__ void push_children(const Item &it, uint64_t my, const WalkArgs &A) {
-    int j = 0;
-    if (it.split == 1) {
-        for (int x = 0; x < it.na; x++)
-            for (int y = x; y < it.na; y++, j++)
-                if (my + j < (uint64_t)A.qcap)
-                    __hip_atomic_store(&A.queue[my + j], make_item(A.epoch, it.ca + x, it.ca + y),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else if (it.split == 2) {
-        for (; j < it.na; j++)
-            if (my + j < (uint64_t)A.qcap)
-                __hip_atomic_store(&A.queue[my + j], make_item(A.epoch, it.ca + j, it.b),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else if (it.split == 3) {
-        for (; j < it.nb; j++)
-            if (my + j < (uint64_t)A.qcap)
-                __hip_atomic_store(&A.queue[my + j], make_item(A.epoch, it.a, it.cb + j),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
-// The per-target lists of the gravity walk (see the file header).  A lane's items
-// make a stream of appends -- a well-separated pair one to each cell's M2L list, a
-// direct-sum pair one to the list of every leaf below either cell -- whose counter
-// atomics are issued kAppendBatch at a time, so their latencies overlap.
-constexpr int kAppendBatch = 8;
-
-template <int IPL>
-__device__ __forceinline__ void append_targets(const Item (&it)[IPL], const WalkArgs &A) {
-    int nreq[IPL], ea[IPL], nla[IPL], eb[IPL];
-    int total = 0;
-#pragma unroll
-    for (int k = 0; k < IPL; k++) {
-        ea[k] = eb[k] = nla[k] = 0;
-        int nlb = 0;
-        if (it[k].kind == 2) {
-            ea[k] = it[k].ea;
-            nla[k] = it[k].la;
-            if (it[k].a != it[k].b) {
-                eb[k] = it[k].eb;
-                nlb = it[k].lb;
-            }
-        }
-        nreq[k] = it[k].kind == 1 ? 2 : (it[k].kind == 2 ? nla[k] + nlb : 0);
-        total += nreq[k];
-    }
-    for (int r0 = 0; r0 < total; r0 += kAppendBatch) {
-        int slot[kAppendBatch], tgt[kAppendBatch], val[kAppendBatch];
-        bool p2p[kAppendBatch];
-#pragma unroll
-        for (int q = 0; q < kAppendBatch; q++) {
-            int r = r0 + q, k = 0;
-#pragma unroll
-            for (int m = 0; m + 1 < IPL; m++)
-                if (k == m && r >= nreq[m]) { r -= nreq[m]; k = m + 1; }
-            int t = 0, v = 0;
-            bool isp = false;
-#pragma unroll
-            for (int m = 0; m < IPL; m++) {
-                if (m != k) continue;
-                if (it[m].kind == 1) {
-                    t = r == 0 ? it[m].a : it[m].b;
-                    v = r == 0 ? it[m].b : it[m].a;
-                } else {
-                    isp = true;
-                    t = r < nla[m] ? ea[m] + r : eb[m] + (r - nla[m]);
-                    v = r < nla[m] ? it[m].b : it[m].a;
-                }
-            }
-            tgt[q] = t;
-            val[q] = v;
-            p2p[q] = isp;
-            slot[q] = r0 + q < total ? atomicAdd(isp ? &A.p2p_cnt[t] : &A.m2l_cnt[t], 1) : 0;
-        }
-#pragma unroll
-        for (int q = 0; q < kAppendBatch; q++) {
-            if (r0 + q >= total) continue;
-            if (p2p[q])
-                store_slot(slot[q], A.p2p_seg, A.p2p_stride, tgt[q], val[q], kP2PListLDS,
-                           &A.st->nlong_p2p, A.long_p2p, A.st);
-            else
-                store_slot(slot[q], A.m2l_seg, A.m2l_stride, tgt[q], val[q], kM2LListLDS,
-                           &A.st->nlong_m2l, A.long_m2l, A.st);
-        }
-    }
-}
-
-// Every wave claims kWave * kItemsPerLane queue slots at a time (lane l takes slots
-// l, l + 64, ...), so the shared counters are touched once per that many items.
-constexpr int kItemsPerLane = 2;
-
-template <int MODE>
-__global__ void __launch_bounds__(kWalkBlock) k_walk(WalkArgs A0) {
-    constexpr int IPL = kItemsPerLane;
-    WalkArgs A = A0;
-    A.epoch = A0.wq->epoch_next;
-    if (blockIdx.x == 0 && threadIdx.x == 0) A0.wq->epoch = A.epoch;   // nothing here reads it
+__global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
+    constexpr int WPB = kWalkBlock / kWave;
+    __shared__ WalkLds lds_all[WPB];
+    __shared__ WalkPairs<MODE> pairs_all[WPB];
+    __shared__ unsigned long long s_visited, s_busy, s_busymax;
+    __shared__ int s_m2l, s_p2p, s_longm, s_left;
     const int lane = threadIdx.x % kWave;
-    WalkQueue *wq = A.wq;
-    const int ncells = A.st->ncells;
-    const uint32_t tag = A.epoch & 0xffffu;
+    WalkLds &W = lds_all[threadIdx.x / kWave];
+    int2 *const pbuf = pairs_all[threadIdx.x / kWave].p;
+    if (threadIdx.x == 0) { s_visited = s_busy = s_busymax = 0; s_m2l = s_p2p = s_longm = 0; s_left = WPB; }
+    __syncthreads();
+    const int nc = A.wq->ncells;
+    const int cls = (int)blockIdx.x % kWalkClasses, xcd = cls % kXcds;
+    int32_t *ticket = walk_ctr(A.ctr, cls, kCtrTicket);
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const long long t_start = (MODE == 0 && A.timing) ? clock64() : 0;
-    uint64_t spins = 0;
-    int64_t visited = 0;
-    bool finished = false;
-    Chunk cm = {-1, kListChunk, 0}, cp = {-1, kListChunk, 0};
-    while (!finished) {
-        uint64_t base = 0;
-        if (lane == 0)
-            base = atomicAdd((unsigned long long *)&wq->head, (unsigned long long)(kWave * IPL));
-        base = __shfl(base, 0);
-        // every later claim lies beyond the queue too: this wave can get no more work
-        if (base >= (uint64_t)A.qcap) break;
-        uint64_t slot[IPL];
-        bool pending[IPL];
-        bool any_pending = false;
-#pragma unroll
-        for (int k = 0; k < IPL; k++) {
-            slot[k] = base + lane + (uint64_t)k * kWave;
-            pending[k] = slot[k] < (uint64_t)A.qcap;
-            any_pending = any_pending || pending[k];
-        }
-        while (__any(any_pending)) {
-            bool valid[IPL];
-            uint64_t item[IPL];
-            bool any_valid = false;
-#pragma unroll
-            for (int k = 0; k < IPL; k++) {
-                item[k] = pending[k] ? ld_relaxed(&A.queue[slot[k]]) : 0;
-                valid[k] = pending[k] && (uint32_t)(item[k] >> 48) == tag;
-                any_valid = any_valid || valid[k];
-            }
-            if (!__any(any_valid)) {
-                // nothing arrived: the walk is over once every pushed item has
-                // been processed (slots beyond the queue were never written).  Idle
-                // waves read the shared word only every 8th empty poll and sleep longer
-                // the longer they find nothing, so the working waves' atomics on it
-                // and their loads meet less traffic.
-                int done = 0;
-                if ((spins & 7) == 0 && lane == 0) {
-                    const uint64_t v = __hip_atomic_load(&wq->tp, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
-                    const uint64_t pr = v & 0xffffffffull;
-                    uint64_t t = v >> 32;
-                    if (t > (uint64_t)A.qcap) t = (uint64_t)A.qcap;
-                    done = pr >= t;
-                }
-                done = __shfl(done, 0);
-                if (done) { finished = true; break; }
-                if (++spins > kSpinLimit) {
-                    if (lane == 0) atomicOr(&A.st->status, (int32_t)ST_WALK_STALL);
-                    finished = true;
+    unsigned long long visited = 0;
+    int nm2l = 0, np2p = 0, nlongm = 0;           // pairs of the cells taken; long M2L lists
+    int npb = 0;                                  // candidates staged
+    int nxt = 0;
+    if (lane == 0) nxt = atomicAdd(ticket, 1);
+    for (;;) {
+        const int i = __builtin_amdgcn_readlane(nxt, 0);
+        const int64_t c64 = ((int64_t)(i / kWalkRun) * kWalkClasses + cls) * kWalkRun + i % kWalkRun;
+        if (i < 0 || c64 >= nc) break;
+        if (lane == 0) nxt = atomicAdd(ticket, 1);   // the next ticket, in flight meanwhile
+        const int c = (int)c64;
+        const WCell wa = A.cell[c];
+        const int par = wa.parent;
+        const bool leaf = wa.nchild == 0;
+        int top = 0;                              // open pairs on the stack
+        uint32_t slack = 0;
+        if (MODE == 0) slack = slack_bits(wa.rcrit - A.c_rmax[c]);
+        int64_t in_off = 0;                       // entries of the parent's list left to take
+        int in_n = 0, in_prev = -1;
+        int in_prev_n = 0;
+        if (par < 0) {
+            if (lane == 0) W.stack[0] = c;
+            top = 1;
+        } else {
+            uint64_t h = 0;
+            uint32_t spins = 0;
+            for (;;) {
+                h = ld_relaxed(&A.hdr[par]);
+                if (__builtin_amdgcn_readfirstlane((int)(uint32_t)(h >> 32)) != 0 ||
+                    ++spins > kSpinLimit)
                     break;
-                }
-                const int nap = spins < 4 ? 1 : (spins < 16 ? 4 : 16);
-                for (int z = 0; z < nap; z++) __builtin_amdgcn_s_sleep(4);
-                continue;
+                if (spins < 16) __builtin_amdgcn_s_sleep(4);
+                else __builtin_amdgcn_s_sleep(16);
             }
-            spins = 0;
-            Item it[IPL];
-            int npush = 0;
-#pragma unroll
-            for (int k = 0; k < IPL; k++) {
-                it[k] = classify<MODE>(valid[k], item[k], A, ncells);
-                npush += it[k].npush;
+            const uint32_t hl = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)h);
+            const uint32_t hh = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(h >> 32));
+            if (hh == 0) {                        // waited too long
+                if (lane == 0) atomicOr(&A.st->status, (int32_t)ST_WALK_STALL);
+                break;
             }
-            int nproc = 0;
-#pragma unroll
-            for (int k = 0; k < IPL; k++) nproc += __popcll(__ballot(valid[k]));
-            // ---------------- push children and retire this round's items (one
-            // atomic per wave: tail += children, processed += items)
-            int tot_push;
-            const int off = wave_excl_sum(npush, lane, tot_push);
-            if (tot_push > 0) {
-                uint64_t pbase = 0;
-                if (lane == 0)
-                    pbase = atomicAdd((unsigned long long *)&wq->tp,
-                                      ((unsigned long long)tot_push << 32) +
-                                          (unsigned long long)nproc) >> 32;
-                pbase = __shfl(pbase, 0);
-                uint64_t my = pbase + (uint64_t)off;
-#pragma unroll
-                for (int k = 0; k < IPL; k++) {
-                    push_children(it[k], my, A);
-                    my += (uint64_t)it[k].npush;
-                }
-                if (pbase + (uint64_t)tot_push > (uint64_t)A.qcap && lane == 0) {
-                    atomicOr(&A.st->status, (int32_t)ST_CAP_QUEUE);
-                    atomicMax((unsigned long long *)&A.st->required,
-                              (unsigned long long)(pbase + tot_push));
-                }
-            } else if (lane == 0) {
-                __hip_atomic_fetch_add(&wq->tp, (uint64_t)nproc, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-            }
-            // ---------------- interaction lists
-#pragma unroll
-            for (int k = 0; k < IPL; k++) {
-                if (MODE == 0)
-                    emit(it[k].kind == 1, it[k].a, it[k].b, lane, cm, A.m2l_slots, A.m2l,
-                         A.m2l_cap, A.st, ST_CAP_M2L);
-                emit(it[k].kind == 2, it[k].a, it[k].b, lane, cp, A.p2p_slots, A.p2p, A.p2p_cap,
-                     A.st, ST_CAP_P2P);
-            }
-            if (MODE == 0 && A.m2l_cnt) append_targets<IPL>(it, A);
-            visited += nproc;
-            any_pending = false;
-#pragma unroll
-            for (int k = 0; k < IPL; k++) {
-                pending[k] = pending[k] && !valid[k];
-                any_pending = any_pending || pending[k];
+            in_n = (int)(hh & 0xfffu);
+            const uint32_t ps = (hh >> 12) & 0xffffu;
+            slack = ps < slack ? ps : slack;
+            if (hh & 0x40000000u) {
+                in_off = (int64_t)par * A.inl;
+            } else if (in_n > 0) {
+                in_off = (int64_t)hl + 2;
+                in_prev = __builtin_amdgcn_readfirstlane(ld_relaxed(&A.space[hl]));
+                in_prev_n = __builtin_amdgcn_readfirstlane(ld_relaxed(&A.space[hl + 1]));
             }
         }
+        int nm = 0, np = 0, nd = 0;               // own lists, staged hand-down entries
+        int seg_off = -1, seg_n = 0;              // last hand-down segment written
+        int32_t *const mrow = MODE == 0 ? A.m2l_seg + (int64_t)c * A.m2l_stride : nullptr;
+        int32_t *const prow = MODE == 0 ? A.p2p_seg + (int64_t)wa.entry * A.p2p_stride : nullptr;
+        for (;;) {
+            // ---- take entries of the parent's list while the stack is short
+            if (top < kWave && (in_n > 0 || in_prev >= 0)) {
+                if (in_n == 0) {                  // the segment before this one
+                    const int o = in_prev;
+                    in_n = in_prev_n;
+                    in_off = (int64_t)o + 2;
+                    in_prev = __builtin_amdgcn_readfirstlane(ld_relaxed(&A.space[o]));
+                    in_prev_n = __builtin_amdgcn_readfirstlane(ld_relaxed(&A.space[o + 1]));
+                }
+                const int m = in_n < 4 * kWave ? in_n : 4 * kWave;
+                int32_t e[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    e[u] = u * kWave + lane < m ? ld_relaxed(&A.space[in_off + u * kWave + lane]) : 0;
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    if (u * kWave + lane < m) W.stack[top + u * kWave + lane] = e[u];
+                top += m;
+                in_off += m;
+                in_n -= m;
+            }
+            if (top == 0) break;
+            wave_sync();
+            // ---- classify up to 64 open pairs (A, B)
+            int k = top < kWave ? top : kWave;
+            int kind = 0, B = 0, child = 0, npush = 0, tot = 0, off = 0;
+            int32_t down = 0;
+            for (;;) {
+                kind = 0; npush = 0; down = 0; B = -1; child = 0;
+                if (lane < k) {
+                    const int32_t v = W.stack[top - 1 - lane];
+                    B = v & 0x7fffffff;
+                    if ((uint32_t)B >= (uint32_t)nc) {    // cannot happen; never follow it
+                        atomicOr(&A.st->status, (int32_t)ST_BAD_ITEM);
+                        B = -1;
+                    } else if (v < 0) {
+                        kind = 3;                         // a direct-sum pair of an ancestor
+                        down = v;
+                    } else if (B == c) {
+                        if (wa.count <= A.ncs || leaf) { kind = 2; down = B | kDownDirect; }
+                        else { kind = 4; down = B; }
+                    } else {
+                        const WCell wb = A.cell[B];
+                        child = wb.child;
+                        if (B == par) {
+                            kind = 5;                     // the parent's self pair: all siblings
+                            npush = wb.nchild;
+                        } else {
+                            const int64_t prod = (int64_t)wa.count * (int64_t)wb.count;
+                            if (prod < (int64_t)A.ncc_pre) {
+                                kind = 2;
+                            } else {
+                                const double dx = wa.x - wb.x, dy = wa.y - wb.y, dz = wa.z - wb.z;
+                                const double d = sqrt(dx * dx + dy * dy + dz * dz);
+                                if (wa.rcrit + wb.rcrit <= d) {
+                                    kind = 1;
+                                } else if (prod < (int64_t)A.ncc_post ||
+                                           (leaf && wb.nchild == 0)) {
+                                    kind = 2;
+                                } else {
+                                    // Alg. 2 opens the first of the pair (the one with
+                                    // the earlier moonlets) if the second is a leaf or
+                                    // has the smaller critical radius, else the second
+                                    const bool early = wa.first < wb.first;
+                                    const int n1 = early ? wa.nchild : wb.nchild;
+                                    const int n2 = early ? wb.nchild : wa.nchild;
+                                    const double r1 = early ? wa.rcrit : wb.rcrit;
+                                    const double r2 = early ? wb.rcrit : wa.rcrit;
+                                    const bool open1 = n2 == 0 || (n1 != 0 && r1 > r2);
+                                    if (open1 == early) { kind = 4; down = B; }
+                                    else { kind = 6; npush = wb.nchild; }
+                                }
+                            }
+                            if (kind == 2) down = B | kDownDirect;
+                        }
+                    }
+                }
+                int x = npush;                    // wave prefix sum of the pushes
+#pragma unroll
+                for (int o = 1; o < kWave; o <<= 1) {
+                    const int t = __shfl_up(x, o);
+                    if (lane >= o) x += t;
+                }
+                tot = __builtin_amdgcn_readlane(x, kWave - 1);
+                off = x - npush;
+                if (k == 1 || top - k + tot <= kStack - kStackFree) break;
+                k = k > 4 ? k / 4 : 1;
+            }
+            wave_sync();
+            top -= k;
+            for (int q = 0; q < npush; q++) W.stack[top + off + q] = child + q;
+            top += tot;
+            visited += __popcll(__ballot(B >= 0 && kind != 3 && kind != 5 && c <= B));
+            // ---- A's own lists
+            if (MODE == 0) {
+                const uint64_t m1 = __ballot(kind == 1);
+                if (m1) {
+                    const int pos = nm + __popcll(m1 & lt);
+                    if (kind == 1 && pos < A.m2l_stride) mrow[pos] = B;
+                    nm += __popcll(m1);
+                    nm2l += __popcll(__ballot(kind == 1 && c < B));
+                }
+            }
+            const bool direct = kind == 2 || (MODE == 0 && kind == 3);
+            const uint64_t m2 = __ballot(direct);
+            if (m2) {
+                if (MODE == 0 && leaf) {
+                    const int pos = np + __popcll(m2 & lt);
+                    if (direct && pos < A.p2p_stride) prow[pos] = B;
+                    np += __popcll(m2);
+                }
+                const uint64_t mo = __ballot(kind == 2 && c <= B);   // once per unordered pair
+                np2p += __popcll(mo);
+                if (MODE == 1) {
+                    if (kind == 2 && c <= B) pbuf[npb + __popcll(mo & lt)] = make_int2(c, B);
+                    npb += __popcll(mo);
+                    if (npb > kCandBuf - kWave) flush_cand(pbuf, npb, lane, cls, A.cand, A.st);
+                }
+            }
+            const bool todown = kind == 4 || (MODE == 0 && direct && !leaf);
+            const uint64_t md = __ballot(todown);
+            if (md) {
+                if (nd + __popcll(md) > kDown) flush_down(A, xcd, W.down, nd, lane, seg_off, seg_n);
+                if (todown) W.down[nd + __popcll(md & lt)] = down;
+                nd += __popcll(md);
+            }
+        }
+        // ---- publish: the children may start
+        if (!leaf) {
+            uint64_t h;
+            if (seg_off < 0 && nd <= A.inl) {
+                wave_sync();
+                for (int q = lane; q < nd; q += kWave)
+                    st_relaxed(&A.space[(int64_t)c * A.inl + q], W.down[q]);
+                h = down_header(true, slack, nd, 0u);
+            } else {
+                if (nd > 0) flush_down(A, xcd, W.down, nd, lane, seg_off, seg_n);
+                h = down_header(false, slack, seg_off < 0 ? 0 : seg_n,
+                                seg_off < 0 ? 0u : (uint32_t)seg_off);
+            }
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0);        // the entries are stored
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            if (lane == 0)
+                __hip_atomic_store(&A.hdr[c], h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (MODE == 0) {
+            if (lane == 0) {
+                A.m2l_cnt[c] = nm;
+                if (leaf) {
+                    A.p2p_cnt[wa.entry] = np;
+                    A.leaf_slack[wa.entry] = __int_as_float((int)(slack << 16));
+                }
+                if (nm > A.m2l_stride) latch_cap(A.st, ST_CAP_LISTS, nm);
+                if (np > A.p2p_stride) latch_cap(A.st, ST_CAP_LISTS, np);
+            }
+            if (nm > kM2LListLDS) nlongm++;
+        }
+        wave_sync();
     }
-    if (MODE == 0) close_chunk(cm, lane, A.m2l, A.m2l_cap);
-    close_chunk(cp, lane, A.p2p, A.p2p_cap);
+    if (MODE == 1) flush_cand(pbuf, npb, lane, cls, A.cand, A.st);
     if (lane == 0) {
-        if (MODE == 0 && cm.total) atomicAdd(A.nm2l, cm.total);
-        if (cp.total) atomicAdd(A.np2p, cp.total);
-    }
-    if (lane == 0 && visited)
-        atomicAdd((unsigned long long *)&A.st->visited, (unsigned long long)visited);
-    if (MODE == 0 && A.timing && lane == 0) {
-        const unsigned long long busy = (unsigned long long)(clock64() - t_start);
-        atomicAdd((unsigned long long *)&A.st->walk_busy_sum, busy);
-        atomicMax((unsigned long long *)&A.st->walk_busy_max, busy);
+        // the block's counts, added to its class's by the last wave
+        atomicAdd(&s_visited, visited);
+        atomicAdd(&s_m2l, nm2l);
+        atomicAdd(&s_p2p, np2p);
+        atomicAdd(&s_longm, nlongm);
+        if (MODE == 0 && A.timing) {
+            const unsigned long long busy = (unsigned long long)(clock64() - t_start);
+            atomicAdd(&s_busy, busy);
+            atomicMax(&s_busymax, busy);
+        }
+        if (atomicSub(&s_left, 1) == 1) {
+            const unsigned long long v = atomicAdd(&s_visited, 0ull);
+            const int m = atomicAdd(&s_m2l, 0), p = atomicAdd(&s_p2p, 0);
+            const int lm = atomicAdd(&s_longm, 0);
+            if (v) atomicAdd((unsigned long long *)walk_ctr(A.ctr, cls, kCtrVisited), v);
+            if (m) atomicAdd(walk_ctr(A.ctr, cls, kCtrM2L), m);
+            if (p) atomicAdd(walk_ctr(A.ctr, cls, kCtrP2P), p);
+            if (lm) atomicAdd(walk_ctr(A.ctr, cls, kCtrLongM2L), lm);
+            if (MODE == 0 && A.timing) {
+                atomicAdd((unsigned long long *)walk_ctr(A.ctr, cls, kCtrBusy), atomicAdd(&s_busy, 0ull));
+                atomicMax((unsigned long long *)walk_ctr(A.ctr, cls, kCtrBusyMax),
+                          atomicAdd(&s_busymax, 0ull));
+                atomicAdd(walk_ctr(A.ctr, cls, kCtrWaves), WPB);
+            }
+        }
     }
 }
 
-// waves: persistent waves of the gravity walk (the collision walk runs its own count)
-hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_post, int waves,
+// Workgroups of a walk: as many as fit on the chip at once (`most`, if positive, limits
+// them), one wave per cell at most, and a multiple of the classes, whose tickets each
+// need a taker.
+template <int MODE>
+static int walk_grid(int64_t cell_cap, int most) {
+    static int cached[64] = {};                     // per device
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    int g = dev >= 0 && dev < 64 ? cached[dev] : 0;
+    if (g == 0) {
+        int per_cu = 0, ncu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k_walk<MODE>,
+                                                         kWalkBlock, 0) != hipSuccess ||
+            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) !=
+                hipSuccess ||
+            per_cu < 1 || ncu < 1) {
+            (void)hipGetLastError();
+            per_cu = 2;
+            ncu = 256;
+        }
+        g = per_cu * ncu;
+        if (dev >= 0 && dev < 64) cached[dev] = g;
+    }
+    int64_t want = (cell_cap + kWalkBlock / kWave - 1) / (kWalkBlock / kWave);
+    if (want > g) want = g;
+    if (most > 0 && want > most) want = most;
+    want = want / kWalkClasses * kWalkClasses;
+    return (int)(want < kWalkClasses ? kWalkClasses : want);
+}
+
+// most: most workgroups of the gravity walk (0: as many as fit)
+hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_post, int most,
                        hipStream_t s, const ncorp_params *rcrit_prm) {
     RcritArgs R = {};
     if (rcrit_prm) R = rcrit_args(ws, *rcrit_prm);
-    k_walk_init<<<1024, 256, 0, s>>>(ws.st, ws.wq, ws.queue, ws.queue_cap, mode, ws.m2l_cnt,
-                                     ws.p2p_cnt, ws.clear_queue ? 1 : 0, R, rcrit_prm ? 1 : 0);
-    ws.clear_queue = false;
+    // the headers take the other walk's cell records, which each walk's own climb
+    // rewrites before they are read again
+    uint64_t *hdr = reinterpret_cast<uint64_t *>(mode == 0 ? ws.wc : ws.wg);
+    int64_t gi = (ws.cell_cap + 255) / 256;
+    gi = gi < 1 ? 1 : (gi > 1024 ? 1024 : gi);
+    k_walk_init<<<(int)gi, 256, 0, s>>>(ws.st, ws.wq, hdr, ws.walk_ctr,
+                                        (mode == 0 ? kWalkClasses : kWalkClasses + kCandRegions) *
+                                            kCtrStride,
+                                        mode, R, rcrit_prm ? 1 : 0);
     WalkArgs A = {};
-    A.st = ws.st; A.wq = ws.wq; A.queue = ws.queue; A.qcap = ws.queue_cap;
+    A.st = ws.st; A.wq = ws.wq; A.hdr = hdr; A.ctr = ws.walk_ctr;
     A.ncs = ncs; A.ncc_pre = ncc_pre; A.ncc_post = ncc_post;
+    // List space: the 2 queue_cap words set aside for a walk's open pairs, or those of
+    // p2p_cap pairs where a caller asked for a smaller queue than that.  A
+    // pair is handed down at most once, so queue_cap words hold a walk of queue_cap
+    // visits; the rest is inline slots where it reaches, and room for segment heads and
+    // inherited direct-sum pairs.
+    const bool own = ws.queue_cap >= ws.p2p_cap;
+    const int64_t words = 2 * (own ? ws.queue_cap : ws.p2p_cap);
+    A.space = own ? reinterpret_cast<int32_t *>(ws.queue)
+                  : reinterpret_cast<int32_t *>(ws.p2p);
+    A.visit_cap = ws.queue_cap;
+    A.inl = words / 2 >= kWalkInline * ws.cell_cap &&
+                    words - kWalkInline * ws.cell_cap >= ws.queue_cap
+                ? (int)kWalkInline : 0;
+    A.shared0 = (int64_t)A.inl * ws.cell_cap;
+    A.shared_n = (words - A.shared0) / kXcds;
     if (mode == 0) {
         A.cell = ws.wg;
-        A.m2l = ws.m2l; A.m2l_cap = ws.m2l_cap; A.nm2l = &ws.st->nm2l;
-        A.p2p = ws.p2p; A.p2p_cap = ws.p2p_cap; A.np2p = &ws.st->np2p;
-        A.m2l_slots = &ws.st->m2l_slots; A.p2p_slots = &ws.st->p2p_slots;
         A.m2l_cnt = ws.m2l_cnt; A.m2l_seg = ws.m2l_seg; A.m2l_stride = ws.m2l_stride;
         A.p2p_cnt = ws.p2p_cnt; A.p2p_seg = ws.p2p_seg; A.p2p_stride = ws.p2p_stride;
-        A.long_m2l = ws.long_m2l; A.long_p2p = ws.long_p2p;
+        A.c_rmax = ws.c_rmax;
+        A.leaf_slack = ws.leaf_slack;
         A.timing = ws.timing ? 1 : 0;
-        const int grid = (waves > 0 ? waves : kWalkWaves) / (kWalkBlock / kWave);
-        k_walk<0><<<grid, kWalkBlock, 0, s>>>(A);
+        k_walk<0><<<walk_grid<0>(ws.cell_cap, most), kWalkBlock, 0, s>>>(A);
     } else {
         A.cell = ws.wc;
-        A.m2l = ws.m2l; A.m2l_cap = 0; A.nm2l = &ws.st->nm2l;
-        A.p2p = ws.cand; A.p2p_cap = ws.p2p_cap; A.np2p = &ws.st->ncand;
-        A.m2l_slots = &ws.st->m2l_slots; A.p2p_slots = &ws.st->cand_slots;
-        k_walk<1><<<kWalkGridCollide, kWalkBlock, 0, s>>>(A);
+        A.cand = cand_out(ws);
+        k_walk<1><<<walk_grid<1>(ws.cell_cap, 0), kWalkBlock, 0, s>>>(A);
     }
     return hipGetLastError();
-}
-
-// Lists too long for the consumers' LDS sort (the walk recorded their targets)
-// are sorted here, in place, one single-wave block per list (rank sort in LDS).
-__global__ void __launch_bounds__(kWave)
-k_sort_long_lists(const DevState *__restrict__ st, const int32_t *__restrict__ m2l_cnt,
-                  int32_t *m2l_seg, int m2l_stride, const int32_t *__restrict__ long_m2l,
-                  const int32_t *__restrict__ p2p_cnt, int32_t *p2p_seg, int p2p_stride,
-                  const int32_t *__restrict__ long_p2p) {
-    extern __shared__ __align__(16) int32_t scr[];   // round_up(largest stride, 4) ints
-    if (st->status & kSkipMask) return;
-    // the first half of the blocks sorts the M2L lists, the second the direct-sum lists
-    const int half = (int)gridDim.x / 2;
-    const int which = (int)blockIdx.x < half ? 0 : 1;
-    const int32_t *cnt = which == 0 ? m2l_cnt : p2p_cnt;
-    int32_t *seg = which == 0 ? m2l_seg : p2p_seg;
-    const int stride = which == 0 ? m2l_stride : p2p_stride;
-    const int32_t *longs = which == 0 ? long_m2l : long_p2p;
-    const int nl = which == 0 ? st->nlong_m2l : st->nlong_p2p;
-    const int lane = threadIdx.x;
-    for (int q = (int)blockIdx.x - which * half; q < nl; q += half) {
-        const int t = longs[q];
-        const int len = cnt[t];
-        int32_t *list = seg + (int64_t)t * stride;
-        const int len4 = (len + 3) & ~3;
-        __syncthreads();
-        for (int i = lane; i < len4; i += kWave) scr[i] = i < len ? list[i] : 0x7fffffff;
-        __syncthreads();
-        const int4 *s4 = reinterpret_cast<const int4 *>(scr);
-        for (int i = lane; i < len; i += kWave) {
-            const int v = scr[i];
-            int r = 0;
-            #pragma unroll 8
-            for (int j = 0; j < len4 / 4; j++) {
-                const int4 w = s4[j];
-                r += (w.x < v) + (w.y < v) + (w.z < v) + (w.w < v);
-            }
-            list[r] = v;
-        }
-    }
 }
 
 // directed moonlet interactions of the direct sums: per leaf, its moonlets times
@@ -583,16 +548,6 @@ __global__ void k_zero_inter(DevState *st) {
         st->p2p_maxlist = 0;
         st->p2p_src_max = 0;
     }
-}
-
-hipError_t launch_sort_long_lists(const Workspace &ws, hipStream_t s) {
-    if (!ws.m2l_cnt) return hipSuccess;
-    const size_t lm = (size_t)((ws.m2l_stride + 3) & ~3) * sizeof(int32_t);
-    const size_t lp = (size_t)((ws.p2p_stride + 3) & ~3) * sizeof(int32_t);
-    k_sort_long_lists<<<2 * kSortLongBlocks, kWave, lm > lp ? lm : lp, s>>>(
-        ws.st, ws.m2l_cnt, ws.m2l_seg, ws.m2l_stride, ws.long_m2l, ws.p2p_cnt, ws.p2p_seg,
-        ws.p2p_stride, ws.long_p2p);
-    return hipGetLastError();
 }
 
 hipError_t launch_count_interactions(const Workspace &ws, hipStream_t s) {
