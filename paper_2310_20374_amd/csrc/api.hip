@@ -315,7 +315,7 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.c_nent = (int32_t *)take(4 * cell_cap);
     ws.c_prefix = (uint64_t *)take(8 * cell_cap);
     ws.c_arrive = (int32_t *)take(4 * cell_cap);
-    ws.climb_next = (int32_t *)take(4 * kXcds * 32);
+    (void)take(4 * kXcds * 32);
     ws.gcell = (double4 *)take(32 * cell_cap);
     ws.c_mass = (double *)take(8 * cell_cap);
     ws.c_rmax = (double *)take(8 * cell_cap);
@@ -371,8 +371,11 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.pair_flag = (int32_t *)take(4 * ws.pair_cap);
     ws.mbest = (int32_t *)take(4 * n);
     ws.mmatch = (int32_t *)take(4 * n);
-    static_assert((kWalkClasses + kCandRegions) * kCtrStride <= 8192, "counter lines must fit");
+    // counter lines: walk classes, candidate regions, climb classes
+    static_assert((kWalkClasses + kCandRegions + kClimbClasses) * kCtrStride <= 8192,
+                  "counter lines must fit");
     ws.walk_ctr = (int32_t *)take(4 * 8192);
+    ws.climb_next = ws.walk_ctr ? ws.walk_ctr + (kWalkClasses + kCandRegions) * kCtrStride : nullptr;
     // per-block partials: the box pass's 16384 and the pair tests' kCollideGrid blocks,
     // 2 per mesh block plus 1024, or one per standard-tree wave, whichever needs most
     static_assert(kCollideGrid <= 2 * 16384 + 1024 + 128, "pair-test partials must fit");

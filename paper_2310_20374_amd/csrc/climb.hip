@@ -54,13 +54,19 @@ constexpr int kPowChunk = 32;
 
 // Leaves of the climbs in XCD slices: the leaves, in tree order, are cut into 8
 // contiguous slices and the waves of XCD x (workgroups b with b mod 8 = x) take the
-// leaves of slice x in order: the first of each wave by its position, later ones
-// one at a time from a counter of that slice.  Siblings
-// and most of their ancestors' chains then stay on one XCD and every XCD gets the
-// same number of leaves (with leaves dealt round robin, an XCD that falls behind
-// arrives last more often, inherits more of the upward chains and falls further
-// behind).  The waves are persistent, as many as fit on the chip at once, so no
-// leaf waits for a workgroup launch.
+// leaves of slice x.  Siblings and most of their ancestors' chains then stay on one XCD
+// and every XCD gets the same number of leaves (with leaves dealt round robin, an XCD
+// that falls behind arrives last more often, inherits more of the upward chains and
+// falls further behind).  Inside a slice, runs of kClimbRun leaves are dealt to 8
+// classes of waves, each with a counter on a line of its own: atomics on one address
+// take about 15 ns each and a wave's later loads return behind its own, so with one
+// counter per slice the counters paced the climb (5.3e4 leaves of 17 moonlets: 151 ->
+// 107 us; its collision form 131 -> 80 us; N = 1e6, s = 96, p = 6: 131 -> 126 us).  Runs
+// of 16 keep the class's siblings on one wave's neighbours: 1, 4 and 16 took 139, 113
+// and 107 us there, and 586, 463 and 411 us for 4e6 clumped moonlets.  The waves are
+// persistent, as many as fit on the chip at once, so no leaf waits for a workgroup
+// launch.
+constexpr int kClimbRun = 16;
 
 template <int KERNEL_ID>
 static int climb_grid(const void *kernel, int64_t leaf_cap) {
@@ -81,17 +87,23 @@ static int climb_grid(const void *kernel, int64_t leaf_cap) {
         if (g < kXcds) g = kXcds;
         if (dev >= 0 && dev < 64) cached[dev] = g;
     }
-    int64_t want = (leaf_cap + kXcds - 1) / kXcds * kXcds;
-    if (want < kXcds) want = kXcds;
-    return (int)(want < g ? want : g);
+    // a multiple of the classes, so that each has a taker
+    int64_t want = leaf_cap < g ? leaf_cap : g;
+    want = want / kClimbClasses * kClimbClasses;
+    return (int)(want < kClimbClasses ? kClimbClasses : want);
 }
 
-// next leaf index of this wave's slice after the first round (lane 0 takes it from
-// the slice's counter; every lane reads it later)
+// next turn of this wave's class after the first round (lane 0 takes it from the
+// class's counter; every lane reads it later)
 __device__ __forceinline__ int take_leaf(int32_t *ctr) {
     int i = 0;
-    if (threadIdx.x == 0) i = atomicAdd(ctr, 1) + (int)(gridDim.x / kXcds);
+    if (threadIdx.x == 0) i = atomicAdd(ctr, 1) + (int)(gridDim.x / kClimbClasses);
     return i;
+}
+
+// leaf of its XCD's slice that turn i of a class stands for
+__device__ __forceinline__ int class_leaf(int i, int cls) {
+    return ((i / kClimbRun) * (kClimbClasses / kXcds) + cls / kXcds) * kClimbRun + i % kClimbRun;
 }
 
 // ---------------------------------------------------------------- wave helpers
@@ -282,11 +294,11 @@ k_gravity_climb(const DevState *__restrict__ st, const double *__restrict__ xs,
     if (lane == 0) sterm[ShiftTerms<P>::NT] = 0;
     __syncthreads();
     const int per = (K + kXcds - 1) / kXcds;       // leaves per XCD slice
-    const int xcd = (int)blockIdx.x % kXcds;
-    int32_t *ctr = climb_next + xcd * kCtrStride;
-    int nxt = (int)blockIdx.x / kXcds;             // first round: one leaf per wave, no counter
+    const int cls = (int)blockIdx.x % kClimbClasses, xcd = cls % kXcds;
+    int32_t *ctr = climb_next + cls * kCtrStride;
+    int nxt = (int)blockIdx.x / kClimbClasses;     // first round: one leaf per wave, no counter
     for (;;) {
-        const int i = __builtin_amdgcn_readlane(nxt, 0);
+        const int i = class_leaf(__builtin_amdgcn_readlane(nxt, 0), cls);
         const int e = xcd * per + i;
         if (i >= per || e >= K) break;
         nxt = take_leaf(ctr);                       // the next one, in flight meanwhile
@@ -483,7 +495,7 @@ __global__ void k_arrive_reset(const DevState *__restrict__ st, int32_t *c_arriv
     for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += gridDim.x * blockDim.x)
         c_arrive[c] = 0;
     if (blockIdx.x == 0)
-        for (int t = threadIdx.x; t < kXcds * kCtrStride; t += blockDim.x) climb_next[t] = 0;
+        for (int t = threadIdx.x; t < kClimbClasses; t += blockDim.x) climb_next[t * kCtrStride] = 0;
 }
 
 static int cell_grid(int64_t cap, int block) {
@@ -543,11 +555,11 @@ k_collision_climb(const DevState *__restrict__ st, const double *__restrict__ xs
     const double L = st->L;
     const int lane = threadIdx.x;
     const int per = (K + kXcds - 1) / kXcds;       // leaves per XCD slice
-    const int xcd = (int)blockIdx.x % kXcds;
-    int32_t *ctr = climb_next + xcd * kCtrStride;
-    int nxt = (int)blockIdx.x / kXcds;             // first round: one leaf per wave, no counter
+    const int cls = (int)blockIdx.x % kClimbClasses, xcd = cls % kXcds;
+    int32_t *ctr = climb_next + cls * kCtrStride;
+    int nxt = (int)blockIdx.x / kClimbClasses;     // first round: one leaf per wave, no counter
     for (;;) {
-        const int i = __builtin_amdgcn_readlane(nxt, 0);
+        const int i = class_leaf(__builtin_amdgcn_readlane(nxt, 0), cls);
         const int e = xcd * per + i;
         if (i >= per || e >= K) break;
         nxt = take_leaf(ctr);                       // the next one, in flight meanwhile

@@ -16,8 +16,10 @@ constexpr int kWave = 64;
 // The hardware deals the workgroups of a launch to the 8 XCDs in turn (workgroup b
 // runs on XCD b mod 8), and each XCD has its own L2.
 constexpr int kXcds = 8;
-// the climbs' per-XCD leaf counters: one counter per 128-byte line
+// counters that many waves add to: each on a 128-byte line of its own
 constexpr int kCtrStride = 32;
+// the climbs deal their leaves to this many classes of waves
+constexpr int kClimbClasses = 64;
 
 // ---------------------------------------------------------------- tensor sizes
 // Symmetric tensors are stored per order n as the (n+1)(n+2)/2 components
@@ -282,7 +284,7 @@ struct Workspace {
     int32_t *c_nent = nullptr;                        // number of leaves below
     uint64_t *c_prefix = nullptr;
     int32_t *c_arrive = nullptr;                      // climb counters
-    int32_t *climb_next = nullptr;   // climbs: next leaf of each XCD slice (kXcds x 32)
+    int32_t *climb_next = nullptr;   // climbs: next turn of each class (lines of walk_ctr)
     double4 *gcell = nullptr;                         // s_x, s_y, s_z, r_crit
     double *c_mass = nullptr, *c_rmax = nullptr, *c_theta = nullptr;
     double *mult = nullptr;                           // cell_cap x nm (FP64)

@@ -281,7 +281,7 @@ __global__ void k_cell_ranges(DevState *st, int64_t n,
     const bool first = blockIdx.x == 0 && threadIdx.x == 0;
     if (first) st->max_abs = 0.0;
     if (blockIdx.x == 0)
-        for (int t = threadIdx.x; t < kXcds * kCtrStride; t += blockDim.x) climb_next[t] = 0;
+        for (int t = threadIdx.x; t < kClimbClasses; t += blockDim.x) climb_next[t * kCtrStride] = 0;
     if (st->status & ST_CAP_CELLS) {
         if (first) {
             st->ncells = 0;
