@@ -292,7 +292,7 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.xs = (double *)take(8 * n);
     ws.ys = (double *)take(8 * n);
     ws.zs = (double *)take(8 * n);
-    ws.mus = (double *)take(8 * n);
+    (void)take(8 * n);
     ws.vxs = (double *)take(8 * n);
     ws.vys = (double *)take(8 * n);
     ws.vzs = (double *)take(8 * n);
@@ -329,9 +329,9 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.wg = (WCell *)take(sizeof(WCell) * cell_cap);
     ws.wc = (WCell *)take(sizeof(WCell) * cell_cap);
     ws.queue = (uint64_t *)take(8 * q_cap);
-    // (room for a plain list of the well-separated pairs: the lists are per target now,
-    // but the size a caller computes for an n must not shrink or grow)
-    (void)take(8 * m2l_cap);
+    // (the size of a plain list of the well-separated pairs, which are listed per target:
+    // the size a caller computes for an n must not shrink or grow)
+    ws.split_p2p = (int32_t *)take(8 * m2l_cap);
     ws.p2p = (int2 *)take(8 * p2p_cap);
     ws.cand = (int2 *)take(8 * p2p_cap);
     if (ws.p > 0) {
@@ -459,8 +459,8 @@ static int setup_workspace(ncorp_ctx *c, int64_t n, void *workspace, int64_t ws_
 
 // disk_off: device offsets of a batched call (n_disks + 1 of them), or nullptr;
 // m: the masses, when the caller has them (the step): G m then comes into tree order
-// with the positions (ws.mus), and the step's gravity evaluation on this tree skips
-// its own gather
+// with the positions (the records in ws.vcol), and the step's gravity evaluation on
+// this tree skips its own gather
 static int build_tree_impl(ncorp_ctx *c, const double *x, const double *y, const double *z,
                            int64_t n, hipStream_t s, bool fresh, const int64_t *disk_off,
                            int n_disks, const double *m = nullptr, bool max_ready = false) {
@@ -578,7 +578,7 @@ extern "C" int ncorp_build_tree_batched(ncorp_ctx *c, const int64_t *disk_offset
     return build_tree_impl(c, x, y, z, n, (hipStream_t)stream, true, disk_offsets, n_disks);
 }
 
-// mus_packed: the build of the current tree already put G m in ws.mus (the step)
+// mus_packed: the build of the current tree already packed G m (the step)
 // Does a gravity evaluation end in the falcON L2P pass (which can write packed records)?
 static bool gravity_by_l2p(const ncorp_params &p) {
     return p.p > 0 && p.gravity_method == NCORP_GRAVITY_FALCON;
@@ -601,7 +601,7 @@ static int gravity_impl(ncorp_ctx *c, const double *m, double *ax, double *ay, d
         if (ws.ndisks > 1)
             return fail(c, NCORP_E_UNSUPPORTED, "brute-force gravity takes plain calls only");
         PhaseTimer t(c, NCORP_PHASE_P2P, s);
-        HIPCHK(c, launch_gather_scaled(ws, m, c->prm.G, ws.mus, n, s));
+        HIPCHK(c, launch_gather_mass(ws, m, c->prm.G, n, s));
         HIPCHK(c, launch_brute_gravity(ws, n, ax, ay, az, s));
         c->grav_lists = false;
         c->last = s;
@@ -616,7 +616,7 @@ static int gravity_impl(ncorp_ctx *c, const double *m, double *ax, double *ay, d
     }
     {
         PhaseTimer t(c, NCORP_PHASE_GCLIMB, s);
-        if (!mus_packed) HIPCHK(c, launch_gather_scaled(ws, m, c->prm.G, ws.mus, n, s));
+        if (!mus_packed) HIPCHK(c, launch_gather_mass(ws, m, c->prm.G, n, s));
         const bool reset = !ws.arrive_clean;
         ws.arrive_clean = false;
         // falcON: the walk's init pass forms the critical radii
@@ -644,7 +644,7 @@ static int gravity_impl(ncorp_ctx *c, const double *m, double *ax, double *ay, d
     }
     {
         PhaseTimer t(c, NCORP_PHASE_DESCENT, s);
-        HIPCHK(c, launch_l2l(ws, c->prm.p, s));
+        HIPCHK(c, launch_l2l(ws, c->prm.p, c->prm.precision, c->prm.p2p_tile, s));
     }
     {
         PhaseTimer t(c, NCORP_PHASE_P2P, s);
@@ -970,7 +970,7 @@ extern "C" int ncorp_get_status(ncorp_ctx *c, int64_t *required) {
 // Totals of the last walk (its classes' counters) and the lengths of the candidate
 // regions of the last collision search.
 struct WalkCounts {
-    int64_t visited = 0, m2l = 0, p2p = 0, long_m2l = 0, cand = 0;
+    int64_t visited = 0, m2l = 0, p2p = 0, long_m2l = 0, long_p2p = 0, cand = 0;
     int64_t busy = 0, busy_max = 0, waves = 0;
     int32_t region[kCandRegions];
 };
@@ -987,6 +987,7 @@ static int read_counts(ncorp_ctx *c, WalkCounts &w) {
         w.m2l += c->walked == 1 ? line[kCtrM2L] : 0;
         w.p2p += c->walked == 1 ? line[kCtrP2P] : 0;
         w.long_m2l += c->walked == 1 ? line[kCtrLongM2L] : 0;
+        w.long_p2p += c->walked == 1 ? line[kCtrLongP2P] : 0;
         int64_t busy, most;
         std::memcpy(&busy, line + kCtrBusy, sizeof(busy));
         std::memcpy(&most, line + kCtrBusyMax, sizeof(most));
@@ -1020,7 +1021,7 @@ extern "C" int ncorp_tree_info(ncorp_ctx *c, int64_t *info) {
     info[NCORP_INFO_M2L_DIR] = 2 * w.m2l;
     info[NCORP_INFO_NROOTS] = h.level_count[0];
     info[NCORP_INFO_LONG_M2L] = w.long_m2l;
-    info[NCORP_INFO_LONG_P2P] = h.nlong_p2p;
+    info[NCORP_INFO_LONG_P2P] = w.long_p2p;
     info[NCORP_INFO_P2P_INTER] = h.p2p_inter;
     info[NCORP_INFO_M2L_MAXLIST] = h.m2l_maxlist;
     info[NCORP_INFO_P2P_MAXLIST] = h.p2p_maxlist;

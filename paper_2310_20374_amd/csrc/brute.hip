@@ -21,21 +21,20 @@ __device__ __forceinline__ void neumaier(double &s, double &c, double v) {
 }
 
 __global__ void __launch_bounds__(kBruteBlock)
-k_brute_gravity(const DevState *__restrict__ st, const double *__restrict__ xs,
-                const double *__restrict__ ys, const double *__restrict__ zs,
-                const double *__restrict__ mus, const uint32_t *__restrict__ idx, int64_t n,
+k_brute_gravity(const DevState *__restrict__ st, const double4 *__restrict__ pos4,
+                const uint32_t *__restrict__ idx, int64_t n,
                 double *__restrict__ ax, double *__restrict__ ay, double *__restrict__ az) {
     __shared__ double4 tile[kBruteBlock];
     if (st->status & kSkipMask) return;
     const int64_t i = blockIdx.x * (int64_t)kBruteBlock + threadIdx.x;
     const bool live = i < n;
-    const double x = live ? xs[i] : 0.0, y = live ? ys[i] : 0.0, z = live ? zs[i] : 0.0;
+    const double4 p = live ? pos4[i] : make_double4(0.0, 0.0, 0.0, 0.0);
+    const double x = p.x, y = p.y, z = p.z;
     double sx = 0.0, cx = 0.0, sy = 0.0, cy = 0.0, sz = 0.0, cz = 0.0;
     for (int64_t t0 = 0; t0 < n; t0 += kBruteBlock) {
         const int64_t j = t0 + threadIdx.x;
         __syncthreads();
-        tile[threadIdx.x] = j < n ? make_double4(xs[j], ys[j], zs[j], mus[j])
-                                  : make_double4(0.0, 0.0, 0.0, 0.0);
+        tile[threadIdx.x] = j < n ? pos4[j] : make_double4(0.0, 0.0, 0.0, 0.0);
         __syncthreads();
         const int cnt = n - t0 < kBruteBlock ? (int)(n - t0) : kBruteBlock;
         // one tile summed plainly, then added to the compensated total
@@ -118,8 +117,7 @@ hipError_t launch_brute_gravity(const Workspace &ws, int64_t n, double *ax, doub
                                 double *az, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int64_t blocks = (n + kBruteBlock - 1) / kBruteBlock;
-    k_brute_gravity<<<(unsigned)blocks, kBruteBlock, 0, s>>>(ws.st, ws.xs, ws.ys, ws.zs, ws.mus,
-                                                             ws.idx, n, ax, ay, az);
+    k_brute_gravity<<<(unsigned)blocks, kBruteBlock, 0, s>>>(ws.st, ws.vcol, ws.idx, n, ax, ay, az);
     return hipGetLastError();
 }
 

@@ -249,7 +249,7 @@ template <int P>
 __global__ void __launch_bounds__(kWave)
 k_gravity_climb(const DevState *__restrict__ st, const double *__restrict__ xs,
                 const double *__restrict__ ys, const double *__restrict__ zs,
-                const double *__restrict__ mus, const int32_t *__restrict__ ent_cell,
+                const double4 *__restrict__ pos4, const int32_t *__restrict__ ent_cell,
                 const int32_t *__restrict__ c_level, const int32_t *__restrict__ c_first,
                 const int32_t *__restrict__ c_count, const int32_t *__restrict__ c_child,
                 const int32_t *__restrict__ c_nchild, const int32_t *__restrict__ c_parent,
@@ -312,10 +312,10 @@ k_gravity_climb(const DevState *__restrict__ st, const double *__restrict__ xs,
             for (int c0 = 0; c0 < cnt; c0 += kWave) {
                 const bool in = c0 + lane < cnt;
                 const int k = f + c0 + (in ? lane : 0);
-                const double mu = mus[k], x = xs[k], y = ys[k], z = zs[k];
+                const double4 p = pos4[k];
                 __syncthreads();
-                sq[lane][0] = 1.0; sq[lane][1] = x; sq[lane][2] = y; sq[lane][3] = z;
-                sqm[lane] = mu;
+                sq[lane][0] = 1.0; sq[lane][1] = p.x; sq[lane][2] = p.y; sq[lane][3] = p.z;
+                sqm[lane] = p.w;
                 __syncthreads();
                 const int nk = cnt - c0 < kWave ? cnt - c0 : kWave;
                 if (lane < 4) {
@@ -329,7 +329,8 @@ k_gravity_climb(const DevState *__restrict__ st, const double *__restrict__ xs,
             for (int c0 = 0; c0 < cnt; c0 += kPowChunk) {
                 const bool in = lane < kPowChunk && c0 + lane < cnt;
                 const int k = f + c0 + (in ? lane : 0);
-                const double mu = mus[k], x = xs[k], y = ys[k], z = zs[k];
+                const double4 p = pos4[k];
+                const double mu = p.w, x = p.x, y = p.y, z = p.z;
                 if (in) {
                     const double d = 0.0 + dist3(x, y, z, sx, sy, sz);
                     if (d > rm) rm = d;
@@ -506,7 +507,7 @@ static int cell_grid(int64_t cap, int block) {
 template <int P>
 static void launch_gc(const Workspace &ws, hipStream_t s) {
     const int g = climb_grid<P>((const void *)k_gravity_climb<P>, ws.leaf_cap);
-    k_gravity_climb<P><<<g, kWave, 0, s>>>(ws.st, ws.xs, ws.ys, ws.zs, ws.mus, ws.ent_cell,
+    k_gravity_climb<P><<<g, kWave, 0, s>>>(ws.st, ws.xs, ws.ys, ws.zs, ws.vcol, ws.ent_cell,
                                          ws.c_level, ws.c_first, ws.c_count, ws.c_child,
                                          ws.c_nchild, ws.c_parent, ws.c_arrive, ws.climb_next,
                                          ws.gcell,

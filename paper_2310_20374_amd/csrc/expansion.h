@@ -1,5 +1,6 @@
 // Derivative tensors of 1/|R| and their contraction with scaled multipole moments,
-// shared by the M2L kernel (Eq. 25) and the standard tree code's cell-moonlet terms.
+// shared by the M2L kernel (Eq. 25) and the standard tree code's cell-moonlet terms, and
+// the 1/r^3 of their FP64 direct sums.
 //
 // D comes from the recurrence of McMurchie & Davidson (J. Comput. Phys. 26, 1978)
 // written for 1/r: with R^n_000 = (-1)^n (2n-1)!! r^-(2n+1),
@@ -86,6 +87,18 @@ __device__ __forceinline__ void m2l_contract(const T *D, const T *__restrict__ m
                         }
             }
     }
+}
+
+// m r2^(-3/2) in FP64 from the hardware's approximate reciprocal square root y: with
+// e = 1 - r2 y^2 (below 2^-22), r2^(-3/2) = y^3 (1 - e)^(-3/2) = y^3 (1 + 3/2 e + 15/8 e^2)
+// to the last bit or two.  Seven operations where refining 1/r first and cubing it takes
+// eleven; r2 must be normal and finite.
+__device__ __forceinline__ double over_r3(double m, double r2) {
+    const double y = __builtin_amdgcn_rsq(r2);
+    const double y2 = y * y;
+    const double e = fma(-r2, y2, 1.0);
+    const double w = m * y * y2;
+    return fma(w * e, fma(e, 1.875, 1.5), w);
 }
 
 }  // namespace ncorp

@@ -533,18 +533,19 @@ hipError_t launch_radix_sort(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t 
 
 // ------------------------------------------------------------------ gathers
 // Positions in tree order from the packed records k_keys wrote in input order: one
-// 32-byte record per moonlet instead of three scattered 8-byte words (and the scaled
-// masses G m from the same record, when k_keys had them: mus != nullptr).
+// 32-byte record per moonlet instead of three scattered 8-byte words.  When k_keys had
+// the scaled masses G m too (pos4 != nullptr), the whole record, which the gravity climb
+// and the direct sums read.
 __global__ void k_gather_pack4(const double4 *__restrict__ pack4, const uint32_t *__restrict__ idx,
                               int64_t n, double *__restrict__ xs, double *__restrict__ ys,
-                              double *__restrict__ zs, double *__restrict__ mus) {
+                              double *__restrict__ zs, double4 *__restrict__ pos4) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const double4 p = pack4[idx[i]];
         xs[i] = p.x;
         ys[i] = p.y;
         zs[i] = p.z;
-        if (mus) mus[i] = p.w;
+        if (pos4) pos4[i] = p;
     }
 }
 
@@ -557,20 +558,23 @@ __global__ void k_gather1(const double *__restrict__ src, const uint32_t *__rest
 
 hipError_t launch_gather_pos(const Workspace &ws, int64_t n, bool with_mus, hipStream_t s) {
     k_gather_pack4<<<grid_for(n, 256), 256, 0, s>>>(ws.pack4, ws.idx, n, ws.xs, ws.ys, ws.zs,
-                                                    with_mus ? ws.mus : nullptr);
+                                                    with_mus ? ws.vcol : nullptr);
     return hipGetLastError();
 }
 
-__global__ void k_gather_scaled(const double *__restrict__ src, const uint32_t *__restrict__ idx,
-                                int64_t n, double scale, double *__restrict__ dst) {
+// the (x, y, z, G m) records in tree order, when the build had no masses to pack
+__global__ void k_gather_mass(const double *__restrict__ m, const uint32_t *__restrict__ idx,
+                              int64_t n, double G, const double *__restrict__ xs,
+                              const double *__restrict__ ys, const double *__restrict__ zs,
+                              double4 *__restrict__ pos4) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = scale * src[idx[i]];
+        pos4[i] = make_double4(xs[i], ys[i], zs[i], G * m[idx[i]]);
 }
 
-hipError_t launch_gather_scaled(const Workspace &ws, const double *src, double scale,
-                                double *dst, int64_t n, hipStream_t s) {
-    k_gather_scaled<<<grid_for(n, 256), 256, 0, s>>>(src, ws.idx, n, scale, dst);
+hipError_t launch_gather_mass(const Workspace &ws, const double *m, double G, int64_t n,
+                              hipStream_t s) {
+    k_gather_mass<<<grid_for(n, 256), 256, 0, s>>>(m, ws.idx, n, G, ws.xs, ws.ys, ws.zs, ws.vcol);
     return hipGetLastError();
 }
 

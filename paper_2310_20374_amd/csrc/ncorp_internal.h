@@ -70,10 +70,10 @@ constexpr int kWalkRun = 8;
 constexpr int kWalkClasses = 64;
 // Counters of a walk, one 128-byte line per class (kCtrStride words): the ticket, the
 // entries taken of the shared list space (the first kXcds lines), and the class's part
-// of the pairs visited, well separated and summed directly, of the long M2L lists and,
+// of the pairs visited, well separated and summed directly, of the long lists and,
 // in timing runs, of its waves' busy cycles (sum, maximum, waves).
 constexpr int kCtrTicket = 0, kCtrSpace = 2, kCtrVisited = 4, kCtrM2L = 6, kCtrP2P = 7,
-              kCtrLongM2L = 8, kCtrBusy = 10, kCtrBusyMax = 12, kCtrWaves = 14;
+              kCtrLongM2L = 8, kCtrBusy = 10, kCtrBusyMax = 12, kCtrWaves = 14, kCtrLongP2P = 9;
 // the collision candidates lie in kCandRegions equal parts of their list, each with a
 // counter line of its own after the walk's
 constexpr int kCandRegions = 64;
@@ -98,10 +98,9 @@ constexpr int kMaxPerTarget = 8192;
 // lists beyond one LDS batch of their consumer are recorded by the walk and split
 constexpr int kM2LListLDS = 512;
 constexpr int kP2PListLDS = kWave;
-// direct sums of a leaf with a long source list are split over kLongSlots waves
-// (kLongGrid extra four-wave blocks); their partial sums meet in p2p_part
+// the direct sums of a leaf are split over at most kLongSlots waves, whose partial sums
+// meet in p2p_part
 constexpr int kLongSlots = 8;
-constexpr int kLongGrid = 2048;
 
 constexpr int32_t kSkipMask = ST_CAP_CELLS | ST_CAP_QUEUE | ST_CAP_M2L | ST_CAP_P2P |
                               ST_CAP_LISTS | ST_WALK_STALL | ST_BAD_ITEM | ST_BAD_OFFSETS |
@@ -124,7 +123,8 @@ struct DevState {
     int32_t ndisks, nroots;    // disks of the call; level-0 cells (non-empty disks)
     // gravity walk
     int32_t m2l_maxlist, p2p_maxlist;  // longest per-target lists (timing runs only)
-    int32_t nlong_p2p;         // direct-sum lists longer than kP2PListLDS
+    int32_t nsplit;            // slots in the list of split or long direct sums
+    int32_t nlong;             // direct-sum lists longer than kP2PListLDS
     // collision walk
     int64_t col_tests;
     int64_t npairs;            // colliding pairs found (may exceed capacity)
@@ -261,21 +261,25 @@ struct Workspace {
     uint64_t *keys = nullptr, *keys_alt = nullptr;
     uint32_t *idx = nullptr, *idx_alt = nullptr;      // tree position -> input index
     uint32_t *code = nullptr;                         // tree-build per-moonlet code
-    double *xs = nullptr, *ys = nullptr, *zs = nullptr, *mus = nullptr;
+    double *xs = nullptr, *ys = nullptr, *zs = nullptr;
     double *vxs = nullptr, *vys = nullptr, *vzs = nullptr, *rads = nullptr;
     // packed 32-byte records in input order, staging for the gathers into tree or
     // mesh order: (x, y, z, 0) from the key passes, (vx, vy, vz, R) before a
     // collision search
     double4 *pack4 = nullptr;
     double4 *pcol = nullptr;                          // x, y, z, R + dt |v| (collisions)
-    double4 *vcol = nullptr;                          // vx, vy, vz, R (tree order, collisions)
+    // tree order: (vx, vy, vz, R) during a collision search; from a gravity evaluation's
+    // gather to its direct sums, (x, y, z, G m), which the climb reads too
+    double4 *vcol = nullptr;
     double4 *cbox = nullptr;                          // per leaf: box low corner + largest
                                                       // R + dt |v|, box high corner
     double *acc = nullptr;                            // 3 x n, input order (step)
     double *acc_s = nullptr;                          // 3 x n, tree order (direct sums)
     // leaves in moonlet order ("entries")
     int32_t *ent_start = nullptr;                     // first moonlet
-    uint32_t *ent_code = nullptr;                     // dv | L << 8
+    uint32_t *ent_code = nullptr;                     // dv | L << 8; after the build, the
+                                                      // source moonlets and then the slots
+                                                      // of each leaf's direct sums
     int32_t *ent_cell = nullptr;                      // cell index of the leaf
     // cells, breadth-first
     int32_t *c_level = nullptr, *c_first = nullptr, *c_count = nullptr;
@@ -304,6 +308,7 @@ struct Workspace {
     // per-target lists written by the gravity walk
     int32_t *m2l_cnt = nullptr, *m2l_seg = nullptr;   // by target cell, m2l_stride slots
     int32_t *p2p_cnt = nullptr, *p2p_seg = nullptr;   // by target leaf, p2p_stride slots
+    int32_t *split_p2p = nullptr;                     // slots of split or long direct sums
     int32_t *long_p2p = nullptr;                      // leaves with a long direct-sum list
     double *p2p_part = nullptr;                       // kLongSlots x 3 x n partial sums
     int32_t *cnt_a = nullptr;                         // tree-build level counters
@@ -372,8 +377,9 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max,
 // ---------------------------------------------------------------- launchers
 // (each returns hipSuccess or the first launch error)
 hipError_t launch_reset_state(const Workspace &ws, hipStream_t s);
-hipError_t launch_gather_scaled(const Workspace &ws, const double *src, double scale,
-                                double *dst, int64_t n, hipStream_t s);
+// (x, y, z, G m) into tree order (ws.vcol)
+hipError_t launch_gather_mass(const Workspace &ws, const double *m, double G, int64_t n,
+                              hipStream_t s);
 // disk_off: n_disks + 1 device offsets of a batched call (nullptr for a plain call);
 // m: masses (input order) to pack as G m beside the positions, or nullptr;
 // max_ready (plain calls): the step's drift has already formed max |coordinate|
@@ -386,7 +392,7 @@ hipError_t launch_sort(const Workspace &ws, int64_t n, hipStream_t s);
 // writes where it starts)
 bool bucket_sort_applies(const Workspace &ws, int64_t n);
 hipError_t launch_bucket_sort(const Workspace &ws, int64_t n, hipStream_t s);
-// with_mus: the keys packed G m, which lands in ws.mus too
+// with_mus: the keys packed G m, and the whole record lands in ws.vcol
 hipError_t launch_gather_pos(const Workspace &ws, int64_t n, bool with_mus, hipStream_t s);
 hipError_t launch_gather(const Workspace &ws, const double *src, double *dst, int64_t n,
                          hipStream_t s);
@@ -413,7 +419,8 @@ hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_po
 hipError_t launch_count_interactions(const Workspace &ws, hipStream_t s);
 
 hipError_t launch_m2l(const Workspace &ws, int p, int precision, hipStream_t s);
-hipError_t launch_l2l(const Workspace &ws, int p, hipStream_t s);
+// also orders and splits the direct sums' lists, for launch_p2p with the same tile
+hipError_t launch_l2l(const Workspace &ws, int p, int precision, int tile, hipStream_t s);
 hipError_t launch_p2p(const Workspace &ws, int64_t n, int precision, int tile, int tmax,
                       hipStream_t s);
 // acc4 non-null: the accelerations as one (ax, ay, az, 0) record per moonlet in

@@ -6,14 +6,16 @@
 // and its ancestors' walk tensors, each shifted to the leaf's centre; that sum is
 // formed directly per leaf (shifts compose exactly), so no pass waits on another.
 //
-// Evaluation: one wave per leaf.  Its sources (every cell the walk paired with
-// the leaf or one of its ancestors for a direct sum) are prefix-summed into one
-// flat range and streamed through LDS 256 moonlets at a time; leaves with fewer
-// than 64 moonlets split each tile over lane groups.  In the FP32-bulk form offsets from the leaf centre are formed in
-// FP64 and rounded, each source tile is summed in FP32, and the tile sums are
-// added with Kahan compensation.  The leaf's C tensors then give
+// Evaluation: one wave per leaf, or several where a leaf's sums would outlast the others'.
+// Its sources (every cell the walk paired with the leaf or one of its ancestors for a
+// direct sum) are prefix-summed 64 cells at a time into one flat range and streamed
+// through LDS 256 moonlets at a time; leaves with fewer than 64 moonlets split each tile
+// over lane groups.  In the FP32-bulk form offsets from the leaf centre are formed in FP64
+// and rounded, each source tile is summed in FP32, and the tile sums are added with Kahan
+// compensation.  The leaf's C tensors then give
 // a_i += sum_{|b| <= p-1} C_{e+b}(s_leaf) (x_i - s_leaf)^b / b!.
 #include "ncorp_internal.h"
+#include "expansion.h"
 
 namespace ncorp {
 
@@ -105,14 +107,72 @@ __device__ __forceinline__ void walk_totals(DevState *st, const int32_t *ctr,
     }
 }
 
+// How many waves share a leaf's direct sums (up to kLongSlots): as many as it has shares
+// of about `quantum` moonlet interactions.  The chip holds some 6000 waves and an average
+// leaf has 15000 to 60000 interactions (s = 48 and 96), so a small tree's leaves are
+// all split, and in a large one only those that would outlast the others.  A share costs
+// about 10 us of dependent loads before its first tile, hence the lower limit; in between
+// four interactions a leaf, and never so many that the heaviest leaves are left whole.
+// The rule knows its own tree only, so a disk's sums are the same in a batch and alone.
+// Unsplit -> split, direct sums alone: 9973 moonlets in 519 leaves 129 -> 46 us, 1e6 in
+// 2.7e4 FP32 582 -> 435 us; a quantum of 2048 instead for 1e5 in 2700: 88 -> 103 us.
+constexpr int64_t kQuantumMin = 2048, kQuantumMax = 49152;
+struct SplitArgs {
+    const int32_t *p2p_cnt, *c_count, *c_first, *c_nent;
+    const uint16_t *seg;                 // batched: disk of every tree position, else nullptr
+    const int32_t *disk_root;
+    uint32_t *src;                       // per leaf: source moonlets in, slots out
+    int32_t *longs;                      // leaves whose list is beyond one LDS batch
+    int32_t *split;                      // slots (leaf | slot << 24) of the leaves with more
+    int64_t split_cap;                   // than one or a long list, and room for them
+    int unit;                            // source moonlets handed out at a time
+};
+__device__ __forceinline__ void split_leaf(DevState *st, const SplitArgs &S, int e, int c) {
+    const int64_t src = S.src[e];
+    const int K = S.seg ? S.c_nent[S.disk_root[S.seg[S.c_first[c]]]] : st->nleaves;
+    int64_t quantum = 4 * (int64_t)K;
+    quantum = quantum < kQuantumMin ? kQuantumMin : (quantum > kQuantumMax ? kQuantumMax : quantum);
+    int64_t slots = (src * S.c_count[c] + quantum / 2) / quantum;
+    const int64_t units = (src + S.unit - 1) / S.unit;
+    slots = slots < units ? slots : units;
+    int64_t most = S.split_cap / st->nleaves;
+    most = most > kLongSlots ? kLongSlots : most;
+    slots = slots > most ? most : slots;
+    slots = slots < 1 ? 1 : slots;
+    S.src[e] = (uint32_t)slots;
+    // one atomic per wave for the list's length
+    const bool lng = S.p2p_cnt[e] > kP2PListLDS;
+    if (const uint64_t ml = __ballot(lng)) {
+        const int ln = threadIdx.x & (kWave - 1), first = __ffsll((unsigned long long)ml) - 1;
+        int at = 0;
+        if (ln == first) at = atomicAdd(&st->nlong, __popcll(ml));
+        at = __shfl(at, first);
+        if (lng) S.longs[at + __popcll(ml & (ln == 0 ? 0ull : (~0ull >> (64 - ln))))] = e;
+    }
+    // a list that cannot hold every leaf is left empty (k_p2p knows)
+    const int add = (slots > 1 || lng) && most > 0 ? (int)slots : 0;
+    if (!__any(add)) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int lead = __ffsll((unsigned long long)__ballot(1)) - 1;
+    int off = 0, tot = 0;                // the slots of the lanes below and of all
+    for (uint64_t act = __ballot(add > 0); act; act &= act - 1) {
+        const int l = __ffsll((unsigned long long)act) - 1;
+        if (lane == l) off = tot;
+        tot += __shfl(add, l);
+    }
+    int base = 0;
+    if (lane == lead) base = atomicAdd(&st->nsplit, tot);
+    base = __shfl(base, lead) + off;
+    for (int k = 0; k < add; k++) S.split[base + k] = e | (k << 24);
+}
+
 template <int P>
 __global__ void __launch_bounds__(128)
 k_leaf_local(DevState *st, const int32_t *__restrict__ ent_cell,
              const int32_t *__restrict__ c_parent, const double4 *__restrict__ gcell,
              const double *__restrict__ local, const int32_t *__restrict__ m2l_cnt,
-             double *__restrict__ cleaf, const int32_t *__restrict__ p2p_cnt,
-             int32_t *__restrict__ longs, const int32_t *__restrict__ walk_ctr,
-             const WalkCaps caps) {
+             double *__restrict__ cleaf, const SplitArgs S,
+             const int32_t *__restrict__ walk_ctr, const WalkCaps caps) {
     constexpr int NL = n_local(P);
     if (blockIdx.x == 0 && threadIdx.x < kWave) walk_totals(st, walk_ctr, caps);
     if (st->status & kSkipMask) return;
@@ -121,20 +181,7 @@ k_leaf_local(DevState *st, const int32_t *__restrict__ ent_cell,
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
          t += (int64_t)gridDim.x * blockDim.x) {
         const int m = (int)(t / K) + 1, e = (int)(t % K);
-        if (m == 1) {
-            // leaves whose direct sums are split over several waves, one atomic per wave
-            const bool lng = p2p_cnt[e] > kP2PListLDS;
-            const uint64_t act = __ballot(1), ml = __ballot(lng);
-            if (ml) {
-                const int lane = threadIdx.x & (kWave - 1);
-                const int lead = __ffsll((unsigned long long)act) - 1;
-                int base = 0;
-                if (lane == lead) base = atomicAdd(&st->nlong_p2p, __popcll(ml));
-                base = __shfl(base, lead);
-                const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-                if (lng) longs[base + __popcll(ml & lt)] = e;
-            }
-        }
+        if (m == 1) split_leaf(st, S, e, ent_cell[e]);
         const int cl = ent_cell[e];
         double *out = cleaf + (int64_t)e * NL;
         switch (m) {
@@ -153,7 +200,8 @@ k_leaf_local(DevState *st, const int32_t *__restrict__ ent_cell,
 template <typename T> struct Acc3;
 template <> struct Acc3<double> {
     double x = 0, y = 0, z = 0;
-    __device__ void add_tile(double px, double py, double pz) { x += px; y += py; z += pz; }
+    __device__ void open_tile(double &px, double &py, double &pz) const { px = x; py = y; pz = z; }
+    __device__ void close_tile(double px, double py, double pz) { x = px; y = py; z = pz; }
     __device__ void fold(double &ox, double &oy, double &oz) const { ox = x; oy = y; oz = z; }
 };
 // Kahan-compensated FP32 sums of FP32 tile partials
@@ -165,7 +213,8 @@ template <> struct Acc3<float> {
         c = (t - s) - yv;
         s = t;
     }
-    __device__ void add_tile(float px, float py, float pz) {
+    __device__ void open_tile(float &px, float &py, float &pz) const { px = py = pz = 0.0f; }
+    __device__ void close_tile(float px, float py, float pz) {
         kahan(x, cx, px); kahan(y, cy, py); kahan(z, cz, pz);
     }
     __device__ void fold(double &ox, double &oy, double &oz) const {
@@ -184,9 +233,6 @@ __device__ __forceinline__ int wave_excl_sum_p(int v, int lane, int &total) {
     return x - v;
 }
 
-template <typename T> __device__ __forceinline__ T rsq(T v);
-template <> __device__ __forceinline__ double rsq<double>(double v) { return rsqrt(v); }
-template <> __device__ __forceinline__ float rsq<float>(float v) { return rsqrtf(v); }
 template <typename T> __device__ __forceinline__ T fmat(T a, T b, T c);
 template <> __device__ __forceinline__ double fmat<double>(double a, double b, double c) { return fma(a, b, c); }
 template <> __device__ __forceinline__ float fmat<float>(float a, float b, float c) { return fmaf(a, b, c); }
@@ -195,9 +241,8 @@ template <typename T> struct Vec4;
 template <> struct Vec4<float> { using type = float4; };
 template <> struct Vec4<double> { using type = double4; };
 // r^2 floor: a moonlet meets itself (dx = 0) in its own leaf; the floor keeps
-// 1/r^3 finite there so the term is exactly 0, and is far below any pair distance
-// (FP32: added to r^2; FP64: a lower bound on r^2).  m / floor^(3/2) stays finite for
-// G m up to ~3e11 (FP32) and ~1e158 (FP64).
+// 1/r^3 finite there so the term is exactly 0; it is added to r^2 and far below any pair
+// distance.  m / floor^(3/2) stays finite for G m up to ~3e11 (FP32) and ~1e158 (FP64).
 template <typename T> __device__ __forceinline__ T r2_floor();
 template <> __device__ __forceinline__ float r2_floor<float>() { return 1e-18f; }
 template <> __device__ __forceinline__ double r2_floor<double>() { return 1e-100; }
@@ -215,6 +260,16 @@ __device__ __forceinline__ int batch_prefix(int cnt, int32_t *s_pref, int lane) 
     return tot;
 }
 
+// An offset from the leaf centre: in FP64 held to +-1e150, so that r2 stays finite (at
+// such distances the term is 0 either way).
+template <typename T> __device__ __forceinline__ T offset_of(double d) {
+    if constexpr (sizeof(T) == 8) {
+        const double lim = 1e150;
+        return d > lim ? lim : (d < -lim ? -lim : d);
+    }
+    return (T)d;
+}
+
 // One source against the NT targets a lane holds.
 template <typename T, int NT>
 __device__ __forceinline__ void interact(const typename Vec4<T>::type &v, const T (&xi)[NT],
@@ -224,66 +279,80 @@ __device__ __forceinline__ void interact(const typename Vec4<T>::type &v, const 
 #pragma unroll
     for (int k = 0; k < NT; k++) {
         const T dx = v.x - xi[k], dy = v.y - yi[k], dz = v.z - zi[k];
-        T rinv;
+        // the floor enters as an addend, so r2 is a normal number and the hardware
+        // reciprocal square root needs no handling of small ones
+        const T r2 = fmat<T>(dz, dz, fmat<T>(dy, dy, fmat<T>(dx, dx, floor2)));
+        T w;
         if constexpr (sizeof(T) == 4) {
-            // the floor enters as an addend, so r2 >= 1e-24 is a normal float and the
-            // hardware reciprocal square root needs no denormal handling
-            const T r2 = fmat<T>(dz, dz, fmat<T>(dy, dy, fmat<T>(dx, dx, floor2)));
-            rinv = __builtin_amdgcn_rsqf(r2);
+            const T rinv = __builtin_amdgcn_rsqf(r2);
+            w = v.w * (rinv * rinv) * rinv;
         } else {
-            T r2 = fmat<T>(dz, dz, fmat<T>(dy, dy, dx * dx));
-            r2 = r2 > floor2 ? r2 : floor2;
-            rinv = rsq<T>(r2);
+            w = over_r3(v.w, r2);
         }
-        const T w = v.w * (rinv * rinv) * rinv;
         px[k] = fmat<T>(dx, w, px[k]);
         py[k] = fmat<T>(dy, w, py[k]);
         pz[k] = fmat<T>(dz, w, pz[k]);
     }
 }
 
-// Direct sums of the NT targets a lane holds over a batch of source cells whose
-// moonlet ranges are s_first[k] .. + (s_pref[k+1] - s_pref[k]), k < nsb, tot
-// moonlets in all; the batch is streamed through LDS TILE moonlets at a time and
-// the lane's group takes sources j0, j0 + G, ... of every tile.
+// The tiles of a batch one wave takes: source moonlets [q0, q1) in tiles q0, q0 + step,
+// ...  (a leaf's whole batch, or one slot's share of it).
+struct TileRange {
+    int q0, q1, step;
+};
+
+// Slot `slot` of nslots of a batch of tot moonlets.  FP32: every nslots-th tile, so the
+// tiles and their FP32 sums are those of the undivided batch.  FP64: an equal share of
+// the moonlets, which fills the slots of a batch of few tiles.
+template <typename T, int TILE>
+__device__ __forceinline__ TileRange slot_tiles(int tot, int slot, int nslots) {
+    if (sizeof(T) == 4) return TileRange{slot * TILE, tot, nslots * TILE};
+    const int per = ((tot + nslots - 1) / nslots + kWave - 1) / kWave * kWave;
+    const int q0 = slot * per;
+    return TileRange{q0, q0 + per < tot ? q0 + per : tot, TILE};
+}
+
+// Direct sums of the NT targets a lane holds over a range of a batch of source cells
+// whose moonlet ranges are s_first[k] .. + (s_pref[k+1] - s_pref[k]), k < nsb; the
+// range is streamed through LDS TILE moonlets at a time and the lane's group takes
+// sources j0, j0 + G, ... of every tile.
 template <typename T, int NT, int TILE>
-__device__ __forceinline__ void p2p_batch(int tot, int nsb, const int32_t *s_first,
+__device__ __forceinline__ void p2p_batch(const TileRange tr, int nsb, const int32_t *s_first,
                                           const int32_t *s_pref,
                                           typename Vec4<T>::type *tile,
-                                          const double *__restrict__ xs,
-                                          const double *__restrict__ ys,
-                                          const double *__restrict__ zs,
-                                          const double *__restrict__ mus, const double4 g,
+                                          const double4 *__restrict__ pos4, const double4 g,
                                           const T (&xi)[NT], const T (&yi)[NT], const T (&zi)[NT],
                                           int j0, int G, Acc3<T> (&acc)[NT]) {
     using V = typename Vec4<T>::type;
     const int lane = threadIdx.x & (kWave - 1);
-    for (int p0 = 0; p0 < tot; p0 += TILE) {
-        const int nj = tot - p0 < TILE ? tot - p0 : TILE;
+    for (int p0 = tr.q0; p0 < tr.q1; p0 += tr.step) {
+        const int nj = tr.q1 - p0 < TILE ? tr.q1 - p0 : TILE;
         // stage the tile: source moonlet q of the batch -> its cell by binary
         // search over the prefix sums
 #pragma unroll
         for (int k = 0; k < TILE / 64; k++) {
             const int q = p0 + lane + 64 * k;
-            if (q < tot) {
+            if (q < tr.q1) {
                 int lo = 0, hi = nsb;          // s_pref[lo] <= q < s_pref[hi]
                 while (hi - lo > 1) {
                     const int mid = (lo + hi) >> 1;
                     if (s_pref[mid] <= q) lo = mid; else hi = mid;
                 }
                 const int j = s_first[lo] + (q - s_pref[lo]);
+                const double4 s = pos4[j];
                 V v;
-                v.x = (T)(xs[j] - g.x);
-                v.y = (T)(ys[j] - g.y);
-                v.z = (T)(zs[j] - g.z);
-                v.w = (T)mus[j];
+                v.x = offset_of<T>(s.x - g.x);
+                v.y = offset_of<T>(s.y - g.y);
+                v.z = offset_of<T>(s.z - g.z);
+                v.w = (T)s.w;
                 tile[lane + 64 * k] = v;
             }
         }
         wave_sync();
+        // FP64 adds to the running sums; FP32 sums each tile by itself
         T px[NT], py[NT], pz[NT];
 #pragma unroll
-        for (int k = 0; k < NT; k++) px[k] = py[k] = pz[k] = (T)0;
+        for (int k = 0; k < NT; k++) acc[k].open_tile(px[k], py[k], pz[k]);
         if constexpr (NT == 1) {
 #pragma unroll 4
             for (int j = j0; j < nj; j += G) interact<T, NT>(tile[j], xi, yi, zi, px, py, pz);
@@ -294,26 +363,67 @@ __device__ __forceinline__ void p2p_batch(int tot, int nsb, const int32_t *s_fir
             for (int j = j0; j < nj; j += G) interact<T, NT>(tile[j], xi, yi, zi, px, py, pz);
         }
 #pragma unroll
-        for (int k = 0; k < NT; k++) acc[k].add_tile(px[k], py[k], pz[k]);
+        for (int k = 0; k < NT; k++) acc[k].close_tile(px[k], py[k], pz[k]);
         wave_sync();
     }
 }
 
-// Direct sums for ntc <= 64 targets (moonlets tb .. tb+ntc-1) of one leaf, over
-// the whole list (one LDS batch) or over its batches b0, b0 + bstep, ... of
-// kP2PSrc source cells.  The lanes form G = 64 / lpg groups of lpg = ceil(ntc / NT)
-// lanes; lane li of a group holds targets li and li + lpg (NT = 2), and the groups
-// split every tile's sources.  The group partials are added in group order and
-// written to out[d * n + i], d = x, y, z.
+// Stages batch b of a leaf's source list: the moonlet ranges of its up to kP2PSrc cells
+// in s_first and s_pref; returns the batch's moonlets.  FP64 takes the cells in the
+// walk's order.  FP32 takes them in cell order, which its tile sums are rounded in: a
+// list of one batch is ranked here (`rank`: scratch of kP2PSrc ints, free until the
+// first tile), a longer one was sorted by the pre-pass.
+template <typename T>
+__device__ __forceinline__ int stage_batch(const int32_t *__restrict__ list, int len, int b,
+                                           const int32_t *__restrict__ c_first,
+                                           const int32_t *__restrict__ c_count,
+                                           int32_t *s_first, int32_t *s_pref, int32_t *rank) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool in = b * kP2PSrc + lane < len;
+    const int v = in ? list[b * kP2PSrc + lane] : 0x7fffffff;
+    int cf = 0, cn = 0;
+    if (in) {
+        cf = c_first[v];
+        cn = c_count[v];
+    }
+    wave_sync();                                  // the last batch is done with
+    if (sizeof(T) == 4 && len <= kP2PSrc) {
+        rank[lane] = v;
+        wave_sync();
+        if (in) {
+            const int4 *s4 = reinterpret_cast<const int4 *>(rank);
+            int rk = 0;
+#pragma unroll
+            for (int j = 0; j < kP2PSrc / 4; j++) {
+                const int4 t = s4[j];
+                rk += (t.x < v) + (t.y < v) + (t.z < v) + (t.w < v);
+            }
+            s_first[rk] = cf;
+            s_pref[rk] = cn;
+        }
+        wave_sync();
+        cn = in ? s_pref[lane] : 0;
+        wave_sync();
+    } else {
+        s_first[lane] = cf;
+    }
+    const int tot = batch_prefix(cn, s_pref, lane);
+    wave_sync();
+    return tot;
+}
+
+// Direct sums for ntc <= 64 targets (moonlets tb .. tb+ntc-1) of one leaf, over slot
+// `slot` of nslots of its list: the batches of kP2PSrc source cells are dealt to the
+// slots, and where there are fewer batches than slots, each batch's tiles to its share
+// of them.  The lanes form G = 64 / lpg groups of lpg = ceil(ntc / NT) lanes; lane li
+// of a group holds targets li, li + lpg, ..., and the groups split every tile's
+// sources.  The group partials are added in a fixed tree and written to out[d * n + i],
+// d = x, y, z.
 template <typename T, int NT, int TILE>
-__device__ __forceinline__ void p2p_targets(int ntc, int tb, bool one, int tot1, int len,
-                                            int b0, int bstep,
+__device__ __forceinline__ void p2p_targets(int ntc, int tb, int len, int slot, int nslots,
                                             const int32_t *__restrict__ list, int32_t *s_first,
                                             int32_t *s_pref, typename Vec4<T>::type *tile,
-                                            const double *__restrict__ xs,
-                                            const double *__restrict__ ys,
-                                            const double *__restrict__ zs,
-                                            const double *__restrict__ mus,
+                                            const double4 *__restrict__ pos4,
                                             const int32_t *__restrict__ c_first,
                                             const int32_t *__restrict__ c_count, const double4 g,
                                             double *__restrict__ out, int64_t n) {
@@ -326,49 +436,48 @@ __device__ __forceinline__ void p2p_targets(int ntc, int tb, bool one, int tot1,
     for (int k = 0; k < NT; k++) {
         const int t = li + k * lpg;
         const int i = tb + (t < ntc ? t : 0);
-        xi[k] = (T)(xs[i] - g.x);
-        yi[k] = (T)(ys[i] - g.y);
-        zi[k] = (T)(zs[i] - g.z);
+        const double4 p = pos4[i];
+        xi[k] = offset_of<T>(p.x - g.x);
+        yi[k] = offset_of<T>(p.y - g.y);
+        zi[k] = offset_of<T>(p.z - g.z);
     }
     const int j0 = grp < G ? grp : TILE;           // lanes beyond the groups idle
     Acc3<T> acc[NT];
-    if (one) {
-        p2p_batch<T, NT, TILE>(tot1, len, s_first, s_pref, tile, xs, ys, zs, mus, g, xi, yi, zi, j0,
-                         G, acc);
-    } else {
-        for (int sb = b0 * kP2PSrc; sb < len; sb += bstep * kP2PSrc) {
-            const int nsb = len - sb < kP2PSrc ? len - sb : kP2PSrc;
-            wave_sync();
-            int cf = 0, cn = 0;
-            if (lane < nsb) {
-                const int B = list[sb + lane];
-                cf = c_first[B];
-                cn = c_count[B];
-            }
-            s_first[lane] = cf;
-            const int tot = batch_prefix(cn, s_pref, lane);
-            wave_sync();
-            p2p_batch<T, NT, TILE>(tot, nsb, s_first, s_pref, tile, xs, ys, zs, mus, g, xi, yi, zi,
-                             j0, G, acc);
+    const int nb = (len + kP2PSrc - 1) / kP2PSrc;
+    const int b0 = nb < nslots ? slot * nb / nslots : slot;
+    // the slots that share batch b0: those with slot * nb / nslots = b0
+    const int s0 = nb < nslots ? (b0 * nslots + nb - 1) / nb : slot;
+    const int s1 = nb < nslots ? ((b0 + 1) * nslots + nb - 1) / nb : slot + 1;
+    for (int b = b0; b < nb; b += nb < nslots ? nb : nslots) {
+        const int tot = stage_batch<T>(list, len, b, c_first, c_count, s_first, s_pref,
+                                       reinterpret_cast<int32_t *>(tile));
+        const int nsb = len - b * kP2PSrc < kP2PSrc ? len - b * kP2PSrc : kP2PSrc;
+        p2p_batch<T, NT, TILE>(slot_tiles<T, TILE>(__builtin_amdgcn_readfirstlane(tot),
+                                                   slot - s0, s1 - s0),
+                               nsb, s_first, s_pref, tile, pos4, g, xi, yi, zi, j0, G, acc);
+    }
+    // the groups' partials, added pairwise in a fixed tree (a leaf of 5 targets has 32
+    // groups: one after the other they took as long as its sums)
+    double px[NT], py[NT], pz[NT];
+#pragma unroll
+    for (int k = 0; k < NT; k++) acc[k].fold(px[k], py[k], pz[k]);
+    for (int o = 1; o < G; o <<= 1) {
+        const bool add = (grp & (2 * o - 1)) == 0 && grp + o < G;
+#pragma unroll
+        for (int k = 0; k < NT; k++) {
+            const double ox = __shfl_down(px[k], o * lpg);
+            const double oy = __shfl_down(py[k], o * lpg);
+            const double oz = __shfl_down(pz[k], o * lpg);
+            if (add) { px[k] += ox; py[k] += oy; pz[k] += oz; }
         }
     }
-    // add the partials of groups 1 .. G-1 to group 0's, in group order
 #pragma unroll
     for (int k = 0; k < NT; k++) {
-        double px, py, pz;                     // this lane's partials
-        acc[k].fold(px, py, pz);
-        double ox = px, oy = py, oz = pz;
-        for (int gi = 1; gi < G; gi++) {
-            const int src = gi * lpg + li;
-            ox += __shfl(px, src);
-            oy += __shfl(py, src);
-            oz += __shfl(pz, src);
-        }
         const int t = li + k * lpg;
         if (grp == 0 && t < ntc) {
-            out[tb + t] = ox;
-            out[n + tb + t] = oy;
-            out[2 * n + tb + t] = oz;
+            out[tb + t] = px[k];
+            out[n + tb + t] = py[k];
+            out[2 * n + tb + t] = pz[k];
         }
     }
 }
@@ -391,132 +500,81 @@ __device__ __forceinline__ int targets_per_lane(int ntc, int tmax) {
 }
 
 template <typename T, int TILE>
-__device__ __forceinline__ void p2p_targets_any(int ntc, int tmax, int tb, bool one, int tot1,
-                                                int len, int b0, int bstep,
-                                                const int32_t *__restrict__ list,
+__device__ __forceinline__ void p2p_targets_any(int ntc, int tmax, int tb, int len, int slot,
+                                                int nslots, const int32_t *__restrict__ list,
                                                 int32_t *s_first, int32_t *s_pref,
                                                 typename Vec4<T>::type *tile,
-                                                const double *__restrict__ xs,
-                                                const double *__restrict__ ys,
-                                                const double *__restrict__ zs,
-                                                const double *__restrict__ mus,
+                                                const double4 *__restrict__ pos4,
                                                 const int32_t *__restrict__ c_first,
                                                 const int32_t *__restrict__ c_count,
                                                 const double4 g, double *__restrict__ out,
                                                 int64_t n) {
     switch (targets_per_lane(ntc, tmax)) {
         case 1:
-            p2p_targets<T, 1, TILE>(ntc, tb, one, tot1, len, b0, bstep, list, s_first, s_pref, tile,
-                              xs, ys, zs, mus, c_first, c_count, g, out, n);
+            p2p_targets<T, 1, TILE>(ntc, tb, len, slot, nslots, list, s_first, s_pref, tile, pos4,
+                                    c_first, c_count, g, out, n);
             break;
         case 2:
-            p2p_targets<T, 2, TILE>(ntc, tb, one, tot1, len, b0, bstep, list, s_first, s_pref, tile,
-                              xs, ys, zs, mus, c_first, c_count, g, out, n);
+            p2p_targets<T, 2, TILE>(ntc, tb, len, slot, nslots, list, s_first, s_pref, tile, pos4,
+                                    c_first, c_count, g, out, n);
             break;
         case 3:
-            p2p_targets<T, 3, TILE>(ntc, tb, one, tot1, len, b0, bstep, list, s_first, s_pref, tile,
-                              xs, ys, zs, mus, c_first, c_count, g, out, n);
+            p2p_targets<T, 3, TILE>(ntc, tb, len, slot, nslots, list, s_first, s_pref, tile, pos4,
+                                    c_first, c_count, g, out, n);
             break;
         default:
-            p2p_targets<T, 4, TILE>(ntc, tb, one, tot1, len, b0, bstep, list, s_first, s_pref, tile,
-                              xs, ys, zs, mus, c_first, c_count, g, out, n);
+            p2p_targets<T, 4, TILE>(ntc, tb, len, slot, nslots, list, s_first, s_pref, tile, pos4,
+                                    c_first, c_count, g, out, n);
             break;
     }
 }
 
-constexpr int kP2PWaves = 4;        // independent waves per block
-static_assert(kP2PListLDS == kP2PSrc, "one LDS batch holds a list that is not split");
+constexpr int kP2PRun = 8;
+constexpr int64_t kP2PGrid = 65536;  // most blocks, of one wave each
+static_assert(kP2PListLDS == kP2PSrc, "one LDS batch holds a list that is not long");
 
-// Direct sums of every leaf, one wave per work item.  A leaf whose source list fits
-// one LDS batch is one item.  A leaf whose list is longer (the descent recorded it)
-// would keep a single wave busy long after all others finished, so it is split over
-// kLongSlots items: item `slot` takes the batches slot, slot + kLongSlots, ... and
-// writes its partial sums to part[slot], which the evaluation kernel adds in slot
-// order.  The split items come first, so they start first and the short leaves fill
-// in around them within the same launch.
+// Direct sums of every leaf, one wave per work item: a leaf, or one of the slots of a
+// leaf that is split (split_leaf), whose partial sums the evaluation kernel adds in slot
+// order.  The split and the long leaves come first, so they start first and the others
+// fill in around them within the same launch, which the hardware deals out as waves end:
+// blocks of one wave, an item each.  Four waves a block and items by position took 582 us
+// at N = 1e6, s = 96 in FP32, where this takes 435; persistent waves with counters 490.
 template <typename T, int TILE>
-__global__ void __launch_bounds__(kWave * kP2PWaves)
-k_p2p(const DevState *__restrict__ st, const double *__restrict__ xs,
-      const double *__restrict__ ys, const double *__restrict__ zs,
-      const double *__restrict__ mus, const int32_t *__restrict__ ent_cell,
+__global__ void __launch_bounds__(kWave, sizeof(T) == 8 ? 5 : 4)
+k_p2p(const DevState *__restrict__ st, const double4 *__restrict__ pos4,
+      const int32_t *__restrict__ ent_cell,
       const int32_t *__restrict__ c_first, const int32_t *__restrict__ c_count,
       const double4 *__restrict__ gcell, const int32_t *__restrict__ p2p_cnt,
-      const int32_t *__restrict__ p2p_seg, int stride, const int32_t *__restrict__ longs,
-      double *__restrict__ part, double *__restrict__ acc_s, int64_t n, int tmax) {
+      const int32_t *__restrict__ p2p_seg, int stride, const int32_t *__restrict__ split,
+      int64_t split_cap,
+      const uint32_t *__restrict__ slots, double *__restrict__ part,
+      double *__restrict__ acc_s, int64_t n, int tmax) {
     using V = typename Vec4<T>::type;
     static_assert(TILE % 64 == 0, "a tile is staged one moonlet per lane");
-    __shared__ __align__(16) V tiles[kP2PWaves][TILE];
-    __shared__ int32_t firsts[kP2PWaves][kP2PSrc], prefs[kP2PWaves][kP2PSrc + 1];
+    __shared__ __align__(16) V tile[TILE];
+    __shared__ int32_t firsts[kP2PSrc], prefs[kP2PSrc + 1];
     if (st->status & kSkipMask) return;
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    V *tile = tiles[wid];
-    int32_t *s_first = firsts[wid], *s_pref = prefs[wid];
     const int K = st->nleaves;
-    const int nlong = st->nlong_p2p * kLongSlots;
-    for (int w = blockIdx.x * kP2PWaves + wid; w < nlong + K; w += gridDim.x * kP2PWaves) {
-        if (w < nlong) {
-            const int e = longs[w / kLongSlots], slot = w % kLongSlots;
-            const int c = ent_cell[e];
-            const int f = c_first[c], nt = c_count[c];
-            const double4 g = gcell[c];
-            const int32_t *list = p2p_seg + (int64_t)e * stride;
-            const int len = p2p_cnt[e];
-            double *out = part + (int64_t)slot * 3 * n;
-            wave_sync();                              // this wave's LDS is free again
-            for (int t0 = 0; t0 < nt; t0 += kWave) {
-                const int ntc = nt - t0 < kWave ? nt - t0 : kWave;
-                p2p_targets_any<T, TILE>(ntc, tmax, f + t0, false, 0, len, slot, kLongSlots,
-                                         list, s_first, s_pref, tile, xs, ys, zs, mus, c_first,
-                                         c_count, g, out, n);
-            }
-            continue;
-        }
-        const int e = w - nlong;
+    const int nsplit = st->nsplit;
+    const int items = nsplit + K;
+    const bool listed = K <= split_cap;   // split and long leaves are in the list
+    // runs of kP2PRun items (the slots of a leaf, neighbouring leaves) stay on an XCD
+    constexpr int kRound = kXcds * kP2PRun;
+    for (int b = blockIdx.x; b < (items + kRound - 1) / kRound * kRound; b += gridDim.x) {
+        const int w = (b / kRound * kXcds + b % kXcds) * kP2PRun + b / kXcds % kP2PRun;
+        if (w >= items) continue;
+        const bool lng = w < nsplit;
+        const int ent = lng ? split[w] : w - nsplit;
+        const int e = ent & 0xffffff, slot = ent >> 24;
+        const int nslots = (int)slots[e], len = p2p_cnt[e];
+        if (!lng && listed && (nslots > 1 || len > kP2PSrc)) continue;
         const int c = ent_cell[e];
         const int f = c_first[c], nt = c_count[c];
-        const double4 g = gcell[c];
-        const int32_t *list = p2p_seg + (int64_t)e * stride;
-        const int len = p2p_cnt[e];
-        if (len > kP2PSrc) continue;                  // split into the items above
-        wave_sync();                                  // this wave's LDS is free again
-        int tot1;
-        if constexpr (sizeof(T) == 8) {
-            // one batch, in the walk's order
-            const int v = lane < len ? list[lane] : 0;
-            s_first[lane] = lane < len ? c_first[v] : 0;
-            tot1 = batch_prefix(lane < len ? c_count[v] : 0, s_pref, lane);
-        } else {
-            // one batch, in cell order (the FP32 tile sums are rounded in that order):
-            // rank the sources in LDS and place each source's moonlet range at its rank
-            const int v = lane < len ? list[lane] : 0x7fffffff;
-            const int cf = lane < len ? c_first[v] : 0;
-            const int cn = lane < len ? c_count[v] : 0;
-            int32_t *scratch = reinterpret_cast<int32_t *>(tile);   // no moonlet staged yet
-            scratch[lane] = v;
-            wave_sync();
-            if (lane < len) {
-                const int4 *s4 = reinterpret_cast<const int4 *>(scratch);
-                int rk = 0;
-#pragma unroll
-                for (int j = 0; j < kP2PSrc / 4; j++) {
-                    const int4 t = s4[j];
-                    rk += (t.x < v) + (t.y < v) + (t.z < v) + (t.w < v);
-                }
-                s_first[rk] = cf;
-                s_pref[rk] = cn;
-            }
-            wave_sync();
-            const int c1 = lane < len ? s_pref[lane] : 0;
-            wave_sync();
-            tot1 = batch_prefix(c1, s_pref, lane);
-        }
-        wave_sync();
-        for (int t0 = 0; t0 < nt; t0 += kWave) {
-            const int ntc = nt - t0 < kWave ? nt - t0 : kWave;
-            p2p_targets_any<T, TILE>(ntc, tmax, f + t0, true, tot1, len, 0, 1, list, s_first,
-                                     s_pref, tile, xs, ys, zs, mus, c_first, c_count, g, acc_s,
-                                     n);
-        }
+        double *out = nslots > 1 ? part + (int64_t)slot * 3 * n : acc_s;
+        for (int t0 = 0; t0 < nt; t0 += kWave)
+            p2p_targets_any<T, TILE>(nt - t0 < kWave ? nt - t0 : kWave, tmax, f + t0, len, slot,
+                                     nslots, p2p_seg + (int64_t)e * stride, firsts, prefs,
+                                     tile, pos4, c_first, c_count, gcell[c], out, n);
     }
 }
 
@@ -531,7 +589,7 @@ k_l2p(const DevState *__restrict__ st, const double *__restrict__ xs,
       const uint32_t *__restrict__ perm, const int32_t *__restrict__ ent_cell,
       const int32_t *__restrict__ c_first, const int32_t *__restrict__ c_count,
       const double4 *__restrict__ gcell, const double *__restrict__ cleaf,
-      const double *__restrict__ acc_s, const int32_t *__restrict__ p2p_cnt,
+      const double *__restrict__ acc_s, const uint32_t *__restrict__ slots,
       const double *__restrict__ part, int64_t n, double *__restrict__ ax,
       double *__restrict__ ay, double *__restrict__ az, double4 *__restrict__ acc4) {
     constexpr int NL = n_local(P);
@@ -542,7 +600,7 @@ k_l2p(const DevState *__restrict__ st, const double *__restrict__ xs,
         const int c = ent_cell[e];
         const int f = c_first[c], nt = c_count[c];
         const double4 g = gcell[c];
-        const bool longlist = p2p_cnt[e] > kP2PListLDS;   // direct sums in kLongSlots parts
+        const int nsl = (int)slots[e];                // direct sums in nsl parts
         // the leaf's C is wave-uniform: scalar loads, no copy in LDS
         const double *__restrict__ cle = cleaf + (int64_t)__builtin_amdgcn_readfirstlane(e) * NL;
         for (int t0 = 0; t0 < nt; t0 += 64) {
@@ -573,9 +631,8 @@ k_l2p(const DevState *__restrict__ st, const double *__restrict__ xs,
                         lz += cle[cidx(a2, b2, 1 + c2)] * w;
                     }
             double dx = 0.0, dy = 0.0, dz = 0.0;       // direct sums
-            if (longlist) {
-#pragma unroll
-                for (int sl = 0; sl < kLongSlots; sl++) {
+            if (nsl > 1) {
+                for (int sl = 0; sl < nsl; sl++) {
                     const double *ps = part + (int64_t)sl * 3 * n;
                     dx += ps[i];
                     dy += ps[n + i];
@@ -599,27 +656,16 @@ k_l2p(const DevState *__restrict__ st, const double *__restrict__ xs,
 }
 
 template <int P>
-static void launch_leaf_local(const Workspace &ws, hipStream_t s) {
+static void launch_leaf_local(const Workspace &ws, int split_unit, hipStream_t s) {
+    const SplitArgs S = {ws.p2p_cnt, ws.c_count, ws.c_first, ws.c_nent,
+                         ws.ndisks > 1 ? ws.seg : nullptr, ws.disk_root, ws.ent_code,
+                         ws.long_p2p, ws.split_p2p, 2 * ws.m2l_cap, split_unit};
     int64_t g = ((int64_t)ws.n_max * P + 127) / 128;
     if (g > 8192) g = 8192;
     if (g < 1) g = 1;
     k_leaf_local<P><<<(int)g, 128, 0, s>>>(ws.st, ws.ent_cell, ws.c_parent, ws.gcell, ws.local,
-                                           ws.m2l_cnt, ws.cleaf, ws.p2p_cnt, ws.long_p2p,
-                                           ws.walk_ctr,
+                                           ws.m2l_cnt, ws.cleaf, S, ws.walk_ctr,
                                            WalkCaps{ws.queue_cap, ws.m2l_cap, ws.p2p_cap});
-}
-
-hipError_t launch_l2l(const Workspace &ws, int p, hipStream_t s) {
-    switch (p) {
-        case 1: launch_leaf_local<1>(ws, s); break;
-        case 2: launch_leaf_local<2>(ws, s); break;
-        case 3: launch_leaf_local<3>(ws, s); break;
-        case 4: launch_leaf_local<4>(ws, s); break;
-        case 5: launch_leaf_local<5>(ws, s); break;
-        case 6: launch_leaf_local<6>(ws, s); break;
-        default: break;
-    }
-    return hipGetLastError();
 }
 
 // Direct-sum lists beyond one LDS batch, sorted in place, one block per list (rank sort
@@ -633,7 +679,7 @@ k_sort_long_lists(const DevState *__restrict__ st, const int32_t *__restrict__ c
                   int32_t *seg, int stride, const int32_t *__restrict__ longs) {
     extern __shared__ __align__(16) int32_t scr[];   // round_up(stride, 4) ints
     if (st->status & kSkipMask) return;
-    const int nl = st->nlong_p2p;
+    const int nl = st->nlong;
     for (int q = blockIdx.x; q < nl; q += gridDim.x) {
         const int t = longs[q];
         const int len = cnt[t];
@@ -657,14 +703,33 @@ k_sort_long_lists(const DevState *__restrict__ st, const int32_t *__restrict__ c
     }
 }
 
+hipError_t launch_l2l(const Workspace &ws, int p, int precision, int tile, hipStream_t s) {
+    const int split_unit = precision == NCORP_FP32_BULK ? (tile > 0 ? tile : kP2PTile) : kWave;
+    switch (p) {
+        case 1: launch_leaf_local<1>(ws, split_unit, s); break;
+        case 2: launch_leaf_local<2>(ws, split_unit, s); break;
+        case 3: launch_leaf_local<3>(ws, split_unit, s); break;
+        case 4: launch_leaf_local<4>(ws, split_unit, s); break;
+        case 5: launch_leaf_local<5>(ws, split_unit, s); break;
+        case 6: launch_leaf_local<6>(ws, split_unit, s); break;
+        default: break;
+    }
+    if (precision == NCORP_FP32_BULK) {
+        const size_t lds = (size_t)((ws.p2p_stride + 3) & ~3) * sizeof(int32_t);
+        k_sort_long_lists<<<kSortLongBlocks, kSortThreads, lds, s>>>(ws.st, ws.p2p_cnt, ws.p2p_seg,
+                                                                     ws.p2p_stride, ws.long_p2p);
+    }
+    return hipGetLastError();
+}
+
 template <typename T, int TILE>
 static void launch_p2p_t(const Workspace &ws, int64_t n, int tmax, hipStream_t s) {
-    // one item per leaf plus kLongSlots - 1 more per long leaf; the grid strides
-    int64_t g = (ws.leaf_cap + kP2PWaves - 1) / kP2PWaves + kLongGrid;
-    g = g < 1 ? 1 : (g > 16384 ? 16384 : g);
-    k_p2p<T, TILE><<<(int)g, kWave * kP2PWaves, 0, s>>>(
-        ws.st, ws.xs, ws.ys, ws.zs, ws.mus, ws.ent_cell, ws.c_first, ws.c_count, ws.gcell,
-        ws.p2p_cnt, ws.p2p_seg, ws.p2p_stride, ws.long_p2p, ws.p2p_part, ws.acc_s, n, tmax);
+    // about 1 ns a block to deal out, empty or not: no more than a small tree can use
+    const int64_t most = ws.leaf_cap + 2048;
+    const int64_t g = most < kP2PGrid ? most : kP2PGrid;
+    k_p2p<T, TILE><<<(int)g, kWave, 0, s>>>(
+        ws.st, ws.vcol, ws.ent_cell, ws.c_first, ws.c_count, ws.gcell, ws.p2p_cnt, ws.p2p_seg,
+        ws.p2p_stride, ws.split_p2p, 2 * ws.m2l_cap, ws.ent_code, ws.p2p_part, ws.acc_s, n, tmax);
 }
 
 template <typename T>
@@ -681,12 +746,7 @@ static void launch_p2p_tile(const Workspace &ws, int64_t n, int tile, int tmax, 
 hipError_t launch_p2p(const Workspace &ws, int64_t n, int precision, int tile, int tmax,
                       hipStream_t s) {
     const int tm = tmax > 0 ? tmax : 4;
-    if (precision == NCORP_FP32_BULK) {
-        const size_t lds = (size_t)((ws.p2p_stride + 3) & ~3) * sizeof(int32_t);
-        k_sort_long_lists<<<kSortLongBlocks, kSortThreads, lds, s>>>(ws.st, ws.p2p_cnt, ws.p2p_seg,
-                                                                     ws.p2p_stride, ws.long_p2p);
-        launch_p2p_tile<float>(ws, n, tile, tm, s);
-    }
+    if (precision == NCORP_FP32_BULK) launch_p2p_tile<float>(ws, n, tile, tm, s);
     else launch_p2p_tile<double>(ws, n, tile, tm, s);
     return hipGetLastError();
 }
@@ -697,7 +757,7 @@ static void launch_l2p_p(const Workspace &ws, int64_t n, double *ax, double *ay,
     int64_t g = (ws.leaf_cap + kL2PWaves - 1) / kL2PWaves;
     g = g < 1 ? 1 : (g > 16384 ? 16384 : g);
     k_l2p<P><<<(int)g, kWave * kL2PWaves, 0, s>>>(ws.st, ws.xs, ws.ys, ws.zs, ws.idx, ws.ent_cell, ws.c_first,
-                              ws.c_count, ws.gcell, ws.cleaf, ws.acc_s, ws.p2p_cnt, ws.p2p_part, n,
+                              ws.c_count, ws.gcell, ws.cleaf, ws.acc_s, ws.ent_code, ws.p2p_part, n,
                               ax, ay, az, acc4);
 }
 

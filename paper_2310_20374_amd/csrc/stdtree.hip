@@ -43,30 +43,28 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 }
 
 // direct sum of the moonlets j in [b, e) on the moonlet at (x, y, z); a source at
-// the same position (the moonlet itself) is skipped
-__device__ __forceinline__ void direct_sum(const double *__restrict__ xs,
-                                           const double *__restrict__ ys,
-                                           const double *__restrict__ zs,
-                                           const double *__restrict__ mus, int b, int e, double x,
-                                           double y, double z, double &a0, double &a1,
+// the same position (the moonlet itself) adds nothing
+__device__ __forceinline__ void direct_sum(const double4 *__restrict__ pos4, int b, int e,
+                                           double x, double y, double z, double &a0, double &a1,
                                            double &a2) {
+#pragma unroll 4
     for (int j = b; j < e; j++) {
-        const double dx = xs[j] - x, dy = ys[j] - y, dz = zs[j] - z;
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        if (r2 == 0.0) continue;
-        const double r = sqrt(r2);
-        const double f = mus[j] / (r2 * r);      // one division per pair
-        a0 += f * dx;
-        a1 += f * dy;
-        a2 += f * dz;
+        const double4 s = pos4[j];               // the same for every lane: scalar loads
+        const double dx = s.x - x, dy = s.y - y, dz = s.z - z;
+        // 1e-100 keeps a zero distance finite (its term is then exactly 0) and is far
+        // below any other; beyond 1e150 the term is 0 either way
+        const double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, 1e-100)));
+        const double f = over_r3(s.w, fmin(r2, 1e300));
+        a0 = fma(f, dx, a0);
+        a1 = fma(f, dy, a1);
+        a2 = fma(f, dz, a2);
     }
 }
 
 template <int P>
 __global__ __launch_bounds__(kStdBlock) void k_std_tree(
     DevState *st, const WCell *__restrict__ wg, const double *__restrict__ mult,
-    const double *__restrict__ xs, const double *__restrict__ ys, const double *__restrict__ zs,
-    const double *__restrict__ mus, const uint32_t *__restrict__ idx,
+    const double4 *__restrict__ pos4, const uint32_t *__restrict__ idx,
     const uint16_t *__restrict__ seg, const int32_t *__restrict__ disk_root, int64_t n,
     int ncb_pre, int ncb_post, double *__restrict__ ax, double *__restrict__ ay,
     double *__restrict__ az) {
@@ -80,7 +78,8 @@ __global__ __launch_bounds__(kStdBlock) void k_std_tree(
     double x = 0.0, y = 0.0, z = 0.0;
     int root = 0;
     if (live) {
-        x = xs[k]; y = ys[k]; z = zs[k];
+        const double4 p = pos4[k];
+        x = p.x; y = p.y; z = p.z;
         root = seg ? disk_root[seg[k]] : 0;
     }
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
@@ -131,7 +130,7 @@ __global__ __launch_bounds__(kStdBlock) void k_std_tree(
             }
             if (__ballot(action == 1)) {
                 if (action == 1)
-                    direct_sum(xs, ys, zs, mus, cw.first, cw.first + cw.count, x, y, z, a0, a1, a2);
+                    direct_sum(pos4, cw.first, cw.first + cw.count, x, y, z, a0, a1, a2);
             }
         }
     }
@@ -240,7 +239,7 @@ hipError_t launch_std_t(const Workspace &ws, int64_t n, int ncb_pre, int ncb_pos
                         double *ay, double *az, hipStream_t s) {
     const int64_t blocks = (n + kStdBlock - 1) / kStdBlock;
     k_std_tree<P><<<(unsigned)blocks, kStdBlock, 0, s>>>(
-        ws.st, ws.wg, ws.mult, ws.xs, ws.ys, ws.zs, ws.mus, ws.idx,
+        ws.st, ws.wg, ws.mult, ws.vcol, ws.idx,
         ws.ndisks > 1 ? ws.seg : nullptr, ws.disk_root, n, ncb_pre, ncb_post, ax, ay, az);
     return hipGetLastError();
 }

@@ -65,7 +65,7 @@ __global__ void k_walk_init(DevState *st, WalkQueue *wq, uint64_t *hdr, int32_t 
     if (gid != 0) return;
     wq->ncells = go ? nc : 0;
     if (mode == 0) {
-        st->nlong_p2p = 0;
+        st->nsplit = 0; st->nlong = 0;
     } else {
         st->npairs = 0; st->col_tests = 0;      // of the search on this walk's candidates
     }
@@ -121,6 +121,7 @@ struct WalkArgs {
     int m2l_stride, p2p_stride;
     const double *c_rmax;
     float *leaf_slack;
+    uint32_t *leaf_src;                  // per leaf: source moonlets of its direct sums
     int timing;                          // record the waves' busy cycles
 };
 
@@ -166,11 +167,11 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
     __shared__ WalkLds lds_all[WPB];
     __shared__ WalkPairs<MODE> pairs_all[WPB];
     __shared__ unsigned long long s_visited, s_busy, s_busymax;
-    __shared__ int s_m2l, s_p2p, s_longm, s_left;
+    __shared__ int s_m2l, s_p2p, s_longm, s_longp, s_left;
     const int lane = threadIdx.x % kWave;
     WalkLds &W = lds_all[threadIdx.x / kWave];
     int2 *const pbuf = pairs_all[threadIdx.x / kWave].p;
-    if (threadIdx.x == 0) { s_visited = s_busy = s_busymax = 0; s_m2l = s_p2p = s_longm = 0; s_left = WPB; }
+    if (threadIdx.x == 0) { s_visited = s_busy = s_busymax = 0; s_m2l = s_p2p = s_longm = s_longp = 0; s_left = WPB; }
     __syncthreads();
     const int nc = A.wq->ncells;
     const int cls = (int)blockIdx.x % kWalkClasses, xcd = cls % kXcds;
@@ -178,7 +179,7 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const long long t_start = (MODE == 0 && A.timing) ? clock64() : 0;
     unsigned long long visited = 0;
-    int nm2l = 0, np2p = 0, nlongm = 0;           // pairs of the cells taken; long M2L lists
+    int nm2l = 0, np2p = 0, nlongm = 0, nlongp = 0;           // pairs of the cells taken; long lists
     int npb = 0;                                  // candidates staged
     int nxt = 0;
     if (lane == 0) nxt = atomicAdd(ticket, 1);
@@ -228,6 +229,7 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
                 in_prev_n = __builtin_amdgcn_readfirstlane(ld_relaxed(&A.space[hl + 1]));
             }
         }
+        unsigned src = 0;                         // this lane's direct-sum sources
         int nm = 0, np = 0, nd = 0;               // own lists, staged hand-down entries
         int seg_off = -1, seg_n = 0;              // last hand-down segment written
         int32_t *const mrow = MODE == 0 ? A.m2l_seg + (int64_t)c * A.m2l_stride : nullptr;
@@ -258,10 +260,10 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
             wave_sync();
             // ---- classify up to 64 open pairs (A, B)
             int k = top < kWave ? top : kWave;
-            int kind = 0, B = 0, child = 0, npush = 0, tot = 0, off = 0;
+            int kind = 0, B = 0, child = 0, npush = 0, tot = 0, off = 0, cnt = 0;
             int32_t down = 0;
             for (;;) {
-                kind = 0; npush = 0; down = 0; B = -1; child = 0;
+                kind = 0; npush = 0; down = 0; B = -1; child = 0; cnt = 0;
                 if (lane < k) {
                     const int32_t v = W.stack[top - 1 - lane];
                     B = v & 0x7fffffff;
@@ -271,8 +273,9 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
                     } else if (v < 0) {
                         kind = 3;                         // a direct-sum pair of an ancestor
                         down = v;
+                        if (MODE == 0 && leaf) cnt = A.cell[B].count;
                     } else if (B == c) {
-                        if (wa.count <= A.ncs || leaf) { kind = 2; down = B | kDownDirect; }
+                        if (wa.count <= A.ncs || leaf) { kind = 2; down = B | kDownDirect; cnt = wa.count; }
                         else { kind = 4; down = B; }
                     } else {
                         const WCell wb = A.cell[B];
@@ -306,7 +309,7 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
                                     else { kind = 6; npush = wb.nchild; }
                                 }
                             }
-                            if (kind == 2) down = B | kDownDirect;
+                            if (kind == 2) { down = B | kDownDirect; cnt = wb.count; }
                         }
                     }
                 }
@@ -342,6 +345,7 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
                 if (MODE == 0 && leaf) {
                     const int pos = np + __popcll(m2 & lt);
                     if (direct && pos < A.p2p_stride) prow[pos] = B;
+                    if (direct) src += (unsigned)cnt;
                     np += __popcll(m2);
                 }
                 const uint64_t mo = __ballot(kind == 2 && c <= B);   // once per unordered pair
@@ -380,16 +384,20 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
                 __hip_atomic_store(&A.hdr[c], h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (MODE == 0) {
+            if (leaf)
+                for (int o = kWave / 2; o > 0; o >>= 1) src += __shfl_xor(src, o);
             if (lane == 0) {
                 A.m2l_cnt[c] = nm;
                 if (leaf) {
                     A.p2p_cnt[wa.entry] = np;
+                    A.leaf_src[wa.entry] = src;
                     A.leaf_slack[wa.entry] = __int_as_float((int)(slack << 16));
                 }
                 if (nm > A.m2l_stride) latch_cap(A.st, ST_CAP_LISTS, nm);
                 if (np > A.p2p_stride) latch_cap(A.st, ST_CAP_LISTS, np);
             }
             if (nm > kM2LListLDS) nlongm++;
+            if (leaf && np > kP2PListLDS) nlongp++;
         }
         wave_sync();
     }
@@ -400,6 +408,7 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
         atomicAdd(&s_m2l, nm2l);
         atomicAdd(&s_p2p, np2p);
         atomicAdd(&s_longm, nlongm);
+        atomicAdd(&s_longp, nlongp);
         if (MODE == 0 && A.timing) {
             const unsigned long long busy = (unsigned long long)(clock64() - t_start);
             atomicAdd(&s_busy, busy);
@@ -408,11 +417,12 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
         if (atomicSub(&s_left, 1) == 1) {
             const unsigned long long v = atomicAdd(&s_visited, 0ull);
             const int m = atomicAdd(&s_m2l, 0), p = atomicAdd(&s_p2p, 0);
-            const int lm = atomicAdd(&s_longm, 0);
+            const int lm = atomicAdd(&s_longm, 0), lp = atomicAdd(&s_longp, 0);
             if (v) atomicAdd((unsigned long long *)walk_ctr(A.ctr, cls, kCtrVisited), v);
             if (m) atomicAdd(walk_ctr(A.ctr, cls, kCtrM2L), m);
             if (p) atomicAdd(walk_ctr(A.ctr, cls, kCtrP2P), p);
             if (lm) atomicAdd(walk_ctr(A.ctr, cls, kCtrLongM2L), lm);
+            if (lp) atomicAdd(walk_ctr(A.ctr, cls, kCtrLongP2P), lp);
             if (MODE == 0 && A.timing) {
                 atomicAdd((unsigned long long *)walk_ctr(A.ctr, cls, kCtrBusy), atomicAdd(&s_busy, 0ull));
                 atomicMax((unsigned long long *)walk_ctr(A.ctr, cls, kCtrBusyMax),
@@ -491,6 +501,7 @@ hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_po
         A.p2p_cnt = ws.p2p_cnt; A.p2p_seg = ws.p2p_seg; A.p2p_stride = ws.p2p_stride;
         A.c_rmax = ws.c_rmax;
         A.leaf_slack = ws.leaf_slack;
+        A.leaf_src = ws.ent_code;
         A.timing = ws.timing ? 1 : 0;
         k_walk<0><<<walk_grid<0>(ws.cell_cap, most), kWalkBlock, 0, s>>>(A);
     } else {
