@@ -514,13 +514,15 @@ static bool mesh_collisions(const ncorp_params &p) {
     return p.collision_method == NCORP_COLLISIONS_MESH;
 }
 
-// fresh: also reset the device state (no tree build precedes this one)
+// fresh: also reset the device state (no tree build precedes this one); m: the masses,
+// for a gravity evaluation on this mesh that is told they are there
 static int build_mesh_impl(ncorp_ctx *c, const double *x, const double *y, const double *z,
-                           const double *R, int64_t n, hipStream_t s, bool fresh) {
+                           const double *R, int64_t n, hipStream_t s, bool fresh,
+                           const double *m = nullptr) {
     Workspace &ws = c->ws;
     PhaseTimer t(c, NCORP_PHASE_TREE, s);
     if (fresh) HIPCHK(c, launch_reset_state(ws, s));
-    HIPCHK(c, launch_mesh_build(ws, x, y, z, R, n, c->prm, !c->mesh_init, s));
+    HIPCHK(c, launch_mesh_build(ws, x, y, z, R, m, n, c->prm, !c->mesh_init, s));
     ws.clear_mesh = false;
     c->mesh_init = true;
     c->have_mesh = true;
@@ -579,16 +581,16 @@ extern "C" int ncorp_build_tree_batched(ncorp_ctx *c, const int64_t *disk_offset
 }
 
 // mus_packed: the build of the current tree already packed G m (the step)
-// Does a gravity evaluation end in the falcON L2P pass (which can write packed records)?
-static bool gravity_by_l2p(const ncorp_params &p) {
-    return p.p > 0 && p.gravity_method == NCORP_GRAVITY_FALCON;
+// Does a gravity evaluation end in a pass that can write packed records?
+static bool gravity_in_records(const ncorp_params &p) {
+    return p.p > 0 && (p.gravity_method == NCORP_GRAVITY_FALCON || mesh_gravity(p));
 }
 
-// acc4 (falcON evaluations, gravity_by_l2p): the accelerations as (ax, ay, az, 0)
+// acc4 (falcON and mesh evaluations, gravity_in_records): the accelerations as (ax, ay, az, 0)
 // records in input order instead of the three arrays
 static int gravity_impl(ncorp_ctx *c, const double *m, double *ax, double *ay, double *az,
                         hipStream_t s, bool mus_packed = false, double4 *acc4 = nullptr) {
-    if (!gravity_by_l2p(c->prm)) acc4 = nullptr;
+    if (!gravity_in_records(c->prm)) acc4 = nullptr;
     Workspace &ws = c->ws;
     const int64_t n = c->n;
     if (c->prm.p == 0) {
@@ -609,7 +611,8 @@ static int gravity_impl(ncorp_ctx *c, const double *m, double *ax, double *ay, d
     }
     if (mesh_gravity(c->prm)) {
         PhaseTimer t(c, NCORP_PHASE_GWALK, s);
-        HIPCHK(c, launch_mesh_gravity(ws, m, c->prm.G, n, !c->mesh_counted, ax, ay, az, s));
+        HIPCHK(c, launch_mesh_gravity(ws, m, c->prm.G, n, !c->mesh_counted, mus_packed, ax, ay,
+                                      az, acc4, s));
         c->mesh_counted = true;
         c->last = s;
         return NCORP_OK;
@@ -686,7 +689,7 @@ static int collide_impl(ncorp_ctx *c, const double *vx, const double *vy, const 
     PhaseTimer t(c, NCORP_PHASE_COLLIDE, s);
     bool tree_tests = false;    // the tree's pair tests left per-block counts to add
     if (mesh_collisions(c->prm)) {
-        HIPCHK(c, launch_mesh_collide(ws, vx, vy, vz, R, n, dt, !c->mesh_counted, s));
+        HIPCHK(c, launch_mesh_collide(ws, vx, vy, vz, R, n, dt, !c->mesh_counted, packed, s));
         c->mesh_counted = true;
     } else if (c->prm.collision_method == NCORP_COLLISIONS_BRUTE_FORCE) {
         if (ws.ndisks > 1)
@@ -812,15 +815,16 @@ static int step_impl(ncorp_ctx *c, const int64_t *disk_off, int n_disks, double 
                                               mutual ? m : nullptr,
                                               !fresh && drift_max)) != NCORP_OK)
             return q;
-        if (need_mesh) q = build_mesh_impl(c, x, y, z, R, n, s, fresh && !need_tree);
+        if (need_mesh) q = build_mesh_impl(c, x, y, z, R, n, s, fresh && !need_tree,
+                                           mutual && mesh_gravity(c->prm) ? m : nullptr);
         return q;
     };
     if ((r = rebuild(true)) != NCORP_OK) return r;
     k_zero_cursor<<<1, 64, 0, s>>>(ws.st);
-    // falcON evaluations hand the kick one (ax, ay, az, 0) record per moonlet: the
+    // falcON and mesh evaluations hand the kick one (ax, ay, az, 0) record per moonlet: the
     // collision records' buffer is free from the evaluation to the kick after it (the
     // next search rewrites it)
-    double4 *const acc4 = mutual && gravity_by_l2p(c->prm) ? ws.pcol : nullptr;
+    double4 *const acc4 = mutual && gravity_in_records(c->prm) ? ws.pcol : nullptr;
     // each evaluation follows a rebuild that brought G m into tree order
     if (mutual && (r = gravity_impl(c, m, ax, ay, az, s, true, acc4)) != NCORP_OK) return r;
     {

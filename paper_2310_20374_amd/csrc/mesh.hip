@@ -20,6 +20,7 @@
 #include <climits>
 
 #include "contact.h"
+#include "expansion.h"
 
 namespace ncorp {
 namespace {
@@ -96,8 +97,13 @@ __device__ __forceinline__ void add_pull(double4 src, double x, double y, double
     const double dx = src.x - x, dy = src.y - y, dz = src.z - z;
     const double r2 = dx * dx + dy * dy + dz * dz;
     if (r2 == 0.0) return;
-    const double r = sqrt(r2);
-    const double f = src.w / (r2 * r);          // one division per pair
+    double f;
+    if (r2 > 1e-200 && r2 < 1e200) {
+        f = over_r3(src.w, r2);
+    } else {                                    // beyond the hardware root's good range
+        const double r = sqrt(r2);
+        f = src.w / (r2 * r);
+    }
     a0 += f * dx;
     a1 += f * dy;
     a2 += f * dz;
@@ -135,6 +141,49 @@ __device__ __forceinline__ int2 cell_range(const CellIndex &ci, int x, int y, in
         return ci.grid[ix + (int64_t)ci.dx * (iy + (int64_t)ci.dy * iz)];
     }
     return lookup(ci.tab, ci.mask, cell_key(x, y, z));
+}
+
+// Dense grid: the moonlets of cells x - 1 .. x + 1 of row (y, z) of the box.  The grid
+// index grows along x, so they are one run of the sorted array.  (0, 0): none.
+__device__ __forceinline__ int2 row_range(const CellIndex &ci, int ix, int iy, int iz) {
+    const bool in = (unsigned)iy < (unsigned)ci.dy && (unsigned)iz < (unsigned)ci.dz;
+    const int64_t row = in ? ci.dx * (iy + (int64_t)ci.dy * iz) : 0;
+    int s = INT_MAX, e = 0;
+#pragma unroll
+    for (int k = -1; k <= 1; k++) {
+        const bool ok = in && (unsigned)(ix + k) < (unsigned)ci.dx;
+        const int2 v = ci.grid[row + (ok ? ix + k : 0)];
+        if (ok && v.y > 0) {
+            s = v.x < s ? v.x : s;
+            e = v.y;
+        }
+    }
+    return e > 0 ? make_int2(s, e) : make_int2(0, 0);
+}
+
+// The rows of a moonlet's neighbourhood that hold moonlets, in row order, as runs of the
+// sorted array in rows[0..], one column per thread; returns the moonlets in them.  The
+// lookups of a plane go out together, and what follows walks one flat list: the wave then
+// takes as many rounds as its fullest neighbourhood has moonlets, not the sum over the
+// cells of its fullest cells.
+constexpr int kMeshRows = 9;
+typedef int2 MeshRows[kMeshRows][kMeshBlock];
+__device__ __forceinline__ int mesh_rows(const CellIndex &ci, const int4 c, MeshRows &rows) {
+    const int ix = c.x - ci.x0, iy = c.y - ci.y0, iz = c.z - ci.z0;
+    int nr = 0, total = 0;
+#pragma unroll
+    for (int dz = -1; dz <= 1; dz++) {
+        int2 e[3];
+#pragma unroll
+        for (int dy = -1; dy <= 1; dy++) e[dy + 1] = row_range(ci, ix, iy + dy, iz + dz);
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+            if (e[k].y > 0) {
+                rows[nr++][threadIdx.x] = e[k];
+                total += e[k].y - e[k].x;
+            }
+    }
+    return total;
 }
 
 // sum of v over the block, valid in thread 0 (every thread calls it)
@@ -288,16 +337,16 @@ __device__ __forceinline__ int block_min_i(int v, int *red) {
 __global__ void __launch_bounds__(256)
 k_mesh_keys(DevState *st, const MeshState *__restrict__ ms, const double *__restrict__ x,
             const double *__restrict__ y, const double *__restrict__ z,
-            const double *__restrict__ R, int64_t n, uint64_t *keys, uint32_t *vals,
-            int32_t *box_part, double4 *__restrict__ pack4) {
-    __shared__ int red[256 / kWave];
+            const double *__restrict__ R, const double *__restrict__ m, int64_t n, uint64_t *keys,
+            uint32_t *vals, int32_t *box_part, double4 *__restrict__ pack4) {
+    __shared__ int red[6][256 / kWave];
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const double g = ms->gamma;
     int4 c = make_int4(INT_MAX, INT_MAX, INT_MAX, 0);
     bool in = false;
     if (i < n) {
         const double px = x[i], py = y[i], pz = z[i];
-        pack4[i] = make_double4(px, py, pz, 0.0);   // one record per moonlet for the gather
+        pack4[i] = make_double4(px, py, pz, m ? m[i] : 0.0);   // one record for the gather
         uint64_t key = kMeshEmpty;                 // out of the mesh: sorted last
         if (!(2.0 * R[i] > g)) {
             if (cell_of(px, py, pz, g, c)) {
@@ -312,15 +361,18 @@ k_mesh_keys(DevState *st, const MeshState *__restrict__ ms, const double *__rest
         keys[i] = key;
         vals[i] = (uint32_t)i;
     }
-    const int mnx = block_min_i(in ? c.x : INT_MAX, red);
-    const int mny = block_min_i(in ? c.y : INT_MAX, red);
-    const int mnz = block_min_i(in ? c.z : INT_MAX, red);
-    const int mxx = block_min_i(in ? -c.x : INT_MAX, red);
-    const int mxy = block_min_i(in ? -c.y : INT_MAX, red);
-    const int mxz = block_min_i(in ? -c.z : INT_MAX, red);
-    if (threadIdx.x == 0) {
-        int32_t *b = box_part + 6 * (int64_t)blockIdx.x;
-        b[0] = mnx; b[1] = mny; b[2] = mnz; b[3] = mxx; b[4] = mxy; b[5] = mxz;
+    const int v[6] = {in ? c.x : INT_MAX, in ? c.y : INT_MAX, in ? c.z : INT_MAX,
+                      in ? -c.x : INT_MAX, in ? -c.y : INT_MAX, in ? -c.z : INT_MAX};
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        const int t = wave_min_i(v[k]);
+        if ((threadIdx.x & (kWave - 1)) == 0) red[k][threadIdx.x / kWave] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        int t = INT_MAX;
+        for (int w = 0; w < 256 / kWave; w++) t = min(t, red[threadIdx.x][w]);
+        box_part[6 * (int64_t)blockIdx.x + threadIdx.x] = t;
     }
 }
 
@@ -352,13 +404,14 @@ k_mesh_box(const int32_t *__restrict__ box_part, int nblk, MeshState *ms, int64_
     }
 }
 
-// sorted positions and cells; the first out-of-mesh position is n_in; the first
-// moonlet of every cell claims the cell's slot.  Keys are grid indices (empty:
+// sorted positions and cells, with the masses (m and G m) when the key pass had them; the
+// first out-of-mesh position is n_in; the first moonlet of every cell claims the cell's
+// slot and, in the dense grid, closes the cell before.  Keys are grid indices (empty:
 // dense_empty) with the dense grid, Morton keys (empty: kMeshEmpty) otherwise.
 __global__ void k_mesh_runs(DevState *st, MeshState *ms, const uint64_t *__restrict__ keys,
                             const uint32_t *__restrict__ idx, const double4 *__restrict__ pack4,
                             int64_t n, MeshSlot *tab, int64_t mask, int2 *grid, double4 *mpos,
-                            int4 *mcell, uint64_t dense_empty) {
+                            int4 *mcell, double *mmass, double G, uint64_t dense_empty) {
     const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (q >= n || (st->status & kSkipMask)) return;
     const uint32_t i = idx[q];
@@ -366,17 +419,26 @@ __global__ void k_mesh_runs(DevState *st, MeshState *ms, const uint64_t *__restr
     const bool dense = ms->dense != 0;
     const uint64_t empty = dense ? dense_empty : kMeshEmpty;
     const double4 p = pack4[i];
-    mpos[q] = p;
-    const uint64_t k = keys[q];
+    if (mmass) mmass[q] = p.w;
+    mpos[q] = make_double4(p.x, p.y, p.z, G * p.w);
+    const uint64_t k = keys[q], before = q > 0 ? keys[q - 1] : empty;
+    if (dense) {
+        if (q > 0 && before != k && before != empty) grid[before].y = (int32_t)q;
+        if (q == n - 1 && k != empty) grid[k].y = (int32_t)n;
+        if (q == 0) {                              // the grid now holds this build's cells
+            ms->grid_sparse = 1;
+            ms->prev_n = (int32_t)n;
+        }
+    }
     if (k == empty) {
-        if (q == 0 || keys[q - 1] != empty) ms->n_in = (int32_t)q;
+        if (q == 0 || before != empty) ms->n_in = (int32_t)q;
         mcell[q] = make_int4(0, 0, 0, 0);
         return;
     }
     int4 c;
     cell_of(p.x, p.y, p.z, g, c);                  // in range: checked by k_mesh_keys
     mcell[q] = c;
-    if (q > 0 && keys[q - 1] == k) return;
+    if (q > 0 && before == k) return;
     if (dense) {
         grid[k].x = (int32_t)q;
         return;
@@ -394,35 +456,28 @@ __global__ void k_mesh_runs(DevState *st, MeshState *ms, const uint64_t *__restr
     atomicOr(&st->status, (int32_t)ST_CAP_MESH);   // unreachable at half load
 }
 
-// the last moonlet of every cell closes its range
-__global__ void k_mesh_run_ends(const DevState *__restrict__ st, MeshState *ms,
+// hash table: the last moonlet of every cell closes its range
+__global__ void k_mesh_run_ends(const DevState *__restrict__ st, const MeshState *__restrict__ ms,
                                 const uint64_t *__restrict__ keys, int64_t n, MeshSlot *tab,
-                                int64_t mask, int2 *grid, uint64_t dense_empty) {
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q >= n || (st->status & kSkipMask)) return;
-    const bool dense = ms->dense != 0;
-    if (q == 0 && dense) {                         // the grid now holds this build's cells
-        ms->grid_sparse = 1;
-        ms->prev_n = (int32_t)n;
-    }
-    const uint64_t k = keys[q];
-    if (k == (dense ? dense_empty : kMeshEmpty) || (q + 1 < n && keys[q + 1] == k)) return;
-    if (dense) {
-        grid[k].y = (int32_t)(q + 1);
-        return;
-    }
-    int64_t h = slot_of(k, mask);
-    for (int64_t probes = 0; probes <= mask; probes++) {
-        if (tab[h].key == k) {
-            tab[h].end = (int32_t)(q + 1);
-            return;
+                                int64_t mask) {
+    if (ms->dense != 0 || (st->status & kSkipMask)) return;
+    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n;
+         q += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t k = keys[q];
+        if (k == kMeshEmpty || (q + 1 < n && keys[q + 1] == k)) continue;
+        int64_t h = slot_of(k, mask);
+        for (int64_t probes = 0; probes <= mask; probes++) {
+            if (tab[h].key == k) {
+                tab[h].end = (int32_t)(q + 1);
+                break;
+            }
+            h = (h + 1) & mask;
         }
-        h = (h + 1) & mask;
     }
 }
 
 // ------------------------------------------------------------------ gravity
-// mu = G m and m in sorted order
+// mu = G m and m in sorted order, when the build had no masses
 __global__ void k_mesh_mu(const uint32_t *__restrict__ idx, const double *__restrict__ m,
                           double G, int64_t n, double4 *mpos, double *mmass) {
     const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -575,17 +630,34 @@ k_mesh_top_final(DevState *st, MeshState *ms, int64_t n, const Cand *__restrict_
         for (int k = threadIdx.x; k < nover; k += blockDim.x) big[k] = n_in + k;
 }
 
+__device__ __forceinline__ void put_acc(uint32_t i, double a0, double a1, double a2, double *ax,
+                                        double *ay, double *az, double4 *acc4) {
+    if (acc4) {
+        acc4[i] = make_double4(a0, a1, a2, 0.0);
+    } else {
+        ax[i] = a0; ay[i] = a1; az[i] = a2;
+    }
+}
+
 // One thread per moonlet of the mesh (sorted order): its neighbours (not among the
 // all-pairs moonlets) cell by cell, then the all-pairs moonlets.  The three most
-// massive only count their neighbours here; their sums come from k_mesh_big_sum.
+// massive only count their neighbours here; their sums come from k_mesh_big_sum.  The
+// result goes to the three arrays, or to (ax, ay, az, 0) records where the kick reads
+// those (one scattered line a moonlet instead of three).
+// Bound by the latency of its lookups and loads, not by their 60 MB or the pairs' some
+// 20 FP64 operations: with the dense grid nine runs are looked up at once, and the next
+// moonlet is loaded while the last is summed.  1e6 moonlets of 8 neighbours: 27 cells one
+// after the other 206 us, now 130.
 __global__ void __launch_bounds__(kMeshBlock)
 k_mesh_gravity(DevState *st, MeshState *ms, const MeshSlot *__restrict__ tab, int64_t mask,
                const int2 *__restrict__ grid,
                const double4 *__restrict__ mpos, const int4 *__restrict__ mcell,
                const uint32_t *__restrict__ idx, const int32_t *__restrict__ big,
                int count, double *__restrict__ ax, double *__restrict__ ay,
-               double *__restrict__ az, unsigned long long *cnt_part) {
+               double *__restrict__ az, double4 *__restrict__ acc4,
+               unsigned long long *cnt_part) {
     __shared__ unsigned long long s_red[kMeshBlock / kWave];
+    __shared__ MeshRows rows;
     if (st->status & kSkipMask) {
         if (threadIdx.x == 0) cnt_part[blockIdx.x] = 0;
         return;
@@ -601,24 +673,47 @@ k_mesh_gravity(DevState *st, MeshState *ms, const MeshSlot *__restrict__ tab, in
         const double4 p = mpos[q];
         const bool top = q == t0 || q == t1 || q == t2;
         double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-        for (int dz = -1; dz <= 1; dz++)
-            for (int dy = -1; dy <= 1; dy++)
-                for (int dx = -1; dx <= 1; dx++) {
-                    const int2 e = cell_range(ci, c.x + dx, c.y + dy, c.z + dz);
-                    for (int r = e.x; r < e.y; r++) {
-                        if (r == q) continue;
-                        cnt++;
-                        if (top || r == t0 || r == t1 || r == t2) continue;
-                        add_pull(mpos[r], p.x, p.y, p.z, a0, a1, a2);
+        if (ci.dense) {
+            int left = mesh_rows(ci, c, rows);     // q itself is in one of them
+            cnt = (unsigned long long)(left - 1);
+            if (top) left = 0;
+            int row = 0;
+            int2 e = rows[0][threadIdx.x];
+            int r = e.x;
+            double4 next = left > 0 ? mpos[r] : p;
+            while (left-- > 0) {
+                const int at = r;
+                const double4 src = next;
+                if (left > 0) {
+                    if (++r == e.y) {
+                        e = rows[++row][threadIdx.x];
+                        r = e.x;
                     }
+                    next = mpos[r];
                 }
+                if (at == q || at == t0 || at == t1 || at == t2) continue;
+                add_pull(src, p.x, p.y, p.z, a0, a1, a2);
+            }
+        } else {
+            for (int dz = -1; dz <= 1; dz++)
+                for (int dy = -1; dy <= 1; dy++)
+                    for (int dx = -1; dx <= 1; dx++) {
+                        const int2 e = cell_range(ci, c.x + dx, c.y + dy, c.z + dz);
+                        for (int r = e.x; r < e.y; r++) {
+                            if (r == q) continue;
+                            cnt++;
+                            if (top || r == t0 || r == t1 || r == t2) continue;
+                            add_pull(mpos[r], p.x, p.y, p.z, a0, a1, a2);
+                        }
+                    }
+        }
         if (!top) {
             for (int k = 0; k < nbig; k++) {
                 const int r = big[k];
                 if (r != q) add_pull(mpos[r], p.x, p.y, p.z, a0, a1, a2);
             }
             const uint32_t i = idx[q];
-            ax[i] = a0; ay[i] = a1; az[i] = a2;
+            put_acc(i, a0, a1, a2, ax, ay, az, acc4);
         }
     }
     if (count) {
@@ -644,8 +739,22 @@ k_mesh_big_sum(const DevState *__restrict__ st, const MeshState *__restrict__ ms
         const int b = big[k];
         const double4 p = mpos[b];
         double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-        for (int64_t j = j0 + threadIdx.x; j < j1; j += kMeshBlock)
-            if (j != b) add_pull(mpos[j], p.x, p.y, p.z, a0, a1, a2);
+        // eight sources per round, their loads issued together: with the usual three big
+        // moonlets a thread has some 60 one after the other (1e6 moonlets: 31 -> 17 us)
+        constexpr int kBatch = 8;
+        for (int64_t j = j0 + threadIdx.x; j < j1; j += kBatch * kMeshBlock) {
+            double4 src[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; u++) {
+                const int64_t ju = j + u * kMeshBlock;
+                src[u] = mpos[ju < j1 ? ju : j];
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; u++) {
+                const int64_t ju = j + u * kMeshBlock;
+                if (ju < j1 && ju != b) add_pull(src[u], p.x, p.y, p.z, a0, a1, a2);
+            }
+        }
         for (int o = 32; o > 0; o >>= 1) {
             a0 += __shfl_xor(a0, o);
             a1 += __shfl_xor(a1, o);
@@ -665,15 +774,16 @@ k_mesh_big_sum(const DevState *__restrict__ st, const MeshState *__restrict__ ms
 __global__ void k_mesh_big_final(const DevState *__restrict__ st,
                                  const MeshState *__restrict__ ms, const int32_t *__restrict__ big,
                                  const uint32_t *__restrict__ idx, const double *__restrict__ part,
-                                 double *ax, double *ay, double *az) {
+                                 double *ax, double *ay, double *az, double4 *acc4) {
     if (st->status & kSkipMask) return;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= ms->nbig) return;
     double a[3] = {0.0, 0.0, 0.0};
+#pragma unroll 16
     for (int c = 0; c < kMeshChunks; c++)
         for (int d = 0; d < 3; d++) a[d] += part[((int64_t)k * kMeshChunks + c) * 3 + d];
     const uint32_t i = idx[big[k]];
-    ax[i] = a[0]; ay[i] = a[1]; az[i] = a[2];
+    put_acc(i, a[0], a[1], a[2], ax, ay, az, acc4);
 }
 
 // ------------------------------------------------------------------ collisions
@@ -689,7 +799,9 @@ __global__ void k_mesh_col_init(DevState *st) {
     if (threadIdx.x == 0 && blockIdx.x == 0) { st->npairs = 0; st->col_tests = 0; }
 }
 
-// one thread per moonlet of the mesh: its neighbours later in sorted order
+// one thread per moonlet of the mesh: its neighbours later in sorted order (with the
+// dense grid the runs' ends after q; the rows before q's own hold none and are looked up
+// only for the count).  1e6 moonlets of 8 neighbours: 126 -> 82 us.
 __global__ void __launch_bounds__(kMeshBlock)
 k_mesh_collide(DevState *st, MeshState *ms, const MeshSlot *__restrict__ tab, int64_t mask,
                const int2 *__restrict__ grid,
@@ -698,6 +810,7 @@ k_mesh_collide(DevState *st, MeshState *ms, const MeshSlot *__restrict__ tab, in
                int count, int64_t *out, int64_t cap, unsigned long long *cnt_part,
                unsigned long long *tests_part) {
     __shared__ unsigned long long s_red[kMeshBlock / kWave];
+    __shared__ MeshRows rows;
     if (st->status & kSkipMask) {
         if (threadIdx.x == 0) { cnt_part[blockIdx.x] = 0; tests_part[blockIdx.x] = 0; }
         return;
@@ -710,21 +823,60 @@ k_mesh_collide(DevState *st, MeshState *ms, const MeshSlot *__restrict__ tab, in
     if (live) {
         const int4 c = mcell[q];
         const double4 p = mpos[q], v = mvel[q];
-        for (int dz = -1; dz <= 1; dz++)
-            for (int dy = -1; dy <= 1; dy++)
-                for (int dx = -1; dx <= 1; dx++) {
-                    const int2 e = cell_range(ci, c.x + dx, c.y + dy, c.z + dz);
-                    for (int r = e.x; r < e.y; r++) {
-                        if (r == q) continue;
-                        cnt++;
-                        if (r < q) continue;
-                        const double4 pr = mpos[r], vr = mvel[r];
-                        tests++;
-                        if (pair_test(p.x, p.y, p.z, v.x, v.y, v.z, v.w, pr.x, pr.y, pr.z, vr.x,
-                                      vr.y, vr.z, vr.w, dt))
-                            record(out, cap, (unsigned long long *)&st->npairs, idx[q], idx[r]);
-                    }
+        if (ci.dense) {
+            const int ix = c.x - ci.x0, iy = c.y - ci.y0, iz = c.z - ci.z0;
+            if (count) cnt = (unsigned long long)(mesh_rows(ci, c, rows) - 1);
+            int2 e[5];
+            e[0] = row_range(ci, ix, iy, iz);
+            e[1] = row_range(ci, ix, iy + 1, iz);
+#pragma unroll
+            for (int dy = -1; dy <= 1; dy++) e[3 + dy] = row_range(ci, ix, iy + dy, iz + 1);
+            e[0].x = (int)q + 1;
+            int nr = 0, left = 0;
+#pragma unroll
+            for (int k = 0; k < 5; k++)
+                if (e[k].y > e[k].x) {
+                    rows[nr++][threadIdx.x] = e[k];
+                    left += e[k].y - e[k].x;
                 }
+            tests = (unsigned long long)left;
+            int row = 0;
+            int2 run = left > 0 ? rows[0][threadIdx.x] : make_int2(0, 0);
+            int r = run.x;
+            double4 pn = p, vn = v;
+            if (left > 0) { pn = mpos[r]; vn = mvel[r]; }
+            while (left-- > 0) {
+                const int at = r;
+                const double4 pr = pn, vr = vn;
+                if (left > 0) {
+                    if (++r == run.y) {
+                        run = rows[++row][threadIdx.x];
+                        r = run.x;
+                    }
+                    pn = mpos[r];
+                    vn = mvel[r];
+                }
+                if (pair_test(p.x, p.y, p.z, v.x, v.y, v.z, v.w, pr.x, pr.y, pr.z, vr.x, vr.y,
+                              vr.z, vr.w, dt))
+                    record(out, cap, (unsigned long long *)&st->npairs, idx[q], idx[at]);
+            }
+        } else {
+            for (int dz = -1; dz <= 1; dz++)
+                for (int dy = -1; dy <= 1; dy++)
+                    for (int dx = -1; dx <= 1; dx++) {
+                        const int2 e = cell_range(ci, c.x + dx, c.y + dy, c.z + dz);
+                        for (int r = e.x; r < e.y; r++) {
+                            if (r == q) continue;
+                            cnt++;
+                            if (r < q) continue;
+                            const double4 pr = mpos[r], vr = mvel[r];
+                            tests++;
+                            if (pair_test(p.x, p.y, p.z, v.x, v.y, v.z, v.w, pr.x, pr.y, pr.z, vr.x,
+                                          vr.y, vr.z, vr.w, dt))
+                                record(out, cap, (unsigned long long *)&st->npairs, idx[q], idx[r]);
+                        }
+                    }
+        }
     }
     const unsigned long long tt = block_sum_u64(tests, s_red);
     const unsigned long long tc = block_sum_u64(cnt, s_red);
@@ -760,13 +912,25 @@ k_mesh_collide_out(DevState *st, const MeshState *__restrict__ ms,
     for (int k = blockIdx.y; k < nover; k += gridDim.y) {
         const int b = n_in + k;
         const double4 p = mpos[b], v = mvel[b];
-        for (int64_t j = j0 + threadIdx.x; j < j1; j += kMeshBlock) {
-            if (j == b || (j >= n_in && j < b)) continue;
-            const double4 pr = mpos[j], vr = mvel[j];
-            tests++;
-            if (pair_test(p.x, p.y, p.z, v.x, v.y, v.z, v.w, pr.x, pr.y, pr.z, vr.x, vr.y, vr.z,
-                          vr.w, dt))
-                record(out, cap, (unsigned long long *)&st->npairs, idx[b], idx[j]);
+        // four per round, their loads issued together (1e6 moonlets: 32 -> 21 us)
+        constexpr int kBatch = 4;
+        for (int64_t jb = j0 + threadIdx.x; jb < j1; jb += kBatch * kMeshBlock) {
+            double4 pr[kBatch], vr[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; u++) {
+                const int64_t j = jb + u * kMeshBlock < j1 ? jb + u * kMeshBlock : jb;
+                pr[u] = mpos[j];
+                vr[u] = mvel[j];
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; u++) {
+                const int64_t j = jb + u * kMeshBlock;
+                if (j >= j1 || j == b || (j >= n_in && j < b)) continue;
+                tests++;
+                if (pair_test(p.x, p.y, p.z, v.x, v.y, v.z, v.w, pr[u].x, pr[u].y, pr[u].z,
+                              vr[u].x, vr[u].y, vr[u].z, vr[u].w, dt))
+                    record(out, cap, (unsigned long long *)&st->npairs, idx[b], idx[j]);
+            }
         }
     }
     const unsigned long long t = block_sum_u64(tests, s_red);
@@ -778,8 +942,8 @@ int grid_of(int64_t n, int block) { return (int)((n + block - 1) / block); }
 }  // namespace
 
 hipError_t launch_mesh_build(const Workspace &ws, const double *x, const double *y,
-                             const double *z, const double *R, int64_t n, const ncorp_params &prm,
-                             bool first, hipStream_t s) {
+                             const double *z, const double *R, const double *m, int64_t n,
+                             const ncorp_params &prm, bool first, hipStream_t s) {
     const int64_t mask = ws.mtab_n - 1;
     if (ws.clear_mesh) k_mesh_clear_state<<<1, 64, 0, s>>>(ws.mesh);
     if (first && prm.mesh_gamma <= 0.0 && prm.mesh_rmax <= 0.0)
@@ -791,7 +955,7 @@ hipError_t launch_mesh_build(const Workspace &ws, const double *x, const double 
     // the box partials use the counter partials' buffer (free during a build)
     int32_t *box_part = reinterpret_cast<int32_t *>(ws.count_part);
     const int kblk = grid_of(n, 256);
-    k_mesh_keys<<<kblk, 256, 0, s>>>(ws.st, ws.mesh, x, y, z, R, n, ws.mkeys, ws.midx,
+    k_mesh_keys<<<kblk, 256, 0, s>>>(ws.st, ws.mesh, x, y, z, R, m, n, ws.mkeys, ws.midx,
                                      box_part, ws.pack4);
     k_mesh_box<<<1, 1024, 0, s>>>(box_part, kblk, ws.mesh, ws.mgrid_n);
     // dense grid: keys become grid indices below 2^gbits, all-ones in those bits when
@@ -812,15 +976,18 @@ hipError_t launch_mesh_build(const Workspace &ws, const double *x, const double 
     if (in_b) return hipErrorInvalidValue;
     k_mesh_runs<<<grid_of(n, 256), 256, 0, s>>>(ws.st, ws.mesh, ws.mkeys, ws.midx, ws.pack4, n,
                                                 ws.mtab, mask, ws.mgrid, ws.mpos, ws.mcell,
-                                                dense_empty);
-    k_mesh_run_ends<<<grid_of(n, 256), 256, 0, s>>>(ws.st, ws.mesh, ws.mkeys, n, ws.mtab, mask,
-                                                    ws.mgrid, dense_empty);
+                                                m ? ws.mmass : nullptr, prm.G, dense_empty);
+    const int64_t eg = grid_of(n, 256);
+    k_mesh_run_ends<<<(int)(eg < 2048 ? eg : 2048), 256, 0, s>>>(ws.st, ws.mesh, ws.mkeys, n,
+                                                                ws.mtab, mask);
     return hipGetLastError();
 }
 
 hipError_t launch_mesh_gravity(const Workspace &ws, const double *m, double G, int64_t n,
-                               bool count, double *ax, double *ay, double *az, hipStream_t s) {
-    k_mesh_mu<<<grid_of(n, 256), 256, 0, s>>>(ws.midx, m, G, n, ws.mpos, ws.mmass);
+                               bool count, bool mus_packed, double *ax, double *ay, double *az,
+                               double4 *acc4, hipStream_t s) {
+    if (!mus_packed)
+        k_mesh_mu<<<grid_of(n, 256), 256, 0, s>>>(ws.midx, m, G, n, ws.mpos, ws.mmass);
     Cand *part = reinterpret_cast<Cand *>(ws.mtop_part);
     k_mesh_top_part<<<kMeshTopBlocks, kMeshBlock, 0, s>>>(ws.st, ws.mmass, ws.midx, n, part);
     k_mesh_top_final<<<1, kMeshTopBlocks, 0, s>>>(ws.st, ws.mesh, n, part, ws.mbig);
@@ -828,21 +995,23 @@ hipError_t launch_mesh_gravity(const Workspace &ws, const double *m, double G, i
     k_mesh_gravity<<<nblk, kMeshBlock, 0, s>>>(ws.st, ws.mesh, ws.mtab, ws.mtab_n - 1, ws.mgrid,
                                                ws.mpos,
                                                ws.mcell, ws.midx, ws.mbig, count ? 1 : 0, ax, ay,
-                                               az, ws.count_part);
+                                               az, acc4, ws.count_part);
     if (count) k_mesh_count_done<<<1, 1024, 0, s>>>(ws.count_part, nblk, ws.mesh);
     k_mesh_big_sum<<<dim3(kMeshChunks, kMeshBigRows), kMeshBlock, 0, s>>>(ws.st, ws.mesh,
                                                                          ws.mpos, ws.mbig, n,
                                                                          ws.mbig_part);
     k_mesh_big_final<<<kMaxMeshBig / 256, 256, 0, s>>>(ws.st, ws.mesh, ws.mbig, ws.midx,
-                                                      ws.mbig_part, ax, ay, az);
+                                                      ws.mbig_part, ax, ay, az, acc4);
     return hipGetLastError();
 }
 
 hipError_t launch_mesh_collide(const Workspace &ws, const double *vx, const double *vy,
                                const double *vz, const double *R, int64_t n, double dt,
-                               bool count, hipStream_t s) {
-    hipError_t e0 = launch_pack_vr(ws, vx, vy, vz, R, n, s);
-    if (e0 != hipSuccess) return e0;
+                               bool count, bool packed, hipStream_t s) {
+    if (!packed) {
+        const hipError_t e0 = launch_pack_vr(ws, vx, vy, vz, R, n, s);
+        if (e0 != hipSuccess) return e0;
+    }
     k_mesh_vel<<<grid_of(n, 256), 256, 0, s>>>(ws.midx, ws.pack4, n, ws.mvel);
     k_mesh_col_init<<<1, 64, 0, s>>>(ws.st);
     // partials: neighbour counts [0, nblk), tests [nblk, 2 nblk), tests of the moonlets

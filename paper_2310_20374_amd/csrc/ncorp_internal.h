@@ -478,14 +478,17 @@ hipError_t launch_sum_u64(const unsigned long long *part, int64_t n, unsigned lo
 hipError_t launch_radix_sort(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *vb, int64_t n,
                              int bits, uint32_t *hist, bool *in_b, hipStream_t s,
                              const int32_t *skip = nullptr, int skip_from = 0);
+// m (or nullptr): the masses, brought into mesh order with the positions; launch_mesh_gravity
+// on that mesh then has mus_packed.  acc4, packed: as in the tree's evaluation and search.
 hipError_t launch_mesh_build(const Workspace &ws, const double *x, const double *y,
-                             const double *z, const double *R, int64_t n, const ncorp_params &prm,
-                             bool first, hipStream_t s);
+                             const double *z, const double *R, const double *m, int64_t n,
+                             const ncorp_params &prm, bool first, hipStream_t s);
 hipError_t launch_mesh_gravity(const Workspace &ws, const double *m, double G, int64_t n,
-                               bool count, double *ax, double *ay, double *az, hipStream_t s);
+                               bool count, bool mus_packed, double *ax, double *ay, double *az,
+                               double4 *acc4, hipStream_t s);
 hipError_t launch_mesh_collide(const Workspace &ws, const double *vx, const double *vy,
                                const double *vz, const double *R, int64_t n, double dt,
-                               bool count, hipStream_t s);
+                               bool count, bool packed, hipStream_t s);
 
 // what the kick adds besides the mutual gravity: G M_c, G M_c R^2 J2, and the
 // distant body (G M_sun, its position, a^2, a^3); zero factors switch terms off
