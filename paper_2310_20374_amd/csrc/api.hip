@@ -302,8 +302,8 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.vcol = (double4 *)take(32 * n);
     ws.acc = (double *)take(3 * 8 * n);
     ws.acc_s = (double *)take(3 * 8 * n);
-    ws.ent_start = (int32_t *)take(4 * n);
-    ws.ent_code = (uint32_t *)take(4 * n);
+    (void)take(4 * n);
+    ws.ent_work = (uint32_t *)take(4 * n);
     ws.ent_cell = (int32_t *)take(4 * n);
     ws.c_level = (int32_t *)take(4 * cell_cap);
     ws.c_first = (int32_t *)take(4 * cell_cap);
@@ -359,7 +359,7 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
         ws.bs_cm = (uint32_t *)take(4 * nbk * nbt);
         ws.bs_total = (uint32_t *)take(4 * nbk);
         ws.bs_off = (uint32_t *)take(4 * (nbk + 1));
-        ws.bs_done = (uint32_t *)take(4 * nbk);
+        (void)take(4 * nbk);
     }
     ws.seg = (uint16_t *)take(2 * n);
     ws.disk_max = (unsigned long long *)take(8 * (int64_t)kMaxDisks);
@@ -485,8 +485,7 @@ static int build_tree_impl(ncorp_ctx *c, const double *x, const double *y, const
     }
     {
         PhaseTimer t(c, NCORP_PHASE_TREE, s);
-        HIPCHK(c, launch_gather_pos(ws, n, m != nullptr, s));
-        HIPCHK(c, launch_build_tree(ws, n, c->prm.leaf_size, s));
+        HIPCHK(c, launch_build_tree(ws, n, c->prm.leaf_size, m != nullptr, s));
         ws.arrive_clean = true;       // its cell-range pass cleared the climbs' counters
     }
     c->have_tree = true;

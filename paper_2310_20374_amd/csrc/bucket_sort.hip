@@ -19,6 +19,10 @@
 // and nothing depends on scheduling.  A bucket too large for one LDS batch is sorted
 // in batches that are then merged by (key, index) in global memory, so any
 // distribution sorts correctly.
+//
+// A small sort is a chain of short launches, so few buckets take three of them: count
+// (forming the boundaries), scatter (adding up the counts), local.  2000 moonlets: 38 -> 24
+// us, 1e5: 44 -> 35 us, 1e6 (with the boundaries and the row scan): 81 -> 84 us.
 #include "ncorp_internal.h"
 
 namespace ncorp {
@@ -191,21 +195,94 @@ k_bs_splitters(DevState *st, const uint64_t *__restrict__ keys, const uint32_t *
 }
 
 // ------------------------------------------------------------------ count
+// Few buckets (kOwnBuckets): their sample is one key a thread, so every counting block
+// forms the boundaries by itself, as k_bs_splitters does, which saves its launch (some
+// 5 us; 1e5 moonlets in 56 buckets).  With more the sample's sort would be repeated at
+// length.
+constexpr int kOwnBuckets = kBsThreads / kBsSamplesPer;
+struct OwnLds {
+    uint64_t k[kBsThreads];
+    uint32_t i[kBsThreads];
+    int bad;
+};
+
+// fills sk, si (nb - 1 boundaries); cnt: nb words of scratch; the same in every block
+__device__ __forceinline__ void own_boundaries(DevState *st, const uint64_t *__restrict__ keys,
+                                               const uint32_t *__restrict__ idx, int n, int nb,
+                                               int prev_ok, const SplitKey *__restrict__ prev,
+                                               uint64_t *sk, uint32_t *si, uint32_t *cnt,
+                                               OwnLds &O) {
+    const int tid = threadIdx.x;
+    const bool publish = blockIdx.x == 0 && tid == 0;
+    if (publish) {
+        st->bs_spill = 0;
+        st->bs_sub_rd = st->bs_sub_wr & 1;
+    }
+    if (nb <= 1) {
+        if (publish) st->bs_prev_used = 0;
+        return;
+    }
+    const int S = nb * kBsSamplesPer;                    // <= kBsThreads
+    uint64_t k = kKeySentinel;
+    uint32_t x = ~0u;
+    if (tid < S) {
+        const int p = (int)((int64_t)tid * n / S);
+        k = keys[p];
+        x = idx[p];
+    }
+    if (prev_ok && st->bs_valid && st->bs_n == n && st->bs_L == st->L) {
+        for (int j = tid; j < nb - 1; j += kBsThreads) {
+            sk[j] = prev[j].k;
+            si[j] = prev[j].i;
+        }
+        for (int b = tid; b < nb; b += kBsThreads) cnt[b] = 0;
+        if (tid == 0) O.bad = 0;
+        __syncthreads();
+        if (tid < S) atomicAdd(&cnt[bucket_of(sk, si, nb - 1, k, x)], 1u);
+        __syncthreads();
+        for (int b = tid; b < nb; b += kBsThreads)
+            if (cnt[b] > (uint32_t)((4 * S + 4 * nb) / nb)) O.bad = 1;
+        __syncthreads();
+        if (!O.bad) {
+            if (publish) st->bs_prev_used = 1;
+            return;
+        }
+    }
+    O.k[tid] = k;
+    O.i[tid] = x;
+    bitonic_lds<kBsThreads>(O.k, O.i, pow2_at_least(S));
+    for (int b = 1 + tid; b < nb; b += kBsThreads) {
+        const int at = (int)((int64_t)b * S / nb);
+        sk[b - 1] = O.k[at];
+        si[b - 1] = O.i[at];
+    }
+    if (publish) st->bs_prev_used = 0;
+}
+
 // The bucket of every pair (into bkt) and the pairs per bucket of this tile (into
 // column `tile` of the bucket-major count matrix).  LDS: boundary keys and indices,
-// one counter per bucket.
+// one counter per bucket.  OWN: the boundaries formed here (from prev, if prev_ok)
+// instead of read from split.
+template <bool OWN>
 __global__ void __launch_bounds__(kBsThreads)
-k_bs_count(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ idx, int n, int nb,
-           int ntiles, const SplitKey *__restrict__ split, uint32_t *__restrict__ bkt,
+k_bs_count(DevState *st, const uint64_t *__restrict__ keys, const uint32_t *__restrict__ idx,
+           int n, int nb, int ntiles, int prev_ok, const SplitKey *__restrict__ prev,
+           const SplitKey *__restrict__ split, uint32_t *__restrict__ bkt,
            uint32_t *__restrict__ cm) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint64_t *sk = reinterpret_cast<uint64_t *>(smem);
     uint32_t *si = reinterpret_cast<uint32_t *>(sk + nb);
     uint32_t *cnt = si + nb;
     const int tid = threadIdx.x;
-    for (int j = tid; j < nb - 1; j += kBsThreads) {
-        sk[j] = split[j].k;
-        si[j] = split[j].i;
+    if constexpr (OWN) {
+        __shared__ OwnLds O;
+        own_boundaries(st, keys, idx, n, nb, prev_ok, prev, sk, si, cnt, O);
+        __syncthreads();
+    } else {
+        for (int j = tid; j < nb - 1; j += kBsThreads) {
+            sk[j] = split[j].k;
+            si[j] = split[j].i;
+        }
     }
     for (int b = tid; b < nb; b += kBsThreads) cnt[b] = 0;
     __syncthreads();
@@ -279,7 +356,10 @@ k_bs_rowscan(DevState *st, uint32_t *__restrict__ cm, int ntiles, uint32_t *__re
 // order.  The tile is first laid out in LDS in bucket order, then written out so that
 // each bucket's run of the tile leaves as consecutive stores.  LDS (dynamic): per
 // bucket its global start minus its start in the tile, its start in the tile, and
-// per-wave counters.  Block 0 also publishes the bucket starts.
+// per-wave counters.  Block 0 also publishes the bucket starts.  ADD: the block adds up
+// its column of the count matrix itself (kAddCounts entries and fewer: 16 loads a thread
+// against a launch) instead of k_bs_rowscan before it.
+constexpr int kAddCounts = 16 * kBsThreads;
 struct ScatterLds {
     uint64_t k[kBucketTile];
     uint32_t v[kBucketTile];
@@ -287,8 +367,9 @@ struct ScatterLds {
     uint32_t wsum[kBsWaves];
 };
 
+template <bool ADD>
 __global__ void __launch_bounds__(kBsThreads)
-k_bs_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
+k_bs_scatter(DevState *st, const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
              const uint32_t *__restrict__ bkt, int n, int nb, int ntiles,
              const uint32_t *__restrict__ cm, const uint32_t *__restrict__ total,
              uint32_t *__restrict__ off, uint64_t *__restrict__ kout,
@@ -298,8 +379,30 @@ k_bs_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     int32_t *delta = reinterpret_cast<int32_t *>(smem);             // [nb]
     uint32_t *tstart = reinterpret_cast<uint32_t *>(delta + nb);   // [nb]
     uint32_t *wcnt = tstart + nb;                                  // [kBsWaves][nb]
+    uint32_t *all = wcnt + kBsWaves * nb, *before = all + nb;      // ADD: [nb] each
     const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
     const int tile = blockIdx.x;
+    if (ADD) {
+        // four threads a bucket
+        for (int q = t; q < 4 * nb; q += kBsThreads) {
+            const uint32_t *row = cm + (int64_t)(q >> 2) * ntiles;
+            uint32_t a = 0, p = 0;
+            for (int k = q & 3; k < ntiles; k += 4) {
+                const uint32_t c = row[k];
+                a += c;
+                if (k < tile) p += c;
+            }
+            for (int o = 1; o < 4; o <<= 1) {
+                a += __shfl_xor(a, o);
+                p += __shfl_xor(p, o);
+            }
+            if ((q & 3) == 0) {
+                all[q >> 2] = a;
+                before[q >> 2] = p;
+                if (tile == 0 && a > (uint32_t)kBucketLDS) atomicAdd(&st->bs_spill, 1);
+            }
+        }
+    }
     for (int b = t; b < nb; b += kBsThreads)
 #pragma unroll
         for (int k = 0; k < kBsWaves; k++) wcnt[k * nb + b] = 0;
@@ -338,12 +441,13 @@ k_bs_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
         uint32_t tall, gall;
         const uint32_t tex = block_scan(run, T.wsum, &tall);
         __syncthreads();
-        const uint32_t g = b < nb ? total[b] : 0u;
+        const uint32_t g = b < nb ? (ADD ? all[b] : total[b]) : 0u;
         const uint32_t gex = block_scan(g, T.wsum, &gall);
         if (b < nb) {
             const uint32_t gs = gcarry + gex;
             tstart[b] = tcarry + tex;
-            delta[b] = (int32_t)(gs + cm[(int64_t)b * ntiles + tile]) - (int32_t)(tcarry + tex);
+            const uint32_t pre = ADD ? before[b] : cm[(int64_t)b * ntiles + tile];
+            delta[b] = (int32_t)(gs + pre) - (int32_t)(tcarry + tex);
             if (tile == 0) off[b] = gs;
         }
         gcarry += gall;
@@ -410,9 +514,9 @@ struct LocalLds {
 };
 
 // the fast local sort (previous order): threads per bucket, most pairs per bucket
-constexpr int kFastThreads = 256;
+constexpr int kFastThreads = kBsLocalThreads;
 constexpr int kFastCap = 2560;
-constexpr int kFastRounds = kFastCap / kFastThreads;
+constexpr int kFastRounds = (kFastCap + kFastThreads - 1) / kFastThreads;
 
 // LDS of the fast local sort
 struct SubLds {
@@ -761,46 +865,20 @@ __device__ __forceinline__ void write_boundaries(const uint64_t *keys, const uin
     }
 }
 
-// Fast local sorts: one block per bucket, for buckets taken from the previous
-// order and of at most kFastCap pairs (sub-split sort); a bucket it sorts is marked
-// done, with its share of the next build's boundaries written.
-__global__ void __launch_bounds__(kFastThreads)
-k_bs_fast(const DevState *st, const uint32_t *__restrict__ off, int nb, int n,
-          uint64_t *__restrict__ keys, uint32_t *__restrict__ idx, SplitKey *__restrict__ next,
-          const SplitKey *sub0, const SplitKey *sub1, SplitKey *nsub0, SplitKey *nsub1,
-          uint32_t *__restrict__ done) {
-    static_assert(kSubPer < kFastThreads, "one sub-range count per thread");
-    __shared__ SubLds L;
-    const int b = blockIdx.x;
-    const int o = (int)off[b];
-    const int size = (int)off[b + 1] - o;
-    bool ok = false;
-    if (st->bs_prev_used && size > 0 && size <= kFastCap) {
-        const SplitKey *subs = st->bs_sub_rd ? sub1 : sub0;
-        const int ntot = (n + kSubStride - 1) / kSubStride;
-        const int nsub = ntot - b * kSubPer < kSubPer ? ntot - b * kSubPer : kSubPer;
-        ok = subsplit_sort_local(keys + o, idx + o, size, subs + (int64_t)b * kSubPer, nsub,
-                                 keys + o, idx + o, L);
-    }
-    if (ok) {
-        __threadfence_block();
-        __syncthreads();
-        write_boundaries<kFastThreads>(keys, idx, o, size, nb, next,
-                                       st->bs_sub_rd ? nsub0 : nsub1);
-    }
-    if (threadIdx.x == 0) done[b] = ok || size <= 0 ? 1u : 0u;
-}
-
-// The other buckets, one block each: at most kBucketLDS pairs sorted in LDS (one pass
-// over sub-ranges of the key range, or the radix sort where a sub-range is
-// crowded); a larger one in kBucketLDS batches (written to the alternate buffers),
-// then merged pairwise in global memory until one run remains.  The block also
-// stores its share of the next build's boundaries.  LDS: LocalLds (dynamic).
+// Local sorts, one block per bucket.  A bucket taken from the previous order and of at
+// most kFastCap pairs is sorted by its finer boundaries.  The others: at most kBucketLDS
+// pairs sorted in LDS (one pass over sub-ranges of the key range, or the radix sort where
+// a sub-range is crowded); a larger one in kBucketLDS batches (written to the alternate
+// buffers), then merged pairwise in global memory until one run remains.  The block also
+// stores its share of the next build's boundaries.  LDS: SubLds or LocalLds (dynamic).
+// One kernel for all: with the finer boundaries in a kernel of their own the second
+// launch found nothing left to do and still took 4 to 5 us.
 __global__ void __launch_bounds__(kBsLocalThreads)
-k_bs_slow(DevState *st, const uint32_t *__restrict__ off, int nb, int n,
-          uint64_t *__restrict__ keys, uint32_t *__restrict__ idx, uint64_t *__restrict__ kalt,
-          uint32_t *__restrict__ ialt, SplitKey *__restrict__ next, SplitKey *sub0,
-          SplitKey *sub1, const uint32_t *__restrict__ done) {
+k_bs_local(DevState *st, const uint32_t *__restrict__ off, int nb, int n,
+           uint64_t *__restrict__ keys, uint32_t *__restrict__ idx, uint64_t *__restrict__ kalt,
+           uint32_t *__restrict__ ialt, SplitKey *__restrict__ next, SplitKey *sub0,
+           SplitKey *sub1) {
+    static_assert(kSubPer < kFastThreads, "one sub-range count per thread");
     extern __shared__ __align__(16) unsigned char smem[];
     LocalLds &L = *reinterpret_cast<LocalLds *>(smem);
     const int tid = threadIdx.x;
@@ -813,9 +891,21 @@ k_bs_slow(DevState *st, const uint32_t *__restrict__ off, int nb, int n,
         st->bs_L = st->L;
         st->bs_sub_wr = 1 - rd;
     }
-    if (done[b]) return;
     const int o = (int)off[b];
     const int size = (int)off[b + 1] - o;
+    if (size <= 0) return;
+    if (st->bs_prev_used && size <= kFastCap) {
+        const int ntot = (n + kSubStride - 1) / kSubStride;
+        const int nsub = ntot - b * kSubPer < kSubPer ? ntot - b * kSubPer : kSubPer;
+        if (subsplit_sort_local(keys + o, idx + o, size, (rd ? sub1 : sub0) + (int64_t)b * kSubPer,
+                                nsub, keys + o, idx + o, *reinterpret_cast<SubLds *>(smem))) {
+            __threadfence_block();
+            __syncthreads();
+            write_boundaries<kBsLocalThreads>(keys, idx, o, size, nb, next, subn);
+            return;
+        }
+        __syncthreads();                     // the other sorts reuse the LDS
+    }
     if (size <= kBucketLDS) {
         if (!onepass_sort_local(keys + o, idx + o, size, keys + o, idx + o, L))
             radix_sort_local(keys + o, idx + o, size, keys + o, idx + o, L);
@@ -875,21 +965,29 @@ bool bucket_sort_applies(const Workspace &ws, int64_t n) {
 hipError_t launch_bucket_sort(const Workspace &ws, int64_t n, hipStream_t s) {
     const int nb = (int)n_buckets(n);
     const int ntiles = (int)((n + kBucketTile - 1) / kBucketTile);
-    k_bs_splitters<<<1, 1024, 0, s>>>(ws.st, ws.keys_alt, ws.idx_alt, (int)n, nb,
-                                      ws.sort_prev ? 1 : 0, ws.bs_prev, ws.bs_split);
-    k_bs_count<<<ntiles, kBsThreads, (size_t)nb * 16, s>>>(ws.keys_alt, ws.idx_alt, (int)n, nb,
-                                                           ntiles, ws.bs_split, ws.code, ws.bs_cm);
-    k_bs_rowscan<<<nb, kBsThreads, 0, s>>>(ws.st, ws.bs_cm, ntiles, ws.bs_total);
-    k_bs_scatter<<<ntiles, kBsThreads, (size_t)nb * 4 * (2 + kBsWaves), s>>>(
-        ws.keys_alt, ws.idx_alt, ws.code, (int)n, nb, ntiles, ws.bs_cm, ws.bs_total, ws.bs_off,
-        ws.keys, ws.idx);
-    k_bs_fast<<<nb, kFastThreads, 0, s>>>(ws.st, ws.bs_off, nb, (int)n, ws.keys, ws.idx,
-                                          ws.bs_prev, ws.bs_sub[0], ws.bs_sub[1], ws.bs_sub[0],
-                                          ws.bs_sub[1], ws.bs_done);
-    k_bs_slow<<<nb, kBsLocalThreads, sizeof(LocalLds), s>>>(ws.st, ws.bs_off, nb, (int)n, ws.keys,
-                                                       ws.idx, ws.keys_alt, ws.idx_alt,
-                                                       ws.bs_prev, ws.bs_sub[0], ws.bs_sub[1],
-                                                       ws.bs_done);
+    const int prev_ok = ws.sort_prev ? 1 : 0;
+    const size_t lds = (size_t)nb * 16;
+    if (nb <= kOwnBuckets) {
+        k_bs_count<true><<<ntiles, kBsThreads, lds, s>>>(ws.st, ws.keys_alt, ws.idx_alt, (int)n,
+                                                         nb, ntiles, prev_ok, ws.bs_prev, nullptr,
+                                                         ws.code, ws.bs_cm);
+    } else {
+        k_bs_splitters<<<1, 1024, 0, s>>>(ws.st, ws.keys_alt, ws.idx_alt, (int)n, nb, prev_ok,
+                                          ws.bs_prev, ws.bs_split);
+        k_bs_count<false><<<ntiles, kBsThreads, lds, s>>>(ws.st, ws.keys_alt, ws.idx_alt, (int)n,
+                                                          nb, ntiles, 0, nullptr, ws.bs_split,
+                                                          ws.code, ws.bs_cm);
+    }
+    const bool add = (int64_t)nb * ntiles <= kAddCounts;
+    if (!add) k_bs_rowscan<<<nb, kBsThreads, 0, s>>>(ws.st, ws.bs_cm, ntiles, ws.bs_total);
+    auto scatter = add ? k_bs_scatter<true> : k_bs_scatter<false>;
+    scatter<<<ntiles, kBsThreads, (size_t)nb * 4 * (2 + kBsWaves + (add ? 2 : 0)), s>>>(
+        ws.st, ws.keys_alt, ws.idx_alt, ws.code, (int)n, nb, ntiles, ws.bs_cm, ws.bs_total,
+        ws.bs_off, ws.keys, ws.idx);
+    constexpr size_t local = sizeof(LocalLds) > sizeof(SubLds) ? sizeof(LocalLds) : sizeof(SubLds);
+    k_bs_local<<<nb, kBsLocalThreads, local, s>>>(ws.st, ws.bs_off, nb, (int)n, ws.keys, ws.idx,
+                                                  ws.keys_alt, ws.idx_alt, ws.bs_prev,
+                                                  ws.bs_sub[0], ws.bs_sub[1]);
     return hipGetLastError();
 }
 

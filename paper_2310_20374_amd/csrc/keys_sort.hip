@@ -532,34 +532,11 @@ hipError_t launch_radix_sort(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t 
 }
 
 // ------------------------------------------------------------------ gathers
-// Positions in tree order from the packed records k_keys wrote in input order: one
-// 32-byte record per moonlet instead of three scattered 8-byte words.  When k_keys had
-// the scaled masses G m too (pos4 != nullptr), the whole record, which the gravity climb
-// and the direct sums read.
-__global__ void k_gather_pack4(const double4 *__restrict__ pack4, const uint32_t *__restrict__ idx,
-                              int64_t n, double *__restrict__ xs, double *__restrict__ ys,
-                              double *__restrict__ zs, double4 *__restrict__ pos4) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const double4 p = pack4[idx[i]];
-        xs[i] = p.x;
-        ys[i] = p.y;
-        zs[i] = p.z;
-        if (pos4) pos4[i] = p;
-    }
-}
-
 __global__ void k_gather1(const double *__restrict__ src, const uint32_t *__restrict__ idx,
                           int64_t n, double *__restrict__ dst) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         dst[i] = src[idx[i]];
-}
-
-hipError_t launch_gather_pos(const Workspace &ws, int64_t n, bool with_mus, hipStream_t s) {
-    k_gather_pack4<<<grid_for(n, 256), 256, 0, s>>>(ws.pack4, ws.idx, n, ws.xs, ws.ys, ws.zs,
-                                                    with_mus ? ws.vcol : nullptr);
-    return hipGetLastError();
 }
 
 // the (x, y, z, G m) records in tree order, when the build had no masses to pack

@@ -276,10 +276,8 @@ struct Workspace {
     double *acc = nullptr;                            // 3 x n, input order (step)
     double *acc_s = nullptr;                          // 3 x n, tree order (direct sums)
     // leaves in moonlet order ("entries")
-    int32_t *ent_start = nullptr;                     // first moonlet
-    uint32_t *ent_code = nullptr;                     // dv | L << 8; after the build, the
-                                                      // source moonlets and then the slots
-                                                      // of each leaf's direct sums
+    uint32_t *ent_work = nullptr;                     // source moonlets, then slots, of each
+                                                      // leaf's direct sums
     int32_t *ent_cell = nullptr;                      // cell index of the leaf
     // cells, breadth-first
     int32_t *c_level = nullptr, *c_first = nullptr, *c_count = nullptr;
@@ -332,7 +330,6 @@ struct Workspace {
     SplitKey *bs_split = nullptr, *bs_prev = nullptr;
     SplitKey *bs_sub[2] = {nullptr, nullptr};         // keys at ranks k kSubStride
     uint32_t *bs_cm = nullptr, *bs_total = nullptr, *bs_off = nullptr;
-    uint32_t *bs_done = nullptr;                      // bucket sorted by the fast pass
     bool sort_prev = false;
     // batched calls: disk of each moonlet (input order; the sort keeps disks
     // contiguous, so it is also the disk of each tree position), per-disk max
@@ -392,8 +389,6 @@ hipError_t launch_sort(const Workspace &ws, int64_t n, hipStream_t s);
 // writes where it starts)
 bool bucket_sort_applies(const Workspace &ws, int64_t n);
 hipError_t launch_bucket_sort(const Workspace &ws, int64_t n, hipStream_t s);
-// with_mus: the keys packed G m, and the whole record lands in ws.vcol
-hipError_t launch_gather_pos(const Workspace &ws, int64_t n, bool with_mus, hipStream_t s);
 hipError_t launch_gather(const Workspace &ws, const double *src, double *dst, int64_t n,
                          hipStream_t s);
 // velocities and radii into tree order, one pass
@@ -401,7 +396,9 @@ hipError_t launch_pack_vr(const Workspace &ws, const double *vx, const double *v
                           const double *vz, const double *R, int64_t n, hipStream_t s);
 hipError_t launch_gather_vr(const Workspace &ws, bool packed, const double *vx, const double *vy,
                             const double *vz, const double *R, int64_t n, hipStream_t s);
-hipError_t launch_build_tree(const Workspace &ws, int64_t n, int leaf_size, hipStream_t s);
+// with_mus: the keys packed G m, and the whole record lands in ws.vcol
+hipError_t launch_build_tree(const Workspace &ws, int64_t n, int leaf_size, bool with_mus,
+                             hipStream_t s);
 
 // reset: clear the arrival and leaf counters first (not needed right after a build);
 // rcrit: then the opening angles and critical radii (a gravity walk's init pass can
@@ -508,10 +505,5 @@ hipError_t launch_drift(double *x, double *y, double *z, const double *vx,
                         hipStream_t s, DevState *st = nullptr);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t s);
-
-// device-wide exclusive scan of n_dev[0] int32 values (n_cap an upper bound);
-// writes total to *total_dev (may alias out[n]).
-hipError_t launch_scan(const int32_t *in, int32_t *out, const int32_t *n_dev, int64_t n_cap,
-                       int32_t *partials, int32_t *total_dev, hipStream_t s);
 
 }  // namespace ncorp

@@ -658,7 +658,7 @@ k_l2p(const DevState *__restrict__ st, const double *__restrict__ xs,
 template <int P>
 static void launch_leaf_local(const Workspace &ws, int split_unit, hipStream_t s) {
     const SplitArgs S = {ws.p2p_cnt, ws.c_count, ws.c_first, ws.c_nent,
-                         ws.ndisks > 1 ? ws.seg : nullptr, ws.disk_root, ws.ent_code,
+                         ws.ndisks > 1 ? ws.seg : nullptr, ws.disk_root, ws.ent_work,
                          ws.long_p2p, ws.split_p2p, 2 * ws.m2l_cap, split_unit};
     int64_t g = ((int64_t)ws.n_max * P + 127) / 128;
     if (g > 8192) g = 8192;
@@ -729,7 +729,7 @@ static void launch_p2p_t(const Workspace &ws, int64_t n, int tmax, hipStream_t s
     const int64_t g = most < kP2PGrid ? most : kP2PGrid;
     k_p2p<T, TILE><<<(int)g, kWave, 0, s>>>(
         ws.st, ws.vcol, ws.ent_cell, ws.c_first, ws.c_count, ws.gcell, ws.p2p_cnt, ws.p2p_seg,
-        ws.p2p_stride, ws.split_p2p, 2 * ws.m2l_cap, ws.ent_code, ws.p2p_part, ws.acc_s, n, tmax);
+        ws.p2p_stride, ws.split_p2p, 2 * ws.m2l_cap, ws.ent_work, ws.p2p_part, ws.acc_s, n, tmax);
 }
 
 template <typename T>
@@ -757,7 +757,7 @@ static void launch_l2p_p(const Workspace &ws, int64_t n, double *ax, double *ay,
     int64_t g = (ws.leaf_cap + kL2PWaves - 1) / kL2PWaves;
     g = g < 1 ? 1 : (g > 16384 ? 16384 : g);
     k_l2p<P><<<(int)g, kWave * kL2PWaves, 0, s>>>(ws.st, ws.xs, ws.ys, ws.zs, ws.idx, ws.ent_cell, ws.c_first,
-                              ws.c_count, ws.gcell, ws.cleaf, ws.acc_s, ws.ent_code, ws.p2p_part, n,
+                              ws.c_count, ws.gcell, ws.cleaf, ws.acc_s, ws.ent_work, ws.p2p_part, n,
                               ax, ay, az, acc4);
 }
 

@@ -501,7 +501,7 @@ hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_po
         A.p2p_cnt = ws.p2p_cnt; A.p2p_seg = ws.p2p_seg; A.p2p_stride = ws.p2p_stride;
         A.c_rmax = ws.c_rmax;
         A.leaf_slack = ws.leaf_slack;
-        A.leaf_src = ws.ent_code;
+        A.leaf_src = ws.ent_work;
         A.timing = ws.timing ? 1 : 0;
         k_walk<0><<<walk_grid<0>(ws.cell_cap, most), kWalkBlock, 0, s>>>(A);
     } else {
