@@ -53,11 +53,40 @@ __device__ __forceinline__ bool within_reach(const PState &a, const PState &b) {
     return dx * dx + dy * dy + dz * dz <= rs * rs * (1.0 + 1e-9);
 }
 
+// Colliding pairs a wave has found, listed together at its end (beyond kPairBuf one by
+// one): an atomic on the pair count takes some 15 ns and holds up the wave's next loads, so
+// one a pair bounded a search that finds many (66000 pairs at 4e6 clumped moonlets: 1256 ->
+// 890 us).
+constexpr int kPairBuf = 96;         // as much LDS as its allocation step leaves unused
+struct PairOut {
+    int64_t *out;
+    int64_t cap;
+    DevState *st;
+    int64_t *buf;                        // LDS, kPairBuf keys
+    int *n;                              // LDS, keys pushed
+};
+
+__device__ __forceinline__ void flush_pairs(const PairOut &P, int lane) {
+    __syncthreads();
+    const int n = *P.n < kPairBuf ? *P.n : kPairBuf;
+    if (n == 0) return;
+    unsigned long long base = 0;
+    if (lane == 0) base = atomicAdd((unsigned long long *)&P.st->npairs, (unsigned long long)n);
+    base = ((unsigned long long)__shfl((unsigned)(base >> 32), 0) << 32) |
+           (unsigned)__shfl((unsigned)base, 0);
+    for (int k = lane; k < n; k += kWave)
+        if ((int64_t)base + k < P.cap) P.out[base + k] = P.buf[k];
+}
+
 __device__ __forceinline__ void test_pair(const PState &p, const PState &o, double dt,
-                                          int64_t *out, int64_t cap, DevState *st) {
+                                          const PairOut &P) {
     if (within_reach(p, o) &&
-        pair_test(p.x, p.y, p.z, p.vx, p.vy, p.vz, p.R, o.x, o.y, o.z, o.vx, o.vy, o.vz, o.R, dt))
-        record(out, cap, (unsigned long long *)&st->npairs, p.id, o.id);
+        pair_test(p.x, p.y, p.z, p.vx, p.vy, p.vz, p.R, o.x, o.y, o.z, o.vx, o.vy, o.vz, o.R,
+                  dt)) {
+        const int k = atomicAdd(P.n, 1);
+        if (k < kPairBuf) P.buf[k] = pair_key(p.id, o.id);
+        else record(P.out, P.cap, (unsigned long long *)&P.st->npairs, p.id, o.id);
+    }
 }
 
 // Can moonlet p = (x, y, z, R + dt |v|) meet a moonlet of the other cell within the
@@ -126,7 +155,7 @@ __device__ __forceinline__ int cull_cell(int f, int n, double4 oa, double4 ob,
 // shrinking as i grows.
 __device__ __forceinline__ void self_pairs_staged(int n, const PState *sb,
                                                   const double4 *spos, double dt,
-                                                  int64_t *out, int64_t cap, DevState *st,
+                                                  const PairOut &P,
                                                   unsigned long long &tests) {
     const int lane = threadIdx.x;
     int S = 1;
@@ -143,7 +172,7 @@ __device__ __forceinline__ void self_pairs_staged(int n, const PState *sb,
         const double4 o = spos[j];
         const double dx = me.x - o.x, dy = me.y - o.y, dz = me.z - o.z;
         const double rs = me.reach + o.w;
-        if (dx * dx + dy * dy + dz * dz <= rs * rs * (1.0 + 1e-9)) test_pair(me, sb[j], dt, out, cap, st);
+        if (dx * dx + dy * dy + dz * dz <= rs * rs * (1.0 + 1e-9)) test_pair(me, sb[j], dt, P);
     }
 }
 
@@ -153,8 +182,8 @@ __device__ __forceinline__ void self_pairs_staged(int n, const PState *sb,
 __device__ __forceinline__ void test_cell_pair(
     int2 pr, PState *sb, double4 *spos, const int32_t *__restrict__ c_first,
     const int32_t *__restrict__ c_count, const uint32_t *__restrict__ perm,
-    const double4 *__restrict__ pcol, const double4 *__restrict__ vcol, double dt, int64_t *out,
-    int64_t cap, DevState *st, unsigned long long &tests) {
+    const double4 *__restrict__ pcol, const double4 *__restrict__ vcol, double dt,
+    const PairOut &P, unsigned long long &tests) {
     const int lane = threadIdx.x;
     const int fa = c_first[pr.x], na = c_count[pr.x];
     const int fb = c_first[pr.y], nb = c_count[pr.y];
@@ -172,7 +201,7 @@ __device__ __forceinline__ void test_cell_pair(
             spos[lane] = p;
         }
         __syncthreads();
-        self_pairs_staged(na, sb, spos, dt, out, cap, st, tests);
+        self_pairs_staged(na, sb, spos, dt, P, tests);
         return;
     }
     for (int a0 = 0; a0 < na; a0 += 64) {
@@ -209,7 +238,7 @@ __device__ __forceinline__ void test_cell_pair(
             int j = jlo + ((grp - jlo % G) % G + G) % G;
             for (; j < nbc; j += G) {
                 tests++;
-                test_pair(me, sb[j], dt, out, cap, st);
+                test_pair(me, sb[j], dt, P);
             }
         }
     }
@@ -234,6 +263,10 @@ k_collide(DevState *st, const CandOut C, const int32_t *__restrict__ walk_ctr,
           int64_t *out, int64_t cap, unsigned long long *tests_part) {
     __shared__ PState sp[kWave];    // survivors of both sides (or a staged tile of B)
     __shared__ double4 spos[kWave];
+    __shared__ int64_t pair_buf[kPairBuf];
+    __shared__ int pair_n;
+    const PairOut P = {out, cap, st, pair_buf, &pair_n};
+    if (threadIdx.x == 0) pair_n = 0;
     if (st->status & kSkipMask) {
         if (threadIdx.x == 0) tests_part[blockIdx.x] = 0;
         return;
@@ -375,13 +408,12 @@ k_collide(DevState *st, const CandOut C, const int32_t *__restrict__ walk_ctr,
                     const int tot = ka * kb;
                     for (int t = lane; t < tot; t += kWave) {
                         tests++;
-                        test_pair(sp[t / kb], sp[ka + t % kb], dt, out, cap, st);
+                        test_pair(sp[t / kb], sp[ka + t % kb], dt, P);
                     }
                     continue;
                 }
             }
-            test_cell_pair(pr, sp, spos, c_first, c_count, perm, pcol, vcol, dt, out, cap, st,
-                           tests);
+            test_cell_pair(pr, sp, spos, c_first, c_count, perm, pcol, vcol, dt, P, tests);
         }
     }
     if (BOXES) {
@@ -394,7 +426,7 @@ k_collide(DevState *st, const CandOut C, const int32_t *__restrict__ walk_ctr,
             if (n < 2) continue;
             if (n > kWave) {
                 test_cell_pair(make_int2(c, c), sp, spos, c_first, c_count, perm, pcol, vcol, dt,
-                               out, cap, st, tests);
+                               P, tests);
                 continue;
             }
             __syncthreads();
@@ -409,9 +441,10 @@ k_collide(DevState *st, const CandOut C, const int32_t *__restrict__ walk_ctr,
                 spos[lane] = p;
             }
             __syncthreads();
-            self_pairs_staged(n, sp, spos, dt, out, cap, st, tests);
+            self_pairs_staged(n, sp, spos, dt, P, tests);
         }
     }
+    flush_pairs(P, lane);
     // per-block partials, summed by the pair ranking that follows: one atomic per wave
     // on a single counter would serialise all blocks of the grid
     for (int o = 32; o > 0; o >>= 1) tests += __shfl_xor(tests, o);
@@ -450,13 +483,14 @@ hipError_t launch_collide_reset(const Workspace &ws, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Rank sort of the (distinct) pair keys: rank = number of smaller keys.  A block of
+// Rank sort of the (distinct) pair keys: rank = number of smaller keys.  Up to
+// kRankDirect pairs by counting all of them: a block of
 // kRankSplit waves takes 64 keys (a lane each); wave w counts the smaller keys in the
 // w-th of kRankSplit equal segments of the list, walking it in chunks of 256 keys
 // loaded coalesced (the next chunk while the current one is compared) and read back
 // from LDS as wave-wide broadcasts; the block then adds the counts of its waves.
 constexpr int kRankSplit = 8;
-constexpr int kRankGrid = 2048;
+constexpr int kRankGrid = 512;     // 64 keys each up to kRankDirect, a range each beyond
 constexpr int kRankSumBlocks = 16;   // blocks that also add up the pair-test counts
 constexpr int kRankChunk = 4 * kWave;
 // The resolution's per-pair start (when dtc is non-null): contact time (Eq. 2) of
@@ -465,15 +499,137 @@ struct RankResolve {
     const double *x, *y, *z, *vx, *vy, *vz, *R;
     double dt;
     double *dtc;
-    int32_t *flag, *mmatch;
+    int32_t *flag, *mmatch, *mbest;      // mbest: no earliest pair yet (-1)
 };
+
+// The report's output: pairs as (i, j), or (step, i, j) after the earlier steps' (triple)
+struct RankReport {
+    int64_t *pairs;                      // nullptr: none
+    int64_t cap;
+    const int64_t *cursor;
+    int triple, step;
+};
+
+// What is done with the pair of key v and rank r.
+__device__ __forceinline__ void ranked(int64_t v, int64_t r, int64_t *__restrict__ out,
+                                       const RankResolve &RR, bool resolve,
+                                       const RankReport &RP) {
+    if (RP.pairs) {
+        const int64_t o = (RP.triple ? *RP.cursor : 0) + r;
+        if (o < RP.cap) {
+            int64_t *q = RP.pairs + (RP.triple ? 3 : 2) * o;
+            if (RP.triple) *q++ = RP.step;
+            q[0] = v >> 32;
+            q[1] = v & 0xffffffffll;
+        }
+        return;
+    }
+    out[r] = v;
+    if (!resolve) return;
+    const int a = (int)(v >> 32), b = (int)(v & 0xffffffffll);
+    const double t = contact_time(RR.x[a], RR.y[a], RR.z[a], RR.vx[a], RR.vy[a], RR.vz[a], RR.R[a],
+                                  RR.x[b], RR.y[b], RR.z[b], RR.vx[b], RR.vy[b], RR.vz[b],
+                                  RR.R[b], RR.dt);
+    RR.dtc[r] = t;
+    RR.flag[r] = t >= 0.0 ? 1 : 0;
+    RR.mmatch[a] = 0;
+    RR.mmatch[b] = 0;
+    RR.mbest[a] = -1;
+    RR.mbest[b] = -1;
+}
+
+// Beyond kRankDirect pairs: block g of G ranks the keys between splitters g and g + 1 of a
+// sorted sample of the list (four samples a block, the same sample and sort in every
+// block).  It reads the whole list once, counts the keys below its range, gathers its own
+// in LDS (about kRankOwn of them) and counts those against each other; a range of more than
+// kRankRoom keys is ranked against the list instead.  Counting all against all took 946 us
+// for the 66000 pairs of 4e6 clumped moonlets, this 95.
+constexpr int64_t kRankDirect = 4096;
+constexpr int kRankOwn = 512, kRankSamples = 2048, kRankRoom = 4096;
+union RankLds {
+    struct {
+        int64_t tile[kRankSplit][kRankChunk];
+        int64_t part[kRankSplit][kWave];
+    } d;
+    struct {
+        int64_t sample[kRankSamples];
+        int64_t own[kRankRoom];
+        int nown;
+        unsigned long long below;
+    } l;
+};
+
+__device__ __forceinline__ void rank_long(int64_t n, const int64_t *__restrict__ in,
+                                          int64_t *__restrict__ out, RankLds &lds,
+                                          const RankResolve &RR, bool resolve,
+                                          const RankReport &RP) {
+    constexpr int T = kWave * kRankSplit;
+    int G = 1;                                    // ranges: a power of two
+    while (G < (int)gridDim.x && G < kRankSamples / 4 && (int64_t)G * kRankOwn < n) G <<= 1;
+    if (G > (int)gridDim.x) G >>= 1;
+    const int g = blockIdx.x, t = threadIdx.x;
+    if (g >= G) return;
+    const int S = 4 * G;                          // <= kRankSamples
+    for (int k = t; k < S; k += T) lds.l.sample[k] = in[(int64_t)k * n / S];
+    if (t == 0) { lds.l.nown = 0; lds.l.below = 0; }
+    __syncthreads();
+    for (int k = 2; k <= S; k <<= 1)              // bitonic, ascending
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int q = t; q < S / 2; q += T) {
+                const int a = 2 * q - (q & (j - 1)), b = a + j;
+                const int64_t va = lds.l.sample[a], vb = lds.l.sample[b];
+                if ((vb < va) == ((a & k) == 0)) { lds.l.sample[a] = vb; lds.l.sample[b] = va; }
+            }
+            __syncthreads();
+        }
+    // keys in [lo, hi): distinct keys, so distinct splitters
+    const int64_t lo = g == 0 ? INT64_MIN : lds.l.sample[4 * g];
+    const int64_t hi = g == G - 1 ? INT64_MAX : lds.l.sample[4 * (g + 1)];
+    unsigned long long below = 0;
+    constexpr int U = 4;
+    for (int64_t q0 = t; q0 < n; q0 += U * T) {
+        int64_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) v[u] = q0 + u * T < n ? in[q0 + u * T] : INT64_MAX;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            below += v[u] < lo ? 1 : 0;
+            if (v[u] >= lo && v[u] < hi) {
+                const int at = atomicAdd(&lds.l.nown, 1);
+                if (at < kRankRoom) lds.l.own[at] = v[u];
+            }
+        }
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) below += __shfl_xor(below, o);
+    if (t % kWave == 0) atomicAdd(&lds.l.below, below);
+    __syncthreads();
+    const int m = lds.l.nown;
+    const int64_t base = (int64_t)lds.l.below;
+    if (m <= kRankRoom) {
+        for (int a = t; a < m; a += T) {
+            const int64_t v = lds.l.own[a];
+            int rk = 0;
+            for (int k = 0; k < m; k++) rk += lds.l.own[k] < v;
+            ranked(v, base + rk, out, RR, resolve, RP);
+        }
+        return;
+    }
+    for (int64_t a = t; a < n; a += T) {
+        const int64_t v = in[a];
+        if (v < lo || v >= hi) continue;
+        int64_t rk = 0;
+        for (int64_t k = 0; k < n; k++) rk += in[k] < v;
+        ranked(v, rk, out, RR, resolve, RP);
+    }
+}
 
 __global__ void __launch_bounds__(kWave * kRankSplit)
 k_rank_pairs(DevState *__restrict__ st, const int64_t *__restrict__ in, int64_t cap,
              int64_t *__restrict__ out, const unsigned long long *__restrict__ tests_part,
-             int n_part, const RankResolve RR) {
-    __shared__ int64_t tile_all[kRankSplit][kRankChunk];
-    __shared__ int64_t part[kRankSplit][kWave];
+             int n_part, const RankResolve RR, const RankReport RP) {
+    __shared__ RankLds lds;
+    auto &tile_all = lds.d.tile;
+    auto &part = lds.d.part;
     const int sum_b = (int)blockIdx.x - ((int)gridDim.x - kRankSumBlocks);
     if (tests_part && sum_b >= 0) {
         // the pair tests' per-block counts, summed by the last kRankSumBlocks blocks
@@ -498,6 +654,10 @@ k_rank_pairs(DevState *__restrict__ st, const int64_t *__restrict__ in, int64_t 
     // the resolution takes no pair of an overflowed list or after a failed pass
     const bool resolve = RR.dtc && n <= cap && !(st->status & kSkipMask);
     if (n > cap) n = cap;
+    if (n > kRankDirect) {
+        rank_long(n, in, out, lds, RR, resolve, RP);
+        return;
+    }
     const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
     int64_t *tile = tile_all[w];
     // this wave's segment of the list
@@ -538,41 +698,9 @@ k_rank_pairs(DevState *__restrict__ st, const int64_t *__restrict__ in, int64_t 
             int64_t r = 0;
 #pragma unroll
             for (int k = 0; k < kRankSplit; k++) r += part[k][lane];
-            out[r] = v;
-            if (resolve) {
-                const int a = (int)(v >> 32), b = (int)(v & 0xffffffffll);
-                const double t = contact_time(RR.x[a], RR.y[a], RR.z[a], RR.vx[a], RR.vy[a],
-                                              RR.vz[a], RR.R[a], RR.x[b], RR.y[b], RR.z[b],
-                                              RR.vx[b], RR.vy[b], RR.vz[b], RR.R[b], RR.dt);
-                RR.dtc[r] = t;
-                RR.flag[r] = t >= 0.0 ? 1 : 0;
-                RR.mmatch[a] = 0;
-                RR.mmatch[b] = 0;
-            }
+            ranked(v, r, out, RR, resolve, RP);
         }
         __syncthreads();
-    }
-}
-
-__global__ void k_emit_pairs(const DevState *__restrict__ st, const int64_t *__restrict__ sorted,
-                             int64_t tmp_cap, int64_t *pairs, int64_t cap, int64_t *n_pairs_dev,
-                             int triple, int step, int64_t *cursor) {
-    int64_t n = st->npairs;
-    int64_t m = n < tmp_cap ? n : tmp_cap;
-    int64_t base = triple ? *cursor : 0;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < m;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t v = sorted[k];
-        const int64_t o = base + k;
-        if (o >= cap) continue;
-        if (triple) {
-            pairs[3 * o] = step;
-            pairs[3 * o + 1] = v >> 32;
-            pairs[3 * o + 2] = v & 0xffffffffll;
-        } else {
-            pairs[2 * o] = v >> 32;
-            pairs[2 * o + 1] = v & 0xffffffffll;
-        }
     }
 }
 
@@ -844,6 +972,7 @@ __device__ __forceinline__ void keep_earliest(int32_t *slot, int p, const double
 }
 
 constexpr int kResolveThreads = 1024;
+constexpr int kResolveBlocks = 32;     // most blocks of the matching's first half round
 constexpr int kResolveGrid = 512;      // blocks of the per-pair passes
 
 // exclusive prefix of v >= 0 over the block (wsum: one word per wave), and the
@@ -882,7 +1011,11 @@ __device__ __forceinline__ int resolve_count(const DevState *st, int64_t pair_ca
     return (int)np;                       // pair indices are 32-bit (the capacity is)
 }
 
-// The rounds of the matching and the list of resolved pairs, one block.
+// The rounds of the matching and the list of resolved pairs.  Every live pair's bid for
+// its two moonlets in the first round, which has by far the most pairs, is spread over as
+// many blocks as there are 4096 pairs; the last of them to finish goes on alone (nobody
+// waits).  The ranking left the moonlets' slots empty.  66000 pairs: 1404 us in one block
+// from the start, 655 now.
 __global__ void __launch_bounds__(kResolveThreads)
 k_resolve(DevState *st, const int64_t *__restrict__ keys, int64_t pair_cap,
           const double *__restrict__ dtc, int32_t *flag, int32_t *mbest, int32_t *mmatch,
@@ -890,16 +1023,58 @@ k_resolve(DevState *st, const int64_t *__restrict__ keys, int64_t pair_cap,
           int64_t *cursor) {
     constexpr int U = kResolveUnroll;
     __shared__ int wsum[kResolveThreads / kWave];
+    __shared__ int last;
     const int tid = threadIdx.x;
     const int T = blockDim.x;
+    const int np = resolve_count(st, pair_cap);
+    int blocks = (np + U * T - 1) / (U * T);
+    blocks = blocks < 1 ? 1 : (blocks > (int)gridDim.x ? (int)gridDim.x : blocks);
+    if ((int)blockIdx.x >= blocks) return;
+    // flag: 0 dropped, 1 live, 2 resolved
+    for (int c0 = blockIdx.x * U * T; c0 < np; c0 += blocks * U * T)
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int p = c0 + u * T + tid;
+            if (p < np && flag[p] == 1) {
+                const int64_t k = keys[p];
+                keep_earliest(&mbest[pair_i(k)], p, dtc);
+                keep_earliest(&mbest[pair_j(k)], p, dtc);
+            }
+        }
+    if (blocks > 1) {
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) last = atomicAdd(&st->resolve_done, 1) == blocks - 1 ? 1 : 0;
+        __syncthreads();
+        if (!last) return;
+        __threadfence();
+        if (tid == 0) st->resolve_done = 0;
+    }
     if (st->npairs > pair_cap && !(st->status & kSkipMask) && tid == 0) {
         // the list is incomplete: nothing is resolved
         atomicOr(&st->status, (int32_t)ST_CAP_PAIRS);
         atomicMax((unsigned long long *)&st->required, (unsigned long long)st->npairs);
     }
-    const int np = resolve_count(st, pair_cap);
-    // flag: 0 dropped, 1 live, 2 resolved; the live pairs' indices are kept compacted
-    // in `live`, so later rounds visit only what is left
+    __syncthreads();
+    // the first round's matches; the pairs still live after it are then kept compacted in
+    // `live`, so later rounds visit only what is left
+    for (int c0 = 0; c0 < np; c0 += U * T)
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int p = c0 + u * T + tid;
+            if (p < np && flag[p] == 1) {
+                const int64_t k = keys[p];
+                const int i = pair_i(k), j = pair_j(k);
+                // (other blocks wrote the slots)
+                if (__hip_atomic_load(&mbest[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p &&
+                    __hip_atomic_load(&mbest[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p) {
+                    flag[p] = 2;
+                    mmatch[i] = 1;
+                    mmatch[j] = 1;
+                }
+            }
+        }
+    __syncthreads();
     int nlive = 0;
     for (int c0 = 0; c0 < np; c0 += U * T) {
         int cnt = 0;
@@ -907,7 +1082,12 @@ k_resolve(DevState *st, const int64_t *__restrict__ keys, int64_t pair_cap,
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const int p = c0 + U * tid + u;
-            ok[u] = p < np && flag[p] == 1;
+            ok[u] = false;
+            if (p < np && flag[p] == 1) {
+                const int64_t k = keys[p];
+                if (mmatch[pair_i(k)] || mmatch[pair_j(k)]) flag[p] = 0;
+                else ok[u] = true;
+            }
             cnt += ok[u] ? 1 : 0;
         }
         int tot;
@@ -1068,11 +1248,13 @@ hipError_t launch_resolve(const Workspace &ws, double *x, double *y, double *z, 
                           double f, int64_t *pairs, int64_t cap, int64_t *n_pairs_dev, int step,
                           int64_t *cursor, const unsigned long long *tests_part, int n_part,
                           hipStream_t s) {
-    const RankResolve RR = {x, y, z, vx, vy, vz, R, dt, ws.pair_dt, ws.pair_flag, ws.mmatch};
+    const RankResolve RR = {x, y, z, vx, vy, vz, R, dt, ws.pair_dt, ws.pair_flag, ws.mmatch,
+                            ws.mbest};
     k_rank_pairs<<<kRankGrid, kWave * kRankSplit, 0, s>>>(ws.st, ws.pairs_tmp, ws.pair_cap,
-                                                          ws.pairs_alt, tests_part, n_part, RR);
+                                                          ws.pairs_alt, tests_part, n_part, RR,
+                                                          RankReport{});
     // the unsorted list is no longer needed: its buffer holds the live pair indices
-    k_resolve<<<1, kResolveThreads, 0, s>>>(ws.st, ws.pairs_alt, ws.pair_cap, ws.pair_dt,
+    k_resolve<<<kResolveBlocks, kResolveThreads, 0, s>>>(ws.st, ws.pairs_alt, ws.pair_cap, ws.pair_dt,
                                             ws.pair_flag, ws.mbest, ws.mmatch,
                                             (int32_t *)ws.pairs_tmp, pairs, cap, n_pairs_dev,
                                             step, cursor);
@@ -1096,11 +1278,10 @@ hipError_t launch_collide_pairs(const Workspace &ws, int64_t n, double dt, bool 
 hipError_t launch_emit_pairs(const Workspace &ws, int64_t *pairs, int64_t cap,
                              int64_t *n_pairs_dev, int triple, int step, int64_t *cursor,
                              const unsigned long long *tests_part, int n_part, hipStream_t s) {
+    const RankReport RP = {pairs, cap, cursor, triple, step};
     k_rank_pairs<<<kRankGrid, kWave * kRankSplit, 0, s>>>(ws.st, ws.pairs_tmp, ws.pair_cap,
                                                           ws.pairs_alt, tests_part, n_part,
-                                                          RankResolve{});
-    k_emit_pairs<<<256, 256, 0, s>>>(ws.st, ws.pairs_alt, ws.pair_cap, pairs, cap, n_pairs_dev,
-                                     triple, step, cursor);
+                                                          RankResolve{}, RP);
     k_pairs_done<<<1, 64, 0, s>>>(ws.st, n_pairs_dev, cap, ws.pair_cap, triple, cursor);
     return hipGetLastError();
 }

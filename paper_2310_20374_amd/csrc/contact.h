@@ -34,11 +34,16 @@ __device__ __forceinline__ bool pair_test(double x1, double y1, double z1, doubl
     return contact_time(x1, y1, z1, vx1, vy1, vz1, R1, x2, y2, z2, vx2, vy2, vz2, R2, dt) >= 0.0;
 }
 
+// a pair's key: smaller index, larger index
+__device__ __forceinline__ int64_t pair_key(uint32_t ia, uint32_t ib) {
+    const uint32_t lo = ia < ib ? ia : ib, hi = ia < ib ? ib : ia;
+    return ((int64_t)lo << 32) | (int64_t)hi;
+}
+
 __device__ __forceinline__ void record(int64_t *out, int64_t cap, unsigned long long *count,
                                        uint32_t ia, uint32_t ib) {
-    uint32_t lo = ia < ib ? ia : ib, hi = ia < ib ? ib : ia;
-    unsigned long long k = atomicAdd(count, 1ull);
-    if ((int64_t)k < cap) out[k] = ((int64_t)lo << 32) | (int64_t)hi;
+    const unsigned long long k = atomicAdd(count, 1ull);
+    if ((int64_t)k < cap) out[k] = pair_key(ia, ib);
 }
 
 }  // namespace ncorp

@@ -112,7 +112,7 @@ constexpr int kMaxDisks = NCORP_MAX_DISKS;
 // Device-side counters of one tree / walk, kept in the workspace.
 struct DevState {
     int32_t status;            // StatusBits, latched
-    int32_t pad0;
+    int32_t resolve_done;      // blocks of the matching's first round that have finished
     int64_t required;          // size that would have sufficed for an overflow
     // tree
     int32_t ncells, nleaves, maxlevel, pad1;
