@@ -1,4 +1,5 @@
-// Bucket sort of the (Hilbert key, input index) pairs of a plain tree build.
+// Bucket sort of the (Hilbert key, input index) pairs of a tree build; in batched calls
+// of (disk, key, index), the disk of a pair looked up by its index.
 //
 // From one step to the next the moonlets move little against the tree, so the order
 // of the previous step is nearly the order of this one (Sect. 3.4.6).  The sort uses
@@ -22,7 +23,8 @@
 //
 // A small sort is a chain of short launches, so few buckets take three of them: count
 // (forming the boundaries), scatter (adding up the counts), local.  2000 moonlets: 38 -> 24
-// us, 1e5: 44 -> 35 us, 1e6 (with the boundaries and the row scan): 81 -> 84 us.
+// us, 1e5: 44 -> 35 us, 1e6 (with the boundaries and the row scan): 81 -> 84 us; 64 disks
+// of 12324 moonlets by nine radix passes 198 us, here 76 us.
 #include "ncorp_internal.h"
 
 namespace ncorp {
@@ -38,8 +40,17 @@ constexpr int kBsSampleMax = 8192;     // fewer per bucket beyond 2048 buckets
 constexpr uint64_t kKeySentinel = ~0ull;  // above every 63-bit key
 static_assert(kMaxBuckets <= kBsSampleMax, "at least one sample per bucket");
 
-__device__ __forceinline__ bool pair_less(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib) {
-    return ka < kb || (ka == kb && ia < ib);
+// order of two pairs of disks da, db (0 in plain calls)
+__device__ __forceinline__ bool pair_less(uint32_t da, uint64_t ka, uint32_t ia, uint32_t db,
+                                          uint64_t kb, uint32_t ib) {
+    return da < db || (da == db && (ka < kb || (ka == kb && ia < ib)));
+}
+
+// disk of the pair of input index i; the kernels come with SEG (batched calls) and
+// without, where the disks fold away
+template <bool SEG>
+__device__ __forceinline__ uint32_t disk_of(const uint16_t *__restrict__ seg, uint32_t i) {
+    return SEG ? (uint32_t)seg[i] : 0u;
 }
 
 __device__ __forceinline__ uint64_t bs_lanemask_lt() {
@@ -47,16 +58,25 @@ __device__ __forceinline__ uint64_t bs_lanemask_lt() {
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-// number of boundaries (sk, si)[0..m) that are <= (k, i)
-__device__ __forceinline__ int bucket_of(const uint64_t *sk, const uint32_t *si, int m,
-                                         uint64_t k, uint32_t i) {
+// number of boundaries (sd, sk, si)[0..m) that are <= (d, k, i)
+template <bool SEG>
+__device__ __forceinline__ int bucket_of(const uint16_t *sd, const uint64_t *sk,
+                                         const uint32_t *si, int m, uint32_t d, uint64_t k,
+                                         uint32_t i) {
     int lo = 0, hi = m;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (pair_less(k, i, sk[mid], si[mid])) hi = mid;
+        if (pair_less(d, k, i, SEG ? sd[mid] : 0, sk[mid], si[mid])) hi = mid;
         else lo = mid + 1;
     }
     return lo;
+}
+
+// Are the last sort's boundaries in this sort's order?  Those of a plain build also are
+// in a batched one (all of disk 0), not the other way round.
+template <bool SEG>
+__device__ __forceinline__ bool prev_in_order(const DevState *st) {
+    return SEG ? st->bs_valid != 0 : st->bs_valid == 1;
 }
 
 __device__ __forceinline__ int pow2_at_least(int v) {
@@ -88,10 +108,10 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wsum, uint3
     return before + x - v;
 }
 
-// Ascending bitonic sort of (sk, si)[0..P), P a power of two, by a block of NT
+// Ascending bitonic sort of (sd, sk, si)[0..P), P a power of two, by a block of NT
 // threads (used on the sample only).
-template <int NT>
-__device__ void bitonic_lds(uint64_t *sk, uint32_t *si, int P) {
+template <int NT, bool SEG>
+__device__ void bitonic_lds(uint16_t *sd, uint64_t *sk, uint32_t *si, int P) {
     const int half = P >> 1;
     __syncthreads();
     for (int k = 2; k <= P; k <<= 1) {
@@ -101,9 +121,11 @@ __device__ void bitonic_lds(uint64_t *sk, uint32_t *si, int P) {
                 const int b = a + j;
                 const uint64_t ka = sk[a], kb = sk[b];
                 const uint32_t ia = si[a], ib = si[b];
-                if (pair_less(kb, ib, ka, ia) == ((a & k) == 0)) {
+                const uint16_t da = SEG ? sd[a] : 0, db = SEG ? sd[b] : 0;
+                if (pair_less(db, kb, ib, da, ka, ia) == ((a & k) == 0)) {
                     sk[a] = kb; si[a] = ib;
                     sk[b] = ka; si[b] = ia;
+                    if (SEG) { sd[a] = db; sd[b] = da; }
                 }
             }
             __syncthreads();
@@ -116,12 +138,14 @@ __device__ void bitonic_lds(uint64_t *sk, uint32_t *si, int P) {
 // and root cube) and a sample of this build's keys spreads over them without piling
 // up (no bucket draws more than four times its share of the sample, plus four), else
 // those of the sorted sample.  Clears the spill count of this sort.
+template <bool SEG>
 __global__ void __launch_bounds__(1024)
 k_bs_splitters(DevState *st, const uint64_t *__restrict__ keys, const uint32_t *__restrict__ idx,
-               int n, int nb, int prev_ok, const SplitKey *__restrict__ prev,
+               const uint16_t *__restrict__ seg, int n, int nb, int prev_ok, const SplitKey *__restrict__ prev,
                SplitKey *__restrict__ split) {
     __shared__ uint64_t sk[kBsSampleMax];
     __shared__ uint32_t si[kBsSampleMax];
+    __shared__ uint16_t sd[SEG ? kBsSampleMax : 1];
     __shared__ uint32_t cnt[kMaxBuckets];
     __shared__ int bad;
     const int tid = threadIdx.x;
@@ -134,18 +158,19 @@ k_bs_splitters(DevState *st, const uint64_t *__restrict__ keys, const uint32_t *
         return;
     }
     const int S = nb * kBsSamplesPer < kBsSampleMax ? nb * kBsSamplesPer : kBsSampleMax;
-    const bool use_prev = prev_ok && st->bs_valid && st->bs_n == n && st->bs_L == st->L;
+    const bool use_prev = prev_ok && prev_in_order<SEG>(st) && st->bs_n == n && st->bs_L == st->L;
     if (use_prev) {
         for (int j = tid; j < nb - 1; j += blockDim.x) {
             sk[j] = prev[j].k;
             si[j] = prev[j].i;
+            if (SEG) sd[j] = (uint16_t)prev[j].d;
         }
         for (int b = tid; b < nb; b += blockDim.x) cnt[b] = 0;
         if (tid == 0) bad = 0;
         __syncthreads();
         for (int s0 = tid; s0 < S; s0 += 4 * (int)blockDim.x) {
             uint64_t k[4];
-            uint32_t x[4];
+            uint32_t x[4], d[4];
 #pragma unroll
             for (int u = 0; u < 4; u++) {
                 const int s = s0 + u * (int)blockDim.x;
@@ -153,12 +178,13 @@ k_bs_splitters(DevState *st, const uint64_t *__restrict__ keys, const uint32_t *
                     const int p = (int)((int64_t)s * n / S);
                     k[u] = keys[p];
                     x[u] = idx[p];
+                    d[u] = disk_of<SEG>(seg, x[u]);
                 }
             }
 #pragma unroll
             for (int u = 0; u < 4; u++)
                 if (s0 + u * (int)blockDim.x < S)
-                    atomicAdd(&cnt[bucket_of(sk, si, nb - 1, k[u], x[u])], 1u);
+                    atomicAdd(&cnt[bucket_of<SEG>(sd, sk, si, nb - 1, d[u], k[u], x[u])], 1u);
         }
         __syncthreads();
         for (int b = tid; b < nb; b += blockDim.x)
@@ -177,18 +203,20 @@ k_bs_splitters(DevState *st, const uint64_t *__restrict__ keys, const uint32_t *
             const int p = (int)((int64_t)s * n / S);
             sk[s] = keys[p];
             si[s] = idx[p];
+            if (SEG) sd[s] = seg[si[s]];
         } else {
             sk[s] = kKeySentinel;
             si[s] = ~0u;
+            if (SEG) sd[s] = 0xffffu;
         }
     }
-    bitonic_lds<1024>(sk, si, P);
+    bitonic_lds<1024, SEG>(sd, sk, si, P);
     for (int b = 1 + tid; b < nb; b += blockDim.x) {
         const int s = (int)((int64_t)b * S / nb);
         SplitKey v;
         v.k = sk[s];
         v.i = si[s];
-        v.pad = 0;
+        v.d = SEG ? sd[s] : 0;
         split[b - 1] = v;
     }
     if (tid == 0) st->bs_prev_used = 0;
@@ -203,15 +231,18 @@ constexpr int kOwnBuckets = kBsThreads / kBsSamplesPer;
 struct OwnLds {
     uint64_t k[kBsThreads];
     uint32_t i[kBsThreads];
+    uint16_t d[kBsThreads];
     int bad;
 };
 
-// fills sk, si (nb - 1 boundaries); cnt: nb words of scratch; the same in every block
+// fills sk, si, sd (nb - 1 boundaries); cnt: nb words of scratch; the same in every block
+template <bool SEG>
 __device__ __forceinline__ void own_boundaries(DevState *st, const uint64_t *__restrict__ keys,
-                                               const uint32_t *__restrict__ idx, int n, int nb,
+                                               const uint32_t *__restrict__ idx,
+                                               const uint16_t *__restrict__ seg, int n, int nb,
                                                int prev_ok, const SplitKey *__restrict__ prev,
-                                               uint64_t *sk, uint32_t *si, uint32_t *cnt,
-                                               OwnLds &O) {
+                                               uint64_t *sk, uint32_t *si, uint16_t *sd,
+                                               uint32_t *cnt, OwnLds &O) {
     const int tid = threadIdx.x;
     const bool publish = blockIdx.x == 0 && tid == 0;
     if (publish) {
@@ -224,21 +255,23 @@ __device__ __forceinline__ void own_boundaries(DevState *st, const uint64_t *__r
     }
     const int S = nb * kBsSamplesPer;                    // <= kBsThreads
     uint64_t k = kKeySentinel;
-    uint32_t x = ~0u;
+    uint32_t x = ~0u, d = SEG ? 0xffffu : 0u;
     if (tid < S) {
         const int p = (int)((int64_t)tid * n / S);
         k = keys[p];
         x = idx[p];
+        d = disk_of<SEG>(seg, x);
     }
-    if (prev_ok && st->bs_valid && st->bs_n == n && st->bs_L == st->L) {
+    if (prev_ok && prev_in_order<SEG>(st) && st->bs_n == n && st->bs_L == st->L) {
         for (int j = tid; j < nb - 1; j += kBsThreads) {
             sk[j] = prev[j].k;
             si[j] = prev[j].i;
+            if (SEG) sd[j] = (uint16_t)prev[j].d;
         }
         for (int b = tid; b < nb; b += kBsThreads) cnt[b] = 0;
         if (tid == 0) O.bad = 0;
         __syncthreads();
-        if (tid < S) atomicAdd(&cnt[bucket_of(sk, si, nb - 1, k, x)], 1u);
+        if (tid < S) atomicAdd(&cnt[bucket_of<SEG>(sd, sk, si, nb - 1, d, k, x)], 1u);
         __syncthreads();
         for (int b = tid; b < nb; b += kBsThreads)
             if (cnt[b] > (uint32_t)((4 * S + 4 * nb) / nb)) O.bad = 1;
@@ -250,11 +283,13 @@ __device__ __forceinline__ void own_boundaries(DevState *st, const uint64_t *__r
     }
     O.k[tid] = k;
     O.i[tid] = x;
-    bitonic_lds<kBsThreads>(O.k, O.i, pow2_at_least(S));
+    O.d[tid] = (uint16_t)d;
+    bitonic_lds<kBsThreads, SEG>(O.d, O.k, O.i, pow2_at_least(S));
     for (int b = 1 + tid; b < nb; b += kBsThreads) {
         const int at = (int)((int64_t)b * S / nb);
         sk[b - 1] = O.k[at];
         si[b - 1] = O.i[at];
+        if (SEG) sd[b - 1] = O.d[at];
     }
     if (publish) st->bs_prev_used = 0;
 }
@@ -263,40 +298,44 @@ __device__ __forceinline__ void own_boundaries(DevState *st, const uint64_t *__r
 // column `tile` of the bucket-major count matrix).  LDS: boundary keys and indices,
 // one counter per bucket.  OWN: the boundaries formed here (from prev, if prev_ok)
 // instead of read from split.
-template <bool OWN>
+template <bool OWN, bool SEG>
 __global__ void __launch_bounds__(kBsThreads)
 k_bs_count(DevState *st, const uint64_t *__restrict__ keys, const uint32_t *__restrict__ idx,
-           int n, int nb, int ntiles, int prev_ok, const SplitKey *__restrict__ prev,
+           const uint16_t *__restrict__ seg, int n, int nb, int ntiles, int prev_ok, const SplitKey *__restrict__ prev,
            const SplitKey *__restrict__ split, uint32_t *__restrict__ bkt,
            uint32_t *__restrict__ cm) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint64_t *sk = reinterpret_cast<uint64_t *>(smem);
     uint32_t *si = reinterpret_cast<uint32_t *>(sk + nb);
     uint32_t *cnt = si + nb;
+    uint16_t *sd = reinterpret_cast<uint16_t *>(cnt + nb);        // [nb] (SEG)
     const int tid = threadIdx.x;
     if constexpr (OWN) {
         __shared__ OwnLds O;
-        own_boundaries(st, keys, idx, n, nb, prev_ok, prev, sk, si, cnt, O);
+        own_boundaries<SEG>(st, keys, idx, seg, n, nb, prev_ok, prev, sk, si, sd, cnt, O);
         __syncthreads();
     } else {
         for (int j = tid; j < nb - 1; j += kBsThreads) {
             sk[j] = split[j].k;
             si[j] = split[j].i;
+            if (SEG) sd[j] = (uint16_t)split[j].d;
         }
     }
     for (int b = tid; b < nb; b += kBsThreads) cnt[b] = 0;
     __syncthreads();
     const int base = blockIdx.x * kBucketTile;
     uint64_t k[kBsItems];
-    uint32_t x[kBsItems];
+    uint32_t x[kBsItems], d[kBsItems];
 #pragma unroll
     for (int r = 0; r < kBsItems; r++) {
         const int i = base + r * kBsThreads + tid;
         k[r] = 0;
         x[r] = 0;
+        d[r] = 0;
         if (i < n) {
             k[r] = keys[i];
             x[r] = idx[i];
+            d[r] = disk_of<SEG>(seg, x[r]);
         }
     }
     // all items' searches advance together: one step per level, count of boundaries
@@ -311,7 +350,8 @@ k_bs_count(DevState *st, const uint64_t *__restrict__ keys, const uint32_t *__re
 #pragma unroll
         for (int r = 0; r < kBsItems; r++) {
             const int c = lo[r] + step;
-            if (c <= m && !pair_less(k[r], x[r], sk[c - 1], si[c - 1])) lo[r] = c;
+            if (c <= m && !pair_less(d[r], k[r], x[r], SEG ? sd[c - 1] : 0, sk[c - 1], si[c - 1]))
+                lo[r] = c;
         }
     }
 #pragma unroll
@@ -511,6 +551,7 @@ struct LocalLds {
     uint32_t wsum[kBsLocalWaves];
     uint64_t wmin[kBsLocalWaves], wmax[kBsLocalWaves];
     int crowded;
+    int dmin, dmax;                          // disks of the bucket (batched)
 };
 
 // the fast local sort (previous order): threads per bucket, most pairs per bucket
@@ -524,8 +565,10 @@ struct SubLds {
     uint32_t v[kFastCap];
     uint8_t sb[kFastCap];                    // sub-range of each placed pair
     uint32_t start[kSubPer + 2], cur[kSubPer + 1];
+    uint16_t d[kFastCap];                    // disk of each placed pair (batched)
     uint64_t bk[kSubPer];                    // finer boundaries of the bucket
     uint32_t bi[kSubPer];
+    uint16_t bd[kSubPer];
     uint32_t wsum[kFastThreads / kWave];
     int crowded;
 };
@@ -582,7 +625,9 @@ __device__ __forceinline__ void load_local(const uint64_t *kin, const uint32_t *
 // sub-range below it by (key, index).  Writes (kout, vout) and returns true, or
 // writes nothing and returns false when some sub-range holds more than kSubLimit
 // pairs (moonlets moved far).
+template <bool SEG>
 __device__ __forceinline__ bool subsplit_sort_local(const uint64_t *kin, const uint32_t *vin,
+                                                    const uint16_t *__restrict__ seg,
                                                     int size, const SplitKey *subs, int nsub,
                                                     uint64_t *kout, uint32_t *vout, SubLds &L) {
     const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
@@ -594,11 +639,12 @@ __device__ __forceinline__ bool subsplit_sort_local(const uint64_t *kin, const u
     for (int q = t; q < m; q += kFastThreads) {
         L.bk[q] = subs[q + 1].k;
         L.bi[q] = subs[q + 1].i;
+        if (SEG) L.bd[q] = (uint16_t)subs[q + 1].d;
     }
     for (int q = t; q <= m; q += kFastThreads) start[q] = 0;
     if (t == 0) L.crowded = 0;
     uint64_t key[kFastRounds];
-    uint32_t val[kFastRounds];
+    uint32_t val[kFastRounds], d[kFastRounds];
     bool valid[kFastRounds];
     int sb[kFastRounds];
 #pragma unroll
@@ -607,10 +653,12 @@ __device__ __forceinline__ bool subsplit_sort_local(const uint64_t *kin, const u
         valid[r] = r < R && p < size;
         key[r] = 0;
         val[r] = 0;
+        d[r] = 0;
         sb[r] = 0;
         if (valid[r]) {
             key[r] = kin[p];
             val[r] = vin[p];
+            d[r] = disk_of<SEG>(seg, val[r]);
         }
     }
     __syncthreads();
@@ -620,7 +668,9 @@ __device__ __forceinline__ bool subsplit_sort_local(const uint64_t *kin, const u
 #pragma unroll
         for (int r = 0; r < kFastRounds; r++) {
             const int c = sb[r] + step;
-            if (c <= m && !pair_less(key[r], val[r], L.bk[c - 1], L.bi[c - 1])) sb[r] = c;
+            if (c <= m && !pair_less(d[r], key[r], val[r], SEG ? L.bd[c - 1] : 0, L.bk[c - 1],
+                                     L.bi[c - 1]))
+                sb[r] = c;
         }
     }
 #pragma unroll
@@ -645,15 +695,17 @@ __device__ __forceinline__ bool subsplit_sort_local(const uint64_t *kin, const u
             L.k[slot] = key[r];
             L.v[slot] = val[r];
             L.sb[slot] = (uint8_t)sb[r];
+            if (SEG) L.d[slot] = (uint16_t)d[r];
         }
     __syncthreads();
     for (int j = t; j < size; j += kFastThreads) {
         const uint64_t kj = L.k[j];
-        const uint32_t vj = L.v[j];
+        const uint32_t vj = L.v[j], dj = SEG ? L.d[j] : 0;
         const int q = L.sb[j];
         const int s0 = (int)start[q], s1 = (int)start[q + 1];
         int rank = 0;
-        for (int u = s0; u < s1; u++) rank += pair_less(L.k[u], L.v[u], kj, vj) ? 1 : 0;
+        for (int u = s0; u < s1; u++)
+            rank += pair_less(SEG ? L.d[u] : 0, L.k[u], L.v[u], dj, kj, vj) ? 1 : 0;
         kout[s0 + rank] = kj;
         vout[s0 + rank] = vj;
     }
@@ -712,7 +764,7 @@ __device__ __forceinline__ bool onepass_sort_local(const uint64_t *kin, const ui
         const uint32_t sb = (uint32_t)((kj - kmin) >> sh);
         const int s0 = (int)start[sb], s1 = (int)start[sb + 1];
         int rank = 0;
-        for (int q = s0; q < s1; q++) rank += pair_less(L.k[q], L.v[q], kj, vj) ? 1 : 0;
+        for (int q = s0; q < s1; q++) rank += pair_less(0, L.k[q], L.v[q], 0, kj, vj) ? 1 : 0;
         kout[s0 + rank] = kj;
         vout[s0 + rank] = vj;
     }
@@ -737,9 +789,10 @@ __device__ __forceinline__ uint64_t digit_peers(uint32_t d, uint64_t act) {
 // lane l at w Q + 64 r + l.  Per pass: the lanes sharing a digit in a round (ballots)
 // are counted once by their lowest lane; after the prefix over waves and digits each
 // lane's place is its digit's start, the wave's earlier rounds and its rank among
-// those lanes.
+// those lanes.  SEG: then over the bits of the disk - (smallest disk), L.dmin .. L.dmax.
+template <bool SEG>
 __device__ __forceinline__ void radix_sort_local(const uint64_t *kin, const uint32_t *vin,
-                                                 int size, uint64_t *kout, uint32_t *vout,
+                                                 const uint16_t *__restrict__ seg, int size, uint64_t *kout, uint32_t *vout,
                                                  LocalLds &L) {
     const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
     const int R = (size + kBsLocalThreads - 1) / kBsLocalThreads;
@@ -752,11 +805,21 @@ __device__ __forceinline__ void radix_sort_local(const uint64_t *kin, const uint
     load_local(kin, vin, size, key, val, valid, kmin, kmax, L);
     const uint64_t span = kmax - kmin;
     const int nbits = span ? 64 - __clzll((long long)span) : 0;
-    const int passes = (nbits + 7) / 8;
+    const int kpasses = (nbits + 7) / 8;
+    const uint32_t dmin = SEG ? (uint32_t)L.dmin : 0u;
+    int passes = kpasses;
+    if (SEG) {
+        const uint32_t dspan = (uint32_t)(L.dmax - L.dmin);
+        passes += dspan == 0 ? 0 : (dspan < 256 ? 1 : 2);
+    }
+    auto digit = [&](int pass, uint64_t key, uint32_t val) {
+        if (SEG && pass >= kpasses)
+            return ((uint32_t)seg[val] - dmin) >> (8 * (pass - kpasses)) & 255u;
+        return (uint32_t)(key >> (8 * pass)) & 255u;
+    };
 #pragma unroll
     for (int r = 0; r < kBsRounds; r++) key[r] -= kmin;
     for (int pass = 0; pass < passes; pass++) {
-        const int shift = 8 * pass;
         if (t < 256)
 #pragma unroll
             for (int k = 0; k < kBsLocalWaves; k++) L.aux[k * 256 + t] = 0;
@@ -767,7 +830,7 @@ __device__ __forceinline__ void radix_sort_local(const uint64_t *kin, const uint
             const uint64_t act = __ballot(valid[r]);
             peers[r] = 0;
             if (act != 0ull) {
-                const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
+                const uint32_t d = valid[r] ? digit(pass, key[r], val[r]) : 0u;
                 peers[r] = digit_peers(d, act);
                 if (valid[r] && (peers[r] & lt) == 0ull)
                     atomicAdd(&L.aux[w * 256 + d], (uint32_t)__popcll(peers[r]));
@@ -791,7 +854,7 @@ __device__ __forceinline__ void radix_sort_local(const uint64_t *kin, const uint
 #pragma unroll
         for (int r = 0; r < kBsRounds; r++) {
             if (valid[r]) {
-                const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
+                const uint32_t d = digit(pass, key[r], val[r]);
                 const uint64_t lower = peers[r] & lt;
                 const uint32_t before = L.aux[w * 256 + d];
                 const uint32_t pos = L.dstart[d] + before + (uint32_t)__popcll(lower);
@@ -826,13 +889,15 @@ __device__ __forceinline__ void radix_sort_local(const uint64_t *kin, const uint
     __syncthreads();
 }
 
-// number of pairs in (ka, ia)[lo..hi) that are below (k, i)
-__device__ __forceinline__ int count_below(const uint64_t *ka, const uint32_t *ia, int lo, int hi,
-                                           uint64_t k, uint32_t i) {
+// number of pairs in (ka, ia)[lo..hi) that are below (d, k, i)
+template <bool SEG>
+__device__ __forceinline__ int count_below(const uint64_t *ka, const uint32_t *ia,
+                                           const uint16_t *__restrict__ seg, int lo, int hi,
+                                           uint32_t d, uint64_t k, uint32_t i) {
     const int lo0 = lo;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (pair_less(ka[mid], ia[mid], k, i)) lo = mid + 1;
+        if (pair_less(disk_of<SEG>(seg, ia[mid]), ka[mid], ia[mid], d, k, i)) lo = mid + 1;
         else hi = mid;
     }
     return lo - lo0;
@@ -840,8 +905,9 @@ __device__ __forceinline__ int count_below(const uint64_t *ka, const uint32_t *i
 
 // The next build's boundaries from this sorted bucket [o, o + size): the pairs at
 // ranks j kBucketMean (1 <= j < nb) and at ranks k kSubStride.
-template <int NT>
-__device__ __forceinline__ void write_boundaries(const uint64_t *keys, const uint32_t *idx, int o,
+template <int NT, bool SEG>
+__device__ __forceinline__ void write_boundaries(const uint64_t *keys, const uint32_t *idx,
+                                                 const uint16_t *__restrict__ seg, int o,
                                                  int size, int nb, SplitKey *next,
                                                  SplitKey *subn) {
     const int tid = threadIdx.x;
@@ -851,7 +917,7 @@ __device__ __forceinline__ void write_boundaries(const uint64_t *keys, const uin
         SplitKey v;
         v.k = keys[p];
         v.i = idx[p];
-        v.pad = 0;
+        v.d = disk_of<SEG>(seg, v.i);
         next[j - 1] = v;
     }
     const int q0 = (o + kSubStride - 1) / kSubStride;
@@ -860,7 +926,7 @@ __device__ __forceinline__ void write_boundaries(const uint64_t *keys, const uin
         SplitKey v;
         v.k = keys[p];
         v.i = idx[p];
-        v.pad = 0;
+        v.d = disk_of<SEG>(seg, v.i);
         subn[q] = v;
     }
 }
@@ -873,8 +939,10 @@ __device__ __forceinline__ void write_boundaries(const uint64_t *keys, const uin
 // stores its share of the next build's boundaries.  LDS: SubLds or LocalLds (dynamic).
 // One kernel for all: with the finer boundaries in a kernel of their own the second
 // launch found nothing left to do and still took 4 to 5 us.
+template <bool SEG>
 __global__ void __launch_bounds__(kBsLocalThreads)
-k_bs_local(DevState *st, const uint32_t *__restrict__ off, int nb, int n,
+k_bs_local(DevState *st, const uint32_t *__restrict__ off, const uint16_t *__restrict__ seg,
+           int nb, int n,
            uint64_t *__restrict__ keys, uint32_t *__restrict__ idx, uint64_t *__restrict__ kalt,
            uint32_t *__restrict__ ialt, SplitKey *__restrict__ next, SplitKey *sub0,
            SplitKey *sub1) {
@@ -886,7 +954,7 @@ k_bs_local(DevState *st, const uint32_t *__restrict__ off, int nb, int n,
     const int rd = st->bs_sub_rd;
     SplitKey *subn = rd ? sub0 : sub1;
     if (b == 0 && tid == 0) {
-        st->bs_valid = 1;
+        st->bs_valid = SEG ? 2 : 1;
         st->bs_n = n;
         st->bs_L = st->L;
         st->bs_sub_wr = 1 - rd;
@@ -897,27 +965,42 @@ k_bs_local(DevState *st, const uint32_t *__restrict__ off, int nb, int n,
     if (st->bs_prev_used && size <= kFastCap) {
         const int ntot = (n + kSubStride - 1) / kSubStride;
         const int nsub = ntot - b * kSubPer < kSubPer ? ntot - b * kSubPer : kSubPer;
-        if (subsplit_sort_local(keys + o, idx + o, size, (rd ? sub1 : sub0) + (int64_t)b * kSubPer,
+        if (subsplit_sort_local<SEG>(keys + o, idx + o, seg, size, (rd ? sub1 : sub0) + (int64_t)b * kSubPer,
                                 nsub, keys + o, idx + o, *reinterpret_cast<SubLds *>(smem))) {
             __threadfence_block();
             __syncthreads();
-            write_boundaries<kBsLocalThreads>(keys, idx, o, size, nb, next, subn);
+            write_boundaries<kBsLocalThreads, SEG>(keys, idx, seg, o, size, nb, next, subn);
             return;
         }
         __syncthreads();                     // the other sorts reuse the LDS
     }
+    if (SEG) {                               // the range of the bucket's disks
+        if (tid == 0) { L.dmin = 0xffff; L.dmax = 0; }
+        __syncthreads();
+        int lo = 0xffff, hi = 0;
+        for (int q = tid; q < size; q += kBsLocalThreads) {
+            const int d = (int)seg[idx[o + q]];
+            lo = d < lo ? d : lo;
+            hi = d > hi ? d : hi;
+        }
+        atomicMin(&L.dmin, lo);
+        atomicMax(&L.dmax, hi);
+        __syncthreads();
+    }
     if (size <= kBucketLDS) {
-        if (!onepass_sort_local(keys + o, idx + o, size, keys + o, idx + o, L))
-            radix_sort_local(keys + o, idx + o, size, keys + o, idx + o, L);
+        const bool one_disk = !SEG || L.dmin == L.dmax;
+        if (!one_disk || !onepass_sort_local(keys + o, idx + o, size, keys + o, idx + o, L))
+            radix_sort_local<SEG>(keys + o, idx + o, seg, size, keys + o, idx + o, L);
         __threadfence_block();
         __syncthreads();
-        write_boundaries<kBsLocalThreads>(keys, idx, o, size, nb, next, subn);
+        write_boundaries<kBsLocalThreads, SEG>(keys, idx, seg, o, size, nb, next, subn);
         return;
     }
     // batches of kBucketLDS, sorted, into the alternate buffers
     for (int c0 = 0; c0 < size; c0 += kBucketLDS) {
         const int len = size - c0 < kBucketLDS ? size - c0 : kBucketLDS;
-        radix_sort_local(keys + o + c0, idx + o + c0, len, kalt + o + c0, ialt + o + c0, L);
+        radix_sort_local<SEG>(keys + o + c0, idx + o + c0, seg, len, kalt + o + c0, ialt + o + c0,
+                              L);
     }
     __threadfence_block();
     __syncthreads();
@@ -932,9 +1015,10 @@ k_bs_local(DevState *st, const uint32_t *__restrict__ off, int nb, int n,
             const int b1 = s0 + 2 * w < size ? s0 + 2 * w : size;
             const uint64_t k = sk_src[o + q];
             const uint32_t i = si_src[o + q];
-            int pos;
-            if (q < a1) pos = (q - s0) + count_below(sk_src + o, si_src + o, a1, b1, k, i);
-            else pos = (q - a1) + count_below(sk_src + o, si_src + o, s0, a1, k, i);
+            const uint32_t d = disk_of<SEG>(seg, i);
+            const int pos =
+                q < a1 ? (q - s0) + count_below<SEG>(sk_src + o, si_src + o, seg, a1, b1, d, k, i)
+                       : (q - a1) + count_below<SEG>(sk_src + o, si_src + o, seg, s0, a1, d, k, i);
             sk_dst[o + s0 + pos] = k;
             si_dst[o + s0 + pos] = i;
         }
@@ -951,32 +1035,32 @@ k_bs_local(DevState *st, const uint32_t *__restrict__ off, int nb, int n,
         __threadfence_block();
         __syncthreads();
     }
-    write_boundaries<kBsLocalThreads>(keys, idx, o, size, nb, next, subn);
+    write_boundaries<kBsLocalThreads, SEG>(keys, idx, seg, o, size, nb, next, subn);
 }
 
 // ------------------------------------------------------------------ host side
 static int64_t n_buckets(int64_t n) { return (n + kBucketMean - 1) / kBucketMean; }
 
 bool bucket_sort_applies(const Workspace &ws, int64_t n) {
-    return ws.ndisks <= 1 && n_buckets(n) <= kMaxBuckets && ws.bs_split != nullptr;
+    return n_buckets(n) <= kMaxBuckets && ws.bs_split != nullptr;
 }
 
-// launch_keys wrote the pairs to keys_alt / idx_alt; the result lands in keys / idx
-hipError_t launch_bucket_sort(const Workspace &ws, int64_t n, hipStream_t s) {
+template <bool SEG>
+static void launch_bucket_sort_t(const Workspace &ws, int64_t n, hipStream_t s) {
     const int nb = (int)n_buckets(n);
     const int ntiles = (int)((n + kBucketTile - 1) / kBucketTile);
     const int prev_ok = ws.sort_prev ? 1 : 0;
-    const size_t lds = (size_t)nb * 16;
+    const size_t lds = (size_t)nb * (SEG ? 18 : 16);
     if (nb <= kOwnBuckets) {
-        k_bs_count<true><<<ntiles, kBsThreads, lds, s>>>(ws.st, ws.keys_alt, ws.idx_alt, (int)n,
-                                                         nb, ntiles, prev_ok, ws.bs_prev, nullptr,
-                                                         ws.code, ws.bs_cm);
+        k_bs_count<true, SEG><<<ntiles, kBsThreads, lds, s>>>(
+            ws.st, ws.keys_alt, ws.idx_alt, ws.seg, (int)n, nb, ntiles, prev_ok, ws.bs_prev, nullptr,
+            ws.code, ws.bs_cm);
     } else {
-        k_bs_splitters<<<1, 1024, 0, s>>>(ws.st, ws.keys_alt, ws.idx_alt, (int)n, nb, prev_ok,
-                                          ws.bs_prev, ws.bs_split);
-        k_bs_count<false><<<ntiles, kBsThreads, lds, s>>>(ws.st, ws.keys_alt, ws.idx_alt, (int)n,
-                                                          nb, ntiles, 0, nullptr, ws.bs_split,
-                                                          ws.code, ws.bs_cm);
+        k_bs_splitters<SEG><<<1, 1024, 0, s>>>(ws.st, ws.keys_alt, ws.idx_alt, ws.seg, (int)n, nb,
+                                               prev_ok, ws.bs_prev, ws.bs_split);
+        k_bs_count<false, SEG><<<ntiles, kBsThreads, lds, s>>>(
+            ws.st, ws.keys_alt, ws.idx_alt, ws.seg, (int)n, nb, ntiles, 0, nullptr, ws.bs_split,
+            ws.code, ws.bs_cm);
     }
     const bool add = (int64_t)nb * ntiles <= kAddCounts;
     if (!add) k_bs_rowscan<<<nb, kBsThreads, 0, s>>>(ws.st, ws.bs_cm, ntiles, ws.bs_total);
@@ -985,9 +1069,15 @@ hipError_t launch_bucket_sort(const Workspace &ws, int64_t n, hipStream_t s) {
         ws.st, ws.keys_alt, ws.idx_alt, ws.code, (int)n, nb, ntiles, ws.bs_cm, ws.bs_total,
         ws.bs_off, ws.keys, ws.idx);
     constexpr size_t local = sizeof(LocalLds) > sizeof(SubLds) ? sizeof(LocalLds) : sizeof(SubLds);
-    k_bs_local<<<nb, kBsLocalThreads, local, s>>>(ws.st, ws.bs_off, nb, (int)n, ws.keys, ws.idx,
-                                                  ws.keys_alt, ws.idx_alt, ws.bs_prev,
-                                                  ws.bs_sub[0], ws.bs_sub[1]);
+    k_bs_local<SEG><<<nb, kBsLocalThreads, local, s>>>(ws.st, ws.bs_off, ws.seg, nb, (int)n, ws.keys,
+                                                       ws.idx, ws.keys_alt, ws.idx_alt, ws.bs_prev,
+                                                       ws.bs_sub[0], ws.bs_sub[1]);
+}
+
+// launch_keys wrote the pairs to keys_alt / idx_alt; the result lands in keys / idx
+hipError_t launch_bucket_sort(const Workspace &ws, int64_t n, hipStream_t s) {
+    if (ws.ndisks > 1) launch_bucket_sort_t<true>(ws, n, s);
+    else launch_bucket_sort_t<false>(ws, n, s);
     return hipGetLastError();
 }
 

@@ -53,7 +53,7 @@ enum StatusBits : int32_t {
 // then do nothing rather than follow indices that were never written.
 // items per tile of the radix sort's passes (the workspace sizes its histograms by it)
 constexpr int kSortTileItems = 2048;
-// bucket sort of a plain tree build: buckets of kBucketMean moonlets on average, a
+// bucket sort of a tree build: buckets of kBucketMean moonlets on average, a
 // bucket of up to kBucketLDS sorted in LDS by one block (larger ones in such chunks,
 // merged); at most kMaxBuckets buckets (more moonlets: the radix sort); the count and
 // scatter passes take kBucketTile moonlets per block
@@ -135,7 +135,7 @@ struct DevState {
     // collisions: the largest R + dt |v| of any moonlet (bit pattern of a double >= 0)
     unsigned long long reach_max;
     // bucket sort: the splitters the last bucket sort left for the next one are valid
-    // (bs_valid) for bs_n moonlets under root half-width bs_L (kept by the reset of a
+    // (bs_valid: 1, or 2 from a batched build) for bs_n moonlets under root half-width bs_L (kept by the reset of a
     // fresh build); the last sort took its buckets from them (bs_prev_used) and sorted
     // bs_spill buckets too large for one LDS batch by merging
     double bs_L;
@@ -146,10 +146,10 @@ struct DevState {
     int32_t bs_sub_wr, bs_sub_rd;
 };
 
-// a bucket boundary of the bucket sort: the (key, input index) pair that starts it
+// a bucket boundary of the bucket sort: the (disk, key, input index) that starts it
 struct SplitKey {
     uint64_t k;
-    uint32_t i, pad;
+    uint32_t i, d;             // d: its disk (batched calls)
 };
 
 // ---------------------------------------------------------------- mesh module
@@ -385,7 +385,7 @@ hipError_t launch_keys(const Workspace &ws, const double *x, const double *y,
                        const int64_t *disk_off, const double *m, double G, hipStream_t s,
                        bool max_ready = false);
 hipError_t launch_sort(const Workspace &ws, int64_t n, hipStream_t s);
-// plain builds of up to kMaxBuckets buckets use the bucket sort (launch_keys then
+// builds of up to kMaxBuckets buckets use the bucket sort (launch_keys then
 // writes where it starts)
 bool bucket_sort_applies(const Workspace &ws, int64_t n);
 hipError_t launch_bucket_sort(const Workspace &ws, int64_t n, hipStream_t s);
