@@ -646,7 +646,7 @@ static int gravity_impl(ncorp_ctx *c, const double *m, double *ax, double *ay, d
     }
     {
         PhaseTimer t(c, NCORP_PHASE_DESCENT, s);
-        HIPCHK(c, launch_l2l(ws, c->prm.p, c->prm.precision, c->prm.p2p_tile, s));
+        HIPCHK(c, launch_l2l(ws, c->prm.p, c->prm.precision, s));
     }
     {
         PhaseTimer t(c, NCORP_PHASE_P2P, s);

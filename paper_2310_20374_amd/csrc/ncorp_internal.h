@@ -416,8 +416,8 @@ hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_po
 hipError_t launch_count_interactions(const Workspace &ws, hipStream_t s);
 
 hipError_t launch_m2l(const Workspace &ws, int p, int precision, hipStream_t s);
-// also orders and splits the direct sums' lists, for launch_p2p with the same tile
-hipError_t launch_l2l(const Workspace &ws, int p, int precision, int tile, hipStream_t s);
+// also orders and splits the direct sums' lists
+hipError_t launch_l2l(const Workspace &ws, int p, int precision, hipStream_t s);
 hipError_t launch_p2p(const Workspace &ws, int64_t n, int precision, int tile, int tmax,
                       hipStream_t s);
 // acc4 non-null: the accelerations as one (ax, ay, az, 0) record per moonlet in

@@ -107,6 +107,17 @@ __device__ __forceinline__ void walk_totals(DevState *st, const int32_t *ctr,
     }
 }
 
+constexpr int kP2PSrc = kWave;      // source cells per batch, one per lane (prefix sums in LDS)
+
+// FP32 sums of a list are added up in strands, each by itself: a list of one batch is one
+// strand, a longer one has kLongSlots of them (or as many as it has batches), strand v
+// taking the batches v, v + kLongSlots, ...  A leaf's waves share its strands, so its sums
+// are rounded the same however many waves it has.
+__device__ __forceinline__ int list_strands(int len) {
+    const int nb = (len + kP2PSrc - 1) / kP2PSrc;
+    return nb < kLongSlots ? nb : kLongSlots;
+}
+
 // How many waves share a leaf's direct sums (up to kLongSlots): as many as it has shares
 // of about `quantum` moonlet interactions.  The chip holds some 6000 waves and an average
 // leaf has 15000 to 60000 interactions (s = 48 and 96), so a small tree's leaves are
@@ -114,9 +125,10 @@ __device__ __forceinline__ void walk_totals(DevState *st, const int32_t *ctr,
 // about 10 us of dependent loads before its first tile, hence the lower limit; in between
 // four interactions a leaf, and never so many that the heaviest leaves are left whole.
 // The rule knows its own tree only, so a disk's sums are the same in a batch and alone.
-// Unsplit -> split, direct sums alone: 9973 moonlets in 519 leaves 129 -> 46 us, 1e6 in
-// 2.7e4 FP32 582 -> 435 us; a quantum of 2048 instead for 1e5 in 2700: 88 -> 103 us.
+// Unsplit -> split, direct sums alone: 9973 moonlets in 519 leaves (FP64) 129 -> 46 us, 1e6
+// in 2.7e4 FP32 582 -> 433 us; a quantum of 2048 instead for 1e5 in 2700: 88 -> 103 us.
 constexpr int64_t kQuantumMin = 2048, kQuantumMax = 49152;
+constexpr uint32_t kListed = 0x100;     // a leaf's slots: it is in the list
 struct SplitArgs {
     const int32_t *p2p_cnt, *c_count, *c_first, *c_nent;
     const uint16_t *seg;                 // batched: disk of every tree position, else nullptr
@@ -125,21 +137,25 @@ struct SplitArgs {
     int32_t *longs;                      // leaves whose list is beyond one LDS batch
     int32_t *split;                      // slots (leaf | slot << 24) of the leaves with more
     int64_t split_cap;                   // than one or a long list, and room for them
-    int unit;                            // source moonlets handed out at a time
+    bool fp32;
 };
 __device__ __forceinline__ void split_leaf(DevState *st, const SplitArgs &S, int e, int c) {
     const int64_t src = S.src[e];
     const int K = S.seg ? S.c_nent[S.disk_root[S.seg[S.c_first[c]]]] : st->nleaves;
     int64_t quantum = 4 * (int64_t)K;
     quantum = quantum < kQuantumMin ? kQuantumMin : (quantum > kQuantumMax ? kQuantumMax : quantum);
-    int64_t slots = (src * S.c_count[c] + quantum / 2) / quantum;
-    const int64_t units = (src + S.unit - 1) / S.unit;
+    const int64_t work = src * S.c_count[c];
+    int64_t slots = (work + quantum / 2) / quantum;
+    // what there is to hand out: in FP32 the strands of every chunk of 64 targets, in FP64 64
+    // source moonlets at a time
+    const int64_t units = S.fp32 ? list_strands(S.p2p_cnt[e]) *
+                                       (int64_t)((S.c_count[c] + kWave - 1) / kWave)
+                                 : (src + kWave - 1) / kWave;
     slots = slots < units ? slots : units;
     int64_t most = S.split_cap / st->nleaves;
     most = most > kLongSlots ? kLongSlots : most;
     slots = slots > most ? most : slots;
     slots = slots < 1 ? 1 : slots;
-    S.src[e] = (uint32_t)slots;
     // one atomic per wave for the list's length
     const bool lng = S.p2p_cnt[e] > kP2PListLDS;
     if (const uint64_t ml = __ballot(lng)) {
@@ -149,8 +165,13 @@ __device__ __forceinline__ void split_leaf(DevState *st, const SplitArgs &S, int
         at = __shfl(at, first);
         if (lng) S.longs[at + __popcll(ml & (ln == 0 ? 0ull : (~0ull >> (64 - ln))))] = e;
     }
-    // a list that cannot hold every leaf is left empty (k_p2p knows)
-    const int add = (slots > 1 || lng) && most > 0 ? (int)slots : 0;
+    // listed, to start first: what is split, long or heavy; a list that cannot hold every
+    // leaf is left empty.  Heavy in FP32 from a quantum on, in FP64 from half of one: at
+    // N = 1e6 without the heavy ones 515 us (FP32) and 603 us, from a quantum on 433 and
+    // 581 us, from half of one 502 and 542 us.
+    const bool heavy = (S.fp32 ? work : 2 * work) > quantum;
+    const int add = (slots > 1 || lng || heavy) && most > 0 ? (int)slots : 0;
+    S.src[e] = (uint32_t)slots | (add > 0 ? kListed : 0u);
     if (!__any(add)) return;
     const int lane = threadIdx.x & (kWave - 1);
     const int lead = __ffsll((unsigned long long)__ballot(1)) - 1;
@@ -248,7 +269,6 @@ template <> __device__ __forceinline__ float r2_floor<float>() { return 1e-18f; 
 template <> __device__ __forceinline__ double r2_floor<double>() { return 1e-100; }
 
 constexpr int kP2PTile = 256;       // source moonlets staged per LDS tile (default)
-constexpr int kP2PSrc = kWave;      // source cells per batch, one per lane (prefix sums in LDS)
 
 // Exclusive prefix sums of the moonlet counts of a batch's source cells (one per
 // lane) into s_pref[0..kP2PSrc]; returns the total.
@@ -295,21 +315,14 @@ __device__ __forceinline__ void interact(const typename Vec4<T>::type &v, const 
     }
 }
 
-// The tiles of a batch one wave takes: source moonlets [q0, q1) in tiles q0, q0 + step,
-// ...  (a leaf's whole batch, or one slot's share of it).
+// Slot `slot` of nslots of a batch of tot moonlets (FP64): an equal share of them, [q0, q1).
 struct TileRange {
-    int q0, q1, step;
+    int q0, q1;
 };
-
-// Slot `slot` of nslots of a batch of tot moonlets.  FP32: every nslots-th tile, so the
-// tiles and their FP32 sums are those of the undivided batch.  FP64: an equal share of
-// the moonlets, which fills the slots of a batch of few tiles.
-template <typename T, int TILE>
-__device__ __forceinline__ TileRange slot_tiles(int tot, int slot, int nslots) {
-    if (sizeof(T) == 4) return TileRange{slot * TILE, tot, nslots * TILE};
+__device__ __forceinline__ TileRange slot_range(int tot, int slot, int nslots) {
     const int per = ((tot + nslots - 1) / nslots + kWave - 1) / kWave * kWave;
     const int q0 = slot * per;
-    return TileRange{q0, q0 + per < tot ? q0 + per : tot, TILE};
+    return TileRange{q0, q0 + per < tot ? q0 + per : tot};
 }
 
 // Direct sums of the NT targets a lane holds over a range of a batch of source cells
@@ -325,7 +338,7 @@ __device__ __forceinline__ void p2p_batch(const TileRange tr, int nsb, const int
                                           int j0, int G, Acc3<T> (&acc)[NT]) {
     using V = typename Vec4<T>::type;
     const int lane = threadIdx.x & (kWave - 1);
-    for (int p0 = tr.q0; p0 < tr.q1; p0 += tr.step) {
+    for (int p0 = tr.q0; p0 < tr.q1; p0 += TILE) {
         const int nj = tr.q1 - p0 < TILE ? tr.q1 - p0 : TILE;
         // stage the tile: source moonlet q of the batch -> its cell by binary
         // search over the prefix sums
@@ -413,12 +426,12 @@ __device__ __forceinline__ int stage_batch(const int32_t *__restrict__ list, int
 }
 
 // Direct sums for ntc <= 64 targets (moonlets tb .. tb+ntc-1) of one leaf, over slot
-// `slot` of nslots of its list: the batches of kP2PSrc source cells are dealt to the
-// slots, and where there are fewer batches than slots, each batch's tiles to its share
-// of them.  The lanes form G = 64 / lpg groups of lpg = ceil(ntc / NT) lanes; lane li
-// of a group holds targets li, li + lpg, ..., and the groups split every tile's
-// sources.  The group partials are added in a fixed tree and written to out[d * n + i],
-// d = x, y, z.
+// `slot` of nslots of its list.  FP32: the strands slot, slot + nslots, ...  FP64: the
+// batches of kP2PSrc source cells are dealt to the slots, and where there are fewer batches
+// than slots, each batch's moonlets to its share of them.  The lanes form G = 64 / lpg
+// groups of lpg = ceil(ntc / NT) lanes; lane li of a group holds targets li, li + lpg, ...,
+// and the groups split every tile's sources.  The group partials are added in a fixed tree
+// and written to out[d * n + i], d = x, y, z.
 template <typename T, int NT, int TILE>
 __device__ __forceinline__ void p2p_targets(int ntc, int tb, int len, int slot, int nslots,
                                             const int32_t *__restrict__ list, int32_t *s_first,
@@ -442,25 +455,46 @@ __device__ __forceinline__ void p2p_targets(int ntc, int tb, int len, int slot, 
         zi[k] = offset_of<T>(p.z - g.z);
     }
     const int j0 = grp < G ? grp : TILE;           // lanes beyond the groups idle
-    Acc3<T> acc[NT];
     const int nb = (len + kP2PSrc - 1) / kP2PSrc;
-    const int b0 = nb < nslots ? slot * nb / nslots : slot;
-    // the slots that share batch b0: those with slot * nb / nslots = b0
-    const int s0 = nb < nslots ? (b0 * nslots + nb - 1) / nb : slot;
-    const int s1 = nb < nslots ? ((b0 + 1) * nslots + nb - 1) / nb : slot + 1;
-    for (int b = b0; b < nb; b += nb < nslots ? nb : nslots) {
-        const int tot = stage_batch<T>(list, len, b, c_first, c_count, s_first, s_pref,
-                                       reinterpret_cast<int32_t *>(tile));
-        const int nsb = len - b * kP2PSrc < kP2PSrc ? len - b * kP2PSrc : kP2PSrc;
-        p2p_batch<T, NT, TILE>(slot_tiles<T, TILE>(__builtin_amdgcn_readfirstlane(tot),
-                                                   slot - s0, s1 - s0),
-                               nsb, s_first, s_pref, tile, pos4, g, xi, yi, zi, j0, G, acc);
+    double px[NT], py[NT], pz[NT];
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int k = 0; k < NT; k++) px[k] = py[k] = pz[k] = 0.0;
+        for (int v = slot; v < list_strands(len); v += nslots) {
+            Acc3<T> acc[NT];
+            for (int b = v; b < nb; b += kLongSlots) {
+                const int tot = stage_batch<T>(list, len, b, c_first, c_count, s_first, s_pref,
+                                               reinterpret_cast<int32_t *>(tile));
+                const int nsb = len - b * kP2PSrc < kP2PSrc ? len - b * kP2PSrc : kP2PSrc;
+                p2p_batch<T, NT, TILE>(TileRange{0, __builtin_amdgcn_readfirstlane(tot)}, nsb,
+                                       s_first, s_pref, tile, pos4, g, xi, yi, zi, j0, G, acc);
+            }
+#pragma unroll
+            for (int k = 0; k < NT; k++) {
+                double ox, oy, oz;
+                acc[k].fold(ox, oy, oz);
+                px[k] += ox; py[k] += oy; pz[k] += oz;
+            }
+        }
+    } else {
+        Acc3<T> acc[NT];
+        const int b0 = nb < nslots ? slot * nb / nslots : slot;
+        // the slots that share batch b0: those with slot * nb / nslots = b0
+        const int s0 = nb < nslots ? (b0 * nslots + nb - 1) / nb : slot;
+        const int s1 = nb < nslots ? ((b0 + 1) * nslots + nb - 1) / nb : slot + 1;
+        for (int b = b0; b < nb; b += nb < nslots ? nb : nslots) {
+            const int tot = stage_batch<T>(list, len, b, c_first, c_count, s_first, s_pref,
+                                           reinterpret_cast<int32_t *>(tile));
+            const int nsb = len - b * kP2PSrc < kP2PSrc ? len - b * kP2PSrc : kP2PSrc;
+            p2p_batch<T, NT, TILE>(slot_range(__builtin_amdgcn_readfirstlane(tot), slot - s0,
+                                              s1 - s0),
+                                   nsb, s_first, s_pref, tile, pos4, g, xi, yi, zi, j0, G, acc);
+        }
+#pragma unroll
+        for (int k = 0; k < NT; k++) acc[k].fold(px[k], py[k], pz[k]);
     }
     // the groups' partials, added pairwise in a fixed tree (a leaf of 5 targets has 32
     // groups: one after the other they took as long as its sums)
-    double px[NT], py[NT], pz[NT];
-#pragma unroll
-    for (int k = 0; k < NT; k++) acc[k].fold(px[k], py[k], pz[k]);
     for (int o = 1; o < G; o <<= 1) {
         const bool add = (grp & (2 * o - 1)) == 0 && grp + o < G;
 #pragma unroll
@@ -529,6 +563,14 @@ __device__ __forceinline__ void p2p_targets_any(int ntc, int tmax, int tb, int l
     }
 }
 
+// FP32: the first strand that slot `slot` takes of the chunk of targets at t0 (strand v of
+// chunk k is unit k * strands + v, the units are dealt in turn; none: beyond the strands)
+template <typename T>
+__device__ __forceinline__ int first_strand(int slot, int nslots, int t0, int len) {
+    if (sizeof(T) == 8) return slot;
+    return (slot + nslots - t0 / kWave * list_strands(len) % nslots) % nslots;
+}
+
 constexpr int kP2PRun = 8;
 constexpr int64_t kP2PGrid = 65536;  // most blocks, of one wave each
 static_assert(kP2PListLDS == kP2PSrc, "one LDS batch holds a list that is not long");
@@ -538,7 +580,7 @@ static_assert(kP2PListLDS == kP2PSrc, "one LDS batch holds a list that is not lo
 // order.  The split and the long leaves come first, so they start first and the others
 // fill in around them within the same launch, which the hardware deals out as waves end:
 // blocks of one wave, an item each.  Four waves a block and items by position took 582 us
-// at N = 1e6, s = 96 in FP32, where this takes 435; persistent waves with counters 490.
+// at N = 1e6, s = 96 in FP32, where this takes 433; persistent waves with counters 490.
 template <typename T, int TILE>
 __global__ void __launch_bounds__(kWave, sizeof(T) == 8 ? 5 : 4)
 k_p2p(const DevState *__restrict__ st, const double4 *__restrict__ pos4,
@@ -546,7 +588,6 @@ k_p2p(const DevState *__restrict__ st, const double4 *__restrict__ pos4,
       const int32_t *__restrict__ c_first, const int32_t *__restrict__ c_count,
       const double4 *__restrict__ gcell, const int32_t *__restrict__ p2p_cnt,
       const int32_t *__restrict__ p2p_seg, int stride, const int32_t *__restrict__ split,
-      int64_t split_cap,
       const uint32_t *__restrict__ slots, double *__restrict__ part,
       double *__restrict__ acc_s, int64_t n, int tmax) {
     using V = typename Vec4<T>::type;
@@ -557,7 +598,6 @@ k_p2p(const DevState *__restrict__ st, const double4 *__restrict__ pos4,
     const int K = st->nleaves;
     const int nsplit = st->nsplit;
     const int items = nsplit + K;
-    const bool listed = K <= split_cap;   // split and long leaves are in the list
     // runs of kP2PRun items (the slots of a leaf, neighbouring leaves) stay on an XCD
     constexpr int kRound = kXcds * kP2PRun;
     for (int b = blockIdx.x; b < (items + kRound - 1) / kRound * kRound; b += gridDim.x) {
@@ -566,14 +606,15 @@ k_p2p(const DevState *__restrict__ st, const double4 *__restrict__ pos4,
         const bool lng = w < nsplit;
         const int ent = lng ? split[w] : w - nsplit;
         const int e = ent & 0xffffff, slot = ent >> 24;
-        const int nslots = (int)slots[e], len = p2p_cnt[e];
-        if (!lng && listed && (nslots > 1 || len > kP2PSrc)) continue;
+        const uint32_t sl = slots[e];
+        const int nslots = (int)(sl & 0xffu), len = p2p_cnt[e];
+        if (!lng && (sl & kListed)) continue;
         const int c = ent_cell[e];
         const int f = c_first[c], nt = c_count[c];
         double *out = nslots > 1 ? part + (int64_t)slot * 3 * n : acc_s;
         for (int t0 = 0; t0 < nt; t0 += kWave)
-            p2p_targets_any<T, TILE>(nt - t0 < kWave ? nt - t0 : kWave, tmax, f + t0, len, slot,
-                                     nslots, p2p_seg + (int64_t)e * stride, firsts, prefs,
+            p2p_targets_any<T, TILE>(nt - t0 < kWave ? nt - t0 : kWave, tmax, f + t0, len,
+                                     first_strand<T>(slot, nslots, t0, len), nslots, p2p_seg + (int64_t)e * stride, firsts, prefs,
                                      tile, pos4, c_first, c_count, gcell[c], out, n);
     }
 }
@@ -600,7 +641,7 @@ k_l2p(const DevState *__restrict__ st, const double *__restrict__ xs,
         const int c = ent_cell[e];
         const int f = c_first[c], nt = c_count[c];
         const double4 g = gcell[c];
-        const int nsl = (int)slots[e];                // direct sums in nsl parts
+        const int nsl = (int)(slots[e] & 0xffu);      // direct sums in nsl parts
         // the leaf's C is wave-uniform: scalar loads, no copy in LDS
         const double *__restrict__ cle = cleaf + (int64_t)__builtin_amdgcn_readfirstlane(e) * NL;
         for (int t0 = 0; t0 < nt; t0 += 64) {
@@ -656,10 +697,10 @@ k_l2p(const DevState *__restrict__ st, const double *__restrict__ xs,
 }
 
 template <int P>
-static void launch_leaf_local(const Workspace &ws, int split_unit, hipStream_t s) {
+static void launch_leaf_local(const Workspace &ws, bool fp32, hipStream_t s) {
     const SplitArgs S = {ws.p2p_cnt, ws.c_count, ws.c_first, ws.c_nent,
                          ws.ndisks > 1 ? ws.seg : nullptr, ws.disk_root, ws.ent_work,
-                         ws.long_p2p, ws.split_p2p, 2 * ws.m2l_cap, split_unit};
+                         ws.long_p2p, ws.split_p2p, 2 * ws.m2l_cap, fp32};
     int64_t g = ((int64_t)ws.n_max * P + 127) / 128;
     if (g > 8192) g = 8192;
     if (g < 1) g = 1;
@@ -703,18 +744,18 @@ k_sort_long_lists(const DevState *__restrict__ st, const int32_t *__restrict__ c
     }
 }
 
-hipError_t launch_l2l(const Workspace &ws, int p, int precision, int tile, hipStream_t s) {
-    const int split_unit = precision == NCORP_FP32_BULK ? (tile > 0 ? tile : kP2PTile) : kWave;
+hipError_t launch_l2l(const Workspace &ws, int p, int precision, hipStream_t s) {
+    const bool fp32 = precision == NCORP_FP32_BULK;
     switch (p) {
-        case 1: launch_leaf_local<1>(ws, split_unit, s); break;
-        case 2: launch_leaf_local<2>(ws, split_unit, s); break;
-        case 3: launch_leaf_local<3>(ws, split_unit, s); break;
-        case 4: launch_leaf_local<4>(ws, split_unit, s); break;
-        case 5: launch_leaf_local<5>(ws, split_unit, s); break;
-        case 6: launch_leaf_local<6>(ws, split_unit, s); break;
+        case 1: launch_leaf_local<1>(ws, fp32, s); break;
+        case 2: launch_leaf_local<2>(ws, fp32, s); break;
+        case 3: launch_leaf_local<3>(ws, fp32, s); break;
+        case 4: launch_leaf_local<4>(ws, fp32, s); break;
+        case 5: launch_leaf_local<5>(ws, fp32, s); break;
+        case 6: launch_leaf_local<6>(ws, fp32, s); break;
         default: break;
     }
-    if (precision == NCORP_FP32_BULK) {
+    if (fp32) {
         const size_t lds = (size_t)((ws.p2p_stride + 3) & ~3) * sizeof(int32_t);
         k_sort_long_lists<<<kSortLongBlocks, kSortThreads, lds, s>>>(ws.st, ws.p2p_cnt, ws.p2p_seg,
                                                                      ws.p2p_stride, ws.long_p2p);
@@ -729,7 +770,7 @@ static void launch_p2p_t(const Workspace &ws, int64_t n, int tmax, hipStream_t s
     const int64_t g = most < kP2PGrid ? most : kP2PGrid;
     k_p2p<T, TILE><<<(int)g, kWave, 0, s>>>(
         ws.st, ws.vcol, ws.ent_cell, ws.c_first, ws.c_count, ws.gcell, ws.p2p_cnt, ws.p2p_seg,
-        ws.p2p_stride, ws.split_p2p, 2 * ws.m2l_cap, ws.ent_work, ws.p2p_part, ws.acc_s, n, tmax);
+        ws.p2p_stride, ws.split_p2p, ws.ent_work, ws.p2p_part, ws.acc_s, n, tmax);
 }
 
 template <typename T>
