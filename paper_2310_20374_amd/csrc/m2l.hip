@@ -5,10 +5,20 @@
 //   C^(m)_a(s_A) += sum_{n=0, n!=1}^{p-m} (-1)^n sum_{|b|=n} D_{a+b}(R) Mt_b(B),
 // with R = s_A - s_B, D_g = d^g (1/|R|) and Mt_b = M_b / b! (the n! of Eq. 25 and
 // the multinomial weights of the symmetric inner product cancel into 1/b!).  The
-// wave then sums its 64 partial tensors order by order through LDS.  Both
-// directions of a pair are separate entries of the list, so every target's sum has
-// a fixed order and the result does not depend on scheduling.  D and the
-// contraction are in expansion.h.
+// wave then sums its 64 partial tensors by exchanges between lanes.  Both directions of a
+// pair are separate entries of the list, so every target's sum has a fixed order and the
+// result does not depend on scheduling.  D and the contraction are in expansion.h.
+//
+// Bound by FP64 (FP32) operations at the two to four waves per SIMD that D leaves room
+// for, and by the lines of the sources' rows: a lane reads its own source's row, so a row
+// is loaded at once, while its lines are in L1 (4e6 clumped moonlets, FP32, p = 6: 865 us
+// with loads where they are used, 820 so).  The two highest orders take part with the
+// monopole alone (there is no n = 1 term): where their sums don't fit the registers, D of
+// a batch of 64 sources, times the masses, is summed over the lanes as it stands.  FP64
+// at p = 6 computed D three times before, once per group of orders, and every sum over
+// the wave read 64 rows of LDS: N = 1e6, s = 52: 381 -> 222 us; 1e5: 86 -> 57 us; p = 3,
+// 262144: 99 -> 94 us; FP32, p = 4, 64 disks of 12324: 43 -> 38 us; p = 6, 1e6: 101 us
+// both ways (92 with the highest orders summed per batch there too, but clumps 885).
 #include "ncorp_internal.h"
 #include "expansion.h"
 
@@ -16,89 +26,97 @@ namespace ncorp {
 
 constexpr int kM2LBlock = 64;     // one wave per block, one target per wave
 
-// FP64 at high order splits the output orders over passes (D is recomputed per
-// pass) so that the accumulators and D stay in registers.
-template <int P, typename T> struct M2LSplit { static constexpr int K1 = P, K2 = P; };
-template <> struct M2LSplit<6, double> { static constexpr int K1 = 4, K2 = 5; };
-template <> struct M2LSplit<5, double> { static constexpr int K1 = 3, K2 = 5; };
-
-// Components of C staged per round of the wave sum when one pass covers every order:
-// half of them, so the buffer (and the occupancy it limits) is half as large.
-template <int P> constexpr int red_chunk() { return (n_local(P) + 1) / 2; }
-
-// Row stride (elements) of the wave-sum buffer: one round's components when one pass
-// covers every order, else one order; odd, so a lane's row and a column are both free
-// of bank conflicts.
-template <int P, typename T> constexpr int red_stride() {
-    return (M2LSplit<P, T>::K1 == P ? red_chunk<P>() : ncomp(P)) | 1;
+// Waves per SIMD that the registers are cut for.
+template <int P, typename T> constexpr int m2l_waves() {
+    return sizeof(T) == 8 ? (P >= 5 ? 2 : (P == 4 ? 3 : 4)) : (P >= 6 ? 2 : 4);
 }
 
-// one pass over a target's sources for the output orders MLO..MHI
-template <int P, int MLO, int MHI, typename T>
-__device__ __forceinline__ void m2l_pass(const double4 gA, const double4 *__restrict__ gcell,
-                                         const T *__restrict__ mult,
-                                         const int32_t *__restrict__ srcs, int len, double *out,
-                                         T *red) {
-    constexpr int RS = red_stride<P, T>();
-    constexpr int NM = n_mult(P), ND = off_order(P + 1);
-    constexpr int NA = cidx(MHI + 1, 0, 0) - cidx(MLO, 0, 0);
-    const int lane = threadIdx.x;
-    T acc[NA];
+// Orders whose sums a lane keeps over a long list: all of them, but without the last two
+// in FP64 from p = 5 on.
+template <int P, typename T> constexpr int m2l_orders() {
+    return sizeof(T) == 8 && P >= 5 ? P - 2 : P;
+}
+
+// ---------------------------------------------------------------- sums over the wave
+// v[0..N) of every lane, summed over the wave: in each step a lane pairs with the lane
+// across one bit of the lane index, the lower one keeps the sums of the first half of the
+// values and the upper one those of the second, so 64 lanes share the N results after six
+// steps and some 2 N additions.
+constexpr int halved(int n) { return (n + 1) / 2; }
+constexpr int folded(int n) {
+    return halved(halved(halved(halved(halved(halved(n))))));
+}
+__device__ __forceinline__ double join(unsigned lo, unsigned hi) {
+    return __hiloint2double((int)hi, (int)lo);
+}
+template <int N, int BIT> __device__ __forceinline__ void fold_step(double *v) {
+    constexpr int H = halved(N);
+    const bool upper = (threadIdx.x & BIT) != 0;
 #pragma unroll
-    for (int k = 0; k < NA; k++) acc[k] = (T)0;
-    for (int i = lane; i < len; i += kWave) {
-        const int B = srcs[i];
-        const double4 gB = gcell[B];
-        const T x = (T)(gA.x - gB.x), y = (T)(gA.y - gB.y), z = (T)(gA.z - gB.z);
-        const T r2 = x * x + y * y + z * z;
-        T D[ND];
-        green_derivs<P, T>(x, y, z, rsqrt_t<T>(r2), D);
-        m2l_contract<P, MLO, MHI, T>(D, mult + (int64_t)B * NM, acc);
-    }
-    // wave sum of every component in lane order (FP64)
-    if constexpr (MLO == 1 && MHI == P && M2LSplit<P, T>::K1 == P) {
-        // all orders at once, in two rounds of CH components: lane k sums component
-        // c0 + k of the round
-        constexpr int CH = red_chunk<P>();
-#pragma unroll
-        for (int c0 = 0; c0 < NA; c0 += CH) {
-#pragma unroll
-            for (int k = 0; k < CH; k++)
-                if (c0 + k < NA) red[lane * RS + k] = acc[c0 + k];
-            __syncthreads();
-            const int nk = NA - c0 < CH ? NA - c0 : CH;
-            for (int k = lane; k < nk; k += kWave) {
-                double s = 0.0;
-                for (int l = 0; l < kWave; l++) s += (double)red[l * RS + k];
-                out[cidx(MLO, 0, 0) + c0 + k] = s;
-            }
-            __syncthreads();
-        }
-    } else {
-#pragma unroll
-        for (int m = MLO; m <= MHI; m++) {
-            const int base = cidx(m, 0, 0) - cidx(MLO, 0, 0);
-#pragma unroll
-            for (int k = 0; k < ncomp(m); k++) red[lane * RS + k] = acc[base + k];
-            __syncthreads();
-            if (lane < ncomp(m)) {
-                double s = 0.0;
-                for (int l = 0; l < kWave; l++) s += (double)red[l * RS + lane];
-                out[cidx(m, 0, 0) + lane] = s;
-            }
-            __syncthreads();
+    for (int k = 0; k < H; k++) {
+        const double a = v[k], b = k + H < N ? v[k + H] : 0.0;
+        const unsigned al = (unsigned)__double2loint(a), ah = (unsigned)__double2hiint(a);
+        const unsigned bl = (unsigned)__double2loint(b), bh = (unsigned)__double2hiint(b);
+        if constexpr (BIT == 32) {
+            const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+            const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+            v[k] = join(l[0], h[0]) + join(l[1], h[1]);
+        } else if constexpr (BIT == 16) {
+            const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+            const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+            v[k] = join(l[0], h[0]) + join(l[1], h[1]);
+        } else {
+            // rotation by 8 in rows of 16, mirror in rows of 8, quad permutations
+            constexpr int ctl = BIT == 8 ? 0x128 : (BIT == 4 ? 0x141 : (BIT == 2 ? 0x4e : 0xb1));
+            const double keep = upper ? b : a, send = upper ? a : b;
+            const unsigned l = (unsigned)__builtin_amdgcn_mov_dpp(__double2loint(send), ctl, 0xf,
+                                                                  0xf, true);
+            const unsigned h = (unsigned)__builtin_amdgcn_mov_dpp(__double2hiint(send), ctl, 0xf,
+                                                                  0xf, true);
+            v[k] = keep + join(l, h);
         }
     }
+}
+template <int N> __device__ __forceinline__ void fold(double *v) {
+    constexpr int N2 = halved(N), N3 = halved(N2), N4 = halved(N3), N5 = halved(N4),
+                  N6 = halved(N5);
+    fold_step<N, 32>(v);
+    fold_step<N2, 16>(v);
+    fold_step<N3, 8>(v);
+    fold_step<N4, 4>(v);
+    fold_step<N5, 2>(v);
+    fold_step<N6, 1>(v);
+}
+// which of the N values the lane's k-th result is the sum of, or -1 (a lane left over)
+template <int N> __device__ __forceinline__ int fold_index(int k) {
+    constexpr int N2 = halved(N), N3 = halved(N2), N4 = halved(N3), N5 = halved(N4),
+                  N6 = halved(N5), N7 = halved(N6);
+    const int l = threadIdx.x;
+    int i = k + ((l & 1) ? N7 : 0);
+    bool ok = i < N6;
+    i += (l & 2) ? N6 : 0;
+    ok = ok && i < N5;
+    i += (l & 4) ? N5 : 0;
+    ok = ok && i < N4;
+    i += (l & 8) ? N4 : 0;
+    ok = ok && i < N3;
+    i += (l & 16) ? N3 : 0;
+    ok = ok && i < N2;
+    i += (l & 32) ? N2 : 0;
+    return ok && i < N ? i : -1;
 }
 
 template <int P, typename T>
-__global__ void __launch_bounds__(kM2LBlock, 2)
+__global__ void __launch_bounds__(kM2LBlock, (m2l_waves<P, T>()))
 k_m2l(const DevState *__restrict__ st, const double4 *__restrict__ gcell,
       const T *__restrict__ mult, const int32_t *__restrict__ cnt,
       const int32_t *__restrict__ seg, int stride, double *__restrict__ local) {
-    constexpr int NL = n_local(P);
-    constexpr int K1 = M2LSplit<P, T>::K1, K2 = M2LSplit<P, T>::K2;
-    __shared__ __align__(16) T red[kWave * red_stride<P, T>()];
+    constexpr int NL = n_local(P), NM = n_mult(P), ND = off_order(P + 1);
+    // orders 1 .. M1 have sums in registers; M2 .. P, where they don't fit, are summed over
+    // the lanes after every batch
+    constexpr int M1 = m2l_orders<P, T>(), M2 = M1 + 1;
+    constexpr int BL = cidx(1, 0, 0), BH = cidx(M2, 0, 0);
+    constexpr int NLO = BH - BL, NHI = NL - BH;
     if (st->status & kSkipMask) return;
     const int nc = st->ncells;
     const int lane = threadIdx.x;
@@ -111,9 +129,59 @@ k_m2l(const DevState *__restrict__ st, const double4 *__restrict__ gcell,
         }
         const int32_t *srcs = seg + (int64_t)A * stride;
         const double4 gA = gcell[A];
-        m2l_pass<P, 1, K1, T>(gA, gcell, mult, srcs, len, out, red);
-        if (K2 > K1) m2l_pass<P, (K1 < P ? K1 + 1 : P), K2, T>(gA, gcell, mult, srcs, len, out, red);
-        if (P > K2) m2l_pass<P, (K2 < P ? K2 + 1 : P), P, T>(gA, gcell, mult, srcs, len, out, red);
+        T acc[NLO];
+#pragma unroll
+        for (int k = 0; k < NLO; k++) acc[k] = (T)0;
+        double sum[folded(NHI) + 1];
+#pragma unroll
+        for (int k = 0; k < folded(NHI); k++) sum[k] = 0.0;
+        for (int i0 = 0; i0 < len; i0 += kWave) {
+            double hi[NHI + 1];
+#pragma unroll
+            for (int k = 0; k < NHI; k++) hi[k] = 0.0;
+            if (i0 + lane < len) {
+                const int B = srcs[i0 + lane];
+                const double4 gB = gcell[B];
+                const T *mb = mult + (int64_t)B * NM;
+                const T x = (T)(gA.x - gB.x), y = (T)(gA.y - gB.y), z = (T)(gA.z - gB.z);
+                const T r2 = x * x + y * y + z * z;
+                T D[ND], M[NM];
+                // FP32: the whole row at once, while its lines are in L1
+#pragma unroll
+                for (int k = 0; k < NM; k++) M[k] = mb[k];
+                if constexpr (sizeof(T) == 4) {
+#pragma unroll
+                    for (int k = 0; k < NM; k++) asm volatile("" : "+v"(M[k]));
+                }
+                green_derivs<P, T>(x, y, z, rsqrt_t<T>(r2), D);
+                m2l_contract<P, 1, M1, T>(D, M, acc);
+                const T m0 = M[0];
+#pragma unroll
+                for (int m = M2; m <= P; m++)
+#pragma unroll
+                    for (int b = 0; b <= m; b++)
+#pragma unroll
+                        for (int c = 0; c <= m - b; c++)
+                            hi[cidx(m - b - c, b, c) - BH] = (double)(D[sidx(m - b - c, b, c)] * m0);
+            }
+            if constexpr (NHI > 0) fold<NHI>(hi);
+#pragma unroll
+            for (int k = 0; k < folded(NHI); k++) sum[k] += hi[k];
+        }
+#pragma unroll
+        for (int k = 0; k < folded(NHI); k++) {
+            const int at = fold_index<(NHI > 0 ? NHI : 1)>(k);
+            if (at >= 0) out[BH + at] = sum[k];
+        }
+        double lo[NLO];
+#pragma unroll
+        for (int k = 0; k < NLO; k++) lo[k] = (double)acc[k];
+        fold<NLO>(lo);
+#pragma unroll
+        for (int k = 0; k < folded(NLO); k++) {
+            const int at = fold_index<NLO>(k);
+            if (at >= 0) out[BL + at] = lo[k];
+        }
     }
 }
 
