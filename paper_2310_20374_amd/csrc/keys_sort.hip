@@ -260,9 +260,12 @@ __global__ void k_keys(const double *__restrict__ x, const double *__restrict__ 
     }
 }
 
-// radix passes of a build: 8 over the 63-bit keys, then (batched calls) 1 or 2 over
-// the disk id, the most significant digit
-static int disk_passes(int nd) { return nd <= 1 ? 0 : (nd <= 256 ? 1 : 2); }
+// radix passes of a build: over the 63-bit keys, then (batched calls) 1 or 2 over the disk
+// id, the most significant digit
+constexpr int kRadixBits = 9, kRadixBins = 1 << kRadixBits;
+constexpr int kKeyPasses = 63 / kRadixBits;
+static_assert(63 % kRadixBits == 0, "no digit of fewer bits");
+static int disk_passes(int nd) { return nd <= 1 ? 0 : (nd <= kRadixBins ? 1 : 2); }
 
 hipError_t launch_keys(const Workspace &ws, const double *x, const double *y,
                        const double *z, int64_t n, double root_half_width,
@@ -270,7 +273,8 @@ hipError_t launch_keys(const Workspace &ws, const double *x, const double *y,
                        bool max_ready) {
     // the sort ends in ws.keys / ws.idx: the bucket sort and an odd number of radix
     // passes start in the other buffers
-    const bool odd = bucket_sort_applies(ws, n) || (8 + disk_passes(ws.ndisks)) % 2 == 1;
+    const bool odd =
+        bucket_sort_applies(ws, n) || (kKeyPasses + disk_passes(ws.ndisks)) % 2 == 1;
     uint64_t *kout = odd ? ws.keys_alt : ws.keys;
     uint32_t *vout = odd ? ws.idx_alt : ws.idx;
     if (disk_off) {
@@ -296,70 +300,80 @@ hipError_t launch_keys(const Workspace &ws, const double *x, const double *y,
 }
 
 // ------------------------------------------------------------------ radix sort
-// LSD radix sort of (key, index) by 8-bit digits, 8 passes over 63 bits.  Each
-// pass: per-tile digit histograms, a per-digit scan over tiles, then a stable
-// scatter.  The scatter ranks each wave's 64-item rounds with ballots (wave-private
-// running counters), places the tile in LDS in digit order, and then writes it out
-// so that each digit's run of the tile leaves as consecutive stores.
-constexpr int kSortThreads = 256;
-// 2048 items per tile: about two tiles per compute unit at N = 1e6 (4096-item tiles left
-// every compute unit with one lone block: 0.225 -> 0.190 ms for the 8 passes)
+// LSD radix sort of (key, index) by 9-bit digits, 7 passes over 63 bits, for builds of
+// more moonlets than the bucket sort takes and for the mesh.  A pass is two launches: the
+// tiles' digit counts, then a stable scatter, whose blocks add up the counts before theirs
+// (of whole groups of tiles, then of the tiles of their own group) and all of them.  The
+// scatter ranks each wave's 64-item rounds with ballots (wave-private running counters),
+// places the tile in LDS in digit order, and then writes it out so that each digit's run of
+// the tile leaves as consecutive stores.  With 8-bit digits (tiles of 2048, runs as long)
+// and a scan of the counts as a third launch, a mesh of 1e6 moonlets took 4 passes of 28 us
+// and 4 empty ones of 12, now 3 of 22 and 4 of 11.
+constexpr int kSortThreads = kRadixBins;             // a thread per digit
 constexpr int kSortItems = 8;                        // per thread
-constexpr int kSortTile = kSortThreads * kSortItems; // 2048
+constexpr int kSortTile = kSortThreads * kSortItems; // 4096
 constexpr int kSortWaves = kSortThreads / kWave;
+static_assert(kSortTile <= 0xffff, "a tile's counts are 16-bit");
 
-__device__ __forceinline__ uint32_t sort_digit(const uint64_t *keys, const uint32_t *vals,
-                                               const uint16_t *dseg, int64_t i, int shift) {
-    return dseg ? ((uint32_t)dseg[vals[i]] >> shift) & 255u
-                : (uint32_t)(keys[i] >> shift) & 255u;
+// The counts: a row of 16-bit ones per tile, and with more than kDirectTiles tiles two
+// slices of 32-bit ones per group of `per` tiles, one for the current pass and one that it
+// clears for the next.
+constexpr int kDirectTiles = 16;
+struct RadixCounts {
+    uint16_t *rows;
+    uint32_t *groups;                    // [2][ngroups][kRadixBins]; ngroups 0: none
+    int ntiles, per, ngroups;
+};
+// in the 1024 bytes per 2048 items (and as many again) that ws.hist holds: a row takes
+// 1024 per 4096, a group 4096 per at least 16 rows
+static RadixCounts radix_counts(uint32_t *hist, int64_t n) {
+    RadixCounts c;
+    c.ntiles = (int)((n + kSortTile - 1) / kSortTile);
+    c.rows = reinterpret_cast<uint16_t *>(hist);
+    c.groups = hist + (int64_t)c.ntiles * kRadixBins / 2;
+    int per = kDirectTiles;
+    while ((int64_t)per * per < c.ntiles) per++;
+    c.per = per;
+    c.ngroups = c.ntiles > kDirectTiles ? (c.ntiles + per - 1) / per : 0;
+    return c;
+}
+
+__device__ __forceinline__ uint32_t sort_digit(uint64_t key, uint32_t val, const uint16_t *dseg,
+                                               int shift) {
+    return (dseg ? (uint32_t)dseg[val] >> shift : (uint32_t)(key >> shift)) & (kRadixBins - 1u);
 }
 
 __global__ void __launch_bounds__(kSortThreads)
 k_radix_hist(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ vals,
-             const uint16_t *__restrict__ dseg, int64_t n, int shift, uint32_t *hist,
-             int ntiles, const int32_t *__restrict__ skip) {
-    __shared__ uint32_t h[256];
+             const uint16_t *__restrict__ dseg, int64_t n, int shift, const RadixCounts C,
+             int slice, const int32_t *__restrict__ skip) {
+    __shared__ uint32_t h[kRadixBins];
     if (skip && *skip) return;
-    h[threadIdx.x] = 0;
+    const int t = threadIdx.x;
+    h[t] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int k = 0; k < kSortItems; k++) {
-        const int64_t i = base + k * kSortThreads + threadIdx.x;
-        if (i < n) atomicAdd(&h[sort_digit(keys, vals, dseg, i, shift)], 1u);
-    }
-    __syncthreads();
-    hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
-}
-
-// One block per digit: exclusive scan of that digit's tile counts; digit total out.
-__global__ void __launch_bounds__(256)
-k_radix_scan(uint32_t *hist, int ntiles, uint32_t *totals, const int32_t *__restrict__ skip) {
-    __shared__ uint32_t wtot[256 / kWave];
-    if (skip && *skip) return;
-    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-    uint32_t *row = hist + (int64_t)blockIdx.x * ntiles;
-    uint32_t carry = 0;
-    for (int b0 = 0; b0 < ntiles; b0 += 256) {
-        const int i = b0 + threadIdx.x;
-        const uint32_t x = i < ntiles ? row[i] : 0u;
-        uint32_t v = x;
+    uint64_t key[kSortItems];
+    uint32_t val[kSortItems];
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t y = __shfl_up(v, o);
-            if (lane >= o) v += y;
-        }
-        if (lane == kWave - 1) wtot[w] = v;
-        __syncthreads();
-        uint32_t before = 0, all = 0;
-        for (int k = 0; k < 256 / kWave; k++) {
-            if (k < w) before += wtot[k];
-            all += wtot[k];
-        }
-        if (i < ntiles) row[i] = carry + before + v - x;
-        carry += all;
-        __syncthreads();
+    for (int k = 0; k < kSortItems; k++) {
+        const int64_t i = base + k * kSortThreads + t;
+        key[k] = i < n && !dseg ? keys[i] : 0ull;
+        val[k] = i < n && dseg ? vals[i] : 0u;
     }
-    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+#pragma unroll
+    for (int k = 0; k < kSortItems; k++)
+        if (base + k * kSortThreads + t < n)
+            atomicAdd(&h[sort_digit(key[k], val[k], dseg, shift)], 1u);
+    __syncthreads();
+    C.rows[(int64_t)blockIdx.x * kRadixBins + t] = (uint16_t)h[t];
+    if (C.ngroups == 0) return;
+    const int64_t size = (int64_t)C.ngroups * kRadixBins;
+    if (h[t]) atomicAdd(C.groups + slice * size + blockIdx.x / C.per * kRadixBins + t, h[t]);
+    uint32_t *next = C.groups + (1 - slice) * size;
+    for (int64_t i = (int64_t)blockIdx.x * kSortThreads + t; i < size;
+         i += (int64_t)gridDim.x * kSortThreads)
+        next[i] = 0;
 }
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
@@ -367,9 +381,9 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-// exclusive prefix sum over the block's 256 threads; wsum (4 entries) must not be
+// exclusive prefix sum over the block's threads; wsum (an entry per wave) must not be
 // reused by the caller before its next barrier
-__device__ __forceinline__ uint32_t block_excl_scan256(uint32_t v, uint32_t *wsum) {
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *wsum) {
     const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
     uint32_t x = v;
 #pragma unroll
@@ -384,62 +398,78 @@ __device__ __forceinline__ uint32_t block_excl_scan256(uint32_t v, uint32_t *wsu
     return add + x - v;
 }
 
+struct RadixLds {
+    uint64_t key[kSortTile];             // the tile in digit order
+    uint32_t val[kSortTile];
+    uint16_t dig[kSortTile];
+    uint32_t wcnt[kSortWaves][kRadixBins];   // per-wave digit counters
+    uint32_t start[kRadixBins];          // start of each digit's run in the tile
+    int32_t delta[kRadixBins];           // global start minus tile start, per digit
+    uint32_t wsum_a[kSortWaves], wsum_b[kSortWaves];
+};
+
 __global__ void __launch_bounds__(kSortThreads)
 k_radix_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                 uint64_t *__restrict__ kout, uint32_t *__restrict__ vout,
-                const uint16_t *__restrict__ dseg, int64_t n, int shift,
-                const uint32_t *__restrict__ hist, const uint32_t *__restrict__ totals,
-                int ntiles, const int32_t *__restrict__ skip) {
-    __shared__ uint64_t lkey[kSortTile];         // the tile in digit order
-    __shared__ uint32_t lval[kSortTile];
-    __shared__ uint8_t ldig[kSortTile];
-    __shared__ uint32_t wcnt[kSortWaves][256];   // per-wave digit counters
-    __shared__ uint32_t lstart[256];             // start of each digit's run in the tile
-    __shared__ int32_t delta[256];               // global start minus tile start, per digit
-    __shared__ uint32_t wsum_a[kSortWaves], wsum_b[kSortWaves];
+                const uint16_t *__restrict__ dseg, int64_t n, int shift, const RadixCounts C,
+                int slice, const int32_t *__restrict__ skip) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    RadixLds &S = *reinterpret_cast<RadixLds *>(smem);
     if (skip && *skip) return;
     const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
-    for (int k = 0; k < kSortWaves; k++) wcnt[k][t] = 0;
-    // global start of digit t's run from this tile: digits below t, then earlier tiles
-    const uint32_t gstart = block_excl_scan256(totals[t], wsum_a) +
-                            hist[(int64_t)t * ntiles + blockIdx.x];
-    // phase 1: this wave's items (a contiguous quarter of the tile), kept in registers
-    const int64_t tbase = (int64_t)blockIdx.x * kSortTile;
+    const int tile = blockIdx.x;
+    // this wave's items (a contiguous eighth of the tile), kept in registers
+    const int64_t tbase = (int64_t)tile * kSortTile;
     const int64_t wbase = tbase + (int64_t)w * (kSortTile / kSortWaves);
     uint64_t key[kSortItems];
-    uint32_t val[kSortItems];
-    uint32_t dig[kSortItems];
+    uint32_t val[kSortItems], dig[kSortItems];
 #pragma unroll
     for (int r = 0; r < kSortItems; r++) {
         const int64_t i = wbase + r * kWave + lane;
-        if (i < n) {
-            key[r] = kin[i];
-            val[r] = vin[i];
-            dig[r] = dseg ? ((uint32_t)dseg[val[r]] >> shift) & 255u
-                          : (uint32_t)(key[r] >> shift) & 255u;
-        } else {
-            key[r] = 0;
-            val[r] = 0;
-            dig[r] = 0;
+        key[r] = i < n ? kin[i] : 0ull;
+        val[r] = i < n ? vin[i] : 0u;
+    }
+    for (int k = 0; k < kSortWaves; k++) S.wcnt[k][t] = 0;
+    // digit t: its count in all tiles and in those before this one
+    uint32_t total = 0, before = 0;
+    const int g = tile / C.per;
+    const uint32_t *grp = C.groups + (int64_t)slice * C.ngroups * kRadixBins + t;
+#pragma unroll 4
+    for (int k = 0; k < C.ngroups; k++) {
+        const uint32_t c = grp[(int64_t)k * kRadixBins];
+        total += c;
+        before += k < g ? c : 0u;
+    }
+    const int r0 = C.ngroups ? g * C.per : 0, r1 = C.ngroups ? tile : C.ntiles;
+#pragma unroll 4
+    for (int k = r0; k < r1; k++) {
+        const uint32_t c = C.rows[(int64_t)k * kRadixBins + t];
+        if (!C.ngroups) total += c;
+        before += k < tile ? c : 0u;
+    }
+    const uint32_t gstart = block_excl_scan(total, S.wsum_a) + before;
+#pragma unroll
+    for (int r = 0; r < kSortItems; r++) {
+        dig[r] = 0;
+        if (wbase + r * kWave + lane < n) {
+            dig[r] = sort_digit(key[r], val[r], dseg, shift);
+            atomicAdd(&S.wcnt[w][dig[r]], 1u);
         }
     }
-#pragma unroll
-    for (int r = 0; r < kSortItems; r++)
-        if (wbase + r * kWave + lane < n) atomicAdd(&wcnt[w][dig[r]], 1u);
     __syncthreads();
-    // phase 2: per digit, exclusive prefix over the waves, then over the digits
+    // per digit, exclusive prefix over the waves, then over the digits
     uint32_t run = 0;
     for (int k = 0; k < kSortWaves; k++) {
-        const uint32_t c = wcnt[k][t];
-        wcnt[k][t] = run;
+        const uint32_t c = S.wcnt[k][t];
+        S.wcnt[k][t] = run;
         run += c;
     }
-    const uint32_t ls = block_excl_scan256(run, wsum_b);
-    lstart[t] = ls;
-    delta[t] = (int32_t)(gstart - ls);           // gstart >= ls: see the digit counts
+    const uint32_t ls = block_excl_scan(run, S.wsum_b);
+    S.start[t] = ls;
+    S.delta[t] = (int32_t)(gstart - ls);         // gstart >= ls: see the digit counts
     __syncthreads();
-    // phase 3: stable ranks inside each 64-item round, wave-private running counts;
-    // items go to their place in the tile's digit order
+    // stable ranks inside each 64-item round, wave-private running counts; items go to
+    // their place in the tile's digit order
 #pragma unroll
     for (int r = 0; r < kSortItems; r++) {
         const int64_t i = wbase + r * kWave + lane;
@@ -449,86 +479,78 @@ k_radix_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ v
         const uint32_t d = dig[r];
         uint64_t peers = act;
 #pragma unroll
-        for (int b = 0; b < 8; b++) {
+        for (int b = 0; b < kRadixBits; b++) {
             const uint64_t m = __ballot((d >> b) & 1u);
             peers &= ((d >> b) & 1u) ? m : ~m;
         }
         if (valid) {
             const uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
-            const uint32_t before = wcnt[w][d];
-            const uint32_t lpos = lstart[d] + before + rank;
-            lkey[lpos] = key[r];
-            lval[lpos] = val[r];
-            ldig[lpos] = (uint8_t)d;
+            const uint32_t at = S.wcnt[w][d];
+            const uint32_t lpos = S.start[d] + at + rank;
+            S.key[lpos] = key[r];
+            S.val[lpos] = val[r];
+            S.dig[lpos] = (uint16_t)d;
             const bool leader = (peers & lanemask_lt()) == 0ull;
             __builtin_amdgcn_wave_barrier();
-            if (leader) wcnt[w][d] = before + (uint32_t)__popcll(peers);
+            if (leader) S.wcnt[w][d] = at + (uint32_t)__popcll(peers);
         }
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    // phase 4: write the tile out in digit order; a digit's run is contiguous in the
-    // output too
+    // write the tile out in digit order; a digit's run is contiguous in the output too
     const int cnt = n - tbase < kSortTile ? (int)(n - tbase) : kSortTile;
     for (int j = t; j < cnt; j += kSortThreads) {
-        const int64_t pos = (int64_t)delta[ldig[j]] + j;
+        const int64_t pos = (int64_t)S.delta[S.dig[j]] + j;
         if (pos >= 0 && pos < n) {                // always, by the counts; kept as a guard
-            kout[pos] = lkey[j];
-            vout[pos] = lval[j];
+            kout[pos] = S.key[j];
+            vout[pos] = S.val[j];
         }
     }
 }
 
-hipError_t launch_sort(const Workspace &ws, int64_t n, hipStream_t s) {
-    static_assert(kSortTile == kSortTileItems, "tile size of the workspace layout");
-    int ntiles = (int)((n + kSortTile - 1) / kSortTile);
-    const int npass = 8 + disk_passes(ws.ndisks);
-    // launch_keys wrote the keys where an even number of swaps later lands in ws.keys
-    uint64_t *ka = ws.keys, *kb = ws.keys_alt;
-    uint32_t *va = ws.idx, *vb = ws.idx_alt;
-    if (npass % 2 == 1) {
-        ka = ws.keys_alt; kb = ws.keys;
-        va = ws.idx_alt; vb = ws.idx;
+// `passes` passes over the keys from bit 0, then dpasses over the disk ids; from
+// skip_from on they do nothing when *skip is set
+static hipError_t radix_passes(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *vb,
+                               const uint16_t *dseg, int64_t n, int passes, int dpasses,
+                               uint32_t *hist, const int32_t *skip, int skip_from,
+                               hipStream_t s) {
+    const RadixCounts C = radix_counts(hist, n);
+    if (C.ngroups) {
+        const hipError_t e = launch_fill_i32(reinterpret_cast<int32_t *>(C.groups), 0,
+                                             (int64_t)C.ngroups * kRadixBins, s);
+        if (e != hipSuccess) return e;
     }
-    uint32_t *totals = ws.hist + (int64_t)256 * ntiles;
-    for (int pass = 0; pass < npass; pass++) {
-        // passes 0-7: key digits; then the disk id, low byte first
-        const uint16_t *dseg = pass < 8 ? nullptr : ws.seg;
-        const int shift = pass < 8 ? 8 * pass : 8 * (pass - 8);
-        k_radix_hist<<<ntiles, kSortThreads, 0, s>>>(ka, va, dseg, n, shift, ws.hist, ntiles,
-                                                     nullptr);
-        k_radix_scan<<<256, 256, 0, s>>>(ws.hist, ntiles, totals, nullptr);
-        k_radix_scatter<<<ntiles, kSortThreads, 0, s>>>(ka, va, kb, vb, dseg, n, shift, ws.hist,
-                                                        totals, ntiles, nullptr);
+    for (int pass = 0; pass < passes + dpasses; pass++) {
+        const uint16_t *ds = pass < passes ? nullptr : dseg;
+        const int shift = kRadixBits * (pass < passes ? pass : pass - passes);
+        const int32_t *sk = skip && pass >= skip_from ? skip : nullptr;
+        k_radix_hist<<<C.ntiles, kSortThreads, 0, s>>>(ka, va, ds, n, shift, C, pass & 1, sk);
+        k_radix_scatter<<<C.ntiles, kSortThreads, sizeof(RadixLds), s>>>(ka, va, kb, vb, ds, n,
+                                                                        shift, C, pass & 1, sk);
         uint64_t *tk = ka; ka = kb; kb = tk;
         uint32_t *tv = va; va = vb; vb = tv;
     }
     return hipGetLastError();
 }
 
-// Stable sort of (key, value) by the low `bits` bits of the keys, ping-ponging
-// between the a and b buffers; returns in *in_b whether the result sits in b.  With
-// `skip` given, the passes from `skip_from` on do nothing when *skip is set on the
-// device (keys known there to fit the lower digits); an even number of them keeps
-// the result where the full sort leaves it.
+hipError_t launch_sort(const Workspace &ws, int64_t n, hipStream_t s) {
+    const int dp = disk_passes(ws.ndisks);
+    // launch_keys wrote the keys where an even number of swaps later lands in ws.keys
+    const bool odd = (kKeyPasses + dp) % 2 == 1;
+    return radix_passes(odd ? ws.keys_alt : ws.keys, odd ? ws.idx_alt : ws.idx,
+                        odd ? ws.keys : ws.keys_alt, odd ? ws.idx : ws.idx_alt, ws.seg, n,
+                        kKeyPasses, dp, ws.hist, nullptr, 0, s);
+}
+
+// Stable sort of (key, value) by the low 63 bits of the keys, from the a buffers to the b
+// buffers, ping-ponging.  When *dense is set on the device, keys are known to be below
+// 2^low_bits and the passes above do nothing; an even number of them keeps the result where
+// the full sort leaves it.
 hipError_t launch_radix_sort(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *vb, int64_t n,
-                             int bits, uint32_t *hist, bool *in_b, hipStream_t s,
-                             const int32_t *skip, int skip_from) {
-    const int ntiles = (int)((n + kSortTile - 1) / kSortTile);
-    const int npass = (bits + 7) / 8;
-    uint32_t *totals = hist + (int64_t)256 * ntiles;
-    for (int pass = 0; pass < npass; pass++) {
-        const int32_t *sk = skip && pass >= skip_from ? skip : nullptr;
-        k_radix_hist<<<ntiles, kSortThreads, 0, s>>>(ka, va, nullptr, n, 8 * pass, hist, ntiles,
-                                                     sk);
-        k_radix_scan<<<256, 256, 0, s>>>(hist, ntiles, totals, sk);
-        k_radix_scatter<<<ntiles, kSortThreads, 0, s>>>(ka, va, kb, vb, nullptr, n, 8 * pass,
-                                                        hist, totals, ntiles, sk);
-        uint64_t *tk = ka; ka = kb; kb = tk;
-        uint32_t *tv = va; va = vb; vb = tv;
-    }
-    *in_b = npass % 2 == 1;
-    return hipGetLastError();
+                             uint32_t *hist, const int32_t *dense, int low_bits, hipStream_t s) {
+    static_assert(kKeyPasses % 2 == 1, "from a to b");
+    const int keep = (low_bits + kRadixBits - 1) / kRadixBits | 1;
+    return radix_passes(ka, va, kb, vb, nullptr, n, kKeyPasses, 0, hist, dense, keep, s);
 }
 
 // ------------------------------------------------------------------ gathers

@@ -955,25 +955,20 @@ hipError_t launch_mesh_build(const Workspace &ws, const double *x, const double 
     // the box partials use the counter partials' buffer (free during a build)
     int32_t *box_part = reinterpret_cast<int32_t *>(ws.count_part);
     const int kblk = grid_of(n, 256);
-    k_mesh_keys<<<kblk, 256, 0, s>>>(ws.st, ws.mesh, x, y, z, R, m, n, ws.mkeys, ws.midx,
-                                     box_part, ws.pack4);
+    k_mesh_keys<<<kblk, 256, 0, s>>>(ws.st, ws.mesh, x, y, z, R, m, n, ws.mkeys_alt,
+                                     ws.midx_alt, box_part, ws.pack4);
     k_mesh_box<<<1, 1024, 0, s>>>(box_part, kblk, ws.mesh, ws.mgrid_n);
     // dense grid: keys become grid indices below 2^gbits, all-ones in those bits when
-    // empty, and the sort skips the digits above (an even number of passes, so that
-    // the result lands where the full sort leaves it)
+    // empty, and the sort skips the digits above
     int gbits = 1;
-    while (gbits < 63 && (1ll << gbits) <= ws.mgrid_n) gbits++;
+    while (gbits < 62 && (1ll << gbits) <= ws.mgrid_n) gbits++;
     const uint64_t dense_empty = (1ull << gbits) - 1ull;
-    int keep = (gbits + 7) / 8;
-    if ((8 - keep) % 2) keep++;
     k_mesh_clear_table<<<4096, 256, 0, s>>>(ws.mesh, ws.mtab, ws.mtab_n, ws.mgrid, ws.mgrid_n,
-                                            ws.mkeys, n, dense_empty);
-    // eight 8-bit passes (or `keep` of them) leave the result in mkeys / midx
-    bool in_b = false;
-    hipError_t e = launch_radix_sort(ws.mkeys, ws.midx, ws.mkeys_alt, ws.midx_alt, n, 64, ws.hist,
-                                     &in_b, s, &ws.mesh->dense, keep);
+                                            ws.mkeys_alt, n, dense_empty);
+    // (the empty key's low 63 bits are above every cell's)
+    const hipError_t e = launch_radix_sort(ws.mkeys_alt, ws.midx_alt, ws.mkeys, ws.midx, n, ws.hist,
+                                           &ws.mesh->dense, gbits, s);
     if (e != hipSuccess) return e;
-    if (in_b) return hipErrorInvalidValue;
     k_mesh_runs<<<grid_of(n, 256), 256, 0, s>>>(ws.st, ws.mesh, ws.mkeys, ws.midx, ws.pack4, n,
                                                 ws.mtab, mask, ws.mgrid, ws.mpos, ws.mcell,
                                                 m ? ws.mmass : nullptr, prm.G, dense_empty);

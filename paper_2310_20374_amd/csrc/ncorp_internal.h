@@ -473,8 +473,7 @@ hipError_t launch_sum_u64(const unsigned long long *part, int64_t n, unsigned lo
                           bool add, hipStream_t s);
 // mesh module (Sect. 3.3)
 hipError_t launch_radix_sort(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t *vb, int64_t n,
-                             int bits, uint32_t *hist, bool *in_b, hipStream_t s,
-                             const int32_t *skip = nullptr, int skip_from = 0);
+                             uint32_t *hist, const int32_t *dense, int low_bits, hipStream_t s);
 // m (or nullptr): the masses, brought into mesh order with the positions; launch_mesh_gravity
 // on that mesh then has mus_packed.  acc4, packed: as in the tree's evaluation and search.
 hipError_t launch_mesh_build(const Workspace &ws, const double *x, const double *y,

@@ -90,3 +90,43 @@ def test_batched_order(nc, orc, case):  # noqa: F811
             o = orc.Tree(*(np.ascontiguousarray(dk[c][a:b]) for c in "xyz"), s)
             assert np.array_equal(perm[a:b], o.perm + a), (k, a)
             assert np.array_equal(keys[a:b], o.keys[o.perm]), (k, a)
+
+
+@pytest.mark.parametrize("disks", [1, 3, 600])
+def test_radix_sort_of_large_builds(nc, orc, disks):  # noqa: F811
+    """More moonlets than the bucket sort takes (3200 buckets): the radix sort's order."""
+    import torch
+    n = 3200 * 1792 + 4097
+    g = torch.Generator(device="cuda:0").manual_seed(7)
+    x, y, z = (torch.randn(n, generator=g, device="cuda:0", dtype=torch.float64).clamp_(-2, 2)
+               for _ in range(3))
+    x[100:300] = x[100]                                 # equal keys keep their order
+    y[100:300] = y[100]
+    z[100:300] = z[100]
+    print(f"n {n} disks {disks}", flush=True)
+    ctx = nc.Context(nc.params_default(0, leaf_size=64), n, pair_capacity=1 << 12)
+    off = torch.linspace(0, n, disks + 1).round().to(torch.int64)
+    off[-1] = n
+    if disks == 1:
+        ctx.build_tree(x, y, z)
+    else:
+        ctx.build_tree_batched(off.to("cuda:0"), x, y, z)
+    torch.cuda.synchronize()
+    ctx.check_status()
+    keys = ctx.export("keys")
+    perm = ctx.export("perm").astype(np.int64)
+    assert np.array_equal(np.sort(perm), np.arange(n))
+    o = off.numpy()
+    inner = np.ones(n - 1, bool)
+    inner[o[1:-1] - 1] = False                          # across a disk boundary
+    up = (keys[1:] > keys[:-1]) | ((keys[1:] == keys[:-1]) & (perm[1:] > perm[:-1]))
+    assert up[inner].all()
+    assert np.array_equal(np.searchsorted(o, perm, side="right"),
+                          np.searchsorted(o, np.arange(n), side="right"))
+    # the keys themselves, on a sample of one disk against the oracle
+    if disks == 1:
+        L = float(ctx.tree_info()["L"]) if "L" in ctx.tree_info() else 2.0 ** 2
+        take = np.sort(np.random.default_rng(1).choice(n, 4000, replace=False))
+        xs = [v.cpu().numpy()[perm[take]] for v in (x, y, z)]
+        t = orc.Tree(*(np.ascontiguousarray(v) for v in xs), 8, L)
+        assert np.array_equal(t.keys, keys[take])

@@ -73,3 +73,28 @@ def test_step_brings_the_masses_along(nc):
     for k, c in enumerate("xyz"):
         want = d[c] + dt * (d["v" + c] + 0.5 * dt * a[:, k])
         assert np.abs(got[c] - want).max() < 1e-14 * np.abs(d[c]).max()
+
+
+@pytest.mark.parametrize("n", [4096, 4097, 65536, 65537])
+def test_sort_at_its_edges(nc, orc, n):
+    """The mesh's sort at the edges of a tile and of its groups of tiles.  A massless
+    moonlet far away makes the box larger than the dense grid, so that the cells are
+    hashed and sorted by all digits: the same sums and pairs in another order."""
+    d = _gas(n)
+    g, dt = (n ** (-1 / 3)) * 1.3, 1e-4
+    d["R"][:] = 0.2 * g
+    d["R"][1] = 2 * g                                   # out of the mesh
+    d["m"][0], d["R"][0] = 0.0, 1e-9
+    far = {k: v.copy() for k, v in d.items()}
+    for k in "xyz":
+        d[k][0], far[k][0] = 1.2, 40.0
+    print(f"n {n}", flush=True)
+    a, pairs, st, _ = _mesh_run(nc, d, _prm(nc, g, 64), dt, cap=1 << 18)
+    b, fpairs, fst, _ = _mesh_run(nc, far, _prm(nc, g, 64), dt, cap=1 << 18)
+    assert st["n_out"] == 1 and fst["n_out"] == 1
+    assert rel_err(a[1:], b[1:])[1] < 1e-11
+    assert np.array_equal(pairs, fpairs)
+    assert np.array_equal(pairs, orc.pairs_grid(d, dt))
+    if n <= 4097:
+        assert rel_err(a[1:], orc.mesh_accel(d, g)[1:])[1] < 1e-11
+        assert st["neighbours"] == orc.mesh_neighbours(d, g)
