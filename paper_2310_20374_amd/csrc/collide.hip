@@ -626,10 +626,14 @@ __device__ __forceinline__ void rank_long(int64_t n, const int64_t *__restrict__
 __global__ void __launch_bounds__(kWave * kRankSplit)
 k_rank_pairs(DevState *__restrict__ st, const int64_t *__restrict__ in, int64_t cap,
              int64_t *__restrict__ out, const unsigned long long *__restrict__ tests_part,
-             int n_part, const RankResolve RR, const RankReport RP) {
+             int n_part, const RankResolve RR, const RankReport RP,
+             int32_t *__restrict__ walk_ctr) {
     __shared__ RankLds lds;
     auto &tile_all = lds.d.tile;
     auto &part = lds.d.part;
+    // the next search's reaches start at zero
+    if (blockIdx.x == 0 && threadIdx.x < kWalkClasses)
+        *(double *)(walk_ctr + threadIdx.x * kCtrStride + kCtrReach) = 0.0;
     const int sum_b = (int)blockIdx.x - ((int)gridDim.x - kRankSumBlocks);
     if (tests_part && sum_b >= 0) {
         // the pair tests' per-block counts, summed by the last kRankSumBlocks blocks
@@ -745,18 +749,24 @@ __device__ __forceinline__ CBox leaf_box(const double4 *__restrict__ cbox, int c
 
 // One wave per leaf: every moonlet's (x, y, z, R + dt |v|) record for the culling, the
 // tight box of the leaf's moonlets with their largest R + dt |v|, and the largest of
-// all moonlets (for the cubes of internal cells).
+// all moonlets (for the M2L lists), as maxima on the 64 counter lines, which the walk's init
+// or the last search's ranking left at zero: a line takes a few hundred atomics at most
+// (16384 waves), some 4 us among the other work, where a block adding up partial maxima took
+// 5 to 7 us in a launch of its own.  The pair, test and candidate counts of the search
+// start here.
 __global__ void __launch_bounds__(kWave)
 k_leaf_boxes(DevState *st, const double *__restrict__ xs, const double *__restrict__ ys,
              const double *__restrict__ zs, const double4 *__restrict__ pack4,
              const uint32_t *__restrict__ perm, double dt, const int32_t *__restrict__ ent_cell,
              const int32_t *__restrict__ c_first, const int32_t *__restrict__ c_count,
              double4 *__restrict__ cbox, double4 *__restrict__ pcol,
-             double4 *__restrict__ vcol, unsigned long long *__restrict__ part) {
-    if (st->status & kSkipMask) {
-        if (threadIdx.x == 0) part[blockIdx.x] = 0ull;
-        return;
+             double4 *__restrict__ vcol, int32_t *__restrict__ walk_ctr,
+             int32_t *__restrict__ cand_ctr) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) { st->npairs = 0; st->col_tests = 0; }
+        cand_ctr[threadIdx.x * kCtrStride] = 0;
     }
+    if (st->status & kSkipMask) return;
     const int K = st->nleaves;
     const int lane = threadIdx.x;
     double wmax = 0.0;
@@ -790,37 +800,14 @@ k_leaf_boxes(DevState *st, const double *__restrict__ xs, const double *__restri
         }
         wmax = fmax(wmax, ex);
     }
-    // per-block partial maxima (reaches are >= 0, so their bit patterns order like the
-    // values); one atomic per block on a single word would serialise the grid
-    if (lane == 0) part[blockIdx.x] = (unsigned long long)__double_as_longlong(wmax);
+    // reaches are >= 0, so their bit patterns order like the values
+    if (lane == 0 && wmax > 0.0)
+        atomicMax((unsigned long long *)(walk_ctr + blockIdx.x % kWalkClasses * kCtrStride +
+                                         kCtrReach),
+                  (unsigned long long)__double_as_longlong(wmax));
 }
 
-// st->reach_max = the largest of the n partials
-__global__ void __launch_bounds__(1024)
-k_max_u64(const unsigned long long *__restrict__ part, int64_t n, DevState *st,
-          int32_t *cand_ctr) {
-    __shared__ unsigned long long red[1024 / kWave];
-    // the box pass precedes every search on the gravity lists: the pair, test and
-    // candidate counts of that search start here
-    if (threadIdx.x == 0) { st->npairs = 0; st->col_tests = 0; }
-    if (threadIdx.x < kCandRegions) cand_ctr[threadIdx.x * kCtrStride] = 0;
-    unsigned long long v = 0;
-    for (int64_t i = threadIdx.x; i < n; i += 1024) v = part[i] > v ? part[i] : v;
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long w = __shfl_xor(v, o);
-        v = w > v ? w : v;
-    }
-    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long t = 0;
-        for (int k = 0; k < 1024 / kWave; k++) t = red[k] > t ? red[k] : t;
-        st->reach_max = t;
-    }
-}
-
-// waves of the box pass: 16384, or one per leaf slot of a small tree (the maximum over
-// its partials then reads less)
+// waves of the box pass: 16384, or one per leaf slot of a small tree
 constexpr int kBoxGrid = 16384;
 
 hipError_t launch_leaf_boxes(const Workspace &ws, int64_t n, double dt, hipStream_t s) {
@@ -828,8 +815,7 @@ hipError_t launch_leaf_boxes(const Workspace &ws, int64_t n, double dt, hipStrea
     const int64_t g = ws.leaf_cap < kBoxGrid ? ws.leaf_cap : kBoxGrid;
     k_leaf_boxes<<<(int)g, kWave, 0, s>>>(ws.st, ws.xs, ws.ys, ws.zs, ws.pack4, ws.idx, dt,
                                           ws.ent_cell, ws.c_first, ws.c_count,
-                                          ws.cbox, ws.pcol, ws.vcol, ws.count_part);
-    k_max_u64<<<1, 1024, 0, s>>>(ws.count_part, g, ws.st, cand_out(ws).ctr);
+                                          ws.cbox, ws.pcol, ws.vcol, ws.walk_ctr, cand_out(ws).ctr);
     return hipGetLastError();
 }
 
@@ -845,6 +831,7 @@ struct CandArgs {
     const float *leaf_slack;
     const uint16_t *seg;                 // batched: disk of every tree position, else nullptr
     const double *disk_L;
+    const int32_t *walk_ctr;
 };
 
 // The candidate leaf pairs (c, l), l later than c in leaf order, below the lanes' list
@@ -895,7 +882,9 @@ k_cand_leaves(DevState *st, const CandArgs A, const CandOut C) {
     int2 *const buf = bufs[wid];
     const int cls = (int)blockIdx.x % kCandRegions;
     const int K = st->nleaves;
-    const double r = __longlong_as_double((long long)st->reach_max);
+    // the largest reach of all moonlets: a line a lane
+    double r = *(const double *)(A.walk_ctr + lane * kCtrStride + kCtrReach);
+    for (int o = kWave / 2; o > 0; o >>= 1) r = fmax(r, __shfl_xor(r, o));
     int nb = 0;
     for (int e = blockIdx.x * kCandWaves + wid; e < K; e += gridDim.x * kCandWaves) {
         const int c = A.ent_cell[e];
@@ -945,6 +934,7 @@ hipError_t launch_candidates_from_lists(const Workspace &ws, hipStream_t s) {
     A.leaf_slack = ws.leaf_slack;
     A.seg = ws.ndisks > 1 ? ws.seg : nullptr;
     A.disk_L = ws.disk_L;
+    A.walk_ctr = ws.walk_ctr;
     k_cand_leaves<<<(int)g, kWave * kCandWaves, 0, s>>>(ws.st, A, cand_out(ws));
     return hipGetLastError();
 }
@@ -1252,7 +1242,7 @@ hipError_t launch_resolve(const Workspace &ws, double *x, double *y, double *z, 
                             ws.mbest};
     k_rank_pairs<<<kRankGrid, kWave * kRankSplit, 0, s>>>(ws.st, ws.pairs_tmp, ws.pair_cap,
                                                           ws.pairs_alt, tests_part, n_part, RR,
-                                                          RankReport{});
+                                                          RankReport{}, ws.walk_ctr);
     // the unsorted list is no longer needed: its buffer holds the live pair indices
     k_resolve<<<kResolveBlocks, kResolveThreads, 0, s>>>(ws.st, ws.pairs_alt, ws.pair_cap, ws.pair_dt,
                                             ws.pair_flag, ws.mbest, ws.mmatch,
@@ -1281,7 +1271,7 @@ hipError_t launch_emit_pairs(const Workspace &ws, int64_t *pairs, int64_t cap,
     const RankReport RP = {pairs, cap, cursor, triple, step};
     k_rank_pairs<<<kRankGrid, kWave * kRankSplit, 0, s>>>(ws.st, ws.pairs_tmp, ws.pair_cap,
                                                           ws.pairs_alt, tests_part, n_part,
-                                                          RankResolve{}, RP);
+                                                          RankResolve{}, RP, ws.walk_ctr);
     k_pairs_done<<<1, 64, 0, s>>>(ws.st, n_pairs_dev, cap, ws.pair_cap, triple, cursor);
     return hipGetLastError();
 }

@@ -73,7 +73,8 @@ constexpr int kWalkClasses = 64;
 // of the pairs visited, well separated and summed directly, of the long lists and,
 // in timing runs, of its waves' busy cycles (sum, maximum, waves).
 constexpr int kCtrTicket = 0, kCtrSpace = 2, kCtrVisited = 4, kCtrM2L = 6, kCtrP2P = 7,
-              kCtrLongM2L = 8, kCtrBusy = 10, kCtrBusyMax = 12, kCtrWaves = 14, kCtrLongP2P = 9;
+              kCtrLongM2L = 8, kCtrBusy = 10, kCtrBusyMax = 12, kCtrWaves = 14, kCtrLongP2P = 9,
+              kCtrReach = 16;
 // the collision candidates lie in kCandRegions equal parts of their list, each with a
 // counter line of its own after the walk's
 constexpr int kCandRegions = 64;
@@ -132,8 +133,6 @@ struct DevState {
     int64_t p2p_inter;         // directed moonlet pairs (i != j) of the direct sums
     // the most source moonlets any leaf's direct sums take (timing runs only)
     int64_t p2p_src_max;
-    // collisions: the largest R + dt |v| of any moonlet (bit pattern of a double >= 0)
-    unsigned long long reach_max;
     // bucket sort: the splitters the last bucket sort left for the next one are valid
     // (bs_valid: 1, or 2 from a batched build) for bs_n moonlets under root half-width bs_L (kept by the reset of a
     // fresh build); the last sort took its buckets from them (bs_prev_used) and sorted
