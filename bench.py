@@ -42,11 +42,11 @@ FLOPS_PER_INTERACTION = 20  # directed moonlet pair, the usual N-body convention
 # reported only while it is unchanged.
 # Measured per leaf size (the direct sums' work depends on it).
 P2P_TRAFFIC = {"source": "paper_2310_20374_amd/csrc/p2p.hip",
-               "blob": "24806f309f8c8f758dd3293823e9518d4bee879f",
+               "blob": "b78ed8f2a1a4b94f0eb903c23580039e820bb332",
                "fetch_scale": 2.00, "write_scale": 1.00,
                # measured launch shape: (leaf size, source tile, most targets per lane)
-               "by_shape": {(96, 256, 4): {"fetch_kib": (198843.8,), "write_kib": (25534.3,)},
-                            (96, 128, 4): {"fetch_kib": (197890.7,), "write_kib": (25499.9,)}}}
+               "by_shape": {(96, 256, 4): {"fetch_kib": (155549.8,), "write_kib": (33472.5,)},
+                            (96, 128, 4): {"fetch_kib": (157039.8,), "write_kib": (33468.9,)}}}
 
 
 def _git_blob(path):

@@ -929,7 +929,7 @@ extern "C" int ncorp_step_noalloc(ncorp_ctx *c, double *x, double *y, double *z,
     if (r != NCORP_OK) return r;
     // Another call (of any context) may have used this GPU's array since this context
     // last did: forget every binding so the call starts from cleared device state
-    // (status word, walk queue, mesh state), as on a new workspace.
+    // (status word, walk counters, mesh state), as on a new workspace.
     c->ws = Workspace{};
     c->mesh_init = false;
     c->have_mesh = false;

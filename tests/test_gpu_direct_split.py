@@ -1,8 +1,8 @@
 """Direct sums dealt to several waves a leaf, at the edges of the deal.
 
 A leaf's sums are split into up to eight slots by the work it has, its list taken 64
-source cells and 256 moonlets at a time; FP32 deals whole tiles, FP64 equal shares.  The
-cases: a tree of one leaf below, at and above a wave and a tile; few leaves of several
+source cells and 256 moonlets at a time; FP32 deals strands of whole batches of cells (one
+strand up to 64 cells, eight beyond), FP64 equal shares.  The cases: a tree of one leaf below, at and above a wave and a tile; few leaves of several
 target chunks; lists beyond 64 cells with fewer and with more batches than slots; a tree
 with and one without split leaves; a tile of 128 and of 512.  FP64 differs from the
 oracle by the order of sums only (1e-11).  In FP32 an offset from the leaf centre carries
