@@ -125,7 +125,7 @@ __device__ __forceinline__ int list_strands(int len) {
 // about 10 us of dependent loads before its first tile, hence the lower limit; in between
 // four interactions a leaf, and never so many that the heaviest leaves are left whole.
 // The rule knows its own tree only, so a disk's sums are the same in a batch and alone.
-// Unsplit -> split, direct sums alone: 9973 moonlets in 519 leaves (FP64) 129 -> 46 us, 1e6
+// Unsplit -> split (FP32 at four waves a SIMD), direct sums alone: 9973 moonlets in 519 leaves (FP64) 129 -> 46 us, 1e6
 // in 2.7e4 FP32 582 -> 433 us; a quantum of 2048 instead for 1e5 in 2700: 88 -> 103 us.
 constexpr int64_t kQuantumMin = 2048, kQuantumMax = 49152;
 constexpr uint32_t kListed = 0x100;     // a leaf's slots: it is in the list
@@ -167,7 +167,7 @@ __device__ __forceinline__ void split_leaf(DevState *st, const SplitArgs &S, int
     }
     // listed, to start first: what is split, long or heavy; a list that cannot hold every
     // leaf is left empty.  Heavy in FP32 from a quantum on, in FP64 from half of one: at
-    // N = 1e6 without the heavy ones 515 us (FP32) and 603 us, from a quantum on 433 and
+    // N = 1e6 without the heavy ones 515 us (FP32, four waves a SIMD) and 603 us, from a quantum on 433 and
     // 581 us, from half of one 502 and 542 us.
     const bool heavy = (S.fp32 ? work : 2 * work) > quantum;
     const int add = (slots > 1 || lng || heavy) && most > 0 ? (int)slots : 0;
@@ -580,9 +580,15 @@ static_assert(kP2PListLDS == kP2PSrc, "one LDS batch holds a list that is not lo
 // order.  The split and the long leaves come first, so they start first and the others
 // fill in around them within the same launch, which the hardware deals out as waves end:
 // blocks of one wave, an item each.  Four waves a block and items by position took 582 us
-// at N = 1e6, s = 96 in FP32, where this takes 433; persistent waves with counters 490.
+// at N = 1e6, s = 96 in FP32, where this takes 423; persistent waves with counters 490.
+//
+// Five waves a SIMD, 96 registers: vector instructions of different waves overlap in part,
+// and a fifth wave is worth more than the registers it spills between the tiles.  FP32 with
+// four waves (125 registers, none spilled) 434 us at 1e6, 342 for 64 batched disks, 3100
+// for 4e6 in clumps; with five 423, 331, 2920; with six (91 spilled) 429, 334, 2920 and
+// 1e5 moonlets 86.7 instead of 83.
 template <typename T, int TILE>
-__global__ void __launch_bounds__(kWave, sizeof(T) == 8 ? 5 : 4)
+__global__ void __launch_bounds__(kWave, 5)
 k_p2p(const DevState *__restrict__ st, const double4 *__restrict__ pos4,
       const int32_t *__restrict__ ent_cell,
       const int32_t *__restrict__ c_first, const int32_t *__restrict__ c_count,
