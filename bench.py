@@ -42,11 +42,11 @@ FLOPS_PER_INTERACTION = 20  # directed moonlet pair, the usual N-body convention
 # reported only while it is unchanged.
 # Measured per leaf size (the direct sums' work depends on it).
 P2P_TRAFFIC = {"source": "paper_2310_20374_amd/csrc/p2p.hip",
-               "blob": "b78ed8f2a1a4b94f0eb903c23580039e820bb332",
+               "blob": "2ffb5f52fbe1c57c2ac0ea0609dbe13dc108839a",
                "fetch_scale": 2.00, "write_scale": 1.00,
                # measured launch shape: (leaf size, source tile, most targets per lane)
-               "by_shape": {(96, 256, 4): {"fetch_kib": (155549.8,), "write_kib": (33472.5,)},
-                            (96, 128, 4): {"fetch_kib": (157039.8,), "write_kib": (33468.9,)}}}
+               "by_shape": {(96, 256, 4): {"fetch_kib": (176852.9,), "write_kib": (44501.0,)},
+                            (96, 128, 4): {"fetch_kib": (178488.9,), "write_kib": (44522.1,)}}}
 
 
 def _git_blob(path):

@@ -125,8 +125,9 @@ __device__ __forceinline__ int list_strands(int len) {
 // about 10 us of dependent loads before its first tile, hence the lower limit; in between
 // four interactions a leaf, and never so many that the heaviest leaves are left whole.
 // The rule knows its own tree only, so a disk's sums are the same in a batch and alone.
-// Unsplit -> split (FP32 at four waves a SIMD), direct sums alone: 9973 moonlets in 519 leaves (FP64) 129 -> 46 us, 1e6
-// in 2.7e4 FP32 582 -> 433 us; a quantum of 2048 instead for 1e5 in 2700: 88 -> 103 us.
+// Unsplit -> split, direct sums alone (FP32 at four waves a SIMD): 9973 moonlets in 519
+// leaves (FP64) 129 -> 46 us, 1e6 in 2.7e4 FP32 582 -> 433 us; a quantum of 2048 instead
+// for 1e5 in 2700: 88 -> 103 us.
 constexpr int64_t kQuantumMin = 2048, kQuantumMax = 49152;
 constexpr uint32_t kListed = 0x100;     // a leaf's slots: it is in the list
 struct SplitArgs {
@@ -167,8 +168,8 @@ __device__ __forceinline__ void split_leaf(DevState *st, const SplitArgs &S, int
     }
     // listed, to start first: what is split, long or heavy; a list that cannot hold every
     // leaf is left empty.  Heavy in FP32 from a quantum on, in FP64 from half of one: at
-    // N = 1e6 without the heavy ones 515 us (FP32, four waves a SIMD) and 603 us, from a quantum on 433 and
-    // 581 us, from half of one 502 and 542 us.
+    // N = 1e6 without the heavy ones 515 us (FP32, four waves a SIMD) and 603 us, from a
+    // quantum on 433 and 581 us, from half of one 502 and 542 us.
     const bool heavy = (S.fp32 ? work : 2 * work) > quantum;
     const int add = (slots > 1 || lng || heavy) && most > 0 ? (int)slots : 0;
     S.src[e] = (uint32_t)slots | (add > 0 ? kListed : 0u);
