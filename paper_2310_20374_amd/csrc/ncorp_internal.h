@@ -7,15 +7,13 @@
 #include <stdint.h>
 
 #include "../../include/ncorp.h"
+#include "walk_plan.h"
 
 namespace ncorp {
 
 constexpr int kMaxDepth = 21;          // 63-bit keys: 21 levels of 3 bits
 constexpr int kMaxP = 6;
 constexpr int kWave = 64;
-// The hardware deals the workgroups of a launch to the 8 XCDs in turn (workgroup b
-// runs on XCD b mod 8), and each XCD has its own L2.
-constexpr int kXcds = 8;
 // counters that many waves add to: each on a 128-byte line of its own
 constexpr int kCtrStride = 32;
 // the climbs deal their leaves to this many classes of waves
@@ -79,8 +77,6 @@ constexpr int kCtrTicket = 0, kCtrSpace = 2, kCtrVisited = 4, kCtrM2L = 6, kCtrP
 // counter line of its own after the walk's
 constexpr int kCandRegions = 64;
 constexpr int kCandBuf = 2 * kWave;       // candidates a wave stages before it takes room
-// hand-down entries a cell keeps in a slot of its own
-constexpr int64_t kWalkInline = 64;
 // the plain cell-pair lists carry this many slots on top of the caller's capacity
 // (256 for each of the walk_waves asked for, 1024 by default, 512 at least)
 inline int64_t list_slack(const ncorp_params &p) {

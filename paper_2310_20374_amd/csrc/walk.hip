@@ -480,21 +480,12 @@ hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_po
     WalkArgs A = {};
     A.st = ws.st; A.wq = ws.wq; A.hdr = hdr; A.ctr = ws.walk_ctr;
     A.ncs = ncs; A.ncc_pre = ncc_pre; A.ncc_post = ncc_post;
-    // List space: the 2 queue_cap words set aside for a walk's open pairs, or those of
-    // p2p_cap pairs where a caller asked for a smaller queue than that.  A
-    // pair is handed down at most once, so queue_cap words hold a walk of queue_cap
-    // visits; the rest is inline slots where it reaches, and room for segment heads and
-    // inherited direct-sum pairs.
-    const bool own = ws.queue_cap >= ws.p2p_cap;
-    const int64_t words = 2 * (own ? ws.queue_cap : ws.p2p_cap);
-    A.space = own ? reinterpret_cast<int32_t *>(ws.queue)
-                  : reinterpret_cast<int32_t *>(ws.p2p);
+    const ListSpace sp = list_space(ws.queue_cap, ws.p2p_cap, ws.cell_cap);
+    A.space = sp.own ? reinterpret_cast<int32_t *>(ws.queue) : reinterpret_cast<int32_t *>(ws.p2p);
     A.visit_cap = ws.queue_cap;
-    A.inl = words / 2 >= kWalkInline * ws.cell_cap &&
-                    words - kWalkInline * ws.cell_cap >= ws.queue_cap
-                ? (int)kWalkInline : 0;
-    A.shared0 = (int64_t)A.inl * ws.cell_cap;
-    A.shared_n = (words - A.shared0) / kXcds;
+    A.inl = sp.inl;
+    A.shared0 = sp.shared0;
+    A.shared_n = sp.shared_n;
     if (mode == 0) {
         A.cell = ws.wg;
         A.m2l_cnt = ws.m2l_cnt; A.m2l_seg = ws.m2l_seg; A.m2l_stride = ws.m2l_stride;
