@@ -63,9 +63,6 @@ constexpr int kBucketTile = 2048;
 constexpr int kSubStride = 8;
 constexpr int kWalkBlock = 256;
 constexpr int kWalkWavesMax = 2048;       // the largest walk_waves
-// a walk deals its cells in runs of kWalkRun to kWalkClasses classes of waves
-constexpr int kWalkRun = 8;
-constexpr int kWalkClasses = 64;
 // Counters of a walk, one 128-byte line per class (kCtrStride words): the ticket, the
 // entries taken of the shared list space (the first kXcds lines), and the class's part
 // of the pairs visited, well separated and summed directly, of the long lists and,

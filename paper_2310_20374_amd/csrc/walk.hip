@@ -21,9 +21,11 @@
 // in breadth-first order within each, by the waves of that class, from a ticket counter
 // (atomics on one address take about 15 ns each, so counters are many and nothing else
 // is counted per cell).  A wave waits until its cell's parent has published its list;
-// a class hands out its cells in ascending order and a parent precedes its children,
-// so the lowest unfinished cell never waits on an unclaimed one and the launch ends.  A
-// wave that polls for too long without progress latches ST_WALK_STALL and leaves.
+// a class hands out its cells in ascending order and a parent precedes its children.
+// Where another stream's kernel leaves room for a few workgroups only, the waves that run
+// take the cells they wait for from classes that have none (walk_plan.h), so the launch
+// ends whatever runs beside it.  A wave that polls for too long without progress latches
+// ST_WALK_STALL and leaves.
 //
 // What bounds it: the chain of levels, about 6 us each (the parent's list, one or two
 // rounds of cell loads, publication), and for large or deep trees the rounds' loads.
@@ -81,7 +83,9 @@ constexpr int kDown = 256;                   // hand-down entries staged
 struct WalkLds {
     int32_t stack[kStack];
     int32_t down[kDown];
+    int held[kWalkHeld];                     // cells put aside
 };
+static_assert(kMaxDepth + 2 < kWalkHeld, "a cell a level, and the next one");
 template <int MODE> struct WalkPairs { int2 p[kCandBuf]; };      // collisions: candidates staged
 template <> struct WalkPairs<0> { int2 p[1]; };
 
@@ -161,6 +165,24 @@ __device__ __forceinline__ void flush_down(const WalkArgs &A, int xcd, const int
     n = 0;
 }
 
+// the classes' ticket counters (WaveTurns)
+struct Tickets {
+    int32_t *ctr;
+    int lane;
+    __device__ int take(int cls) const {
+        return lane == 0 ? atomicAdd(walk_ctr(ctr, cls, kCtrTicket), 1) : 0;
+    }
+    __device__ int value(int v) const { return __builtin_amdgcn_readlane(v, 0); }
+    __device__ int taken(int cls) const {
+        return __builtin_amdgcn_readfirstlane(ld_relaxed(walk_ctr(ctr, cls, kCtrTicket)));
+    }
+    __device__ bool claim(int cls, int t) const {
+        int old = 0;
+        if (lane == 0) old = atomicCAS(walk_ctr(ctr, cls, kCtrTicket), t, t + 1);
+        return __builtin_amdgcn_readlane(old, 0) == t;
+    }
+};
+
 template <int MODE>
 __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
     constexpr int WPB = kWalkBlock / kWave;
@@ -175,20 +197,16 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
     __syncthreads();
     const int nc = A.wq->ncells;
     const int cls = (int)blockIdx.x % kWalkClasses, xcd = cls % kXcds;
-    int32_t *ticket = walk_ctr(A.ctr, cls, kCtrTicket);
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const long long t_start = (MODE == 0 && A.timing) ? clock64() : 0;
     unsigned long long visited = 0;
     int nm2l = 0, np2p = 0, nlongm = 0, nlongp = 0;           // pairs of the cells taken; long lists
     int npb = 0;                                  // candidates staged
-    int nxt = 0;
-    if (lane == 0) nxt = atomicAdd(ticket, 1);
-    for (;;) {
-        const int i = __builtin_amdgcn_readlane(nxt, 0);
-        const int64_t c64 = ((int64_t)(i / kWalkRun) * kWalkClasses + cls) * kWalkRun + i % kWalkRun;
-        if (i < 0 || c64 >= nc) break;
-        if (lane == 0) nxt = atomicAdd(ticket, 1);   // the next ticket, in flight meanwhile
-        const int c = (int)c64;
+    const Tickets tickets = {A.ctr, lane};
+    WaveTurns turns;
+    turns.start(tickets, cls);
+    int c = 0;
+    while (turns.get(tickets, W.held, nc, c)) {
         const WCell wa = A.cell[c];
         const int par = wa.parent;
         const bool leaf = wa.nchild == 0;
@@ -204,14 +222,18 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
         } else {
             uint64_t h = 0;
             uint32_t spins = 0;
+            bool aside = false;
             for (;;) {
                 h = ld_relaxed(&A.hdr[par]);
                 if (__builtin_amdgcn_readfirstlane((int)(uint32_t)(h >> 32)) != 0 ||
                     ++spins > kSpinLimit)
                     break;
+                if ((spins & (turns.patience - 1)) == 0 && (aside = turns.help(tickets, W.held, c, par)))
+                    break;
                 if (spins < 16) __builtin_amdgcn_s_sleep(4);
                 else __builtin_amdgcn_s_sleep(16);
             }
+            if (aside) continue;
             const uint32_t hl = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)h);
             const uint32_t hh = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(h >> 32));
             if (hh == 0) {                        // waited too long

@@ -57,3 +57,99 @@ def test_list_offsets_fit_32_bits(tmp_path):
         assert shared0 == inl * c and inl in (0, 64)
         assert shared_n >= 0 and shared0 + 8 * shared_n <= words
         assert inl == 0 or (shared0 <= words // 2 and words - shared0 >= q)
+
+
+# Waves in blocks of four, block b of class b mod 64, of which `room` blocks run at a time;
+# the next one starts when one has ended.  A scheduler picks a running wave at random; it
+# does one thing: get a cell, finish it if its parent is finished, or poll once more.  No
+# wave leaves for a full round of polls of all of them without a cell finished in between:
+# then the walk is stuck.
+TURNS = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <vector>
+#include "walk_plan.h"
+using namespace ncorp;
+struct Mem {
+    std::vector<int> ctr = std::vector<int>(kWalkClasses, 0);
+    int take(int k) { return ctr[k]++; }
+    int value(int v) { return v; }
+    int taken(int k) { return ctr[k]; }
+    bool claim(int k, int t) { if (ctr[k] != t) return false; ctr[k]++; return true; }
+};
+struct Wave { WaveTurns t; int held[kWalkHeld]; int c = -1, polls = 0; bool begun = false; };
+int main(int, char **a) {
+    const int nc = atoi(a[1]), depth = atoi(a[2]), blocks = atoi(a[3]), room = atoi(a[4]);
+    const bool help = atoi(a[5]) != 0;
+    std::mt19937 rng(atoi(a[6]));
+    // a breadth-first tree: levels of growing size, children of consecutive cells in order
+    std::vector<int> par(nc, -1);
+    int lo = 0, hi = 1;
+    for (int l = 1; l < depth && hi < nc; l++) {
+        const int left = depth - l, want = l == depth - 1 ? nc - hi : 1 + (int)(rng() % (1 + (nc - hi) / left));
+        const int n = want < nc - hi ? want : nc - hi;
+        for (int q = 0; q < n; q++) par[hi + q] = lo + (int)((long long)q * (hi - lo) / n);
+        lo = hi;
+        hi += n;
+    }
+    const int cells = hi;
+    Mem m;
+    std::vector<int> done(cells, 0);
+    std::vector<Wave> waves(4 * blocks);
+    std::vector<int> run;
+    int started = 0, most = 0;
+    long long finished = 0, idle = 0;
+    std::vector<int> left(blocks, 4);
+    auto admit = [&]() {
+        int running = 0;
+        for (int b = 0; b < started; b++) running += left[b] > 0;
+        while (started < blocks && running < room) {
+            for (int w = 0; w < 4; w++) run.push_back(4 * started + w);
+            started++;
+            running++;
+        }
+    };
+    admit();
+    while (!run.empty()) {
+        const int at = (int)(rng() % run.size()), id = run[at];
+        Wave &w = waves[id];
+        if (!w.begun) { w.t.start(m, id / 4 % kWalkClasses); w.begun = true; }
+        if (w.c < 0) {
+            if (!w.t.get(m, w.held, cells, w.c)) {
+                run[at] = run.back();
+                run.pop_back();
+                if (--left[id / 4] == 0) admit();
+                idle = 0;
+                continue;
+            }
+            w.polls = 0;
+        }
+        if (par[w.c] < 0 || done[par[w.c]]) {
+            if (done[w.c]++) { printf("twice %d\n", w.c); return 0; }
+            finished++;
+            idle = 0;
+            w.c = -1;
+        } else {
+            if (++w.polls % w.t.patience == 0 && help && w.t.help(m, w.held, w.c, par[w.c])) w.c = -1;
+            if (w.t.nheld > most) most = w.t.nheld;
+            if (++idle > 400ll * (long long)run.size() + 100000) { printf("stuck %lld\n", finished); return 0; }
+        }
+    }
+    printf("%s %lld %d %d\n", finished == cells ? "all" : "missing", finished, cells, most);
+}
+"""
+
+
+def test_walk_ends_with_few_workgroups_running(tmp_path):
+    """Every cell is walked once however few of the walk's workgroups run at a time; with
+    fewer than the classes and no helping, the walk would be stuck."""
+    run = host_program(tmp_path, TURNS)
+    for seed in range(6):
+        for nc, depth in ((1, 1), (9, 3), (700, 5), (5000, 12), (30000, 21), (600, 21)):
+            for blocks, room in ((64, 1), (64, 3), (128, 17), (256, 63), (256, 256)):
+                word, finished, cells, most = run(nc, depth, blocks, room, 1, seed).split()
+                assert word == "all" and finished == cells, (nc, depth, blocks, room, seed)
+                assert int(most) <= depth + 1
+    assert run(30000, 12, 64, 3, 0, 1).startswith("stuck")
+    assert run(30000, 12, 64, 64, 0, 1).startswith("all")
