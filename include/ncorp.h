@@ -306,8 +306,9 @@ int ncorp_step_noalloc(ncorp_ctx *ctx, double *x, double *y, double *z, double *
 
 /* Waits for the context's last stream, then reports the device status word:
  * NCORP_OK, NCORP_E_CAPACITY (required_capacity, if not NULL, receives the size
- * that would have sufficed for the list that overflowed), NCORP_E_INVALID (bad
- * disk offsets of a batched call) or NCORP_E_NONFINITE.
+ * that would have sufficed for the list that overflowed; a walk whose lists outgrew
+ * their space before all its pairs were visited asks for twice its queue_capacity),
+ * NCORP_E_INVALID (bad disk offsets of a batched call) or NCORP_E_NONFINITE.
  * The status is cleared by the next ncorp_build_tree / ncorp_step. */
 int ncorp_get_status(ncorp_ctx *ctx, int64_t *required_capacity);
 

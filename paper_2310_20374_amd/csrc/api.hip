@@ -328,11 +328,16 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.c_crmax = (double *)take(8 * cell_cap);
     ws.wg = (WCell *)take(sizeof(WCell) * cell_cap);
     ws.wc = (WCell *)take(sizeof(WCell) * cell_cap);
-    ws.queue = (uint64_t *)take(8 * q_cap);
-    // (the size of a plain list of the well-separated pairs, which are listed per target:
-    // the size a caller computes for an n must not shrink or grow)
-    ws.split_p2p = (int32_t *)take(8 * m2l_cap);
-    ws.p2p = (int2 *)take(8 * p2p_cap);
+    // the space of a walk's hand-down lists: as much as a queue of q_cap pairs and plain lists
+    // of the well-separated and the direct-sum pairs would take, which the walk's bound on
+    // the lists goes by; the direct sums' slots lie in it once the walk is over
+    {
+        const int64_t at = off;
+        ws.space = (int32_t *)take(8 * q_cap);
+        ws.split_p2p = (int32_t *)take(8 * m2l_cap);
+        (void)take(8 * p2p_cap);
+        ws.space_words = (off - at) / 4;
+    }
     ws.cand = (int2 *)take(8 * p2p_cap);
     if (ws.p > 0) {
         ws.m2l_cnt = (int32_t *)take(4 * cell_cap);

@@ -289,9 +289,9 @@ struct Workspace {
     WCell *wg = nullptr, *wc = nullptr;               // walk records: gravity, collisions
     double *c_crmax = nullptr;
     // walks
-    uint64_t *queue = nullptr;                        // a walk's hand-down lists
     WalkQueue *wq = nullptr;
-    int2 *p2p = nullptr;                              // room of p2p_cap pairs (list space)
+    int32_t *space = nullptr;                         // a walk's hand-down lists
+    int64_t space_words = 0;
     int2 *cand = nullptr;                             // collision candidate cell pairs
     int32_t *walk_ctr = nullptr;                      // counter lines (walk, candidates)
     float *leaf_slack = nullptr;                      // per leaf: slack of its chain (walk)
@@ -299,6 +299,7 @@ struct Workspace {
     int32_t *m2l_cnt = nullptr, *m2l_seg = nullptr;   // by target cell, m2l_stride slots
     int32_t *p2p_cnt = nullptr, *p2p_seg = nullptr;   // by target leaf, p2p_stride slots
     int32_t *split_p2p = nullptr;                     // slots of split or long direct sums
+                                                      // (in the space of the walk's lists)
     int32_t *long_p2p = nullptr;                      // leaves with a long direct-sum list
     double *p2p_part = nullptr;                       // kLongSlots x 3 x n partial sums
     int32_t *cnt_a = nullptr;                         // tree-build level counters

@@ -8,7 +8,9 @@
 // and
 //   - where B is split, goes on with (A, B's children) at once, from a stack in LDS;
 //   - where A is split, leaves B in A's hand-down list, which A's children start from;
-//   - where the pair is well separated or summed directly, appends B to A's own lists.
+//   - where the pair is well separated or summed directly, appends B to A's own lists (if
+//     A is not a leaf, a direct-sum pair goes into the hand-down list: the leaves below A
+//     inherit it).
 // Classification is symmetric in A and B bit for bit (sums, squares and comparisons
 // that commute, and ties broken by which cell holds the earlier moonlets), so the wave
 // of B takes the same decision on the same pair: the pairs are those of the recursion,
@@ -79,7 +81,9 @@ __global__ void k_walk_init(DevState *st, WalkQueue *wq, uint64_t *hdr, int32_t 
 constexpr int kStack = 640;
 constexpr int kStackFree = 160;
 static_assert(7 * kMaxDepth < kStackFree, "a depth-first descent must fit");
-constexpr int kDown = 256;                   // hand-down entries staged
+// hand-down entries staged: the cell's own, and what it inherits (as much as a slot holds)
+constexpr int kDownOwn = 192, kDownInherit = 64, kDown = kDownOwn + kDownInherit;
+static_assert(kDownInherit == kWalkInline && kDownOwn >= kWave, "a slot, and a round");
 struct WalkLds {
     int32_t stack[kStack];
     int32_t down[kDown];
@@ -89,17 +93,28 @@ static_assert(kMaxDepth + 2 < kWalkHeld, "a cell a level, and the next one");
 template <int MODE> struct WalkPairs { int2 p[kCandBuf]; };      // collisions: candidates staged
 template <> struct WalkPairs<0> { int2 p[1]; };
 
-// A hand-down list is published as one 64-bit header per cell: valid | inline | slack
-// (16 bits, see below) | entry count (12 bits) | offset (32 bits) of its last segment in
-// the list space.  A list of
-// up to WalkArgs.inl entries sits in the cell's own slot of inl entries; a longer one
-// in segments of the shared space, each preceded by the offset and size of the one
-// before it (offset -1: none).  An entry is a cell B, with kDownDirect set where (A, B)
-// is a direct-sum pair that every leaf below A inherits.
+// A hand-down list is published as one 64-bit header per cell: valid | inline | linked |
+// above | slack (16 bits, see below) | direct | entry count (9 bits) | offset (32 bits) of
+// its last segment in the list space.  A list of up to WalkArgs.inl entries sits in the
+// cell's own slot of inl entries; a longer one in segments of the shared space, of which
+// all but the first start with the offset and the size (and link) of the one before.  An
+// entry is a cell B, with kDownDirect set where (A, B) is a direct-sum pair ("direct": the
+// list has some).
+//
+// A leaf below A inherits A's direct-sum pairs.  A cell that comes in between copies what
+// its parent's list has of them into its own slot, after its own entries, if all that fits;
+// if not it copies none and is marked "above": the leaf then goes up its ancestors' lists,
+// from the parent to the first that is not marked, and takes their direct-sum pairs.  The
+// leaf meets them in the same order either way.  So the shared space holds nobody's
+// inheritance, and what it needs is bounded by the visits (list_space).
 constexpr int32_t kDownDirect = (int32_t)0x80000000;
-__device__ __forceinline__ uint64_t down_header(bool inl, uint32_t slack16, int n, uint32_t off) {
-    return (1ull << 63) | ((uint64_t)(inl ? 1 : 0) << 62) | ((uint64_t)slack16 << 44) |
-           ((uint64_t)n << 32) | off;
+constexpr int kDownCount = 0x1ff, kDownLinked = 0x200;       // a segment's size and link
+constexpr uint32_t kHdrInline = 1u << 30, kHdrLinked = 1u << 29, kHdrAbove = 1u << 28,
+                   kHdrDirect = 1u << 11;                    // in the header's upper half
+static_assert(kDownOwn <= kDownCount && kWalkInline <= kDownCount, "counts of 9 bits");
+__device__ __forceinline__ uint64_t down_header(uint32_t flags, uint32_t slack16, int n,
+                                                uint32_t off) {
+    return ((uint64_t)(0x80000000u | flags | (slack16 << 12) | (uint32_t)n) << 32) | off;
 }
 // The smallest r_crit - r_max of a cell and its ancestors, as the upper half of a float,
 // rounded towards zero: the moonlets of a cell and of any well-separated partner are at
@@ -134,8 +149,9 @@ __device__ __forceinline__ void latch_cap(DevState *st, int32_t bit, int64_t nee
     atomicMax((unsigned long long *)&st->required, (unsigned long long)need);
 }
 
-// n entries of the shared list space, from this XCD's region or the next with room;
-// returns their offset, or -1 (latched) when no region has any.
+// n words of the shared list space, from this XCD's region or the next with room; returns
+// their offset, or -1 when no region has any: the walk then visits more than queue_cap
+// pairs, by how many is not known, and twice the capacity is asked for.
 __device__ __forceinline__ int64_t take_space(const WalkArgs &A, int xcd, int n, int lane) {
     for (int t = 0; t < kXcds; t++) {
         const int x = (xcd + t) % kXcds;
@@ -146,24 +162,62 @@ __device__ __forceinline__ int64_t take_space(const WalkArgs &A, int xcd, int n,
             return A.shared0 + (int64_t)x * A.shared_n + old;
         if (lane == 0) atomicSub(walk_ctr(A.ctr, x, kCtrSpace), n);   // no room: taken back
     }
-    if (lane == 0) latch_cap(A.st, ST_CAP_QUEUE, 2 * A.visit_cap);
+    const int64_t twice = 2 * A.visit_cap;
+    if (lane == 0)
+        latch_cap(A.st, ST_CAP_QUEUE,
+                  twice > kMaxQueue && A.visit_cap < kMaxQueue ? kMaxQueue : twice);
     return -1;
 }
 
 // Writes the staged hand-down entries as a segment after (poff, pn), which it replaces.
 __device__ __forceinline__ void flush_down(const WalkArgs &A, int xcd, const int32_t *down, int &n,
                                            int lane, int &poff, int &pn) {
-    const int64_t off = take_space(A, xcd, n + 2, lane);
+    const int head = poff >= 0 ? 2 : 0;
+    const int64_t off = take_space(A, xcd, n + head, lane);
     if (off >= 0) {
         wave_sync();
-        if (lane < 2) st_relaxed(&A.space[off + lane], lane == 0 ? poff : pn);
-        for (int i = lane; i < n; i += kWave) st_relaxed(&A.space[off + 2 + i], down[i]);
+        if (lane < head) st_relaxed(&A.space[off + lane], lane == 0 ? poff : pn);
+        for (int i = lane; i < n; i += kWave) st_relaxed(&A.space[off + head + i], down[i]);
         wave_sync();
         poff = (int)off;
-        pn = n;
+        pn = n | (head ? kDownLinked : 0);
     }
     n = 0;
 }
+
+// a cell's header, wave-uniform (upper 0: not published)
+struct Header {
+    uint32_t lower, upper;
+};
+__device__ __forceinline__ Header read_header(const WalkArgs &A, int cell) {
+    const uint64_t h = ld_relaxed(&A.hdr[cell]);
+    return {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)h),
+            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(h >> 32))};
+}
+
+// What is left to take of a hand-down list: one segment, and the one before it.
+struct DownReader {
+    int64_t off = 0;
+    int n = 0, prev = -1, prev_n = 0;
+
+    // the segment of size and link `pn` at o
+    __device__ __forceinline__ void segment(const int32_t *space, int64_t o, int pn) {
+        n = pn & kDownCount;
+        prev = -1;
+        if (pn & kDownLinked) {
+            prev = __builtin_amdgcn_readfirstlane(ld_relaxed(&space[o]));
+            prev_n = __builtin_amdgcn_readfirstlane(ld_relaxed(&space[o + 1]));
+            o += 2;
+        }
+        off = o;
+    }
+    // the list of a cell with header h
+    __device__ __forceinline__ void list(const WalkArgs &A, int cell, const Header &h) {
+        const int count = (int)(h.upper & kDownCount);
+        if (h.upper & kHdrInline) segment(A.space, (int64_t)cell * A.inl, count);
+        else segment(A.space, h.lower, count | (h.upper & kHdrLinked ? kDownLinked : 0));
+    }
+};
 
 // the classes' ticket counters (WaveTurns)
 struct Tickets {
@@ -184,7 +238,7 @@ struct Tickets {
 };
 
 template <int MODE>
-__global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
+__global__ void __launch_bounds__(kWalkBlock, 6) k_walk(const WalkArgs A) {
     constexpr int WPB = kWalkBlock / kWave;
     __shared__ WalkLds lds_all[WPB];
     __shared__ WalkPairs<MODE> pairs_all[WPB];
@@ -213,70 +267,98 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
         int top = 0;                              // open pairs on the stack
         uint32_t slack = 0;
         if (MODE == 0) slack = slack_bits(wa.rcrit - A.c_rmax[c]);
-        int64_t in_off = 0;                       // entries of the parent's list left to take
-        int in_n = 0, in_prev = -1;
-        int in_prev_n = 0;
+        DownReader in;                            // the parent's list (then its ancestors')
+        int anc = par;                            // whose it is
+        bool above = false;                       // direct-sum pairs to inherit from beyond it
         if (par < 0) {
             if (lane == 0) W.stack[0] = c;
             top = 1;
         } else {
-            uint64_t h = 0;
+            Header h;
             uint32_t spins = 0;
             bool aside = false;
             for (;;) {
-                h = ld_relaxed(&A.hdr[par]);
-                if (__builtin_amdgcn_readfirstlane((int)(uint32_t)(h >> 32)) != 0 ||
-                    ++spins > kSpinLimit)
-                    break;
+                h = read_header(A, par);
+                if (h.upper != 0 || ++spins > kSpinLimit) break;
                 if ((spins & (turns.patience - 1)) == 0 && (aside = turns.help(tickets, W.held, c, par)))
                     break;
                 if (spins < 16) __builtin_amdgcn_s_sleep(4);
                 else __builtin_amdgcn_s_sleep(16);
             }
             if (aside) continue;
-            const uint32_t hl = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)h);
-            const uint32_t hh = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(h >> 32));
-            if (hh == 0) {                        // waited too long
+            if (h.upper == 0) {                   // waited too long
                 if (lane == 0) atomicOr(&A.st->status, (int32_t)ST_WALK_STALL);
                 break;
             }
-            in_n = (int)(hh & 0xfffu);
-            const uint32_t ps = (hh >> 12) & 0xffffu;
+            const uint32_t ps = (h.upper >> 12) & 0xffffu;
             slack = ps < slack ? ps : slack;
-            if (hh & 0x40000000u) {
-                in_off = (int64_t)par * A.inl;
-            } else if (in_n > 0) {
-                in_off = (int64_t)hl + 2;
-                in_prev = __builtin_amdgcn_readfirstlane(ld_relaxed(&A.space[hl]));
-                in_prev_n = __builtin_amdgcn_readfirstlane(ld_relaxed(&A.space[hl + 1]));
-            }
+            above = MODE == 0 && (h.upper & kHdrAbove);
+            in.list(A, par, h);
         }
         unsigned src = 0;                         // this lane's direct-sum sources
-        int nm = 0, np = 0, nd = 0;               // own lists, staged hand-down entries
+        int nm = 0, np = 0, nd = 0, ni = 0;       // own lists, staged own and inherited entries
+        bool direct_down = false;                 // own direct-sum pairs among those
         int seg_off = -1, seg_n = 0;              // last hand-down segment written
         int32_t *const mrow = MODE == 0 ? A.m2l_seg + (int64_t)c * A.m2l_stride : nullptr;
         int32_t *const prow = MODE == 0 ? A.p2p_seg + (int64_t)wa.entry * A.p2p_stride : nullptr;
         for (;;) {
             // ---- take entries of the parent's list while the stack is short
-            if (top < kWave && (in_n > 0 || in_prev >= 0)) {
-                if (in_n == 0) {                  // the segment before this one
-                    const int o = in_prev;
-                    in_n = in_prev_n;
-                    in_off = (int64_t)o + 2;
-                    in_prev = __builtin_amdgcn_readfirstlane(ld_relaxed(&A.space[o]));
-                    in_prev_n = __builtin_amdgcn_readfirstlane(ld_relaxed(&A.space[o + 1]));
+            while (top < kWave) {
+                if (in.n == 0) {
+                    if (in.prev >= 0) {           // the segment before this one
+                        in.segment(A.space, in.prev, in.prev_n);
+                    } else if (leaf && above) {   // what the ancestor above has to inherit
+                        anc = A.cell[anc].parent;
+                        const Header h = read_header(A, anc);   // its child has waited for it
+                        above = h.upper & kHdrAbove;
+                        if (h.upper & kHdrDirect) in.list(A, anc, h);
+                        if (h.upper == 0 && lane == 0)
+                            atomicOr(&A.st->status, (int32_t)ST_BAD_ITEM);
+                    } else {
+                        break;
+                    }
+                    continue;
                 }
-                const int m = in_n < 4 * kWave ? in_n : 4 * kWave;
-                int32_t e[4];
+                const int m = in.n;               // a whole segment
+                constexpr int kRounds = kDownOwn / kWave;
+                static_assert(kRounds * kWave == kDownOwn && kWalkInline <= kDownOwn, "whole rounds");
+                int32_t e[kRounds];
 #pragma unroll
-                for (int u = 0; u < 4; u++)
-                    e[u] = u * kWave + lane < m ? ld_relaxed(&A.space[in_off + u * kWave + lane]) : 0;
+                for (int u = 0; u < kRounds; u++)
+                    e[u] = u * kWave + lane < m ? ld_relaxed(&A.space[in.off + u * kWave + lane]) : 0;
+                in.n = 0;
 #pragma unroll
-                for (int u = 0; u < 4; u++)
-                    if (u * kWave + lane < m) W.stack[top + u * kWave + lane] = e[u];
-                top += m;
-                in_off += m;
-                in_n -= m;
+                for (int u = 0; u < kRounds; u++) {
+                    if (u * kWave >= m) break;
+                    const bool have = u * kWave + lane < m;
+                    const uint64_t md = MODE == 0 ? __ballot(have && e[u] < 0) : 0ull;
+                    if (md == 0 && anc == par) {
+                        if (have) W.stack[top + lane] = e[u];
+                        top += m - u * kWave < kWave ? m - u * kWave : kWave;
+                        continue;
+                    }
+                    // direct-sum pairs, and of an ancestor's list nothing else
+                    if (leaf) {
+                        const int B = e[u] & 0x7fffffff, pos = np + __popcll(md & lt);
+                        if (have && e[u] < 0) {
+                            if ((uint32_t)B >= (uint32_t)nc) {       // cannot happen either
+                                atomicOr(&A.st->status, (int32_t)ST_BAD_ITEM);
+                            } else {
+                                if (pos < A.p2p_stride) prow[pos] = B;
+                                src += (unsigned)A.cell[B].count;
+                            }
+                        }
+                        np += __popcll(md);
+                        if (anc != par) continue;
+                    } else {
+                        const int pos = ni + __popcll(md & lt);
+                        if (have && e[u] < 0 && pos < kDownInherit) W.down[kDownOwn + pos] = e[u];
+                        ni += __popcll(md);
+                    }
+                    const uint64_t mo = __ballot(have && e[u] >= 0);
+                    if ((mo >> lane) & 1) W.stack[top + __popcll(mo & lt)] = e[u];
+                    top += __popcll(mo);
+                }
             }
             if (top == 0) break;
             wave_sync();
@@ -287,15 +369,10 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
             for (;;) {
                 kind = 0; npush = 0; down = 0; B = -1; child = 0; cnt = 0;
                 if (lane < k) {
-                    const int32_t v = W.stack[top - 1 - lane];
-                    B = v & 0x7fffffff;
+                    B = W.stack[top - 1 - lane];
                     if ((uint32_t)B >= (uint32_t)nc) {    // cannot happen; never follow it
                         atomicOr(&A.st->status, (int32_t)ST_BAD_ITEM);
                         B = -1;
-                    } else if (v < 0) {
-                        kind = 3;                         // a direct-sum pair of an ancestor
-                        down = v;
-                        if (MODE == 0 && leaf) cnt = A.cell[B].count;
                     } else if (B == c) {
                         if (wa.count <= A.ncs || leaf) { kind = 2; down = B | kDownDirect; cnt = wa.count; }
                         else { kind = 4; down = B; }
@@ -350,7 +427,7 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
             top -= k;
             for (int q = 0; q < npush; q++) W.stack[top + off + q] = child + q;
             top += tot;
-            visited += __popcll(__ballot(B >= 0 && kind != 3 && kind != 5 && c <= B));
+            visited += __popcll(__ballot(B >= 0 && kind != 5 && c <= B));
             // ---- A's own lists
             if (MODE == 0) {
                 const uint64_t m1 = __ballot(kind == 1);
@@ -361,7 +438,7 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
                     nm2l += __popcll(__ballot(kind == 1 && c < B));
                 }
             }
-            const bool direct = kind == 2 || (MODE == 0 && kind == 3);
+            const bool direct = kind == 2;
             const uint64_t m2 = __ballot(direct);
             if (m2) {
                 if (MODE == 0 && leaf) {
@@ -370,10 +447,10 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
                     if (direct) src += (unsigned)cnt;
                     np += __popcll(m2);
                 }
-                const uint64_t mo = __ballot(kind == 2 && c <= B);   // once per unordered pair
+                const uint64_t mo = __ballot(direct && c <= B);      // once per unordered pair
                 np2p += __popcll(mo);
                 if (MODE == 1) {
-                    if (kind == 2 && c <= B) pbuf[npb + __popcll(mo & lt)] = make_int2(c, B);
+                    if (direct && c <= B) pbuf[npb + __popcll(mo & lt)] = make_int2(c, B);
                     npb += __popcll(mo);
                     if (npb > kCandBuf - kWave) flush_cand(pbuf, npb, lane, cls, A.cand, A.st);
                 }
@@ -381,7 +458,8 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
             const bool todown = kind == 4 || (MODE == 0 && direct && !leaf);
             const uint64_t md = __ballot(todown);
             if (md) {
-                if (nd + __popcll(md) > kDown) flush_down(A, xcd, W.down, nd, lane, seg_off, seg_n);
+                if (MODE == 0) direct_down = direct_down || __any(direct);
+                if (nd + __popcll(md) > kDownOwn) flush_down(A, xcd, W.down, nd, lane, seg_off, seg_n);
                 if (todown) W.down[nd + __popcll(md & lt)] = down;
                 nd += __popcll(md);
             }
@@ -389,14 +467,20 @@ __global__ void __launch_bounds__(kWalkBlock) k_walk(const WalkArgs A) {
         // ---- publish: the children may start
         if (!leaf) {
             uint64_t h;
+            const bool copied = MODE == 0 && !above && seg_off < 0 && nd + ni <= A.inl;
+            uint32_t flags = (above || (ni > 0 && !copied) ? kHdrAbove : 0u) |
+                             (direct_down || (copied && ni > 0) ? kHdrDirect : 0u);
             if (seg_off < 0 && nd <= A.inl) {
+                const int all = copied ? nd + ni : nd;
                 wave_sync();
-                for (int q = lane; q < nd; q += kWave)
-                    st_relaxed(&A.space[(int64_t)c * A.inl + q], W.down[q]);
-                h = down_header(true, slack, nd, 0u);
+                for (int q = lane; q < all; q += kWave)
+                    st_relaxed(&A.space[(int64_t)c * A.inl + q],
+                               W.down[q < nd ? q : kDownOwn + (q - nd)]);
+                h = down_header(flags | kHdrInline, slack, all, 0u);
             } else {
                 if (nd > 0) flush_down(A, xcd, W.down, nd, lane, seg_off, seg_n);
-                h = down_header(false, slack, seg_off < 0 ? 0 : seg_n,
+                if (seg_n & kDownLinked) flags |= kHdrLinked;
+                h = down_header(flags, slack, seg_off < 0 ? 0 : seg_n & kDownCount,
                                 seg_off < 0 ? 0u : (uint32_t)seg_off);
             }
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -502,8 +586,8 @@ hipError_t launch_walk(Workspace &ws, int mode, int ncs, int ncc_pre, int ncc_po
     WalkArgs A = {};
     A.st = ws.st; A.wq = ws.wq; A.hdr = hdr; A.ctr = ws.walk_ctr;
     A.ncs = ncs; A.ncc_pre = ncc_pre; A.ncc_post = ncc_post;
-    const ListSpace sp = list_space(ws.queue_cap, ws.p2p_cap, ws.cell_cap);
-    A.space = sp.own ? reinterpret_cast<int32_t *>(ws.queue) : reinterpret_cast<int32_t *>(ws.p2p);
+    const ListSpace sp = list_space(ws.space_words, ws.queue_cap, ws.cell_cap);
+    A.space = ws.space;
     A.visit_cap = ws.queue_cap;
     A.inl = sp.inl;
     A.shared0 = sp.shared0;

@@ -28,35 +28,39 @@ SPACE = r"""
 int main(int argc, char **argv) {
     for (int i = 1; i + 2 < argc; i += 3) {
         const auto s = ncorp::list_space(atoll(argv[i]), atoll(argv[i + 1]), atoll(argv[i + 2]));
-        printf("%d %lld %d %lld %lld\n", s.own ? 1 : 0, (long long)s.words, s.inl,
-               (long long)s.shared0, (long long)s.shared_n);
+        printf("%lld %d %lld %lld\n", (long long)s.words, s.inl, (long long)s.shared0,
+               (long long)s.shared_n);
     }
 }
 """
 
-# (queue_cap, p2p_cap, cell_cap): small and usual sizes; the queue's limit; pair lists
-# around 2^30 (a space of 2^31 words), beyond it, and beyond 2^32 pairs
-CASES = [(1, 131073, 1024), (262145, 262145, 2024), (70_000_000, 12_000_000, 300_000),
-         (100_000_000, 99_999_999, (1 << 24) - 2), (100_000_000, 537_000_000, (1 << 24) - 2)]
-CASES += [(q, p, c) for q in (1, 100_000_000) for c in (1, 200_000, (1 << 24) - 2)
+# (queue_cap, m2l_cap, p2p_cap, cell_cap): small, usual and tight sizes; the queue's limit;
+# pair lists around and beyond 2^30 and 2^32 pairs
+SLACK = 1 << 17
+CASES = [(1, SLACK + 1, SLACK + 1, 1024), (15047, SLACK + 1, SLACK + 1, 49024),
+         (800_000, 400_000, 270_000, 2024), (70_000_000, 40_000_000, 20_000_000, 300_000),
+         (100_000_000, 99_999_999, 99_999_999, (1 << 24) - 2),
+         (100_000_000, 1_080_000_000, 537_000_000, (1 << 24) - 2)]
+CASES += [(q, m, p, c) for q in (1, 100_000_000) for c in (1, 200_000, (1 << 24) - 2)
+          for m in (SLACK + 1, 1 << 30)
           for p in ((1 << 30) - 1, 1 << 30, (1 << 30) + 1, 1_230_000_000, (1 << 31) + 7,
                     (1 << 33) + 5)]
 
 
 def test_list_offsets_fit_32_bits(tmp_path):
     """Every offset into the hand-down lists' space is a non-negative 32-bit number
-    (negative means no list) inside the buffer, whatever the capacities."""
+    (negative means no list) inside the buffer, whatever the capacities, and the regions
+    hold two entries a visit, the segments' heads and the regions' unused ends: as long as
+    the offsets allow, for any queue_cap that the library takes."""
     run = host_program(tmp_path, SPACE)
-    out = run(*[v for c in CASES for v in c]).split("\n")
-    for (q, p, c), line in zip(CASES, out):
-        own, words, inl, shared0, shared_n = map(int, line.split())
-        assert own == (q >= p)
-        buffer = 2 * (q if own else p)
-        assert words <= buffer and words <= 2 ** 31 - 1
-        assert words == min(buffer, 2 ** 31 - 1)           # and no less than that
+    buffers = [2 * (q + m + p) for q, m, p, _ in CASES]
+    out = run(*[v for w, (q, _, _, c) in zip(buffers, CASES) for v in (w, q, c)]).split("\n")
+    for (q, m, p, c), buffer, line in zip(CASES, buffers, out):
+        words, inl, shared0, shared_n = map(int, line.split())
+        assert words == min(buffer, 2 ** 31 - 1)
         assert shared0 == inl * c and inl in (0, 64)
         assert shared_n >= 0 and shared0 + 8 * shared_n <= words
-        assert inl == 0 or (shared0 <= words // 2 and words - shared0 >= q)
+        assert 8 * (shared_n - 300) >= 2 * q * (1 + 2 / 128), (q, m, p, c)
 
 
 # Waves in blocks of four, block b of class b mod 64, of which `room` blocks run at a time;
