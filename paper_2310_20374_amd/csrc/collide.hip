@@ -765,6 +765,7 @@ k_leaf_boxes(DevState *st, const double *__restrict__ xs, const double *__restri
     if (blockIdx.x == 0) {
         if (threadIdx.x == 0) { st->npairs = 0; st->col_tests = 0; }
         cand_ctr[threadIdx.x * kCtrStride] = 0;
+        if (threadIdx.x == 0) cand_ctr[kCandRefused] = 0;
     }
     if (st->status & kSkipMask) return;
     const int K = st->nleaves;

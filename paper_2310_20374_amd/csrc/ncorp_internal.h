@@ -184,7 +184,10 @@ __device__ __forceinline__ int32_t *walk_ctr(int32_t *ctr, int cls, int what) {
     return ctr + cls * kCtrStride + what;
 }
 
-// Collision candidates (cell pairs) of a pass: kCandRegions regions of `per` slots.
+// Collision candidates (cell pairs) of a pass: kCandRegions regions of `per` slots.  A
+// region's counter is word 0 of its line; word kCandRefused of the first line counts the
+// candidates that no region had room for.
+constexpr int kCandRefused = 1;
 struct CandOut {
     int2 *list;
     int32_t *ctr;              // first counter line
@@ -234,9 +237,11 @@ __device__ __forceinline__ void flush_cand(const int2 *buf, int &n, int lane, in
         if (lane == 0) atomicSub(C.ctr + x * kCtrStride, n);       // no room: taken back
     }
     if (t == kCandRegions && lane == 0) {
+        // the last to be refused reports them all
+        const int before = atomicAdd(C.ctr + kCandRefused, n);
         atomicOr(&st->status, (int32_t)ST_CAP_P2P);
         atomicMax((unsigned long long *)&st->required,
-                  (unsigned long long)(C.per * kCandRegions + n));
+                  (unsigned long long)(C.per * kCandRegions) + (unsigned)before + (unsigned)n);
     }
     n = 0;
 }
