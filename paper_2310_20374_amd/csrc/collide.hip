@@ -511,7 +511,7 @@ struct RankReport {
 };
 
 // What is done with the pair of key v and rank r.
-__device__ __forceinline__ void ranked(int64_t v, int64_t r, int64_t *__restrict__ out,
+__device__ __forceinline__ void ranked(int64_t v, int64_t r, int64_t *out,
                                        const RankResolve &RR, bool resolve,
                                        const RankReport &RP) {
     if (RP.pairs) {
@@ -541,11 +541,14 @@ __device__ __forceinline__ void ranked(int64_t v, int64_t r, int64_t *__restrict
 // Beyond kRankDirect pairs: block g of G ranks the keys between splitters g and g + 1 of a
 // sorted sample of the list (four samples a block, the same sample and sort in every
 // block).  It reads the whole list once, counts the keys below its range, gathers its own
-// in LDS (about kRankOwn of them) and counts those against each other; a range of more than
-// kRankRoom keys is ranked against the list instead.  Counting all against all took 946 us
-// for the 66000 pairs of 4e6 clumped moonlets, this 95.
+// in LDS (about kRankOwn of them) and counts those against each other.  A range of more
+// than kRankRoom keys (a list of millions, or an uneven sample) is gathered in memory, in
+// the block's part of a buffer of the list's size, counted against itself by way of LDS
+// and ranked in place.  Counting all against all took 946 us for the 66000 pairs of 4e6
+// clumped moonlets, this 95.
 constexpr int64_t kRankDirect = 4096;
 constexpr int kRankOwn = 512, kRankSamples = 2048, kRankRoom = 4096;
+constexpr int kRankHeld = 8;         // keys a thread counts at a time, of a large range
 union RankLds {
     struct {
         int64_t tile[kRankSplit][kRankChunk];
@@ -560,7 +563,7 @@ union RankLds {
 };
 
 __device__ __forceinline__ void rank_long(int64_t n, const int64_t *__restrict__ in,
-                                          int64_t *__restrict__ out, RankLds &lds,
+                                          int64_t *out, int64_t *tmp, RankLds &lds,
                                           const RankResolve &RR, bool resolve,
                                           const RankReport &RP) {
     constexpr int T = kWave * kRankSplit;
@@ -614,18 +617,47 @@ __device__ __forceinline__ void rank_long(int64_t n, const int64_t *__restrict__
         }
         return;
     }
-    for (int64_t a = t; a < n; a += T) {
-        const int64_t v = in[a];
-        if (v < lo || v >= hi) continue;
-        int64_t rk = 0;
-        for (int64_t k = 0; k < n; k++) rk += in[k] < v;
-        ranked(v, rk, out, RR, resolve, RP);
+    // ranks base .. base + m - 1 are this block's: so are those places of tmp and out
+    int64_t *keys = tmp + base, *sorted = out + base;
+    __syncthreads();
+    if (t == 0) lds.l.nown = 0;
+    __syncthreads();
+    for (int64_t q = t; q < n; q += T) {
+        const int64_t v = in[q];
+        if (v >= lo && v < hi) keys[atomicAdd(&lds.l.nown, 1)] = v;
     }
+    __syncthreads();
+    for (int64_t a0 = 0; a0 < m; a0 += kRankHeld * T) {
+        int64_t v[kRankHeld];
+        int rk[kRankHeld];
+#pragma unroll
+        for (int u = 0; u < kRankHeld; u++) {
+            const int64_t a = a0 + u * T + t;
+            v[u] = a < m ? keys[a] : INT64_MIN;          // (none below it)
+            rk[u] = 0;
+        }
+        for (int k0 = 0; k0 < m; k0 += kRankRoom) {
+            const int len = m - k0 < kRankRoom ? m - k0 : kRankRoom;
+            __syncthreads();
+            for (int k = t; k < len; k += T) lds.l.own[k] = keys[k0 + k];
+            __syncthreads();
+            for (int k = 0; k < len; k++) {
+                const int64_t w = lds.l.own[k];
+#pragma unroll
+                for (int u = 0; u < kRankHeld; u++) rk[u] += w < v[u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kRankHeld; u++)
+            if (a0 + u * T + t < m) sorted[rk[u]] = v[u];
+    }
+    __syncthreads();
+    for (int64_t a = t; a < m; a += T) ranked(sorted[a], base + a, out, RR, resolve, RP);
 }
 
 __global__ void __launch_bounds__(kWave * kRankSplit)
 k_rank_pairs(DevState *__restrict__ st, const int64_t *__restrict__ in, int64_t cap,
-             int64_t *__restrict__ out, const unsigned long long *__restrict__ tests_part,
+             int64_t *out, int64_t *tmp, const unsigned long long *__restrict__ tests_part,
              int n_part, const RankResolve RR, const RankReport RP,
              int32_t *__restrict__ walk_ctr) {
     __shared__ RankLds lds;
@@ -659,7 +691,9 @@ k_rank_pairs(DevState *__restrict__ st, const int64_t *__restrict__ in, int64_t 
     const bool resolve = RR.dtc && n <= cap && !(st->status & kSkipMask);
     if (n > cap) n = cap;
     if (n > kRankDirect) {
-        rank_long(n, in, out, lds, RR, resolve, RP);
+        // (tmp is the contact times' buffer: a block's places there are its own, and it
+        // writes its contact times after its last use of them)
+        rank_long(n, in, out, tmp, lds, RR, resolve, RP);
         return;
     }
     const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
@@ -1242,7 +1276,8 @@ hipError_t launch_resolve(const Workspace &ws, double *x, double *y, double *z, 
     const RankResolve RR = {x, y, z, vx, vy, vz, R, dt, ws.pair_dt, ws.pair_flag, ws.mmatch,
                             ws.mbest};
     k_rank_pairs<<<kRankGrid, kWave * kRankSplit, 0, s>>>(ws.st, ws.pairs_tmp, ws.pair_cap,
-                                                          ws.pairs_alt, tests_part, n_part, RR,
+                                                          ws.pairs_alt, (int64_t *)ws.pair_dt,
+                                                          tests_part, n_part, RR,
                                                           RankReport{}, ws.walk_ctr);
     // the unsorted list is no longer needed: its buffer holds the live pair indices
     k_resolve<<<kResolveBlocks, kResolveThreads, 0, s>>>(ws.st, ws.pairs_alt, ws.pair_cap, ws.pair_dt,
@@ -1271,8 +1306,9 @@ hipError_t launch_emit_pairs(const Workspace &ws, int64_t *pairs, int64_t cap,
                              const unsigned long long *tests_part, int n_part, hipStream_t s) {
     const RankReport RP = {pairs, cap, cursor, triple, step};
     k_rank_pairs<<<kRankGrid, kWave * kRankSplit, 0, s>>>(ws.st, ws.pairs_tmp, ws.pair_cap,
-                                                          ws.pairs_alt, tests_part, n_part,
-                                                          RankResolve{}, RP, ws.walk_ctr);
+                                                          ws.pairs_alt, (int64_t *)ws.pair_dt,
+                                                          tests_part, n_part, RankResolve{}, RP,
+                                                          ws.walk_ctr);
     k_pairs_done<<<1, 64, 0, s>>>(ws.st, n_pairs_dev, cap, ws.pair_cap, triple, cursor);
     return hipGetLastError();
 }
