@@ -3,6 +3,7 @@
 // nothing waits for the GPU except the status / inspection calls.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -1071,19 +1072,47 @@ static int d2h(ncorp_ctx *c, std::vector<T> &v, const T *src, int64_t count) {
     return NCORP_OK;
 }
 
-// the first `width` (the longest length) entries of n per-target lists, packed
-static int read_rows(ncorp_ctx *c, int64_t n, const int32_t *cnt_d, const int32_t *seg,
-                     int64_t stride, std::vector<int32_t> &cnt, std::vector<int32_t> &rows,
-                     int64_t &width) {
+// n per-target lists of the gravity walk, one after the other: list t is
+// v[at[t]] .. v[at[t + 1]].  Entries are cells (others are left out); lists longer than
+// their slots end there.
+struct HostLists {
+    std::vector<int64_t> at;
+    std::vector<int32_t> v;
+};
+
+static int read_lists(ncorp_ctx *c, int64_t n, int64_t ncells, const int32_t *cnt_d,
+                      const int32_t *seg, int64_t stride, HostLists &L) {
+    std::vector<int32_t> cnt, rows;
     int r = d2h(c, cnt, cnt_d, n);
     if (r != NCORP_OK) return r;
-    width = 0;
-    for (int32_t k : cnt) width = k > width ? k : width;
-    if (width > stride) width = stride;
-    rows.resize(n * width);
-    if (!rows.empty())
-        HIPCHK(c, hipMemcpy2D(rows.data(), width * 4, seg, stride * 4, width * 4, n,
-                              hipMemcpyDeviceToHost));
+    L.at.assign(1, 0);
+    constexpr int64_t kRows = 4096;               // lists copied at a time
+    for (int64_t t0 = 0; t0 < n; t0 += kRows) {
+        const int64_t m = n - t0 < kRows ? n - t0 : kRows;
+        int64_t width = 0;
+        for (int64_t t = t0; t < t0 + m; t++) width = cnt[t] > width ? cnt[t] : width;
+        if (width > stride) width = stride;
+        rows.resize(m * width);
+        if (!rows.empty())
+            HIPCHK(c, hipMemcpy2D(rows.data(), width * 4, seg + t0 * stride, stride * 4, width * 4,
+                                  m, hipMemcpyDeviceToHost));
+        for (int64_t t = 0; t < m; t++) {
+            for (int64_t k = 0; k < cnt[t0 + t] && k < width; k++)
+                if (rows[t * width + k] >= 0 && rows[t * width + k] < ncells)
+                    L.v.push_back(rows[t * width + k]);
+            L.at.push_back((int64_t)L.v.size());
+        }
+    }
+    return NCORP_OK;
+}
+
+// Did the last gravity walk write the lists of the tree that h describes?  Not after a
+// build that failed, nor where the walk gave up.
+static int lists_written(ncorp_ctx *c, const DevState &h, bool &written) {
+    WalkQueue q;
+    HIPCHK(c, hipMemcpy(&q, c->ws.wq, sizeof(q), hipMemcpyDeviceToHost));
+    written = c->walked == 1 && h.ncells > 0 && q.ncells == h.ncells &&
+              !(h.status & (ST_WALK_STALL | ST_BAD_ITEM));
     return NCORP_OK;
 }
 
@@ -1159,39 +1188,41 @@ extern "C" int64_t ncorp_export_host(ncorp_ctx *c, int what, void *dst, int64_t 
         }
         case NCORP_EXPORT_M2L: {
             // every pair stands in both cells' lists: take it from the lower cell's
-            std::vector<int32_t> cnt, rows;
-            int64_t width = 0;
-            if ((r = read_rows(c, c->walked == 1 ? nc : 0, ws.m2l_cnt, ws.m2l_seg, ws.m2l_stride,
-                               cnt, rows, width)))
+            bool written = false;
+            HostLists L;
+            if ((r = lists_written(c, h, written)) ||
+                (r = read_lists(c, written ? nc : 0, nc, ws.m2l_cnt, ws.m2l_seg, ws.m2l_stride, L)))
                 return r;
             std::vector<int2> v;
-            for (int64_t A = 0; A < (int64_t)cnt.size(); A++)
-                for (int64_t k = 0; k < cnt[A] && k < width; k++)
-                    if (rows[A * width + k] > A)
-                        v.push_back(make_int2((int)A, rows[A * width + k]));
+            for (int64_t A = 0; A + 1 < (int64_t)L.at.size(); A++)
+                for (int64_t k = L.at[A]; k < L.at[A + 1]; k++)
+                    if (L.v[k] > A) v.push_back(make_int2((int)A, L.v[k]));
             put(v.data(), 8 * (int64_t)v.size()); break;
         }
         case NCORP_EXPORT_P2P: {
             // a cell pair (A, B) stands as B in the list of every leaf below A and as A in
-            // that of every leaf below B: take it from A's first leaf, the lower cell's
-            std::vector<int32_t> cnt, rows, ent, nent;
-            int64_t width = 0;
-            const int64_t nl = c->walked == 1 ? h.nleaves : 0;
-            if ((r = read_rows(c, nl, ws.p2p_cnt, ws.p2p_seg, ws.p2p_stride, cnt, rows, width)) ||
-                (r = d2h(c, ent, ws.c_entry, nc)) || (r = d2h(c, nent, ws.c_nent, nc)))
+            // that of every leaf below B: take it from A's first leaf, the lower cell's.  Of
+            // the cells whose first leaf that is, A is the one that B's first leaf lists.
+            bool written = false;
+            if ((r = lists_written(c, h, written))) return r;
+            const int64_t nl = written ? h.nleaves : 0;
+            HostLists L;
+            std::vector<int32_t> first, par, leaf;
+            if ((r = read_lists(c, nl, nc, ws.p2p_cnt, ws.p2p_seg, ws.p2p_stride, L)) ||
+                (r = d2h(c, first, ws.c_entry, nc)) || (r = d2h(c, par, ws.c_parent, nc)) ||
+                (r = d2h(c, leaf, ws.ent_cell, nl)))
                 return r;
-            auto len = [&](int64_t e) { return cnt[e] < width ? (int64_t)cnt[e] : width; };
+            std::vector<int32_t> sorted = L.v;
+            for (int64_t e = 0; e < nl; e++)
+                std::sort(sorted.begin() + L.at[e], sorted.begin() + L.at[e + 1]);
             std::vector<int2> v;
             for (int64_t e = 0; e < nl; e++)
-                for (int64_t k = 0; k < len(e); k++) {
-                    const int32_t B = rows[e * width + k];
-                    const int64_t f = ent[B];
-                    for (int64_t q = 0; q < len(f); q++) {
-                        const int32_t A = rows[f * width + q];
-                        if (e < ent[A] || e >= ent[A] + nent[A]) continue;
-                        if (e == ent[A] && A <= B) v.push_back(make_int2(A, B));
-                        break;
-                    }
+                for (int64_t k = L.at[e]; k < L.at[e + 1]; k++) {
+                    const int32_t B = L.v[k], f = first[B];
+                    for (int32_t A = leaf[e]; A >= 0 && first[A] == e; A = par[A])
+                        if (A <= B && std::binary_search(sorted.begin() + L.at[f],
+                                                         sorted.begin() + L.at[f + 1], A))
+                            v.push_back(make_int2(A, B));
                 }
             put(v.data(), 8 * (int64_t)v.size()); break;
         }
