@@ -331,13 +331,16 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.wc = (WCell *)take(sizeof(WCell) * cell_cap);
     // the space of a walk's hand-down lists: as much as a queue of q_cap pairs and plain lists
     // of the well-separated and the direct-sum pairs would take, which the walk's bound on
-    // the lists goes by; the direct sums' slots lie in it once the walk is over
+    // the lists goes by.  Once the walk is over the direct sums' slots lie in it, so it has
+    // room for kLongSlots a leaf (the capacities leave that but where a caller cuts them).
     {
-        const int64_t at = off;
+        const int64_t at = off, pairs = q_cap + m2l_cap + p2p_cap;
+        const int64_t slots = 4 * (int64_t)kLongSlots * ws.leaf_cap;
         ws.space = (int32_t *)take(8 * q_cap);
-        ws.split_p2p = (int32_t *)take(8 * m2l_cap);
-        (void)take(8 * p2p_cap);
+        (void)take(8 * m2l_cap);
+        (void)take(8 * p2p_cap + (slots > 8 * pairs ? slots - 8 * pairs : 0));
         ws.space_words = (off - at) / 4;
+        ws.split_p2p = ws.space;
     }
     ws.cand = (int2 *)take(8 * p2p_cap);
     if (ws.p > 0) {

@@ -111,15 +111,16 @@ constexpr int kP2PSrc = kWave;      // source cells per batch, one per lane (pre
 
 // FP32 sums of a list are added up in strands, each by itself: a list of one batch is one
 // strand, a longer one has kLongSlots of them (or as many as it has batches), strand v
-// taking the batches v, v + kLongSlots, ...  A leaf's waves share its strands, so its sums
-// are rounded the same however many waves it has.
+// taking the batches v, v + kLongSlots, ...  A leaf's waves share its strands, so what is
+// added up in FP32 is the same however many waves it has; the strands' sums are then added
+// in FP64, in an order that depends on them.
 __device__ __forceinline__ int list_strands(int len) {
     const int nb = (len + kP2PSrc - 1) / kP2PSrc;
     return nb < kLongSlots ? nb : kLongSlots;
 }
 
 // How many waves share a leaf's direct sums (up to kLongSlots): as many as it has shares
-// of about `quantum` moonlet interactions.  The chip holds some 6000 waves and an average
+// of about `quantum` moonlet interactions.  The chip holds some 5000 waves and an average
 // leaf has 15000 to 60000 interactions (s = 48 and 96), so a small tree's leaves are
 // all split, and in a large one only those that would outlast the others.  A share costs
 // about 10 us of dependent loads before its first tile, hence the lower limit; in between
@@ -137,7 +138,7 @@ struct SplitArgs {
     uint32_t *src;                       // per leaf: source moonlets in, slots out
     int32_t *longs;                      // leaves whose list is beyond one LDS batch
     int32_t *split;                      // slots (leaf | slot << 24) of the leaves with more
-    int64_t split_cap;                   // than one or a long list, and room for them
+                                         // than one or a long list: kLongSlots a leaf fit
     bool fp32;
 };
 __device__ __forceinline__ void split_leaf(DevState *st, const SplitArgs &S, int e, int c) {
@@ -153,10 +154,7 @@ __device__ __forceinline__ void split_leaf(DevState *st, const SplitArgs &S, int
                                        (int64_t)((S.c_count[c] + kWave - 1) / kWave)
                                  : (src + kWave - 1) / kWave;
     slots = slots < units ? slots : units;
-    int64_t most = S.split_cap / st->nleaves;
-    most = most > kLongSlots ? kLongSlots : most;
-    slots = slots > most ? most : slots;
-    slots = slots < 1 ? 1 : slots;
+    slots = slots > kLongSlots ? kLongSlots : (slots < 1 ? 1 : slots);
     // one atomic per wave for the list's length
     const bool lng = S.p2p_cnt[e] > kP2PListLDS;
     if (const uint64_t ml = __ballot(lng)) {
@@ -166,12 +164,11 @@ __device__ __forceinline__ void split_leaf(DevState *st, const SplitArgs &S, int
         at = __shfl(at, first);
         if (lng) S.longs[at + __popcll(ml & (ln == 0 ? 0ull : (~0ull >> (64 - ln))))] = e;
     }
-    // listed, to start first: what is split, long or heavy; a list that cannot hold every
-    // leaf is left empty.  Heavy in FP32 from a quantum on, in FP64 from half of one: at
+    // listed, to start first: what is split, long or heavy.  Heavy in FP32 from a quantum on, in FP64 from half of one: at
     // N = 1e6 without the heavy ones 515 us (FP32, four waves a SIMD) and 603 us, from a
     // quantum on 433 and 581 us, from half of one 502 and 542 us.
     const bool heavy = (S.fp32 ? work : 2 * work) > quantum;
-    const int add = (slots > 1 || lng || heavy) && most > 0 ? (int)slots : 0;
+    const int add = slots > 1 || lng || heavy ? (int)slots : 0;
     S.src[e] = (uint32_t)slots | (add > 0 ? kListed : 0u);
     if (!__any(add)) return;
     const int lane = threadIdx.x & (kWave - 1);
@@ -707,7 +704,7 @@ template <int P>
 static void launch_leaf_local(const Workspace &ws, bool fp32, hipStream_t s) {
     const SplitArgs S = {ws.p2p_cnt, ws.c_count, ws.c_first, ws.c_nent,
                          ws.ndisks > 1 ? ws.seg : nullptr, ws.disk_root, ws.ent_work,
-                         ws.long_p2p, ws.split_p2p, 2 * ws.m2l_cap, fp32};
+                         ws.long_p2p, ws.split_p2p, fp32};
     int64_t g = ((int64_t)ws.n_max * P + 127) / 128;
     if (g > 8192) g = 8192;
     if (g < 1) g = 1;
