@@ -1,5 +1,5 @@
-"""Autotuner of the step's launch shape: leaf size, direct-sum tile shape and walk
-queue depth, each under an error gate.
+"""Autotuner of the step's launch shape: leaf size, direct-sum tile shape and the
+workgroups of the gravity walk, each under an error gate.
 
 The leaf size s is the step's main speed parameter (Sect. 4.2: it moves work between
 the direct sums and the expansions without changing the accuracy class).  The direct
@@ -31,7 +31,8 @@ import time
 CANDIDATES = (16, 24, 32, 48, 64, 96, 128)
 # (p2p_tile, p2p_targets_max); the first is the library's default
 TILE_SHAPES = ((256, 4), (128, 4), (512, 4), (256, 2), (256, 1))
-WALK_WAVES = (1024, 512, 2048)
+# workgroups; the first is the library's default (as many as fit on the GPU)
+WALK_WAVES = (0, 1024, 512, 2048)
 GATE_FACTOR = 2.0
 
 
