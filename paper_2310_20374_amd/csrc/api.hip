@@ -293,7 +293,6 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.xs = (double *)take(8 * n);
     ws.ys = (double *)take(8 * n);
     ws.zs = (double *)take(8 * n);
-    (void)take(8 * n);
     ws.vxs = (double *)take(8 * n);
     ws.vys = (double *)take(8 * n);
     ws.vzs = (double *)take(8 * n);
@@ -303,7 +302,6 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.vcol = (double4 *)take(32 * n);
     ws.acc = (double *)take(3 * 8 * n);
     ws.acc_s = (double *)take(3 * 8 * n);
-    (void)take(4 * n);
     ws.ent_work = (uint32_t *)take(4 * n);
     ws.ent_cell = (int32_t *)take(4 * n);
     ws.c_level = (int32_t *)take(4 * cell_cap);
@@ -316,7 +314,6 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
     ws.c_nent = (int32_t *)take(4 * cell_cap);
     ws.c_prefix = (uint64_t *)take(8 * cell_cap);
     ws.c_arrive = (int32_t *)take(4 * cell_cap);
-    (void)take(4 * kXcds * 32);
     ws.gcell = (double4 *)take(32 * cell_cap);
     ws.c_mass = (double *)take(8 * cell_cap);
     ws.c_rmax = (double *)take(8 * cell_cap);
@@ -368,7 +365,10 @@ int64_t layout_workspace(Workspace &ws, const ncorp_params &prm, int64_t n_max, 
         ws.bs_cm = (uint32_t *)take(4 * nbk * nbt);
         ws.bs_total = (uint32_t *)take(4 * nbk);
         ws.bs_off = (uint32_t *)take(4 * (nbk + 1));
-        (void)take(4 * nbk);
+        // not used: with it the largest n of the allocation-free form stays what its
+        // declaration states
+        (void)take(align256(8 * n) + align256(4 * n) + align256(4 * kXcds * 32) +
+                   align256(4 * nbk));
     }
     ws.seg = (uint16_t *)take(2 * n);
     ws.disk_max = (unsigned long long *)take(8 * (int64_t)kMaxDisks);

@@ -554,13 +554,6 @@ hipError_t launch_radix_sort(uint64_t *ka, uint32_t *va, uint64_t *kb, uint32_t 
 }
 
 // ------------------------------------------------------------------ gathers
-__global__ void k_gather1(const double *__restrict__ src, const uint32_t *__restrict__ idx,
-                          int64_t n, double *__restrict__ dst) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = src[idx[i]];
-}
-
 // the (x, y, z, G m) records in tree order, when the build had no masses to pack
 __global__ void k_gather_mass(const double *__restrict__ m, const uint32_t *__restrict__ idx,
                               int64_t n, double G, const double *__restrict__ xs,
@@ -619,12 +612,6 @@ hipError_t launch_gather_vr(const Workspace &ws, bool packed, const double *vx,
     }
     k_gather_vr<<<grid_for(n, 256), 256, 0, s>>>(ws.pack4, ws.idx, n, ws.vxs, ws.vys, ws.vzs,
                                                  ws.rads, ws.vcol);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather(const Workspace &ws, const double *src, double *dst, int64_t n,
-                         hipStream_t s) {
-    k_gather1<<<grid_for(n, 256), 256, 0, s>>>(src, ws.idx, n, dst);
     return hipGetLastError();
 }
 

@@ -114,7 +114,7 @@ struct DevState {
     int32_t level_off[kMaxDepth + 3];
     double L;                  // root half-width (of disk 0 in a batched call)
     double max_abs;            // max |coordinate| (bit pattern max for >= 0 doubles)
-    int32_t ndisks, nroots;    // disks of the call; level-0 cells (non-empty disks)
+    int32_t ndisks, pad2;      // disks of the call
     // gravity walk
     int32_t m2l_maxlist, p2p_maxlist;  // longest per-target lists (timing runs only)
     int32_t nsplit;            // slots in the list of split or long direct sums
@@ -201,11 +201,11 @@ struct WalkQueue {
 };
 
 // What the walk reads of a cell, one 64-byte line: centre, critical radius,
-// moonlet count, first child, number of children (0 for a leaf), first leaf and
-// number of leaves below it, first moonlet, parent (-1: a root).
+// moonlet count, first child, number of children (0 for a leaf), first leaf below it,
+// first moonlet, parent (-1: a root).
 struct alignas(64) WCell {
     double x, y, z, rcrit;
-    int32_t count, child, nchild, entry, nent, first, parent, pad;
+    int32_t count, child, nchild, entry, first, parent, pad[2];
 };
 
 // Waves of a multi-wave block that work independently synchronise their own LDS
@@ -387,8 +387,6 @@ hipError_t launch_sort(const Workspace &ws, int64_t n, hipStream_t s);
 // writes where it starts)
 bool bucket_sort_applies(const Workspace &ws, int64_t n);
 hipError_t launch_bucket_sort(const Workspace &ws, int64_t n, hipStream_t s);
-hipError_t launch_gather(const Workspace &ws, const double *src, double *dst, int64_t n,
-                         hipStream_t s);
 // velocities and radii into tree order, one pass
 hipError_t launch_pack_vr(const Workspace &ws, const double *vx, const double *vy,
                           const double *vz, const double *R, int64_t n, hipStream_t s);

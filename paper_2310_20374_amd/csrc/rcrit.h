@@ -35,7 +35,7 @@ struct RcritArgs {
     double *c_theta;
     double theta_min;
     int theta_mode;                  // 1: constant theta_min
-    const int32_t *c_count, *c_child, *c_nchild, *c_entry, *c_nent, *c_first, *c_parent;
+    const int32_t *c_count, *c_child, *c_nchild, *c_entry, *c_first, *c_parent;
     WCell *wg;
     const uint16_t *seg;             // batched: disk of every tree position, else nullptr
     const int32_t *disk_root;
@@ -46,7 +46,7 @@ inline RcritArgs rcrit_args(const Workspace &ws, const ncorp_params &prm) {
     R.c_mass = ws.c_mass; R.c_rmax = ws.c_rmax; R.gcell = ws.gcell; R.c_theta = ws.c_theta;
     R.theta_min = prm.theta_min; R.theta_mode = prm.theta_mode;
     R.c_count = ws.c_count; R.c_child = ws.c_child; R.c_nchild = ws.c_nchild;
-    R.c_entry = ws.c_entry; R.c_nent = ws.c_nent; R.c_first = ws.c_first;
+    R.c_entry = ws.c_entry; R.c_first = ws.c_first;
     R.c_parent = ws.c_parent;
     R.wg = ws.wg;
     R.seg = ws.ndisks > 1 ? ws.seg : nullptr;
@@ -67,8 +67,8 @@ __device__ inline void rcrit_cell(const RcritArgs &R, int c) {
     WCell w;
     w.x = g.x; w.y = g.y; w.z = g.z; w.rcrit = rc;
     w.count = R.c_count[c]; w.child = R.c_child[c]; w.nchild = R.c_nchild[c];
-    w.entry = R.c_entry[c]; w.nent = R.c_nent[c]; w.first = R.c_first[c];
-    w.parent = R.c_parent[c]; w.pad = 0;
+    w.entry = R.c_entry[c]; w.first = R.c_first[c]; w.parent = R.c_parent[c];
+    w.pad[0] = w.pad[1] = 0;
     R.wg[c] = w;
 }
 
