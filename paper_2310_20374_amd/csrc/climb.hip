@@ -11,6 +11,8 @@
 //
 // Operation order of the centres, radii and angles is fixed (children or moonlets
 // in tree order, no contraction) so they are reproducible bit for bit.
+#include <atomic>
+
 #include "ncorp_internal.h"
 #include "rcrit.h"
 
@@ -70,10 +72,10 @@ constexpr int kClimbRun = 16;
 
 template <int KERNEL_ID>
 static int climb_grid(const void *kernel, int64_t leaf_cap) {
-    static int cached[64] = {};                     // per device, for this kernel
+    static std::atomic<int> cached[64];             // per device; any thread fills it in
     int dev = 0;
     (void)hipGetDevice(&dev);
-    int g = dev >= 0 && dev < 64 ? cached[dev] : 0;
+    int g = dev >= 0 && dev < 64 ? cached[dev].load(std::memory_order_relaxed) : 0;
     if (g == 0) {
         int per_cu = 0, ncu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kWave, 0) != hipSuccess ||
@@ -85,7 +87,7 @@ static int climb_grid(const void *kernel, int64_t leaf_cap) {
         }
         g = per_cu * ncu / kXcds * kXcds;
         if (g < kXcds) g = kXcds;
-        if (dev >= 0 && dev < 64) cached[dev] = g;
+        if (dev >= 0 && dev < 64) cached[dev].store(g, std::memory_order_relaxed);
     }
     // a multiple of the classes, so that each has a taker
     int64_t want = leaf_cap < g ? leaf_cap : g;

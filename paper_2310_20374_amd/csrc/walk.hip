@@ -34,6 +34,8 @@
 // A queue of cell pairs with atomics on its head and tail and on every list took 283 us
 // at N = 1e6 (s = 96, p = 6), 244 us at 1e5 (s = 52) and 1030 us for 2.6e5 moonlets in
 // leaves of 17; this takes 88, 57 and 176 us, and no list needs a sort afterwards.
+#include <atomic>
+
 #include "ncorp_internal.h"
 #include "rcrit.h"
 
@@ -544,10 +546,10 @@ __global__ void __launch_bounds__(kWalkBlock, 6) k_walk(const WalkArgs A) {
 // need a taker.
 template <int MODE>
 static int walk_grid(int64_t cell_cap, int most) {
-    static int cached[64] = {};                     // per device
+    static std::atomic<int> cached[64];             // per device; any thread fills it in
     int dev = 0;
     (void)hipGetDevice(&dev);
-    int g = dev >= 0 && dev < 64 ? cached[dev] : 0;
+    int g = dev >= 0 && dev < 64 ? cached[dev].load(std::memory_order_relaxed) : 0;
     if (g == 0) {
         int per_cu = 0, ncu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k_walk<MODE>,
@@ -560,7 +562,7 @@ static int walk_grid(int64_t cell_cap, int most) {
             ncu = 256;
         }
         g = per_cu * ncu;
-        if (dev >= 0 && dev < 64) cached[dev] = g;
+        if (dev >= 0 && dev < 64) cached[dev].store(g, std::memory_order_relaxed);
     }
     int64_t want = (cell_cap + kWalkBlock / kWave - 1) / (kWalkBlock / kWave);
     if (want > g) want = g;
