@@ -42,11 +42,11 @@ FLOPS_PER_INTERACTION = 20  # directed moonlet pair, the usual N-body convention
 # reported only while it is unchanged.
 # Measured per leaf size (the direct sums' work depends on it).
 P2P_TRAFFIC = {"source": "paper_2310_20374_amd/csrc/p2p.hip",
-               "blob": "2ffb5f52fbe1c57c2ac0ea0609dbe13dc108839a",
+               "blob": "8742e7fbd56888d596b408125db39e3c89d72ebe",
                "fetch_scale": 2.00, "write_scale": 1.00,
                # measured launch shape: (leaf size, source tile, most targets per lane)
-               "by_shape": {(96, 256, 4): {"fetch_kib": (176852.9,), "write_kib": (44501.0,)},
-                            (96, 128, 4): {"fetch_kib": (178488.9,), "write_kib": (44522.1,)}}}
+               "by_shape": {(96, 256, 4): {"fetch_kib": (177925.3,), "write_kib": (44504.4,)},
+                            (96, 128, 4): {"fetch_kib": (178134.9,), "write_kib": (44537.9,)}}}
 
 
 def _git_blob(path):

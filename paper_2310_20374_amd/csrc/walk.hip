@@ -33,7 +33,7 @@
 // rounds of cell loads, publication), and for large or deep trees the rounds' loads.
 // A queue of cell pairs with atomics on its head and tail and on every list took 283 us
 // at N = 1e6 (s = 96, p = 6), 244 us at 1e5 (s = 52) and 1030 us for 2.6e5 moonlets in
-// leaves of 17; this takes 88, 57 and 176 us, and no list needs a sort afterwards.
+// leaves of 17; this takes 94, 60 and 176 us, and no list needs a sort afterwards.
 #include <atomic>
 
 #include "ncorp_internal.h"
