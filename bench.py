@@ -46,7 +46,9 @@ P2P_TRAFFIC = {"source": "paper_2310_20374_amd/csrc/p2p.hip",
                "fetch_scale": 2.00, "write_scale": 1.00,
                # measured launch shape: (leaf size, source tile, most targets per lane)
                "by_shape": {(96, 256, 4): {"fetch_kib": (177925.3,), "write_kib": (44504.4,)},
-                            (96, 128, 4): {"fetch_kib": (178134.9,), "write_kib": (44537.9,)}}}
+                            (96, 128, 4): {"fetch_kib": (178134.9,), "write_kib": (44537.9,)},
+                            (80, 256, 4): {"fetch_kib": (158789.5,), "write_kib": (40772.4,)},
+                            (80, 128, 4): {"fetch_kib": (159419.8,), "write_kib": (40793.1,)}}}
 
 
 def _git_blob(path):
